@@ -1,18 +1,20 @@
 """Build libechokv.so (HIP, gfx950) in-tree.  (The oracle is NumPy: there is no C to compile for it.)"""
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import re
 import shutil
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libechokv.so")
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument",
     "-Rpass-analysis=kernel-resource-usage",
@@ -33,16 +35,25 @@ def hipcc_path() -> str:
 
 def build_library(verbose: bool = False, extra_flags=()) -> str:
     """Compile every HIP source into libechokv.so.  Always recompiles."""
-    srcs = [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith(".hip")]
-    cmd = [hipcc_path(), *HIPCC_FLAGS, *extra_flags, "-I", os.path.join(HERE, "..", "include"),
-           "-o", LIB_PATH + ".tmp", *srcs]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building libechokv.so")
-    spilled = check_spills(res.stdout + res.stderr)
+    srcs = [f for f in sorted(os.listdir(CSRC)) if f.endswith(".hip")]
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, f + ".o") for f in srcs]
+        base = [hipcc_path(), *HIPCC_FLAGS, *extra_flags, "-I", os.path.join(HERE, "..", "include")]
+        cmds = [[*base, "-c", "-o", o, os.path.join(CSRC, f)] for f, o in zip(srcs, objs)]
+
+        def run(cmd):
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            res = subprocess.run(cmd, capture_output=True, text=True)
+            if res.returncode != 0:
+                sys.stderr.write(res.stdout + res.stderr)
+                raise RuntimeError("hipcc failed building libechokv.so")
+            return res.stdout + res.stderr
+
+        with concurrent.futures.ThreadPoolExecutor(4) as ex:      # one compiler per source file
+            remarks = "".join(ex.map(run, cmds))
+        run([hipcc_path(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH + ".tmp", *objs])
+    spilled = check_spills(remarks)
     if spilled:
         raise RuntimeError("scratch memory (spills or stack objects) in kernels that count their own loads: "
                            + ", ".join(f"{k} ({n})" for k, n in spilled))

@@ -1,0 +1,221 @@
+// Split-K streaming decode attention over heads that are stored as rows: the target layer's
+// retained heads, materialised predicted heads, or the uncompressed window.
+#pragma once
+#include "common.h"
+
+namespace echokv {
+
+// ---------------------------------------------------------------------------
+// Uncompressed window of the target layer (the first n_sink positions and a
+// ring of the n_recent latest, Sec. "Experimental Setting", paragraph "Implement details"): position p lives in
+// row p (p < n_sink) or n_sink + (p - n_sink) % n_recent.
+// ---------------------------------------------------------------------------
+struct Window {
+  int32_t n_sink, n_recent;      // n_sink + n_recent == 0: no window
+  __host__ __device__ int rows() const { return n_sink + n_recent; }
+  __host__ __device__ bool on() const { return n_sink + n_recent > 0; }
+  // compressed-cache tokens [lo, hi) of a length-L sequence are NOT in the window
+  __host__ __device__ int lo(int L) const { return on() ? (n_sink < L ? n_sink : L) : 0; }
+  __host__ __device__ int hi(int L) const {
+    if (!on()) return L;
+    const int h = L - n_recent, l = lo(L);
+    return h > l ? h : l;
+  }
+  __host__ __device__ int row_of(int p) const { return p < n_sink ? p : n_sink + (p - n_sink) % n_recent; }
+  // position held by window row w of a length-L sequence, or -1 if the row is empty / stale
+  __host__ __device__ int pos_of(int w, int L) const {
+    if (w < n_sink) return w < L ? w : -1;
+    if (n_recent == 0) return -1;
+    const int t = L - 1 - n_sink, r = w - n_sink;      // ring coordinates of the last token, of the row
+    if (t < 0) return -1;
+    int back = (t - r) % n_recent;
+    if (back < 0) back += n_recent;
+    return t - back >= 0 ? n_sink + t - back : -1;
+  }
+};
+
+// ---------------------------------------------------------------------------
+// Split-K streaming attention over heads that are stored somewhere as rows
+// (the target layer's retained heads, or materialised predicted heads):
+// scores, online softmax and P.V for GT query heads of one KV head over one
+// chunk of `split_tokens` tokens (Eq. 7).  Writes one partial
+// (max, sum-exp, unnormalised o) per (chunk, query head).
+//   LPR = lanes that share one row = d * sizeof(T) / 16.
+// grid.x = chunks (tbase), grid.y = kv heads handled * (G / GT).
+// ---------------------------------------------------------------------------
+template <typename T>
+struct AttnArgs {
+  const T* k; const T* v;   // row r, head g at k + r*ld + col0 + g_local*d
+  int64_t ld;
+  int32_t col0;             // column of the first head handled
+  int32_t head0;            // its KV head index (for the query / output head)
+  int32_t row_mode;         // 0: row = start[b] + j ; 1: sbase[b]*kSlotTokens + j ; 2: j ;
+                            // 3: window rows, row = (seq0 + b) * win.rows() + j, one chunk per sequence
+  const T* q;               // [nseq, H_q, d]
+  int32_t H_q, G, d;
+  float scale;
+  int32_t split_tokens;     // multiple of kSlotTokens
+  float* part_o;            // [slots, H_q, d]
+  float* part_ml;           // [slots, H_q, 2]
+  int32_t slot_tokens = kSlotTokens;   // tokens per slot of SeqMeta::sbase (split_tokens is a multiple)
+  // paper-faithful extras: rotary tables [positions, d/2] (null: none) applied to the key rows by
+  // token position; window: modes 0-2 skip the tokens the window holds, mode 3 attends them
+  const float* rope_cos = nullptr; const float* rope_sin = nullptr;
+  Window win = {0, 0};
+  int32_t seq0 = 0;         // mode 3: index of the launch's first sequence in the window buffers
+  int32_t win_slot0 = 0;    // mode 3: partial of sequence b goes to slot win_slot0 + b
+};
+
+// LDS of one attn_split_body: per wave and query head the max, the sum and the o row.
+template <typename T, int LPR, int GT, int NWAVES>
+constexpr int attn_split_smem_bytes() { return NWAVES * GT * (2 + LPR * Elem<T>::kVec) * 4; }
+
+// One workgroup of NWAVES waves: chunk `chunk` of sequence b, y = KV head * (G / GT) + group of query heads.
+template <typename T, int LPR, int GT, int NWAVES>
+__device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqMeta& meta, int b, int chunk,
+                                                int y, char* smem) {
+  constexpr int VEC = Elem<T>::kVec;
+  constexpr int RPW = 64 / LPR;        // row groups per wave
+  constexpr int NRG = NWAVES * RPW;    // row groups per block
+  const int L = meta.len[b];
+  const int gchunks = a.G / GT;
+  const int hl = y / gchunks;                    // local kv head
+  const int qh0 = (a.head0 + hl) * a.G + (y % gchunks) * GT;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int rg = wave * RPW + lane / LPR;        // row group in block
+  const int li = lane % LPR;                     // lane within row
+  const bool wmode = a.row_mode == 3;
+  const int64_t row0 = a.row_mode == 0 ? meta.start[b]
+                     : a.row_mode == 1 ? (int64_t)meta.sbase[b] * kSlotTokens
+                     : wmode ? (int64_t)(a.seq0 + b) * a.win.rows() : 0;
+  const int col = a.col0 + hl * a.d + li * VEC;
+  // tokens of this chunk: the compressed rows outside the window, or all window rows
+  const int jbeg = wmode ? 0 : max(chunk * a.split_tokens, a.win.lo(L));
+  const int jend = wmode ? a.win.rows() : min(a.win.hi(L), chunk * a.split_tokens + a.split_tokens);
+  const bool rope = a.rope_cos != nullptr;
+  const int hc = (li % (LPR / 2)) * VEC;          // this lane's first column in the d/2-wide tables
+
+  float qv[GT][VEC];
+#pragma unroll
+  for (int g = 0; g < GT; ++g) {
+    load16<T>(a.q + ((int64_t)b * a.H_q + qh0 + g) * a.d + li * VEC, qv[g]);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) qv[g][i] *= a.scale;
+  }
+  float mx[GT], sm[GT], o[GT][VEC];
+#pragma unroll
+  for (int g = 0; g < GT; ++g) {
+    mx[g] = -INFINITY; sm[g] = 0.f;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) o[g][i] = 0.f;
+  }
+  constexpr int UN = 4;
+  for (int j = jbeg + rg; j < jend; j += NRG * UN) {
+    float kv[UN][VEC], vv[UN][VEC];
+    int pos[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      int jj = j + u * NRG; if (jj >= jend) jj = jend - 1;
+      load16<T>(a.k + (row0 + jj) * a.ld + col, kv[u]);
+      load16<T>(a.v + (row0 + jj) * a.ld + col, vv[u]);
+      pos[u] = wmode ? a.win.pos_of(jj, L) : jj;
+      if (rope) {        // feature i pairs with i + d/2, held by the lane LPR / 2 away
+        const int pr = max(pos[u], 0);
+        float cs[VEC], sn[VEC];
+#pragma unroll
+        for (int i = 0; i < VEC; i += 4) {
+          const float4 c4 = *reinterpret_cast<const float4*>(a.rope_cos + (int64_t)pr * (a.d / 2) + hc + i);
+          const float4 s4 = *reinterpret_cast<const float4*>(a.rope_sin + (int64_t)pr * (a.d / 2) + hc + i);
+          cs[i] = c4.x; cs[i + 1] = c4.y; cs[i + 2] = c4.z; cs[i + 3] = c4.w;
+          sn[i] = s4.x; sn[i + 1] = s4.y; sn[i + 2] = s4.z; sn[i + 3] = s4.w;
+        }
+        const float sgn = (li < LPR / 2) ? -1.f : 1.f;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+          const float other = __shfl_xor(kv[u][i], LPR / 2, 64);
+          kv[u][i] = fmaf(kv[u][i], cs[i], sgn * other * sn[i]);
+        }
+      }
+    }
+    // scores of the round's UN rows, then ONE change of the softmax reference per query head and
+    // round (one correction factor instead of one per row)
+#pragma unroll
+    for (int g = 0; g < GT; ++g) {
+      float sc[UN];
+      float mn = mx[g];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const bool live = (j + u * NRG) < jend && pos[u] >= 0;
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) t = fmaf(qv[g][i], kv[u][i], t);
+        t = row_sum<LPR>(t);
+        sc[u] = live ? t : -INFINITY;
+        mn = fmaxf(mn, sc[u]);
+      }
+      if (mn != -INFINITY) {                       // (uniform over the lanes of a row)
+        const float corr = __expf(mx[g] - mn);     // mx = -inf at the start: 0, and o, sm are 0
+        float p[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) p[u] = __expf(sc[u] - mn);     // a dead row: exp(-inf) = 0
+        sm[g] = sm[g] * corr + ((p[0] + p[1]) + (p[2] + p[3]));
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+          float t = o[g][i] * corr;
+#pragma unroll
+          for (int u = 0; u < UN; ++u) t = fmaf(p[u], vv[u][i], t);
+          o[g][i] = t;
+        }
+        mx[g] = mn;
+      }
+    }
+  }
+  // merge the NRG row groups: first inside the wave, then across waves in LDS
+  float (*s_m)[GT] = reinterpret_cast<float (*)[GT]>(smem);
+  float (*s_l)[GT] = s_m + NWAVES;
+  float (*s_o)[GT][LPR * VEC] = reinterpret_cast<float (*)[GT][LPR * VEC]>(s_l + NWAVES);
+#pragma unroll
+  for (int g = 0; g < GT; ++g) {
+    float M = mx[g];
+    for (int off = LPR; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+    const float w = (mx[g] == -INFINITY) ? 0.f : __expf(mx[g] - M);
+    float l = sm[g] * w;
+    for (int off = LPR; off < 64; off <<= 1) l += __shfl_xor(l, off, 64);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      float x = o[g][i] * w;
+      for (int off = LPR; off < 64; off <<= 1) x += __shfl_xor(x, off, 64);
+      o[g][i] = x;
+    }
+    if (lane < LPR) {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) s_o[wave][g][li * VEC + i] = o[g][i];
+    }
+    if (lane == 0) { s_m[wave][g] = M; s_l[wave][g] = l; }
+  }
+  __syncthreads();
+  const int slot = wmode ? a.win_slot0 + b : meta.sbase[b] + chunk * (a.split_tokens / a.slot_tokens);
+  for (int idx = threadIdx.x; idx < GT * a.d; idx += 64 * NWAVES) {
+    const int g = idx / a.d, c = idx % a.d;
+    float M = s_m[0][g];
+#pragma unroll
+    for (int w = 1; w < NWAVES; ++w) M = fmaxf(M, s_m[w][g]);
+    float l = 0.f, acc = 0.f;
+#pragma unroll
+    for (int w = 0; w < NWAVES; ++w) {
+      const float e = (s_m[w][g] == -INFINITY) ? 0.f : __expf(s_m[w][g] - M);
+      l += s_l[w][g] * e; acc += s_o[w][g][c] * e;
+    }
+    const int64_t ph = (int64_t)slot * a.H_q + qh0 + g;
+    a.part_o[ph * a.d + c] = acc;
+    if (c == 0) { a.part_ml[ph * 2] = M; a.part_ml[ph * 2 + 1] = l; }
+  }
+}
+template <typename T, int LPR, int GT>
+__global__ __launch_bounds__(256) void attn_split_kernel(AttnArgs<T> a, SeqMeta meta) {
+  __shared__ __attribute__((aligned(16))) char smem[attn_split_smem_bytes<T, LPR, GT, 4>()];
+  const int b = find_seq(meta.tbase, meta.n, blockIdx.x);
+  attn_split_body<T, LPR, GT, 4>(a, meta, b, blockIdx.x - meta.tbase[b], blockIdx.y, smem);
+}
+
+}  // namespace echokv

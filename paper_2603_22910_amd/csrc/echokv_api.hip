@@ -15,6 +15,7 @@
 #include "fused_decode.h"
 #include "fused_decode_f32.h"
 #include "fused_decode_dma.h"
+#include "fused_decode_small.h"
 #include "prefill_kernels.h"
 #include "absorbed_decode.h"
 #include "fit_kernels.h"
@@ -183,9 +184,9 @@ int fill_tiles(SeqMeta& mt, int tile_tokens) {
   mt.tbase[mt.n] = acc;
   return acc;
 }
-int fill_slots(SeqMeta& mt) {
+int fill_slots(SeqMeta& mt, int slot_tokens = kSlotTokens) {
   int acc = 0;
-  for (int b = 0; b < mt.n; ++b) { mt.sbase[b] = acc; acc += slots_for(mt.len[b]); }
+  for (int b = 0; b < mt.n; ++b) { mt.sbase[b] = acc; acc += (mt.len[b] + slot_tokens - 1) / slot_tokens; }
   mt.sbase[mt.n] = acc;
   return acc;
 }
@@ -296,10 +297,89 @@ int merge_launch(const Dims& dm, const float* po, const float* pml, void* out, f
   return ECHOKV_OK;
 }
 
+// ---- small problems: everything but the merge in one launch (fused_decode_small.h) ------------
+// Workgroups up to which the small kernel is the faster one.  Measured (us, 32 / 64 tokens per workgroup /
+// 256 x 256 kernel): 188 workgroups of 32 tokens 24.7 / 29.5 / 86, 252 of them 32.5 / 29.8 / 86; 504 workgroups of
+// 64 tokens (three layers) 84 / 63 / 87, 202 / 159 / 223, 60 / 45 / 60; 752 of them 120 / 89 / 89, 295 / 233 / 227,
+// 84 / 62 / 61.  fp32 (16 / 32 tokens / 256 x 256): 128 workgroups of 16 16.6 / 22 / 464; 1000 of 32 tokens 79 / 71 / 510,
+// growing by 71 per 1000 while the large kernel stays at 510 until its tiles fill the chip.
+constexpr int kSmallFewWgs = 240, kSmallMaxWgs = 704, kSmallMaxWgsF32 = 6144;
+inline int small_col_tile(const Dims& dm) { return dm.bf16 ? 128 : dm.d; }
+// Token blocks of 16 per workgroup (0: the problem is not small).
+template <typename T>
+int small_token_blocks(const Dims& dm, const SeqMeta& mt) {
+  if (!fused_decode_supported<T>(dm.d, dm.G) || dm.d_out_v == 0) return 0;
+  // 32-bit byte offsets inside a token tile and inside W
+  if ((int64_t)dm.d_in * dm.d_out_v * (int)sizeof(T) >= (int64_t)1 << 31 || 64 * (int64_t)dm.D * (int)sizeof(T) >= (int64_t)1 << 31) return 0;
+  const int bn = small_col_tile(dm);
+  const int64_t ct = (dm.d_out_v + bn - 1) / bn;
+  int64_t t16 = 0, t32 = 0, t64 = 0;
+  for (int b = 0; b < mt.n; ++b) { t16 += (mt.len[b] + 15) / 16; t32 += (mt.len[b] + 31) / 32; t64 += (mt.len[b] + 63) / 64; }
+  if (sizeof(T) == 4) {
+    if (t16 * ct <= 256) return 1;
+    return t32 * ct * dm.d / 64 <= kSmallMaxWgsF32 ? 2 : 0;
+  }
+  if (t32 * ct <= kSmallFewWgs) return 2;
+  return t64 * ct <= kSmallMaxWgs ? 4 : 0;
+}
+// Partial slots a small launch can need at most, the window's one per sequence included.
+int64_t small_max_slots(const Dims& dm, int batch, int64_t total_tokens) {
+  const int bn = small_col_tile(dm);
+  const int64_t ct = std::max(1, (dm.d_out_v + bn - 1) / bn), n = std::min(batch, kMaxSeqPerLaunch);
+  const int64_t wgs = dm.bf16 ? kSmallMaxWgs : (int64_t)kSmallMaxWgsF32 * 64 / dm.d;
+  return std::min<int64_t>(total_tokens / (dm.bf16 ? 32 : 16) + n, wgs / ct) + n;
+}
+
+template <typename T>
+int decode_small(const Dims& dm, int tb, bool packed, const echokv_layer_cache* an, const echokv_layer_cache* tg,
+                 const T* wk, const T* wv, const T* qq, const echokv_decode_extras* ex, const KvExtras& kx,
+                 float* po, float* pml, int b0, const SeqMeta& mt0, int* stream_step, int* win_slot0, hipStream_t st) {
+  fsmall::Meta mt;
+  mt.s = mt0;                                // (sbase counts slots of 16 tb tokens here)
+  const int tok = 16 * tb;
+  fsmall::Args<T> a;
+  a.xa[0] = (const T*)an->k; a.xa[1] = (const T*)an->v; a.xr[0] = (const T*)tg->k; a.xr[1] = (const T*)tg->v;
+  a.w[0] = wk; a.w[1] = wv; a.q = qq; a.part_o = po; a.part_ml = pml;
+  a.D = dm.D; a.m = dm.m; a.d_out = dm.d_out_v; a.H_q = dm.H_q; a.G = dm.G; a.n_ret_heads = dm.g0; a.scale = dm.scale;
+  a.rope_cos = kx.rope_cos; a.rope_sin = kx.rope_sin; a.n_sink = kx.n_sink; a.n_recent = kx.n_recent;
+  const int bn = sizeof(T) == 2 ? 128 : dm.d;
+  a.n_ttiles = fill_tiles(mt.s, tok); a.n_col_tiles = (dm.d_out_v + bn - 1) / bn;
+  a.n_fused = (a.n_ttiles * a.n_col_tiles + 7) / 8 * 8;
+  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1;
+  AttnArgs<T>& r = a.ret;
+  r.k = (const T*)tg->k; r.v = (const T*)tg->v; r.ld = dm.m; r.col0 = 0; r.head0 = 0; r.row_mode = 0;
+  r.q = qq; r.H_q = dm.H_q; r.G = dm.G; r.d = dm.d; r.scale = dm.scale; r.part_o = po; r.part_ml = pml;
+  r.slot_tokens = tok; r.rope_cos = kx.rope_cos; r.rope_sin = kx.rope_sin; r.win = Window{kx.n_sink, kx.n_recent};
+  a.win = r;
+  // chunks of one round of the workgroup's rows, longer ones once they outnumber the product's workgroups
+  const int ny = dm.g0 * (dm.G / gt);
+  r.split_tokens = kSlotTokens;
+  for (;;) {
+    int acc = 0;
+    for (int b = 0; b < mt.s.n; ++b) { mt.cbase[b] = acc; acc += (mt.s.len[b] + r.split_tokens - 1) / r.split_tokens; }
+    mt.cbase[mt.s.n] = acc;
+    a.n_ret_chunks = std::max(acc, 1);
+    if ((int64_t)acc * ny <= 256 || r.split_tokens >= 2048) break;
+    r.split_tokens *= 2;
+  }
+  a.n_ret = dm.g0 > 0 ? a.n_ret_chunks * ny : 0;
+  *stream_step = r.split_tokens / tok;
+  a.n_win = 0; *win_slot0 = -1;
+  if (r.win.on()) {
+    *win_slot0 = mt.s.sbase[mt.s.n];
+    AttnArgs<T>& w = a.win;
+    w.k = (const T*)ex->win_k; w.v = (const T*)ex->win_v; w.ld = dm.D; w.row_mode = 3;
+    w.split_tokens = kSlotTokens; w.seq0 = b0; w.win_slot0 = *win_slot0;
+    a.n_win = mt.s.n * dm.H_kv * (dm.G / gt);
+  }
+  return launch_fused_decode_small<T>(a, mt, tb, packed, st);
+}
+
 template <typename T>
 int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
                 const echokv_layer_cache* tg, const void* w_k, const void* w_v, const void* q,
-                const echokv_decode_extras* ex, void* out, float* lse, char* ws, hipStream_t st) {
+                const echokv_decode_extras* ex, void* out, float* lse, char* ws, size_t ws_bytes,
+                hipStream_t st) {
   const int n_ret_heads = dm.g0, n_rec_heads = dm.H_kv - n_ret_heads;
   KvExtras kx;
   if (ex) {
@@ -329,6 +409,30 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
     const T* qq = (const T*)q + (int64_t)b0 * dm.H_q * dm.d;
     int stream_step = 1, fused_step = 1;
 
+    const int tb = fused && !(flags & ECHOKV_FLAG_STAGED) ? small_token_blocks<T>(dm, mt) : 0;
+    if (tb > 0) {
+      SeqMeta ms = mt;
+      const int sl = fill_slots(ms, 16 * tb);
+      const WsPlan sp = plan_ws(dm, sl + mt.n, 0);
+      if (sp.total <= ws_bytes) {       // (a fixed scratch may hold the larger slots of the other path only)
+        float* spo = (float*)(ws + sp.off_po);
+        float* spml = (float*)(ws + sp.off_pml);
+        ProfScope prof;
+        int rc = prof.begin(0, st);
+        if (rc) return rc;
+        int win_slot0 = -1;
+        rc = decode_small<T>(dm, tb, (flags & ECHOKV_FLAG_W_PACKED) != 0, an, tg, wk, wv, qq, ex, kx, spo, spml, b0,
+                             ms, &stream_step, &win_slot0, st);
+        if (rc) return rc;
+        rc = prof.end();
+        if (rc) return rc;
+        rc = dm.out_bf16
+            ? merge_launch<T, bf16_t>(dm, spo, spml, out, lse, b0, n_ret_heads, stream_step, 1, win_slot0, ms, st)
+            : merge_launch<T, float>(dm, spo, spml, out, lse, b0, n_ret_heads, stream_step, 1, win_slot0, ms, st);
+        if (rc) return rc;
+        continue;
+      }
+    }
     if (n_ret_heads > 0) {
       AttnArgs<T> a;
       a.k = (const T*)tg->k; a.v = (const T*)tg->v; a.ld = dm.m; a.col0 = 0; a.head0 = 0;
@@ -855,7 +959,8 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
 
 size_t decode_ws_bytes(const Dims& dm, int batch, int64_t total_tokens, bool unfused) {
   const int64_t slots = total_tokens / kSlotTokens + 2 * (int64_t)batch;   // + one window partial per sequence
-  return plan_ws(dm, slots, unfused ? slots * kSlotTokens : 0).total;
+  return std::max(plan_ws(dm, slots, unfused ? slots * kSlotTokens : 0).total,
+                  plan_ws(dm, small_max_slots(dm, batch, total_tokens), 0).total);
 }
 // MFMA prefill path: [plan][rotated copy of the retained keys][partials of a launch split over the keys]
 size_t prefill_ws_bytes(const Dims& dm, int64_t Ltot, int max_q) {
@@ -1213,8 +1318,8 @@ int echokv_decode_attn_ex(const echokv_shape* shape, const echokv_layer_cache* a
   if ((uintptr_t)workspace % 256) return ECHOKV_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   const echokv_decode_extras* ex = has_extras ? extras : nullptr;
-  return dm.bf16 ? decode_impl<bf16_t>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, st)
-                 : decode_impl<float>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, st);
+  return dm.bf16 ? decode_impl<bf16_t>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, workspace_bytes, st)
+                 : decode_impl<float>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, workspace_bytes, st);
 }
 
 int echokv_decode_attn(const echokv_shape* shape, const echokv_layer_cache* anchor,

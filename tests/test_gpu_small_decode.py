@@ -1,0 +1,72 @@
+"""GPU parity of the small-problem decode kernel and of the rule that sends a call to it: lengths on
+both sides of its tile sizes (16, 32 and 64 tokens) and of the workgroup counts at which the tile
+size or the kernel changes, every output element against the fp64 oracle; and the fall-back to
+the large kernel when the workspace holds only that one's partials."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_22910_amd import binding as ek
+from paper_2603_22910_amd import synth
+from paper_2603_22910_amd.harness import DeviceWorkload
+
+import oracle_ref as ref
+from test_gpu_parity import PACKED, check, host, make_dw
+
+pytestmark = pytest.mark.gpu
+
+# H_q, H_kv, d, m, dtype, lengths.  Column tiles: 128 columns (fp32: one head).
+CASES = [
+    (8, 4, 128, 128, "bf16", (31, 32, 33, 1)),          # 3 column tiles, edges of a 32-token tile
+    (8, 4, 128, 128, "bf16", (2560,)),                  # 240 workgroups: the last with 32-token tiles
+    (8, 4, 128, 128, "bf16", (2561,)),                  # the first with 64-token tiles
+    (8, 4, 128, 128, "bf16", (14976,)),                 # 702 of at most 704 workgroups
+    (8, 4, 128, 128, "bf16", (15000, 64, 65)),          # over it: the 256 x 256 kernel
+    (10, 5, 64, 128, "bf16", (65, 129, 3)),             # three predicted heads of 64: half of the last tile is empty
+    (16, 2, 128, 64, "bf16", (200, 63)),                # split head (r = 64), G = 8
+    (4, 1, 64, 0, "bf16", (100,)),                      # d_in = 64: two steps for four waves
+    (8, 8, 64, 256, "f32", (15, 16, 17, 1)),            # 4 column tiles, edges of a 16-token tile
+    (8, 8, 64, 256, "f32", (1024,)),                    # 256 workgroups: the last with 16-token tiles
+    (8, 8, 64, 256, "f32", (1025, 700)),
+    (6, 3, 128, 128, "f32", (40, 33)),
+]
+EXTRAS = [pytest.param(False, id="plain"), pytest.param(True, id="rope+window")]
+
+
+@pytest.mark.parametrize("packed", [pytest.param(0, id="row-major"), pytest.param(PACKED, id="packed")])
+@pytest.mark.parametrize("extras", EXTRAS)
+@pytest.mark.parametrize("H_q,H_kv,d,m,dtype,lens", CASES)
+def test_small_decode_against_the_oracle(H_q, H_kv, d, m, dtype, lens, extras, packed):
+    if packed and (dtype != "bf16" or m % d or extras):
+        pytest.skip("packed weights: whole heads of a bf16 layer")
+    w = synth.Workload("small", dtype, H_q, H_kv, d, m, seed=71, seq_lens=lens)
+    inp = synth.generate(w)
+    dw = make_dw(inp, packed)
+    if extras:
+        rope = synth.rope_tables(d, max(lens))
+        window = (*synth.window_rows(inp, 4, 24), 4, 24)
+        out, lse = dw.decode_ex(rope, window)
+        o_ref, l_ref = ref.decode_paper_ref(inp, rope, window)
+    else:
+        out, lse = dw.decode()
+        o_ref, l_ref = ref.decode_ref(inp)
+    torch.cuda.synchronize()
+    check(host(out), o_ref, dtype, f"{w} {lens}")
+    assert np.abs(host(lse) - l_ref).max() <= (1e-5 if dtype == "f32" else 2e-2)
+
+
+def test_workspace_of_the_large_kernel_alone_is_still_accepted():
+    w = synth.Workload("small_ws", "bf16", 8, 4, 128, 128, seed=72, seq_lens=(600,))
+    inp = synth.generate(w)
+    dw = DeviceWorkload(inp)
+    a256 = lambda x: (x + 255) // 256 * 256
+    slots = (600 + 127) // 128 + 1                      # one partial per 128 tokens, one for the window
+    need = a256(slots * 8 * 128 * 4) + a256(slots * 8 * 2 * 4)
+    dw.workspace = dw.workspace[:need]
+    out, lse = dw.decode(); torch.cuda.synchronize()
+    o_ref, l_ref = ref.decode_ref(inp)
+    check(host(out), o_ref, "bf16", "workspace without room for 32-token partials")
+    dw.workspace = dw.workspace[:need - 256]
+    with pytest.raises(ek.EchoKVError) as e:
+        dw.decode()
+    assert e.value.code == ek.ERR_WORKSPACE
