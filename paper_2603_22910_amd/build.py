@@ -23,7 +23,8 @@ HIPCC_FLAGS = [
 # Kernels that count their own outstanding global loads (manual s_waitcnt vmcnt(N) around
 # global -> LDS copies).  Register spills and stack objects go through the same counter, so any
 # scratch memory in one of them would make those waits meaningless: the build refuses it.
-NO_SPILL_KERNELS = ("fused_decode_dma_kernel", "prefill_attn_dma_kernel", "absorbed13scores_kernel")
+NO_SPILL_KERNELS = ("fused_decode_kernel", "fused_kscores_kernel", "recon_mfma_kernel", "prefill_attn_dma_kernel",
+                    "absorbed13scores_kernel")
 
 
 def hipcc_path() -> str:

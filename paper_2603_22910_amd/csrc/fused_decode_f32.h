@@ -17,9 +17,182 @@
 namespace echokv {
 namespace fused32 {
 
-using fused::BM; using fused::BN; using fused::NTHREADS; using fused::WM; using fused::WN;
+using fused::BM; using fused::BN;
+constexpr int NTHREADS = 256, WM = 128, WN = 128;      // 2 x 2 waves of 128 x 128
 constexpr int BK = 16;            // input dims per tile
 constexpr int XP = BK + 1;        // padded row pitch of the X tile (floats): conflict-free column reads
+
+// The epilogues take accumulators of NTB blocks of 32 tokens x 4 blocks of 32 columns (whole heads).
+//
+// Keeps the 256 accumulators in the accumulation registers for the duration of an epilogue loop
+// body: without it the compiler copies all of them to ordinary registers ahead of the loop over
+// query heads and spills whatever else is live.
+template <int I, int J>
+__device__ __forceinline__ void pin_acc(floatx16_t (&acc)[I][J]) {
+#pragma unroll
+  for (int i = 0; i < I; ++i)
+#pragma unroll
+    for (int j = 0; j < J; ++j) asm volatile("" : "+a"(acc[i][j]));
+}
+
+// Softmax numerators of one (head, query head) pair from the lane-partial scores s
+// (token tb * 32 + lane % 32 of the wave; the two lane halves hold the two halves of the head dims).
+template <int NTB>
+__device__ __forceinline__ void score_tail(float (&s)[NTB], float* pp, float* ml, int lane, int jw0, const fused::KExtra& x) {
+  const int lr = lane & 31, lh = lane >> 5;
+  float mx = -INFINITY;
+#pragma unroll
+  for (int tb = 0; tb < NTB; ++tb) {
+    s[tb] += __shfl_xor(s[tb], 32, 64);
+    const int tok = jw0 + tb * 32 + lr;
+    if (tok < x.lo || tok >= x.hi) s[tb] = -INFINITY;
+    mx = fmaxf(mx, s[tb]);
+  }
+  mx = wave_max(mx, 32);
+  float sum = 0.f;
+#pragma unroll
+  for (int tb = 0; tb < NTB; ++tb) {
+    const float p = (s[tb] == -INFINITY) ? 0.f : __expf(s[tb] - mx);
+    sum += p;
+    if (lh == 0) pp[tb * 32 + lr] = p;
+  }
+  sum = wave_sum(sum, 32);
+  if (lane == 0) { ml[0] = mx; ml[1] = sum; }
+}
+
+// After the K pass: acc[cb][tb] holds K_hat^T (rows = head dims of the wave's 128 columns, lanes =
+// tokens).  `tail(s, hw, g)` receives the lane-partial scores (Eq. 7) of head hw of the wave's tile and
+// query head g of its group (token tb * 32 + lane % 32; add the other lane half for the total).
+// qw: the queries of the wave's first head; jw0: its first token.
+template <int HD, bool ROPE, int NTB, class Tail>
+__device__ __forceinline__ void k_scores(floatx16_t (&acc)[4][NTB], const float* qw, int G,
+                                         int lane, int jw0, int L, const fused::KExtra& x, Tail tail) {
+  constexpr int HPW = 128 / HD, CBH = HD / 32;
+  const int lr = lane & 31, lh = lane >> 5;
+  if constexpr (!ROPE) {
+#pragma unroll
+    for (int hw = 0; hw < HPW; ++hw) {
+      for (int g = 0; g < G; ++g) {
+        pin_acc(acc);
+        const float* qs = qw + (hw * G + g) * HD;
+        float s[NTB];
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) s[tb] = 0.f;
+#pragma unroll
+        for (int cb = 0; cb < CBH; ++cb) {
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) {
+            const float4 qv = *reinterpret_cast<const float4*>(qs + cb * 32 + r4 * 8 + lh * 4);
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) {
+              const floatx16_t& c = acc[hw * CBH + cb][tb];
+              s[tb] = fmaf(qv.x, c[r4 * 4 + 0], s[tb]);
+              s[tb] = fmaf(qv.y, c[r4 * 4 + 1], s[tb]);
+              s[tb] = fmaf(qv.z, c[r4 * 4 + 2], s[tb]);
+              s[tb] = fmaf(qv.w, c[r4 * 4 + 3], s[tb]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        tail(s, hw, g);
+      }
+    }
+  } else {
+    // Rotary embedding of the rebuilt key at its token's position, folded into the dot
+    // product: feature c pairs with c + HD/2, which this lane holds HD/64 column blocks
+    // further on.  With a = k_c, b = k_{c+HD/2}:
+    //   q_c (a cos - b sin) + q_{c+HD/2} (b cos + a sin)
+    //     = cos (a q_c + b q_{c+HD/2}) + sin (a q_{c+HD/2} - b q_c)
+    // The accumulators are only read.  Masked tokens borrow the last valid table row.  The
+    // table values and the accumulator reads of a (token block, column block) are shared by
+    // the query heads of the group: the loop over them is innermost, unrolled to the
+    // largest group size with a uniform skip.
+    constexpr int HB = CBH / 2;
+#pragma unroll
+    for (int hw = 0; hw < HPW; ++hw) {
+      float s[fused::MAXPAIR][NTB];
+#pragma unroll
+      for (int g = 0; g < fused::MAXPAIR; ++g)
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) s[g][tb] = 0.f;
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb) {
+        const int pos = min(jw0 + tb * 32 + lr, L - 1);
+        const float* cr = x.cos + (int64_t)pos * (HD / 2) + lh * 4;
+        const float* sr = x.sin + (int64_t)pos * (HD / 2) + lh * 4;
+#pragma unroll
+        for (int cb = 0; cb < HB; ++cb) {
+          pin_acc(acc);
+          float cc[16], ss[16], ka[16], kb[16];
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) {
+            const float4 c4 = *reinterpret_cast<const float4*>(cr + cb * 32 + r4 * 8);
+            const float4 s4 = *reinterpret_cast<const float4*>(sr + cb * 32 + r4 * 8);
+            cc[r4 * 4] = c4.x; cc[r4 * 4 + 1] = c4.y; cc[r4 * 4 + 2] = c4.z; cc[r4 * 4 + 3] = c4.w;
+            ss[r4 * 4] = s4.x; ss[r4 * 4 + 1] = s4.y; ss[r4 * 4 + 2] = s4.z; ss[r4 * 4 + 3] = s4.w;
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            ka[r] = acc[hw * CBH + cb][tb][r];
+            kb[r] = acc[hw * CBH + cb + HB][tb][r];
+          }
+#pragma unroll
+          for (int g = 0; g < fused::MAXPAIR; ++g) {
+            if (g < G) {
+              const float* qs = qw + (hw * G + g) * HD;
+#pragma unroll
+              for (int r4 = 0; r4 < 4; ++r4) {
+                const float4 qa = *reinterpret_cast<const float4*>(qs + cb * 32 + r4 * 8 + lh * 4);
+                const float4 qb = *reinterpret_cast<const float4*>(qs + (cb + HB) * 32 + r4 * 8 + lh * 4);
+                const float q0[4] = {qa.x, qa.y, qa.z, qa.w}, q1[4] = {qb.x, qb.y, qb.z, qb.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                  const float a = ka[r4 * 4 + i], b = kb[r4 * 4 + i];
+                  const float t1 = fmaf(a, q0[i], b * q1[i]);
+                  const float t2 = fmaf(a, q1[i], -b * q0[i]);
+                  s[g][tb] = fmaf(cc[r4 * 4 + i], t1, fmaf(ss[r4 * 4 + i], t2, s[g][tb]));
+                }
+              }
+            }
+          }
+          asm volatile("" ::: "memory");       // keep the table loads of later rounds from piling up
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < fused::MAXPAIR; ++g)
+        if (g < G) tail(s[g], hw, g);
+    }
+  }
+}
+
+// After the V pass: acc[tb][cb] holds V_hat (rows = tokens, lanes = head dims).  sum_j p_j v_hat_j of one
+// (head, query head) pair over the wave's tokens: dim cb * 32 + lane % 32 in o[cb], both lane halves.
+template <int HD, int NTB>
+__device__ __forceinline__ void value_sum(floatx16_t (&acc)[NTB][4], const float* pp, int hw, int lane, float (&o)[HD / 32]) {
+  constexpr int CBH = HD / 32;
+  const int lh = lane >> 5;
+#pragma unroll
+  for (int cb = 0; cb < CBH; ++cb) o[cb] = 0.f;
+#pragma unroll
+  for (int tb = 0; tb < NTB; ++tb) {
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const float4 pv = *reinterpret_cast<const float4*>(pp + tb * 32 + r4 * 8 + lh * 4);
+#pragma unroll
+      for (int cb = 0; cb < CBH; ++cb) {
+        const floatx16_t& c = acc[tb][hw * CBH + cb];
+        o[cb] = fmaf(pv.x, c[r4 * 4 + 0], o[cb]);
+        o[cb] = fmaf(pv.y, c[r4 * 4 + 1], o[cb]);
+        o[cb] = fmaf(pv.z, c[r4 * 4 + 2], o[cb]);
+        o[cb] = fmaf(pv.w, c[r4 * 4 + 3], o[cb]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int cb = 0; cb < CBH; ++cb) o[cb] += __shfl_xor(o[cb], 32, 64);
+}
 
 struct Args {
   const float* xa[2]; const float* xr[2]; const float* w[2];
@@ -35,7 +208,7 @@ struct Args {
 struct Smem {
   float x[BM * XP];
   float w[BK * BN];
-  fused::EpiSmem e;
+  fused::EpiSmem<4, WM> e;
 };
 
 template <bool SWAP>
@@ -107,16 +280,33 @@ __global__ __launch_bounds__(NTHREADS) void fused_decode_f32_kernel(Args a, SeqM
   const int wt = wave >> 1, wc = wave & 1;
   const int last = min(BM, L - j0) - 1;
   const int64_t row0 = meta.start[b] + j0;
-  fused::load_queries<HD>(sm.e, a.q, b, a.H_q, a.G, a.n_ret_heads + n0 / HD, a.scale, tid);
+  fused::load_queries<HD, NTHREADS>(sm.e.q, a.q, b, a.H_q, a.G, a.n_ret_heads + n0 / HD, a.scale, tid);
   floatx16_t acc[4][4];
   gemm_pass<true>(acc, sm, a, a.xa[0] + row0 * a.D, a.xr[0] + row0 * a.m, a.w[0] + n0, last, n0, tid);
   const int jw0 = j0 + wt * WM;
-  fused::k_epilogue<HD, ROPE>(acc, sm.e, a.G, wave, lane, jw0, L,
-                        fused::make_kextra(a.rope_cos, a.rope_sin, a.n_sink, a.n_recent, L));
+  constexpr int HPW = WN / HD, CBH = HD / 32;
+  const fused::KExtra x = fused::make_kextra(a.rope_cos, a.rope_sin, a.n_sink, a.n_recent, L);
+  k_scores<HD, ROPE, 4>(acc, &sm.e.q[wc * HPW * a.G * HD], a.G, lane, jw0, L, x, [&](float (&s)[4], int hw, int g) {
+    score_tail<4>(s, sm.e.p[wave][hw * a.G + g], sm.e.ml[wave][hw * a.G + g], lane, jw0, x);
+  });
   gemm_pass<false>(acc, sm, a, a.xa[1] + row0 * a.D, a.xr[1] + row0 * a.m, a.w[1] + n0, last, n0, tid);
   if (jw0 >= L) return;
-  fused::v_epilogue<HD>(acc, sm.e, a.G, wave, lane, meta.sbase[b] + jw0 / kSlotTokens, a.H_q,
-                        a.n_ret_heads + (n0 + wc * WN) / HD, a.part_o, a.part_ml);
+  const int H_kv = a.H_q / a.G, kvh0 = a.n_ret_heads + (n0 + wc * WN) / HD;
+#pragma unroll
+  for (int hw = 0; hw < HPW; ++hw) {
+    if (kvh0 + hw >= H_kv) continue;
+    for (int g = 0; g < a.G; ++g) {
+      pin_acc(acc);
+      const int pair = hw * a.G + g;
+      const int64_t ph = ((int64_t)meta.sbase[b] + jw0 / kSlotTokens) * a.H_q + (kvh0 + hw) * a.G + g;
+      float o[CBH];
+      value_sum<HD, 4>(acc, sm.e.p[wave][pair], hw, lane, o);
+#pragma unroll
+      for (int cb = 0; cb < CBH; ++cb)
+        if (lane < 32) a.part_o[ph * HD + cb * 32 + lane] = o[cb];
+      if (lane == 0) { a.part_ml[ph * 2] = sm.e.ml[wave][pair][0]; a.part_ml[ph * 2 + 1] = sm.e.ml[wave][pair][1]; }
+    }
+  }
 }
 
 }  // namespace fused32
