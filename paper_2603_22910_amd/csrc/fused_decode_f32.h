@@ -325,7 +325,7 @@ inline int launch_fused_decode_f32(int H_q, int H_kv, int d, int m, int d_out, i
   a.n_ret_heads = n_ret_heads; a.scale = scale;
   a.n_col_tiles = (a.d_out + fused::BN - 1) / fused::BN;
   a.n_tiles = fused_fill_tiles(mt) * a.n_col_tiles;
-  const dim3 g(a.n_tiles), blk(fused::NTHREADS);
+  const dim3 g(a.n_tiles), blk(fused32::NTHREADS);
   const bool rope = ex.rope_cos != nullptr;
   if (d == 128 && rope) hipLaunchKernelGGL((fused32::fused_decode_f32_kernel<128, true>), g, blk, 0, st, a, mt);
   else if (d == 128) hipLaunchKernelGGL((fused32::fused_decode_f32_kernel<128, false>), g, blk, 0, st, a, mt);

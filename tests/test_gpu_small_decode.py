@@ -28,6 +28,7 @@ CASES = [
     (8, 8, 64, 256, "f32", (15, 16, 17, 1)),            # 4 column tiles, edges of a 16-token tile
     (8, 8, 64, 256, "f32", (1024,)),                    # 256 workgroups: the last with 16-token tiles
     (8, 8, 64, 256, "f32", (1025, 700)),
+    (2, 2, 64, 64, "f32", (196608, 31)),                # 6145 workgroups of at most 6144: the 256 x 256 kernel
     (6, 3, 128, 128, "f32", (40, 33)),
 ]
 EXTRAS = [pytest.param(False, id="plain"), pytest.param(True, id="rope+window")]
