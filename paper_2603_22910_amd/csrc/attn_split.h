@@ -71,7 +71,8 @@ template <typename T, int LPR, int GT, int NWAVES>
 constexpr int attn_split_smem_bytes() { return NWAVES * GT * (2 + LPR * Elem<T>::kVec) * 4; }
 
 // One workgroup of NWAVES waves: chunk `chunk` of sequence b, y = KV head * (G / GT) + group of query heads.
-template <typename T, int LPR, int GT, int NWAVES>
+// UN: rows of a row group in flight (4; 8 where few waves share a compute unit).
+template <typename T, int LPR, int GT, int NWAVES, int UN = 4>
 __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqMeta& meta, int b, int chunk,
                                                 int y, char* smem) {
   constexpr int VEC = Elem<T>::kVec;
@@ -109,7 +110,6 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqM
 #pragma unroll
     for (int i = 0; i < VEC; ++i) o[g][i] = 0.f;
   }
-  constexpr int UN = 4;
   for (int j = jbeg + rg; j < jend; j += NRG * UN) {
     float kv[UN][VEC], vv[UN][VEC];
     int pos[UN];
@@ -158,7 +158,10 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqM
         float p[UN];
 #pragma unroll
         for (int u = 0; u < UN; ++u) p[u] = __expf(sc[u] - mn);     // a dead row: exp(-inf) = 0
-        sm[g] = sm[g] * corr + ((p[0] + p[1]) + (p[2] + p[3]));
+        float ps = (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+        for (int u = 4; u < UN; u += 4) ps += (p[u] + p[u + 1]) + (p[u + 2] + p[u + 3]);
+        sm[g] = sm[g] * corr + ps;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
           float t = o[g][i] * corr;
@@ -216,6 +219,33 @@ __global__ __launch_bounds__(256) void attn_split_kernel(AttnArgs<T> a, SeqMeta 
   __shared__ __attribute__((aligned(16))) char smem[attn_split_smem_bytes<T, LPR, GT, 4>()];
   const int b = find_seq(meta.tbase, meta.n, blockIdx.x);
   attn_split_body<T, LPR, GT, 4>(a, meta, b, blockIdx.x - meta.tbase[b], blockIdx.y, smem);
+}
+
+
+// The streaming part of a decode call as further workgroups of another kernel's launch: the retained heads
+// (one workgroup per chunk of split_tokens, KV head and group of query heads), then the window's rows.
+struct StreamMeta {
+  SeqMeta s;
+  int32_t cbase[kMaxSeqPerLaunch + 1];        // prefix sum of the retained heads' chunks per sequence
+};
+template <typename T> struct Streams {
+  AttnArgs<T> ret, win;
+  int32_t n_ret_chunks = 1, n_ret = 0, n_win = 0;     // chunks of all sequences; workgroups
+};
+template <typename T, int HD, int NWAVES>
+constexpr int stream_smem_bytes() { return attn_split_smem_bytes<T, HD * (int)sizeof(T) / 16, 4, NWAVES>(); }
+template <typename T, int HD, int NWAVES, int UN>
+__device__ __forceinline__ void stream_workgroup(const Streams<T>& st, const StreamMeta& meta, int wg, char* smem) {
+  const bool ret = wg < st.n_ret;
+  if (!ret) wg -= st.n_ret;
+  const AttnArgs<T> a = ret ? st.ret : st.win;
+  const int per = ret ? st.n_ret_chunks : meta.s.n, x = wg % per, y = wg / per;
+  const int b = ret ? find_seq(meta.cbase, meta.s.n, x) : x;
+  const int chunk = ret ? x - meta.cbase[b] : 0;
+  constexpr int LPR = HD * (int)sizeof(T) / 16;
+  if (a.G % 4 == 0) attn_split_body<T, LPR, 4, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
+  else if (a.G % 2 == 0) attn_split_body<T, LPR, 2, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
+  else attn_split_body<T, LPR, 1, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
 }
 
 }  // namespace echokv

@@ -308,6 +308,7 @@ inline int small_col_tile(const Dims& dm) { return dm.bf16 ? 128 : dm.d; }
 template <typename T>
 int small_token_blocks(const Dims& dm, const SeqMeta& mt) {
   if (!fused_decode_supported<T>(dm.d, dm.G) || dm.d_out_v == 0) return 0;
+  if (dm.d_in < (sizeof(T) == 2 ? 128 : 64)) return 0;      // every wave needs a step of 32 (fp32: 16) input dims
   // 32-bit byte offsets inside a token tile and inside W
   if ((int64_t)dm.d_in * dm.d_out_v * (int)sizeof(T) >= (int64_t)1 << 31 || 64 * (int64_t)dm.D * (int)sizeof(T) >= (int64_t)1 << 31) return 0;
   const int bn = small_col_tile(dm);
@@ -329,11 +330,45 @@ int64_t small_max_slots(const Dims& dm, int batch, int64_t total_tokens) {
   return std::min<int64_t>(total_tokens / (dm.bf16 ? 32 : 16) + n, wgs / ct) + n;
 }
 
+// Streaming part of a decode call (retained heads, window) as workgroups of the product's launch.  slot_tokens:
+// tokens per partial slot of mt.s.sbase.  Chunks start at one round of a workgroup's rows and double until
+// at most max_wgs workgroups are left or they are max_chunk tokens long.
+template <typename T>
+Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* qq, const echokv_decode_extras* ex,
+                        const KvExtras& kx, float* po, float* pml, int b0, int slot_tokens, int max_wgs, int max_chunk,
+                        StreamMeta& mt, int* stream_step, int* win_slot0) {
+  Streams<T> s;
+  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1, ny = dm.g0 * (dm.G / gt);
+  AttnArgs<T>& r = s.ret;
+  r.k = (const T*)tg->k; r.v = (const T*)tg->v; r.ld = dm.m; r.col0 = 0; r.head0 = 0; r.row_mode = 0;
+  r.q = qq; r.H_q = dm.H_q; r.G = dm.G; r.d = dm.d; r.scale = dm.scale; r.part_o = po; r.part_ml = pml;
+  r.slot_tokens = slot_tokens; r.rope_cos = kx.rope_cos; r.rope_sin = kx.rope_sin; r.win = Window{kx.n_sink, kx.n_recent};
+  s.win = r;
+  for (r.split_tokens = kSlotTokens;; r.split_tokens *= 2) {
+    int acc = 0;
+    for (int b = 0; b < mt.s.n; ++b) { mt.cbase[b] = acc; acc += (mt.s.len[b] + r.split_tokens - 1) / r.split_tokens; }
+    mt.cbase[mt.s.n] = acc;
+    s.n_ret_chunks = acc;
+    if ((int64_t)acc * ny <= max_wgs || r.split_tokens >= max_chunk) break;
+  }
+  s.n_ret = s.n_ret_chunks * ny;
+  *stream_step = r.split_tokens / slot_tokens;
+  *win_slot0 = -1;
+  if (r.win.on()) {
+    *win_slot0 = mt.s.sbase[mt.s.n];          // the window's partials sit behind the regular slots
+    AttnArgs<T>& w = s.win;
+    w.k = (const T*)ex->win_k; w.v = (const T*)ex->win_v; w.ld = dm.D; w.row_mode = 3;
+    w.split_tokens = kSlotTokens; w.seq0 = b0; w.win_slot0 = *win_slot0;
+    s.n_win = mt.s.n * dm.H_kv * (dm.G / gt);
+  }
+  return s;
+}
+
 template <typename T>
 int decode_small(const Dims& dm, int tb, bool packed, const echokv_layer_cache* an, const echokv_layer_cache* tg,
                  const T* wk, const T* wv, const T* qq, const echokv_decode_extras* ex, const KvExtras& kx,
                  float* po, float* pml, int b0, const SeqMeta& mt0, int* stream_step, int* win_slot0, hipStream_t st) {
-  fsmall::Meta mt;
+  StreamMeta mt;
   mt.s = mt0;                                // (sbase counts slots of 16 tb tokens here)
   const int tok = 16 * tb;
   fsmall::Args<T> a;
@@ -341,36 +376,10 @@ int decode_small(const Dims& dm, int tb, bool packed, const echokv_layer_cache* 
   a.w[0] = wk; a.w[1] = wv; a.q = qq; a.part_o = po; a.part_ml = pml;
   a.D = dm.D; a.m = dm.m; a.d_out = dm.d_out_v; a.H_q = dm.H_q; a.G = dm.G; a.n_ret_heads = dm.g0; a.scale = dm.scale;
   a.rope_cos = kx.rope_cos; a.rope_sin = kx.rope_sin; a.n_sink = kx.n_sink; a.n_recent = kx.n_recent;
-  const int bn = sizeof(T) == 2 ? 128 : dm.d;
+  const int bn = small_col_tile(dm);
   a.n_ttiles = fill_tiles(mt.s, tok); a.n_col_tiles = (dm.d_out_v + bn - 1) / bn;
   a.n_fused = (a.n_ttiles * a.n_col_tiles + 7) / 8 * 8;
-  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1;
-  AttnArgs<T>& r = a.ret;
-  r.k = (const T*)tg->k; r.v = (const T*)tg->v; r.ld = dm.m; r.col0 = 0; r.head0 = 0; r.row_mode = 0;
-  r.q = qq; r.H_q = dm.H_q; r.G = dm.G; r.d = dm.d; r.scale = dm.scale; r.part_o = po; r.part_ml = pml;
-  r.slot_tokens = tok; r.rope_cos = kx.rope_cos; r.rope_sin = kx.rope_sin; r.win = Window{kx.n_sink, kx.n_recent};
-  a.win = r;
-  // chunks of one round of the workgroup's rows, longer ones once they outnumber the product's workgroups
-  const int ny = dm.g0 * (dm.G / gt);
-  r.split_tokens = kSlotTokens;
-  for (;;) {
-    int acc = 0;
-    for (int b = 0; b < mt.s.n; ++b) { mt.cbase[b] = acc; acc += (mt.s.len[b] + r.split_tokens - 1) / r.split_tokens; }
-    mt.cbase[mt.s.n] = acc;
-    a.n_ret_chunks = std::max(acc, 1);
-    if ((int64_t)acc * ny <= 256 || r.split_tokens >= 2048) break;
-    r.split_tokens *= 2;
-  }
-  a.n_ret = dm.g0 > 0 ? a.n_ret_chunks * ny : 0;
-  *stream_step = r.split_tokens / tok;
-  a.n_win = 0; *win_slot0 = -1;
-  if (r.win.on()) {
-    *win_slot0 = mt.s.sbase[mt.s.n];
-    AttnArgs<T>& w = a.win;
-    w.k = (const T*)ex->win_k; w.v = (const T*)ex->win_v; w.ld = dm.D; w.row_mode = 3;
-    w.split_tokens = kSlotTokens; w.seq0 = b0; w.win_slot0 = *win_slot0;
-    a.n_win = mt.s.n * dm.H_kv * (dm.G / gt);
-  }
+  a.streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, tok, 256, 2048, mt, stream_step, win_slot0);
   return launch_fused_decode_small<T>(a, mt, tb, packed, st);
 }
 
@@ -432,6 +441,31 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
         continue;
       }
     }
+    if constexpr (sizeof(T) == 2) {
+      if (fused && n_rec_heads > 0) {
+        // one launch: the product's tiles, then (they fill the units that have no tile left) the streaming
+        // workgroups.  Up to 1024 tokens each: longer ones would outlast the last tiles, shorter ones cost
+        // their reductions.
+        StreamMeta sm;
+        sm.s = mt;
+        int win_slot0 = -1;
+        const Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, 1024, 1024, sm, &stream_step, &win_slot0);
+        ProfScope prof;
+        int rc = prof.begin(0, st);
+        if (rc) return rc;
+        rc = launch_fused_decode<T>(dm.H_q, dm.H_kv, dm.d, dm.m, dm.d_out_v, dm.g0, dm.scale,
+                                    (const T*)an->k, (const T*)an->v, (const T*)tg->k, (const T*)tg->v, wk, wv, qq, po,
+                                    pml, sm, &fused_step, st, streams, (flags & ECHOKV_FLAG_W_PACKED) != 0, kx);
+        if (rc) return rc;
+        rc = prof.end();
+        if (rc) return rc;
+        rc = dm.out_bf16
+            ? merge_launch<T, bf16_t>(dm, po, pml, out, lse, b0, n_ret_heads, stream_step, fused_step, win_slot0, mt, st)
+            : merge_launch<T, float>(dm, po, pml, out, lse, b0, n_ret_heads, stream_step, fused_step, win_slot0, mt, st);
+        if (rc) return rc;
+        continue;
+      }
+    }
     if (n_ret_heads > 0) {
       AttnArgs<T> a;
       a.k = (const T*)tg->k; a.v = (const T*)tg->v; a.ld = dm.m; a.col0 = 0; a.head0 = 0;
@@ -453,11 +487,6 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
                                        (const float*)an->k, (const float*)an->v, (const float*)tg->k,
                                        (const float*)tg->v, (const float*)wk, (const float*)wv, qq,
                                        po, pml, mt, &fused_step, st, kx);
-        else
-          rc = launch_fused_decode<T>(dm.H_q, dm.H_kv, dm.d, dm.m, dm.d_out_v, dm.g0, dm.scale,
-                                      (const T*)an->k, (const T*)an->v, (const T*)tg->k,
-                                      (const T*)tg->v, wk, wv, qq, po,
-                                      pml, mt, &fused_step, st, (flags & ECHOKV_FLAG_W_PACKED) != 0, kx);
         if (rc) return rc;
         rc = prof.end();
         if (rc) return rc;
@@ -726,9 +755,11 @@ int mlp_impl(const Dims& dm, const echokv_layer_cache* an, const echokv_layer_ca
       if (rc) return rc;
       SeqMeta hm = mt;                       // H rows of sequence b start at its first slot
       for (int b = 0; b < hm.n; ++b) hm.start[b] = (int64_t)mt.sbase[b] * kSlotTokens;
+      StreamMeta sm;
+      sm.s = hm;
       rc = launch_fused_decode<T>(dm.H_q, dm.H_kv, dm.d, 0, dm.d_out, dm.g0, dm.scale, hk, hv,
-                                  (const T*)nullptr, (const T*)nullptr, w2k, w2v, qq, po, pml, hm,
-                                  &fused_step, st, false, KvExtras(), hidden);
+                                  (const T*)nullptr, (const T*)nullptr, w2k, w2v, qq, po, pml, sm,
+                                  &fused_step, st, Streams<T>(), false, KvExtras(), hidden);
       if (rc) return rc;
       rc = prof.end();
       if (rc) return rc;

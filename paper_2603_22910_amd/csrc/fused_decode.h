@@ -15,6 +15,7 @@
 //   4. joins the two waves of a 128-token slot and writes one split-K partial
 //      (max, sum, unnormalised o) per slot and head.
 // K_hat and V_hat live only in accumulator registers: they never reach LDS or HBM.
+// The retained heads' streaming attention and the window's run in further workgroups of the same launch.
 //
 // The predictor input row [anchor ; retained] (Eq. 3) is never materialised
 // either: the k-loop walks the anchor cache for the first D input dims and
@@ -22,6 +23,7 @@
 #pragma once
 #include "common.h"
 #include "fused_gemm.h"
+#include "attn_split.h"
 
 namespace echokv {
 
@@ -276,8 +278,14 @@ __device__ __forceinline__ Tile make_tile(const Args& a, const SeqMeta& meta, Pi
 }
 
 template <int HD, bool PACKED, bool ROPE>
-__global__ __launch_bounds__(NTHREADS) void fused_decode_kernel(Args a, SeqMeta meta) {
+__global__ __launch_bounds__(NTHREADS) void fused_decode_kernel(Args a, Streams<bf16_t> streams, StreamMeta smeta) {
   __shared__ __attribute__((aligned(1024))) Smem sm;
+  const int n_fused = (a.n_tiles + 7) / 8 * 8;
+  if ((int)blockIdx.x >= n_fused) {
+    stream_workgroup<bf16_t, HD, NWAVES, 8>(streams, smeta, blockIdx.x - n_fused, sm.st);
+    return;
+  }
+  const SeqMeta& meta = smeta.s;
   constexpr int HPW = WN / HD, CBH = HD / 16;
   Pipe<PACKED> pipe;
   const Tile t = make_tile<PACKED>(a, meta, pipe, sm.st, 2, 0);
@@ -470,12 +478,13 @@ template <typename T>
 inline int launch_fused_decode(int H_q, int H_kv, int d, int m, int d_out, int n_ret_heads,
                                float scale, const T* ka,
                                const T* va, const T* kr, const T* vr, const T* wk, const T* wv,
-                               const T* q, float* part_o, float* part_ml, SeqMeta& mt,
-                               int* fused_step, hipStream_t st, bool packed = false,
+                               const T* q, float* part_o, float* part_ml, StreamMeta& smt,
+                               int* fused_step, hipStream_t st, const Streams<T>& streams, bool packed = false,
                                const KvExtras& ex = KvExtras(), int x_width = 0) {
   if constexpr (sizeof(T) != 2) {
     return 6;
   } else {
+    SeqMeta& mt = smt.s;
     fused::Args a;
     a.rope_cos = ex.rope_cos; a.rope_sin = ex.rope_sin; a.n_sink = ex.n_sink; a.n_recent = ex.n_recent;
     a.s_out = nullptr; a.s_ld = 0;
@@ -487,12 +496,12 @@ inline int launch_fused_decode(int H_q, int H_kv, int d, int m, int d_out, int n
     a.n_ret_heads = n_ret_heads; a.scale = scale;
     a.n_col_tiles = (a.d_out + fused::BN - 1) / fused::BN;
     a.n_tiles = fused_fill_tiles(mt) * a.n_col_tiles;
-    const int grid = ((a.n_tiles + 7) / 8) * 8;
+    const int grid = ((a.n_tiles + 7) / 8) * 8 + streams.n_ret + streams.n_win;
     const dim3 g(grid), blk(fused::NTHREADS);
     const bool rope = ex.rope_cos != nullptr;
 #define ECHOKV_FUSED_CASE(HD_, PK_) \
-    do { if (rope) hipLaunchKernelGGL((fused::fused_decode_kernel<HD_, PK_, true>), g, blk, 0, st, a, mt); \
-         else hipLaunchKernelGGL((fused::fused_decode_kernel<HD_, PK_, false>), g, blk, 0, st, a, mt); } while (0)
+    do { if (rope) hipLaunchKernelGGL((fused::fused_decode_kernel<HD_, PK_, true>), g, blk, 0, st, a, streams, smt); \
+         else hipLaunchKernelGGL((fused::fused_decode_kernel<HD_, PK_, false>), g, blk, 0, st, a, streams, smt); } while (0)
     if (d == 128 && packed) ECHOKV_FUSED_CASE(128, true);
     else if (d == 128) ECHOKV_FUSED_CASE(128, false);
     else if (packed) ECHOKV_FUSED_CASE(64, true);

@@ -39,12 +39,6 @@ using fused::KExtra; using fused::MAXPAIR; using fused::u32x4_t; using fused::rs
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int NWAVES = 8, NTHREADS = 64 * NWAVES, KSPLIT = 4;
 
-// Sequences of a launch with the prefix sum of the streaming chunks per sequence as well.
-struct Meta {
-  SeqMeta s;                                  // tbase: token tiles; sbase: slots of 16 * TB tokens
-  int32_t cbase[kMaxSeqPerLaunch + 1];        // streaming chunks of AttnArgs::split_tokens
-};
-
 template <typename T>
 struct Args {
   const T* xa[2]; const T* xr[2];             // anchor / retained cache K, V
@@ -55,8 +49,8 @@ struct Args {
   int32_t n_ttiles, n_col_tiles;
   const float* rope_cos; const float* rope_sin;
   int32_t n_sink, n_recent;
-  AttnArgs<T> ret, win;                       // retained heads; window rows (all KV heads)
-  int32_t n_fused, n_ret_chunks, n_ret, n_win;   // workgroups: product, chunks, retained (chunks * heads ...), window
+  Streams<T> streams;                         // retained heads and window rows, behind the product's workgroups
+  int32_t n_fused;                            // workgroups of the product
 };
 
 template <typename T, int HD> struct Cfg {
@@ -210,8 +204,7 @@ __device__ __forceinline__ void product(Acc<T, HD, TB>& acc, const Io& io, int k
                                         Between between) {
   using C = Cfg<T, HD>;
   constexpr int NST = 2;
-  const int n = (io.d_in / C::KS - kq + KSPLIT - 1) / KSPLIT;      // (0: fewer steps than waves)
-  const int first = n > 0 ? kq : 0;            // a wave without a step requests step 0: every request is of a step that exists
+  const int n = (io.d_in / C::KS - kq + KSPLIT - 1) / KSPLIT;      // at least 1: the caller sees to KSPLIT steps and more
   auto clear = [&]() {
 #pragma unroll
     for (int i = 0; i < C::NCG * C::VW; ++i)
@@ -224,10 +217,10 @@ __device__ __forceinline__ void product(Acc<T, HD, TB>& acc, const Io& io, int k
   if constexpr (TB >= 4) {                     // (no registers left to overlap the two)
     between();
     clear();
-    if (n <= 0) return;
+    if (n <= 0) return;                        // (never; without the exit the registers do not suffice)
   }
 #pragma unroll
-  for (int u = 0; u < NST; ++u) fetch<T, HD, TB, PACKED>(st[u], io, first + KSPLIT * max(0, min(u, n - 1)), lane, n0);
+  for (int u = 0; u < NST; ++u) fetch<T, HD, TB, PACKED>(st[u], io, kq + KSPLIT * min(u, n - 1), lane, n0);
   if constexpr (TB < 4) {
     between();
     clear();
@@ -383,7 +376,7 @@ __device__ __forceinline__ void value_shares(Acc<T, HD, TB>& acc, Smem<TB>& sm, 
 }
 
 template <typename T, int HD, int TB, bool PACKED, bool ROPE>
-__device__ __forceinline__ void fused_tile(const Args<T>& a, const Meta& meta, Smem<TB>& sm, int wg) {
+__device__ __forceinline__ void fused_tile(const Args<T>& a, const StreamMeta& meta, Smem<TB>& sm, int wg) {
   using C = Cfg<T, HD>;
   constexpr int TOK = 16 * TB;
   const int ttile = wg % a.n_ttiles, ctile = wg / a.n_ttiles;
@@ -463,8 +456,8 @@ __device__ __forceinline__ void fused_tile(const Args<T>& a, const Meta& meta, S
 }
 
 template <typename T, int HD, int TB, bool PACKED, bool ROPE>
-__global__ __launch_bounds__(NTHREADS) void fused_decode_small_kernel(Args<T> a, Meta meta) {
-  constexpr int kStream = attn_split_smem_bytes<T, HD * (int)sizeof(T) / 16, 4, NWAVES>();
+__global__ __launch_bounds__(NTHREADS) void fused_decode_small_kernel(Args<T> a, StreamMeta meta) {
+  constexpr int kStream = stream_smem_bytes<T, HD, NWAVES>();
   constexpr int kTile = (int)sizeof(Smem<TB>) + NWAVES * exchange_bytes<TB, PACKED>() + (ROPE ? RopeTile<HD, TB>::kBytes : 0);
   constexpr int kBytes = kTile > kStream ? kTile : kStream;
   __shared__ __attribute__((aligned(16))) char smem[kBytes];
@@ -478,23 +471,13 @@ __global__ __launch_bounds__(NTHREADS) void fused_decode_small_kernel(Args<T> a,
     fused_tile<T, HD, TB, PACKED, ROPE>(a, meta, *reinterpret_cast<Smem<TB>*>(smem), logical);
     return;
   }
-  wg -= a.n_fused;
-  const bool ret = wg < a.n_ret;
-  if (!ret) wg -= a.n_ret;
-  const AttnArgs<T> s = ret ? a.ret : a.win;
-  const int per = ret ? a.n_ret_chunks : meta.s.n, x = wg % per, y = wg / per;
-  const int b = ret ? find_seq(meta.cbase, meta.s.n, x) : x;
-  const int chunk = ret ? x - meta.cbase[b] : 0;
-  constexpr int LPR = HD * (int)sizeof(T) / 16;
-  if (a.G % 4 == 0) attn_split_body<T, LPR, 4, NWAVES>(s, meta.s, b, chunk, y, smem);
-  else if (a.G % 2 == 0) attn_split_body<T, LPR, 2, NWAVES>(s, meta.s, b, chunk, y, smem);
-  else attn_split_body<T, LPR, 1, NWAVES>(s, meta.s, b, chunk, y, smem);
+  stream_workgroup<T, HD, NWAVES, 4>(a.streams, meta, wg - a.n_fused, smem);
 }
 
 }  // namespace fsmall
 
 // tb: token blocks of 16 per workgroup: 2 or 4 (bf16), 1 or 2 (fp32).
 template <typename T>
-int launch_fused_decode_small(const fsmall::Args<T>& a, const fsmall::Meta& mt, int tb, bool packed, hipStream_t st);
+int launch_fused_decode_small(const fsmall::Args<T>& a, const StreamMeta& mt, int tb, bool packed, hipStream_t st);
 
 }  // namespace echokv

@@ -24,7 +24,8 @@ CASES = [
     (8, 4, 128, 128, "bf16", (15000, 64, 65)),          # over it: the 256 x 256 kernel
     (10, 5, 64, 128, "bf16", (65, 129, 3)),             # three predicted heads of 64: half of the last tile is empty
     (16, 2, 128, 64, "bf16", (200, 63)),                # split head (r = 64), G = 8
-    (4, 1, 64, 0, "bf16", (100,)),                      # d_in = 64: two steps for four waves
+    (4, 1, 64, 0, "bf16", (100,)),                      # d_in = 64: fewer steps than waves, the 256 x 256 kernel
+    (4, 2, 64, 0, "bf16", (100,)),                      # d_in = 128: one step for each wave
     (8, 8, 64, 256, "f32", (15, 16, 17, 1)),            # 4 column tiles, edges of a 16-token tile
     (8, 8, 64, 256, "f32", (1024,)),                    # 256 workgroups: the last with 16-token tiles
     (8, 8, 64, 256, "f32", (1025, 700)),
