@@ -19,9 +19,13 @@
 //   phase 2  MFMA W0 Xb | read 3/4 W1         | copy Xa of tile t+2
 //   phase 3  MFMA W1 Xb | read 3/4 W0 of t+1  | copy W0 of tile t+2 -> wait for Xb W1 of t+1, barrier: Xb, W1 are free
 //   phase 4  MFMA W1 Xa | read 1/4 W0, Xa of t+1 | copy Xb of tile t+2
-// Reads (6 KB per wave and phase: 384 of a phase's 512 cycles at the LDS's 128 bytes per clock) and copies (2 per
-// wave and phase, behind the first and third quarter of the MFMAs) are spread evenly: all reads of a tile
-// in two of its phases and all copies in a burst behind a barrier cost 350 cycles per barrier.
+// Reads (6 KB per wave and phase), copies (2 per wave and phase) and the scalar work for them are spread over the phases and,
+// by fences and scheduling groups, between the MFMAs of a phase: two MFMAs, the reads' first third, two MFMAs ..., then
+// at most five scalar or vector instructions per MFMA.  The two waves of a SIMD run in step, so what stands in one place of
+// the loop stops the matrix pipe for both.  All reads of a phase ahead of its MFMAs and ~20 scalar instructions
+// around each copy cost 10 % (4000 tokens, d_in 6144, 2048 predicted dims, one round of workgroups: 256 -> 233 us, packed W 236 -> 211;
+// 8 x 4096 tokens 1297 -> 1221); reads and copies spread over twelve MFMAs +0 / +5 %, reads behind each other MFMA +1-3 %; all
+// reads of a tile in two of its phases and all copies in a burst behind a barrier cost 350 cycles per barrier.
 // (a, b) = (0, 1) for the even tiles of a pass and (1, 0) for the odd ones: the half read ahead in phase 4 goes to the
 // registers that phase 3 has left, so nothing is copied and 80 registers hold all fragments.
 //
@@ -29,13 +33,11 @@
 // come from the LDS transpose read (16 lanes read 4 k x 16 columns, each ends up with one column's 4 k);
 // packed W ([d_out, d_in]) is read like X.
 //
-// What bounds it: power (the clock falls as the pipe fills), and the LDS port, which at the full MFMA rate 192 KB of
-// fragment reads and 64 KB of copies per tile would occupy completely: the matrix pipe is busy 65 % of the cycles, at a
-// higher clock than the 70 % of four waves and the larger MFMA.  Whole calls, four waves of 128 x 128 with
-// 32 x 32 x 16 -> this: 8 x 4096 tokens, d_in 6144, 2048 predicted dims 1328 -> 1273 us; 32 sequences of 1K-64K tokens, packed W,
-// 19.0 -> 17.4 ms; 8 sequences of 2K-36K, d_in 1408, 640 predicted dims (half of the last column tile is idle waves)
-// 431 -> 368 us.  Tried: all reads of a part in one phase and all copies behind a barrier 2-4 % slower; s_setprio around the MFMAs
-// 3 % slower; without barriers (wrong results) 9 % fewer cycles but 4 % less time, without the copies 15 % less time.
+// What bounds it: power.  The matrix pipe is busy 70 % of the cycles at the clock that leaves (1.85 GHz); the rest is
+// waits around the two barriers of a tile and the epilogues.  Whole calls, four waves of 128 x 128 with 32 x 32 x 16 -> this:
+// 8 x 4096 tokens, d_in 6144, 2048 predicted dims 1336 -> 1221 us, packed W 1382 -> 1196; 4000 tokens 243 -> 233,
+// packed 227 -> 211; 3 x 6000 tokens, d_in 1024, 1024 predicted dims 128 -> 114.  Tried: s_setprio around the MFMAs
+// 3 % slower.
 //
 // The LDS reads of the loop are instructions with waits of their own: in builtin form the compiler puts
 // them behind every outstanding copy (s_waitcnt vmcnt(0)), which would drain the pipeline in every phase.
@@ -138,33 +140,37 @@ template <typename P> __device__ __forceinline__ P pick(bool c, P a, P b) {
   const uint64_t m = c ? ~0ull : 0ull;
   return (P)(((uint64_t)a & m) | ((uint64_t)b & ~m));
 }
-struct KTile { int pass, kt; };
-__device__ __forceinline__ KTile k_tile_of(const Operands& op, int t) {
-  KTile r;
+// Where the copies of one k-tile come from: worked out once per tile, uniform.
+struct Src {
+  const bf16_t* x; uint32_t ld2; int xoff;      // token tile in the anchor or retained cache, pitch and dim in bytes
+  const bf16_t* w; int woff;                    // packed: dim in bytes, row-major: first row's offset in bytes
+};
+template <bool PACKED>
+__device__ __forceinline__ Src source_of(const Operands& op, int t) {
+  Src s;
   int i = min(t, op.total - 1);              // past the end: the last tile again (lands, is never multiplied)
-  r.pass = i >= op.nk ? 1 : 0;
-  i -= r.pass ? op.nk : 0;
+  const bool second = i >= op.nk;
+  i -= second ? op.nk : 0;
   i += op.rot;
-  r.kt = i >= op.nk ? i - op.nk : i;
-  return r;
+  const int kt = i >= op.nk ? i - op.nk : i;
+  const bool anchor = kt < op.nka;           // anchor dims first, then retained dims (Eq. 3): uniform selects
+  s.x = pick(second, pick(anchor, op.xa[1], op.xr[1]), pick(anchor, op.xa[0], op.xr[0]));
+  s.ld2 = pick(anchor, (uint32_t)op.D, (uint32_t)op.m) * 2;
+  s.xoff = (anchor ? kt : kt - op.nka) * (BK * 2);
+  s.w = pick(second, op.w[1], op.w[0]);
+  s.woff = PACKED ? kt * (BK * 2) : kt * BK * op.d_out * 2;
+  return s;
 }
-// Copy i (0, 1) of this wave's share of X part h / W part h of tile t.
-__device__ __forceinline__ void copy_x(char* smem, const Operands& op, const Copies& c, int t, int h, int i, int wave) {
-  const KTile k = k_tile_of(op, t);
-  const bool anchor = k.kt < op.nka;         // anchor dims first, then retained dims (Eq. 3): uniform selects
-  const rsrc_t r = make_rsrc(pick(k.pass != 0, pick(anchor, op.xa[1], op.xr[1]), pick(anchor, op.xa[0], op.xr[0])));
-  const uint32_t ld2 = pick(anchor, (uint32_t)op.D, (uint32_t)op.m) * 2;
-  const int soff = (anchor ? k.kt : k.kt - op.nka) * (BK * 2);
-  char* dst = smem + (t & 1) * kStage + h * kPart + (2 * wave + i) * 1024;
-  copy_to_lds(r, dst, __umul24(min(c.xrow + 32 * h + 8 * i, (uint32_t)op.last), ld2) + (c.ch ^ (i * 64)), soff);      // (row < 256, pitch < 2^24)
+// Copy i (0, 1) of this wave's share of X part h / W part h of a tile (stage = its number % 2).
+__device__ __forceinline__ void copy_x(char* smem, const Operands& op, const Copies& c, const Src& s, int stage, int h, int i, int wave) {
+  char* dst = smem + stage * kStage + h * kPart + (2 * wave + i) * 1024;
+  copy_to_lds(make_rsrc(s.x), dst, __umul24(min(c.xrow + 32 * h + 8 * i, (uint32_t)op.last), s.ld2) + (c.ch ^ (i * 64)), s.xoff);      // (row < 256, pitch < 2^24)
 }
 template <bool PACKED>
-__device__ __forceinline__ void copy_w(char* smem, const Operands& op, const Copies& c, int t, int h, int i, int wave) {
-  const KTile k = k_tile_of(op, t);
-  const rsrc_t r = make_rsrc(pick(k.pass != 0, op.w[1], op.w[0]));
-  char* dst = smem + (t & 1) * kStage + (2 + h) * kPart + (2 * wave + i) * 1024;
-  if constexpr (PACKED) copy_to_lds(r, dst, c.w[h][i], k.kt * (BK * 2));
-  else copy_to_lds(r, dst, c.w[h][0], (k.kt * BK + i * 4) * op.d_out * 2);
+__device__ __forceinline__ void copy_w(char* smem, const Operands& op, const Copies& c, const Src& s, int stage, int h, int i, int wave) {
+  char* dst = smem + stage * kStage + (2 + h) * kPart + (2 * wave + i) * 1024;
+  if constexpr (PACKED) copy_to_lds(make_rsrc(s.w), dst, c.w[h][i], s.woff);
+  else copy_to_lds(make_rsrc(s.w), dst, c.w[h][0], s.woff + i * 8 * op.d_out);
 }
 
 // Fragments: X half: 2 k-steps of 32 x 2 blocks of 16 tokens; W half: 2 k-steps x 4 blocks of 16 columns.  A lane
@@ -247,27 +253,41 @@ __device__ __forceinline__ bf16x8_t frag(const WFrag<false>& f, int kk, int b) {
 struct Acc { floatx4_t v[8][4]; };           // [column block][token block]
 // Reads are issued ahead of a phase's MFMAs and waited for behind them: nothing crosses.
 __device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
-// Sixteen MFMAs of one (W half, X half); `copy(i)` is called behind the first and third quarter.
-template <bool SWAP, bool PACKED, class Copy>
-__device__ __forceinline__ void mma16(Acc& acc, const WFrag<PACKED>& w, const XFrag& x, int wh, int xh, Copy copy) {
+// Sixteen MFMAs of one (W half, X half), with the phase's LDS reads in up to three parts (read(0 .. 2)) and
+// its two copies (copy(0 .. 1)) with whatever scalar work there is dealt out between them: the two waves of a SIMD run in
+// step, so a burst of other instructions leaves the matrix pipe idle, while a few behind every MFMA are free.
+template <bool SWAP, bool PACKED, class Read, class Copy>
+__device__ __forceinline__ void mma16(Acc& acc, const WFrag<PACKED>& w, const XFrag& x, int wh, int xh, Read read, Copy copy) {
+  auto mma = [&](int i) __attribute__((always_inline)) {
+    const int kk = i >> 3, t = (i >> 2) & 1, b = i & 3;
+    const bf16x8_t wf = frag(w, kk, b), xf = __builtin_bit_cast(bf16x8_t, x.v[kk][t]);
+    floatx4_t& d = acc.v[4 * wh + b][2 * xh + t];
+    d = SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, xf, d, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, wf, d, 0, 0, 0);
+  };
+#pragma unroll
+  for (int i = 0; i < 6; i += 2) {
+    keep_order();
+    mma(i);
+    mma(i + 1);
+    asm volatile("" : "+v"(acc.v[4 * wh + (i & 3)][2 * xh + ((i >> 2) & 1)]), "+v"(acc.v[4 * wh + (i & 3) + 1][2 * xh + ((i >> 2) & 1)]));
+    keep_order();
+    read(i >> 1);
+  }
+  keep_order();
+  copy(0);
+  copy(1);
+#pragma unroll
+  for (int i = 6; i < 16; ++i) mma(i);
+#pragma unroll
+  for (int i = 6; i < 16; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);       // one MFMA
+    __builtin_amdgcn_sched_group_barrier(0x4, 4, 0);       // up to four scalar instructions
+    __builtin_amdgcn_sched_group_barrier(0x2, 1, 0);       // one vector instruction
+    if (i == 8 || i == 12) __builtin_amdgcn_sched_group_barrier(0x10, 1, 0);      // a copy
+  }
   keep_order();
 #pragma unroll
-  for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const bf16x8_t wf = frag(w, kk, b), xf = __builtin_bit_cast(bf16x8_t, x.v[kk][t]);
-        floatx4_t& d = acc.v[4 * wh + b][2 * xh + t];
-        d = SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, xf, d, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, wf, d, 0, 0, 0);
-      }
-      if (t == 0) {
-        keep_order();
-        copy(kk);
-        keep_order();
-      }
-    }
-  keep_order();
+  for (int b = 0; b < 4; ++b) asm volatile("" : "+v"(acc.v[4 * wh + b][2 * xh]), "+v"(acc.v[4 * wh + b][2 * xh + 1]));
 }
 
 __device__ __forceinline__ void barrier() {
@@ -290,25 +310,36 @@ template <bool PACKED> struct Pipe {
   __device__ __forceinline__ void begin() {
     make_copies<PACKED>(cp, op, wave, lane);
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < 2; ++t) {
+      const Src s = source_of<PACKED>(op, t);
 #pragma unroll
       for (int part = 0; part < 4 - t; ++part)       // Xa, W0, Xb, W1: the order in which they are waited for
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          if (part & 1) copy_w<PACKED>(smem, op, cp, t, part >> 1, i, wave);
-          else copy_x(smem, op, cp, t, t ^ (part >> 1), i, wave);
+          if (part & 1) copy_w<PACKED>(smem, op, cp, s, t, part >> 1, i, wave);
+          else copy_x(smem, op, cp, s, t, t ^ (part >> 1), i, wave);
         }
+    }
   }
 
   // Phases 1-4 of tile t, PAR = its number in the pass % 2 (see the top of the file).  IDLE: the wave's
   // columns do not exist, it only copies and meets the others.
   template <bool SWAP, int PAR, bool IDLE>
-  __device__ __forceinline__ void tile(Acc& acc, XFrag (&x)[2], WFrag<PACKED>& w0, WFrag<PACKED>& w1, int t) {
+  __device__ __forceinline__ void tile(Acc& acc, XFrag (&x)[2], WFrag<PACKED>& w0, WFrag<PACKED>& w1, int t, Src& src) {
     constexpr int A = PAR, B = PAR ^ 1;
-    auto w1_next = [&](int i) __attribute__((always_inline)) { copy_w<PACKED>(smem, op, cp, t + 1, 1, i, wave); };
-    auto xa_next = [&](int i) __attribute__((always_inline)) { copy_x(smem, op, cp, t + 2, A, i, wave); };
-    auto w0_next = [&](int i) __attribute__((always_inline)) { copy_w<PACKED>(smem, op, cp, t + 2, 0, i, wave); };
-    auto xb_next = [&](int i) __attribute__((always_inline)) { copy_x(smem, op, cp, t + 2, B, i, wave); };
+    const int st = t & 1;
+    Src s2;                                  // of tile t + 2; src: of tile t + 1
+    auto w1_next = [&](int i) __attribute__((always_inline)) {
+      copy_w<PACKED>(smem, op, cp, src, st ^ 1, 1, i, wave);
+      if (i == 1) {
+        int t2 = t + 2;
+        asm volatile("" : "+s"(t2));         // (worked out here, between MFMAs, and nowhere else)
+        s2 = source_of<PACKED>(op, t2);
+      }
+    };
+    auto xa_next = [&](int i) __attribute__((always_inline)) { copy_x(smem, op, cp, s2, st, A, i, wave); };
+    auto w0_next = [&](int i) __attribute__((always_inline)) { copy_w<PACKED>(smem, op, cp, s2, st, 0, i, wave); };
+    auto xb_next = [&](int i) __attribute__((always_inline)) { copy_x(smem, op, cp, s2, st, B, i, wave); };
     if constexpr (IDLE) {
       w1_next(0); w1_next(1);
       wait_copies<4>();
@@ -318,26 +349,35 @@ template <bool PACKED> struct Pipe {
       barrier();
       xb_next(0); xb_next(1);
     } else {
-      read_x<B>(x[B], ln.x);
-      read_w<1, 0>(w1, ln);
-      mma16<SWAP, PACKED>(acc, w0, x[A], 0, A, w1_next);
+      mma16<SWAP, PACKED>(acc, w0, x[A], 0, A, [&](int i) __attribute__((always_inline)) {
+        if (i == 0) read_x<B>(x[B], ln.x);
+        if (i == 1) read_w<1, 0>(w1, ln);
+      }, w1_next);
       wait_x(x[B]);
       wait_copies<4>();                      // Xa, W0 of tile t + 1 (this wave's copies; the barrier: everyone's)
       barrier();
-      read_w<1, 1>(w1, ln); read_w<1, 2>(w1, ln); read_w<1, 3>(w1, ln);
-      mma16<SWAP, PACKED>(acc, w0, x[B], 0, B, xa_next);
+      mma16<SWAP, PACKED>(acc, w0, x[B], 0, B, [&](int i) __attribute__((always_inline)) {
+        if (i == 0) read_w<1, 1>(w1, ln);
+        if (i == 1) read_w<1, 2>(w1, ln);
+        if (i == 2) read_w<1, 3>(w1, ln);
+      }, xa_next);
       wait_w(w1);
       ln.next_stage();
-      read_w<0, 0>(w0, ln); read_w<0, 1>(w0, ln); read_w<0, 2>(w0, ln);
-      mma16<SWAP, PACKED>(acc, w1, x[B], 1, B, w0_next);
+      mma16<SWAP, PACKED>(acc, w1, x[B], 1, B, [&](int i) __attribute__((always_inline)) {
+        if (i == 0) read_w<0, 0>(w0, ln);
+        if (i == 1) read_w<0, 1>(w0, ln);
+        if (i == 2) read_w<0, 2>(w0, ln);
+      }, w0_next);
       wait_copies<4>();                      // Xb, W1 of tile t + 1
       barrier();
-      read_w<0, 3>(w0, ln);
-      read_x<B>(x[B], ln.x);                 // (the next tile's Xa is the part that is Xb here)
-      mma16<SWAP, PACKED>(acc, w1, x[A], 1, A, xb_next);
+      mma16<SWAP, PACKED>(acc, w1, x[A], 1, A, [&](int i) __attribute__((always_inline)) {
+        if (i == 0) read_w<0, 3>(w0, ln);
+        if (i == 1) read_x<B>(x[B], ln.x);   // (the next tile's Xa is the part that is Xb here)
+      }, xb_next);
       wait_w(w0);
       wait_x(x[B]);
     }
+    src = s2;
   }
   template <bool SWAP, bool IDLE>
   __device__ __forceinline__ void tiles(Acc& acc, int t0) {
@@ -351,11 +391,12 @@ template <bool PACKED> struct Pipe {
     }
     const int t1 = t0 + op.nk;
     int t = t0;
+    Src src = source_of<PACKED>(op, t0 + 1);
     for (; t + 1 < t1; t += 2) {
-      tile<SWAP, 0, IDLE>(acc, x, w0, w1, t);
-      tile<SWAP, 1, IDLE>(acc, x, w0, w1, t + 1);
+      tile<SWAP, 0, IDLE>(acc, x, w0, w1, t, src);
+      tile<SWAP, 1, IDLE>(acc, x, w0, w1, t + 1, src);
     }
-    if (t < t1) tile<SWAP, 0, IDLE>(acc, x, w0, w1, t);
+    if (t < t1) tile<SWAP, 0, IDLE>(acc, x, w0, w1, t, src);
   }
 
   // One pass: k-tiles [t0, t0 + nk).  Every wave's copies of tile t0 have landed and a barrier has passed
