@@ -234,18 +234,133 @@ template <typename T> struct Streams {
 };
 template <typename T, int HD, int NWAVES>
 constexpr int stream_smem_bytes() { return attn_split_smem_bytes<T, HD * (int)sizeof(T) / 16, 4, NWAVES>(); }
+// Chunk x and head group y of workgroup wg, n chunks x ny groups: the groups of a chunk follow each other 8
+// workgroups apart, on one XCD and at one time, so that its L2 has the chunk's rows (whose heads lie side by side) and rotary
+// tables already.  One head after the other, 131072 tokens with four retained heads read their tables, half
+// the bytes of the rows, four times from memory (the whole call 368 us, like this 351).
+__device__ __forceinline__ void stream_item(int wg, int n, int ny, int& x, int& y) {
+  const int full = n & ~7;
+  if (wg < full * ny) {
+    const int r = wg % (8 * ny);
+    x = wg / (8 * ny) * 8 + (r & 7); y = r >> 3;
+  } else {
+    wg -= full * ny;
+    x = full + wg % (n - full); y = wg / (n - full);
+  }
+}
 template <typename T, int HD, int NWAVES, int UN>
 __device__ __forceinline__ void stream_workgroup(const Streams<T>& st, const StreamMeta& meta, int wg, char* smem) {
   const bool ret = wg < st.n_ret;
   if (!ret) wg -= st.n_ret;
   const AttnArgs<T> a = ret ? st.ret : st.win;
-  const int per = ret ? st.n_ret_chunks : meta.s.n, x = wg % per, y = wg / per;
+  const int n = ret ? st.n_ret_chunks : meta.s.n;
+  int x, y;
+  stream_item(wg, n, (ret ? st.n_ret : st.n_win) / n, x, y);
   const int b = ret ? find_seq(meta.cbase, meta.s.n, x) : x;
   const int chunk = ret ? x - meta.cbase[b] : 0;
   constexpr int LPR = HD * (int)sizeof(T) / 16;
   if (a.G % 4 == 0) attn_split_body<T, LPR, 4, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
   else if (a.G % 2 == 0) attn_split_body<T, LPR, 2, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
   else attn_split_body<T, LPR, 1, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
+}
+
+// ---------------------------------------------------------------------------
+// Scores only, over heads stored as rows (the target layer's retained heads), one workgroup per chunk and y as in
+// attn_split_body: S^T[h, slot * 128 + j] = scale * q_h . rot_j(k_j) for GT query heads of one KV
+// head; base-2 logits if the caller folds log2(e) into the scale.
+// What bounds it: with the rotary tables, their 64 bytes per lane and row beside the row's own.  A lane therefore holds
+// the 8 dims at 8 li and their rotation partners at d / 2 + 8 li (d / 16 lanes per row): with 8 dims per lane both
+// halves of a row loaded the same table entries, and exchanged the partners by shuffle.
+// A wave's UN x (64 / LPR) rows are consecutive tokens, and each lane of a row stores the sums of its own share of the
+// (row, query head) pairs: two stores instead of 16 of 16 bytes each.  As a kernel of its own, 131072 tokens with four retained heads
+and rope: 61 us, and 18 for the window's; here the call went from 376 to 351 us, short ones (4 x 2000-9000 tokens) from 113 to 88.
+// ---------------------------------------------------------------------------
+template <int HD, int GT, int NWAVES>
+__device__ __forceinline__ void row_scores_body(const AttnArgs<bf16_t>& a, float* s_out, int64_t s_ld, const SeqMeta& meta,
+                                                int b, int chunk, int y) {
+  constexpr int LPR = HD / 16, RPW = 64 / LPR, UN = 4, ROWS = UN * RPW;      // rows of a wave and turn
+  constexpr int NS = (UN * GT + LPR - 1) / LPR;
+  const int L = meta.len[b];
+  const int gchunks = a.G / GT, hl = y / gchunks;
+  const int qh0 = (a.head0 + hl) * a.G + (y % gchunks) * GT;
+  const int lane = threadIdx.x & 63, li = lane % LPR, rl = lane / LPR;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int jend = min(L, chunk * a.split_tokens + a.split_tokens);
+  const bool rope = a.rope_cos != nullptr;
+  float q0[GT][8], q1[GT][8];
+#pragma unroll
+  for (int g = 0; g < GT; ++g) {
+    const bf16_t* q = a.q + ((int64_t)b * a.H_q + qh0 + g) * HD + 8 * li;
+    load16<bf16_t>(q, q0[g]);
+    load16<bf16_t>(q + HD / 2, q1[g]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { q0[g][i] *= a.scale; q1[g][i] *= a.scale; }
+  }
+  const bf16_t* k = a.k + meta.start[b] * a.ld + a.col0 + hl * HD + 8 * li;
+  const float* ct = a.rope_cos + 8 * li;
+  const float* st = a.rope_sin + 8 * li;
+  float* dst = s_out + (int64_t)qh0 * s_ld + (int64_t)meta.sbase[b] * kSlotTokens;
+  for (int jb = chunk * a.split_tokens + wave * ROWS; jb < jend; jb += NWAVES * ROWS) {
+    float v[NS];
+#pragma unroll
+    for (int n = 0; n < NS; ++n) v[n] = 0.f;
+    uint4 r0[UN], r1[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const bf16_t* row = k + (int64_t)min(jb + u * RPW + rl, jend - 1) * a.ld;
+      r0[u] = *reinterpret_cast<const uint4*>(row);
+      r1[u] = *reinterpret_cast<const uint4*>(row + HD / 2);
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      float k0[8], k1[8];
+      unpack_bf16x8(r0[u], k0);
+      unpack_bf16x8(r1[u], k1);
+      if (rope) {
+        const int64_t t = (int64_t)min(jb + u * RPW + rl, jend - 1) * (HD / 2);
+#pragma unroll
+        for (int i = 0; i < 8; i += 4) {
+          const float4 c4 = *reinterpret_cast<const float4*>(ct + t + i), s4 = *reinterpret_cast<const float4*>(st + t + i);
+          const float c[4] = {c4.x, c4.y, c4.z, c4.w}, s[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x0 = k0[i + e], x1 = k1[i + e];
+            k0[i + e] = fmaf(x0, c[e], -x1 * s[e]);
+            k1[i + e] = fmaf(x1, c[e], x0 * s[e]);
+          }
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < GT; ++g) {
+        float sc = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sc = fmaf(q0[g][i], k0[i], fmaf(q1[g][i], k1[i], sc));
+        sc = row_sum<LPR>(sc);
+        const int n = u * GT + g;                // lane n % LPR of the row stores pair n
+        v[n / LPR] = li == n % LPR ? sc : v[n / LPR];
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+      const int pair = n * LPR + li, j = jb + (pair / GT) * RPW + rl;
+      if (pair < UN * GT && j < jend) dst[(int64_t)(pair % GT) * s_ld + j] = v[n];
+    }
+  }
+}
+// Workgroup wg of the retained heads' scores (Streams::ret), then of the window.
+template <int HD, int NWAVES>
+__device__ __forceinline__ void score_stream_workgroup(const Streams<bf16_t>& st, const StreamMeta& meta, int wg, float* s_out,
+                                                       int64_t s_ld, char* smem) {
+  if (wg >= st.n_ret) {
+    stream_workgroup<bf16_t, HD, NWAVES, 4>(st, meta, wg, smem);
+    return;
+  }
+  int x, y;
+  stream_item(wg, st.n_ret_chunks, st.n_ret / st.n_ret_chunks, x, y);
+  const int b = find_seq(meta.cbase, meta.s.n, x), chunk = x - meta.cbase[b];
+  if (st.ret.G % 4 == 0) row_scores_body<HD, 4, NWAVES>(st.ret, s_out, s_ld, meta.s, b, chunk, y);
+  else if (st.ret.G % 2 == 0) row_scores_body<HD, 2, NWAVES>(st.ret, s_out, s_ld, meta.s, b, chunk, y);
+  else row_scores_body<HD, 1, NWAVES>(st.ret, s_out, s_ld, meta.s, b, chunk, y);
 }
 
 }  // namespace echokv

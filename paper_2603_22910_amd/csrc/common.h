@@ -54,16 +54,19 @@ template <> struct Elem<float> {
 };
 
 // 16-byte vector of T unpacked to floats
+__device__ __forceinline__ void unpack_bf16x8(uint4 raw, float (&out)[8]) {
+  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    out[2 * i] = __uint_as_float(w[i] << 16);
+    out[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+  }
+}
 template <typename T>
 __device__ __forceinline__ void load16(const T* p, float (&out)[Elem<T>::kVec]) {
   uint4 raw = *reinterpret_cast<const uint4*>(p);
   if constexpr (sizeof(T) == 2) {
-    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      out[2 * i] = __uint_as_float(w[i] << 16);
-      out[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
+    unpack_bf16x8(raw, out);
   } else {
     out[0] = __uint_as_float(raw.x); out[1] = __uint_as_float(raw.y);
     out[2] = __uint_as_float(raw.z); out[3] = __uint_as_float(raw.w);

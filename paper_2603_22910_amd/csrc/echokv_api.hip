@@ -920,38 +920,18 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
       else hipLaunchKernelGGL(absorbed::scores_kernel<2>, dim3(slots, nhb), dim3(256), 0, st, a, mt);
       LAUNCH_CHECK();
     } else {
-      // scores of the retained heads straight from the target cache, of the predicted heads from
-      // the fused predictor product; both in base-2 units, rotated by token position if asked
-      SeqMeta km = mt;
-      if (dm.g0 > 0) {
-        AttnArgs<T> ra;
-        ra.k = (const T*)tg->k; ra.v = nullptr; ra.ld = dm.m; ra.col0 = 0; ra.head0 = 0; ra.row_mode = 0;
-        ra.q = a.q; ra.H_q = dm.H_q; ra.G = dm.G; ra.d = dm.d; ra.scale = a.qscale;
-        ra.split_tokens = pick_split_tokens((int64_t)slots * kSlotTokens, dm.g0);
-        ra.part_o = nullptr; ra.part_ml = nullptr;
-        ra.rope_cos = kx.rope_cos; ra.rope_sin = kx.rope_sin;
-        const int tiles = fill_tiles(km, ra.split_tokens);
-        const int GT = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1;
-        dim3 grid(tiles, dm.g0 * (dm.G / GT));
-        constexpr int LPR64 = 8, LPR128 = 16;
-#define RS_CASE(LPR_, GT_) hipLaunchKernelGGL((row_scores_kernel<T, LPR_, GT_>), grid, dim3(256), 0, st, ra, a.s, (int64_t)a.s_ld, km)
-        if (dm.d == 64) {
-          if (GT == 4) RS_CASE(LPR64, 4); else if (GT == 2) RS_CASE(LPR64, 2); else RS_CASE(LPR64, 1);
-        } else {
-          if (GT == 4) RS_CASE(LPR128, 4); else if (GT == 2) RS_CASE(LPR128, 2); else RS_CASE(LPR128, 1);
-        }
-#undef RS_CASE
-        LAUNCH_CHECK();
-      }
-      if (dm.H_kv - dm.g0 > 0) {
-        rc = launch_fused_kscores<T>(dm.H_q, dm.H_kv, dm.d, dm.m, dm.d_out_v, dm.g0, a.qscale,
-                                     (const T*)an->k, (const T*)tg->k, wk, a.q, a.s, a.s_ld, km, st, kx);
-        if (rc) return rc;
-      }
-      if (win.on()) {       // the window's tokens: one o-space partial per sequence
-        rc = launch_window_attn<T>(dm, ex, kx, a.q, win_po, win_pml, b0, 0, mt, st);
-        if (rc) return rc;
-      }
+      // scores of the retained heads straight from the target cache, of the predicted heads from the fused
+      // predictor product, both in base-2 units, rotated by token position if asked; the window's
+      // tokens: one o-space partial per sequence.  One launch
+      StreamMeta sm;
+      sm.s = mt;
+      int stream_step, win_slot0;
+      Streams<T> streams = plan_streams<T>(dm, tg, a.q, ex, kx, win_po, win_pml, b0, kSlotTokens, 1024, 1024, sm, &stream_step, &win_slot0);
+      streams.ret.scale = a.qscale;
+      streams.win.win_slot0 = 0;
+      rc = launch_fused_kscores<T>(dm.H_q, dm.H_kv, dm.d, dm.m, dm.d_out_v, dm.g0, a.qscale,
+                                   (const T*)an->k, (const T*)tg->k, wk, a.q, a.s, a.s_ld, sm, st, streams, kx);
+      if (rc) return rc;
     }
     // few long pieces: more threads on each
     if ((int64_t)dm.H_q * splits < 1024 && ts >= 2048) hipLaunchKernelGGL(absorbed::softmax_stats_kernel<1024>, dim3(dm.H_q, splits), dim3(1024), 0, st, a, mt);

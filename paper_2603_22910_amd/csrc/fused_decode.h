@@ -362,8 +362,14 @@ __global__ __launch_bounds__(NTHREADS) void fused_decode_kernel(Args a, Streams<
 // into the scale).  Used when the value side is evaluated in the other association order
 // (sum_j p_j x^V_j first, W_V afterwards), which stays valid under a rotary embedding.
 template <int HD, bool ROPE>
-__global__ __launch_bounds__(NTHREADS) void fused_kscores_kernel(Args a, SeqMeta meta) {
+__global__ __launch_bounds__(NTHREADS) void fused_kscores_kernel(Args a, Streams<bf16_t> streams, StreamMeta smeta) {
   __shared__ __attribute__((aligned(1024))) Smem sm;
+  const int n_fused = (a.n_tiles + 7) / 8 * 8;
+  if ((int)blockIdx.x >= n_fused) {
+    score_stream_workgroup<HD, NWAVES>(streams, smeta, blockIdx.x - n_fused, a.s_out, a.s_ld, sm.st);
+    return;
+  }
+  const SeqMeta& meta = smeta.s;
   Pipe<false> pipe;
   const Tile t = make_tile<false>(a, meta, pipe, sm.st, 1, 0);
   if (!t.ok) return;
@@ -518,11 +524,12 @@ inline int launch_fused_decode(int H_q, int H_kv, int d, int m, int d_out, int n
 template <typename T>
 inline int launch_fused_kscores(int H_q, int H_kv, int d, int m, int d_out, int n_ret_heads,
                                 float scale, const T* ka, const T* kr, const T* wk, const T* q,
-                                float* s_out, int64_t s_ld, SeqMeta& mt, hipStream_t st,
-                                const KvExtras& ex = KvExtras()) {
+                                float* s_out, int64_t s_ld, StreamMeta& smt, hipStream_t st,
+                                const Streams<T>& streams, const KvExtras& ex) {
   if constexpr (sizeof(T) != 2) {
     return 6;
   } else {
+    SeqMeta& mt = smt.s;
     fused::Args a;
     a.xa[0] = a.xa[1] = ka; a.xr[0] = a.xr[1] = kr; a.w[0] = a.w[1] = wk;
     a.q = q; a.part_o = nullptr; a.part_ml = nullptr;
@@ -532,13 +539,13 @@ inline int launch_fused_kscores(int H_q, int H_kv, int d, int m, int d_out, int 
     a.rope_cos = ex.rope_cos; a.rope_sin = ex.rope_sin; a.n_sink = 0; a.n_recent = 0;
     a.s_out = s_out; a.s_ld = s_ld;
     a.n_col_tiles = (a.d_out + fused::BN - 1) / fused::BN;
-    a.n_tiles = fused_fill_tiles(mt) * a.n_col_tiles;
-    const dim3 g(((a.n_tiles + 7) / 8) * 8), blk(fused::NTHREADS);
+    a.n_tiles = fused_fill_tiles(mt) * a.n_col_tiles;          // (0: every head is retained)
+    const dim3 g((a.n_tiles + 7) / 8 * 8 + streams.n_ret + streams.n_win), blk(fused::NTHREADS);
     const bool rope = ex.rope_cos != nullptr;
-    if (d == 128 && rope) hipLaunchKernelGGL((fused::fused_kscores_kernel<128, true>), g, blk, 0, st, a, mt);
-    else if (d == 128) hipLaunchKernelGGL((fused::fused_kscores_kernel<128, false>), g, blk, 0, st, a, mt);
-    else if (rope) hipLaunchKernelGGL((fused::fused_kscores_kernel<64, true>), g, blk, 0, st, a, mt);
-    else hipLaunchKernelGGL((fused::fused_kscores_kernel<64, false>), g, blk, 0, st, a, mt);
+    if (d == 128 && rope) hipLaunchKernelGGL((fused::fused_kscores_kernel<128, true>), g, blk, 0, st, a, streams, smt);
+    else if (d == 128) hipLaunchKernelGGL((fused::fused_kscores_kernel<128, false>), g, blk, 0, st, a, streams, smt);
+    else if (rope) hipLaunchKernelGGL((fused::fused_kscores_kernel<64, true>), g, blk, 0, st, a, streams, smt);
+    else hipLaunchKernelGGL((fused::fused_kscores_kernel<64, false>), g, blk, 0, st, a, streams, smt);
     if (hipGetLastError() != hipSuccess) return 7;
     return 0;
   }
