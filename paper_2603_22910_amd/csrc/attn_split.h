@@ -273,7 +273,7 @@ __device__ __forceinline__ void stream_workgroup(const Streams<T>& st, const Str
 // halves of a row loaded the same table entries, and exchanged the partners by shuffle.
 // A wave's UN x (64 / LPR) rows are consecutive tokens, and each lane of a row stores the sums of its own share of the
 // (row, query head) pairs: two stores instead of 16 of 16 bytes each.  As a kernel of its own, 131072 tokens with four retained heads
-and rope: 61 us, and 18 for the window's; here the call went from 376 to 351 us, short ones (4 x 2000-9000 tokens) from 113 to 88.
+// and rope: 61 us, and 18 for the window's; here the call went from 376 to 351 us, short ones (4 x 2000-9000 tokens) from 113 to 88.
 // ---------------------------------------------------------------------------
 template <int HD, int GT, int NWAVES>
 __device__ __forceinline__ void row_scores_body(const AttnArgs<bf16_t>& a, float* s_out, int64_t s_ld, const SeqMeta& meta,
