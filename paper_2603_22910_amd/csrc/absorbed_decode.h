@@ -14,7 +14,8 @@
 // Kernels (all launched back to back on the caller's stream):
 //   absorb_q      u = Wt_K q                       reads W_K once
 //   scores        S^T[h, j] = u_h . x^K_j          streams the K caches, MFMA
-//   softmax_stats per token split: M = max_j S, l = sum_j 2^(S - M)
+//                 (small grids: 32 tokens per workgroup)
+//   softmax_stats per token split (short ones: by pv itself): M = max_j S, l = sum_j 2^(S - M)
 //   pv            Y_part[h, k] = sum_j 2^(S - M) x^V_j[k]   streams the V caches, MFMA
 //   y_sum         Y = merge of the splits' Y_part, normalised
 //   out_partial   O_part = Y Wt_V over a slice of k     reads W_V once
@@ -201,6 +202,23 @@ __device__ __forceinline__ void score_issue(char* buf, const ScoreIo& io, int t,
   }
 }
 
+// a wave's 16 loads of stage t in the small kernel: 32 X rows, 32 U rows
+__device__ __forceinline__ void small_issue(char* buf, const ScoreIo& io, int t, int lane) {
+  const StageDesc d = stage_desc(io, t);
+  const rsrc_t rx = make_rsrc(d.anchor ? io.pa : io.pr);
+  const uint32_t ld2 = d.anchor ? io.D2 : io.m2;
+  const int sub = lane >> 4, slot = lane & 15;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int row = 4 * i + sub;
+    const uint32_t ch = (uint32_t)min(slot ^ (row & 15), d.kw / 8 - 1) * 16;         // a partial stage repeats its last chunk
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (ECHOKV_LDS void*)(buf + 4 * i * kRowBytes),
+                                             16, __umul24((uint32_t)min(row, io.last), ld2) + ch, d.k0 * 2, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(io.ru, (ECHOKV_LDS void*)(buf + (32 + 4 * i) * kRowBytes),
+                                             16, __umul24((uint32_t)row, io.u2) + ch, d.kg0 * 2, 0, 0);
+  }
+}
+
 template <int NST>
 __device__ __forceinline__ void score_wait_landed() {
   constexpr int N = 10 * (NST - 1);            // loads of the younger stages, which may stay in flight
@@ -283,6 +301,79 @@ __global__ __launch_bounds__(256, NST == 2 ? 2 : 1) void scores_kernel(Args a, S
   for (int r = 0; r < 16; ++r) {
     const int head = 8 * (r >> 2) + 4 * lh + (r & 3);      // accumulator row -> head
     srow[(int64_t)(hb * kHB + head) * a.s_ld] = acc[r];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Score pass of small grids: one workgroup (8 waves) = 32 tokens x 32 query heads, and the waves take every 8th
+// stage of 128 input dims, each through 16 KB of LDS of its own (32 X rows, 32 U rows), so that no barrier stands
+// between them until they meet at the end.
+// What bounds it: latency.  With 128 tokens per workgroup 3000 tokens are 24 workgroups whose waves walk all of
+// d_in (1536: 12 stages) one behind the other: 11.6 us, and 6 less like this.  Whole calls, 2 x 1500 tokens: 43.8 -> 38.0 us, 1000
+// tokens with d_in 5120: 70 -> 55.
+// ---------------------------------------------------------------------------
+constexpr int kSmallTok = 32, kSmallWaves = 8;
+constexpr int kSmallSlots = kSlotTokens / kSmallTok;
+__global__ __launch_bounds__(kSmallWaves * 64) void scores_small_kernel(Args a, SeqMeta meta) {
+  constexpr int kBuf = (kSmallTok + kHB) * kRowBytes;                 // 16 KB
+  __shared__ __attribute__((aligned(1024))) char lds[kSmallWaves * kBuf];
+  const int slot = blockIdx.x / kSmallSlots, hb = blockIdx.y;
+  const int b = find_seq(meta.sbase, meta.n, slot);
+  const int j0 = (slot - meta.sbase[b]) * kSlotTokens + (blockIdx.x % kSmallSlots) * kSmallTok;
+  const int L = meta.len[b];
+  if (j0 >= L) return;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t row0 = meta.start[b] + j0;
+  ScoreIo io;
+  io.pa = a.xa[0] + row0 * a.D; io.pr = a.xr[0] + row0 * a.m;
+  io.ru = make_rsrc(a.u + ((int64_t)b * a.H_pad + hb * kHB) * a.d_in);
+  io.D2 = (uint32_t)a.D * 2; io.m2 = (uint32_t)a.m * 2; io.u2 = (uint32_t)a.d_in * 2;
+  io.D = a.D; io.m = a.m;
+  io.nsa = (a.D + kStageK - 1) / kStageK; io.ns = io.nsa + (a.m + kStageK - 1) / kStageK;
+  io.last = min(kSmallTok, L - j0) - 1;
+  io.rot = 0;
+  const bool head_ok = hb * kHB + lr < a.H_q;
+  char* buf = lds + wave * kBuf;
+  floatx16_t acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  if (wave < io.ns) small_issue(buf, io, wave, lane);
+  for (int t = wave; t < io.ns; t += kSmallWaves) {
+    const int kw = head_ok ? stage_desc(io, t).kw : 0;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): this wave's stage is in LDS
+    asm volatile("" ::: "memory");
+    u32x4_t xf[8], uf[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int off = ((2 * s + lh) ^ (lr & 15)) << 4;
+      xf[s] = *reinterpret_cast<const u32x4_t*>(buf + lr * kRowBytes + off);
+      uf[s] = *reinterpret_cast<const u32x4_t*>(buf + (kSmallTok + lr) * kRowBytes + off);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): the fragments are held, the buffer is free
+    asm volatile("" ::: "memory");
+    if (t + kSmallWaves < io.ns) small_issue(buf, io, t + kSmallWaves, lane);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      u32x4_t uu = uf[s];
+      if (16 * s >= kw) uu = u32x4_t{0u, 0u, 0u, 0u};
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, uu),
+                                                    __builtin_bit_cast(bf16x8_t, xf[s]), acc, 0, 0, 0);
+    }
+  }
+  float* part = reinterpret_cast<float*>(buf);   // [16 registers][64 lanes]
+#pragma unroll
+  for (int r = 0; r < 16; ++r) part[r * 64 + lane] = acc[r];
+  __syncthreads();
+  // register r of lane l: head 8 (r / 4) + 4 (l / 32) + r % 4, token l % 32
+  for (int i = tid; i < 1024; i += kSmallWaves * 64) {
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) v += reinterpret_cast<const float*>(lds + w * kBuf)[i];
+    const int r = i >> 6, l = i & 63, head = 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
+    a.s[(int64_t)(hb * kHB + head) * a.s_ld + (int64_t)blockIdx.x * kSmallTok + (l & 31)] = v;
   }
 }
 
@@ -409,8 +500,14 @@ __device__ __forceinline__ void pv_mma(floatx16_t (&acc)[8], const PvStage& st, 
   }
 }
 
+// STATS: the workgroup works out (max, sum) of its split itself, the first column tile writes them.  32 heads x
+// kPvStatsTokens scores from L2 cost each workgroup less than a launch in front of them all (2 x 1500 tokens 38.9 -> 38.0 us);
+// with 384 tokens they cost more (2 x 8192: 53.7 -> 56.7).
+constexpr int kPvStatsTokens = 128;
+template <bool STATS>
 __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta meta) {
   __shared__ float red[2][128][64];       // 64 KB: two waves' accumulators
+  __shared__ float s_ml[STATS ? kHB : 1][2];
   const int ct = blockIdx.x % a.n_col_tiles, sp = blockIdx.x / a.n_col_tiles, hb = blockIdx.y;
   const int b = find_seq(meta.tbase, meta.n, sp);
   const int L = meta.len[b];
@@ -434,7 +531,32 @@ __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta me
   io.nrows = nrows; io.nsteps = (nrows + 15) / 16; io.lh8 = lh * 8;
   io.vlo = max(0, a.win.lo(L) - t_begin); io.vhi = min(nrows, a.win.hi(L) - t_begin);
   const int head = hb * kHB + lr;
-  float M = head < a.H_q ? a.ml[((int64_t)sp * a.H_pad + head) * 2] : 0.f;   // the split's own maximum
+  float* const mls = a.ml + ((int64_t)sp * a.H_pad + hb * kHB) * 2;      // this block of heads
+  float M;                                        // the split's own maximum
+  if constexpr (STATS) {
+    // 8 threads per head, 4 scores at a time
+    const int h = tid >> 3, hs = hb * kHB + h < a.H_q;
+    const float* row = a.s + (int64_t)(hb * kHB + h) * a.s_ld + (int64_t)meta.sbase[b] * kSlotTokens + t_begin;
+    float m0 = -INFINITY, l0 = 0.f;
+    if (hs)
+      for (int j = (tid & 7) * 4; j < io.vhi; j += 32) {
+        const float4 x = *reinterpret_cast<const float4*>(row + j);      // (slots are whole: what is past the end is not used)
+        const float xs[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (j + e >= io.vlo && j + e < io.vhi) ml_push(m0, l0, xs[e]);
+      }
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) ml_merge(m0, l0, __shfl_xor(m0, o, 64), __shfl_xor(l0, o, 64));
+    if ((tid & 7) == 0) {
+      s_ml[h][0] = m0; s_ml[h][1] = l0;
+      if (ct == 0 && hs) { mls[2 * h] = m0; mls[2 * h + 1] = l0; }
+    }
+    __syncthreads();
+    M = head < a.H_q ? s_ml[lr][0] : 0.f;
+  } else {
+    M = head < a.H_q ? mls[2 * lr] : 0.f;
+  }
   if (M == -INFINITY) M = 0.f;                    // a piece with no counted token: every p is masked
 
   floatx16_t acc[8];
@@ -481,9 +603,8 @@ __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta me
   __syncthreads();
   if (wave != 0) return;
   if (a.single_split && ct == 0 && lh == 0 && head < a.H_q) {     // the split is the sequence: its (max, sum) is final
-    const float* ml = a.ml + ((int64_t)sp * a.H_pad + head) * 2;
-    a.y_ml[((int64_t)b * a.H_q + head) * 2] = ml[0];
-    a.y_ml[((int64_t)b * a.H_q + head) * 2 + 1] = ml[1];
+    a.y_ml[((int64_t)b * a.H_q + head) * 2] = STATS ? s_ml[STATS ? lr : 0][0] : mls[2 * lr];
+    a.y_ml[((int64_t)b * a.H_q + head) * 2 + 1] = STATS ? s_ml[STATS ? lr : 0][1] : mls[2 * lr + 1];
   }
   if (!col_ok) return;
   float* yp = a.ypart + ((int64_t)sp * a.H_pad + hb * kHB) * a.d_in + (anchor ? 0 : a.D) + col;
@@ -499,7 +620,7 @@ __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta me
     if (a.single_split) {       // normalised, straight into y (what y_sum would make of one split)
       const int ha = hb * kHB + hr;
       if (ha >= a.H_q) continue;
-      const float l = a.ml[((int64_t)sp * a.H_pad + ha) * 2 + 1];
+      const float l = STATS ? s_ml[STATS ? hr : 0][1] : mls[2 * hr + 1];
       const float inv = l > 0.f ? 1.f / l : 0.f;        // l == 0: every counted token sits in the window
       lo.x *= inv; lo.y *= inv; lo.z *= inv; lo.w *= inv; hi.x *= inv; hi.y *= inv; hi.z *= inv; hi.w *= inv;
       dst = a.y + ((int64_t)b * a.H_q + ha) * a.d_in + (anchor ? 0 : a.D) + col;

@@ -778,26 +778,6 @@ struct AbsPlan {
   int H_pad, n_col_a, n_col_tiles, k_slices, k_slice;
 };
 inline int abs_col_tiles(int width) { return (width + absorbed::kColTile - 1) / absorbed::kColTile; }
-// Tokens per split of the value pass (a multiple of the slot size, at least 1024: the workspace
-// bound counts on that).  One workgroup takes one split x one column tile; the chip runs them in
-// turns of 256 (one per compute unit), and a workgroup costs its tokens plus a fixed part (the
-// reduction over its waves, its partial sums and what the later kernels do per split) worth about
-// 700 tokens.  So the time goes like ceil(workgroups / 256) * (split + 700), and the split that
-// minimises it is taken: measured over 16 split sizes on configurations 1-3 this model orders
-// them as the clock does (configuration 3: 3328 tokens, 240 workgroups, 8 % faster than 1024).
-int abs_split_tokens(const Dims& dm, const echokv_layer_cache* an, int b0, int n) {
-  const int nct = abs_col_tiles(dm.D) + abs_col_tiles(dm.m);
-  int best = 1024;
-  int64_t best_cost = -1;
-  for (int ts = 1024; ts <= 32768; ts += kSlotTokens) {
-    int64_t splits = 0;
-    for (int b = 0; b < n; ++b) splits += (an->seq_len[b0 + b] + ts - 1) / ts;
-    const int64_t turns = (splits * nct + 255) / 256;
-    const int64_t cost = turns * (ts + 700);
-    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ts; }
-  }
-  return best;
-}
 AbsPlan plan_absorbed(const Dims& dm, int nseq, int64_t slots, int64_t splits) {
   AbsPlan p;
   p.H_pad = (dm.H_q + absorbed::kHB - 1) / absorbed::kHB * absorbed::kHB;
@@ -829,6 +809,10 @@ size_t absorbed_ws_bytes(const Dims& dm, int batch, int64_t total_tokens) {
   return abs_pre_bytes(dm) + plan_absorbed(dm, n, total_tokens / kSlotTokens + n, total_tokens / 1024 + n).total +
          abs_win_bytes(dm, n);
 }
+// 32-token workgroups of the score pass up to four rounds of them: 3 x 4000 tokens with d_in 5120 (378) 110 -> 107 us, 4 x 3000
+// with d_in 1536 (376) 54.5 -> 53.5, 12000 (504) the same; more rounds are ordinary streaming, which the 128-token kernel does
+// with a quarter of the reads of the absorbed queries.
+constexpr int64_t kAbsSmallWgs = 1024;
 constexpr uint32_t kAbsModes = ECHOKV_FLAG_ABSORBED | ECHOKV_FLAG_ABSORB_V;
 bool absorbed_supported(const Dims& dm, uint32_t flags) {
   if (!dm.bf16 || (flags & (ECHOKV_FLAG_UNFUSED | ECHOKV_FLAG_W_PACKED | ECHOKV_FLAG_STAGED | ECHOKV_FLAG_W_AUGMENTED))) return false;
@@ -837,8 +821,33 @@ bool absorbed_supported(const Dims& dm, uint32_t flags) {
   return true;
 }
 
+// Tokens per split of the value pass (a multiple of the slot size).  One workgroup takes one split x one column tile; the chip runs them in
+// turns of 256 (one per compute unit), and a workgroup costs its tokens plus a fixed part (the
+// reduction over its waves, its partial sums and what the later kernels do per split) worth about
+// 700 tokens.  So the time goes like ceil(workgroups / 256) * (split + 700), and the split that
+// minimises it is taken: measured over 16 split sizes on three layer shapes this model orders
+// them as the clock does (8 KV heads of 128, 32768 tokens: 3328 tokens, 240 workgroups, 8 % faster than 1024).
+// Splits below 1024 tokens (2 x 1500 tokens, d_in 1536: the value pass 22 -> 10 us with 128) only as far as the workspace holds
+// their partial sums: its bound counts on 1024.
+int abs_split_tokens(const Dims& dm, const SeqMeta& mt, int64_t slots, size_t ws_bytes) {
+  const int nct = abs_col_tiles(dm.D) + abs_col_tiles(dm.m);
+  const size_t fixed = abs_pre_bytes(dm) + abs_win_bytes(dm, mt.n);
+  int best = 1024;
+  int64_t best_cost = -1;
+  for (int ts = kSlotTokens; ts <= 32768; ts += kSlotTokens) {
+    int64_t splits = 0;
+    for (int b = 0; b < mt.n; ++b) splits += (mt.len[b] + ts - 1) / ts;
+    if (ts < 1024 && fixed + plan_absorbed(dm, mt.n, slots, splits).total > ws_bytes) continue;
+    const int64_t turns = (splits * nct + 255) / 256;
+    const int64_t cost = turns * (ts + 700);
+    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ts; }
+  }
+  return best;
+}
+
 // Fills mt for group [b0, b0 + n) and returns (slots, splits, split_tokens) through the plan inputs.
-int absorbed_group(const Dims& dm, const echokv_layer_cache* an, int b0, SeqMeta& mt,
+// ws_bytes: workspace that short splits may use (0: the plan that has to fit).
+int absorbed_group(const Dims& dm, const echokv_layer_cache* an, int b0, size_t ws_bytes, SeqMeta& mt,
                    int* slots, int* splits, int* split_tokens) {
   mt.n = std::min(kMaxSeqPerLaunch, an->batch - b0);
   int64_t tokens = 0;
@@ -846,7 +855,7 @@ int absorbed_group(const Dims& dm, const echokv_layer_cache* an, int b0, SeqMeta
     mt.start[b] = an->seq_start[b0 + b]; mt.len[b] = an->seq_len[b0 + b]; tokens += mt.len[b];
   }
   *slots = fill_slots(mt);
-  *split_tokens = abs_split_tokens(dm, an, b0, mt.n);
+  *split_tokens = abs_split_tokens(dm, mt, *slots, ws_bytes);
   *splits = fill_tiles(mt, *split_tokens);
   // 32-bit byte offsets inside the score matrix
   if ((int64_t)*slots * kSlotTokens * 4 * absorbed::kHB >= (int64_t)1 << 31) return ECHOKV_ERR_UNSUPPORTED;
@@ -857,7 +866,7 @@ size_t absorbed_need(const Dims& dm, const echokv_layer_cache* an) {
   size_t need = 0;
   for (int b0 = 0; b0 < an->batch; b0 += kMaxSeqPerLaunch) {
     SeqMeta mt; int slots, splits, ts;
-    if (absorbed_group(dm, an, b0, mt, &slots, &splits, &ts)) return (size_t)-1;
+    if (absorbed_group(dm, an, b0, 0, mt, &slots, &splits, &ts)) return (size_t)-1;
     need = std::max(need, abs_pre_bytes(dm) + plan_absorbed(dm, mt.n, slots, splits).total + abs_win_bytes(dm, mt.n));
   }
   return need;
@@ -867,7 +876,7 @@ size_t absorbed_need(const Dims& dm, const echokv_layer_cache* an) {
 // and window allowed); values are absorbed either way.
 int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
                   const echokv_layer_cache* tg, const void* w_k, const void* w_v, const void* q,
-                  const echokv_decode_extras* ex, void* out, float* lse, char* ws0, hipStream_t st) {
+                  const echokv_decode_extras* ex, void* out, float* lse, char* ws0, size_t ws_bytes, hipStream_t st) {
   typedef bf16_t T;
   KvExtras kx;
   if (ex) {
@@ -884,7 +893,7 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
   char* ws = ws0 + pre.total;
   for (int b0 = 0; b0 < an->batch; b0 += kMaxSeqPerLaunch) {
     SeqMeta mt; int slots, splits, ts;
-    int rc = absorbed_group(dm, an, b0, mt, &slots, &splits, &ts);
+    int rc = absorbed_group(dm, an, b0, ws_bytes, mt, &slots, &splits, &ts);
     if (rc) return rc;
     const AbsPlan pl = plan_absorbed(dm, mt.n, slots, splits);
     float* win_po = (float*)(ws + pl.total);
@@ -915,8 +924,9 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
       if (dm.d == 128) hipLaunchKernelGGL((absorbed::absorb_q_kernel<128>), qg, dim3(256), 0, st, a, n);
       else hipLaunchKernelGGL((absorbed::absorb_q_kernel<64>), qg, dim3(256), 0, st, a, n);
       LAUNCH_CHECK();
-      // few workgroups: one per compute unit with a deeper pipeline; many: two per compute unit
-      if ((int64_t)slots * nhb <= 384) hipLaunchKernelGGL(absorbed::scores_kernel<4>, dim3(slots, nhb), dim3(256), 0, st, a, mt);
+      // small grids: 32-token workgroups; few of 128 tokens: one per compute unit with a deeper pipeline; many: two per compute unit
+      if ((int64_t)slots * nhb * absorbed::kSmallSlots <= kAbsSmallWgs) hipLaunchKernelGGL(absorbed::scores_small_kernel, dim3(slots * absorbed::kSmallSlots, nhb), dim3(absorbed::kSmallWaves * 64), 0, st, a, mt);
+      else if ((int64_t)slots * nhb <= 384) hipLaunchKernelGGL(absorbed::scores_kernel<4>, dim3(slots, nhb), dim3(256), 0, st, a, mt);
       else hipLaunchKernelGGL(absorbed::scores_kernel<2>, dim3(slots, nhb), dim3(256), 0, st, a, mt);
       LAUNCH_CHECK();
     } else {
@@ -933,14 +943,19 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
                                    (const T*)an->k, (const T*)tg->k, wk, a.q, a.s, a.s_ld, sm, st, streams, kx);
       if (rc) return rc;
     }
-    // few long pieces: more threads on each
-    if ((int64_t)dm.H_q * splits < 1024 && ts >= 2048) hipLaunchKernelGGL(absorbed::softmax_stats_kernel<1024>, dim3(dm.H_q, splits), dim3(1024), 0, st, a, mt);
-    else hipLaunchKernelGGL(absorbed::softmax_stats_kernel<256>, dim3(dm.H_q, splits), dim3(256), 0, st, a, mt);
-    LAUNCH_CHECK();
     int max_splits = 0;
     for (int b = 0; b < n; ++b) max_splits = std::max(max_splits, mt.tbase[b + 1] - mt.tbase[b]);
     a.single_split = max_splits == 1 ? 1 : 0;
-    hipLaunchKernelGGL(absorbed::pv_kernel, dim3(splits * pl.n_col_tiles, nhb), dim3(absorbed::kPvWaves * 64), 0, st, a, mt);
+    const dim3 pg(splits * pl.n_col_tiles, nhb), pb(absorbed::kPvWaves * 64);
+    if (ts <= absorbed::kPvStatsTokens) {
+      hipLaunchKernelGGL(absorbed::pv_kernel<true>, pg, pb, 0, st, a, mt);
+    } else {
+      // few long pieces: more threads on each
+      if ((int64_t)dm.H_q * splits < 1024 && ts >= 2048) hipLaunchKernelGGL(absorbed::softmax_stats_kernel<1024>, dim3(dm.H_q, splits), dim3(1024), 0, st, a, mt);
+      else hipLaunchKernelGGL(absorbed::softmax_stats_kernel<256>, dim3(dm.H_q, splits), dim3(256), 0, st, a, mt);
+      LAUNCH_CHECK();
+      hipLaunchKernelGGL(absorbed::pv_kernel<false>, pg, pb, 0, st, a, mt);
+    }
     LAUNCH_CHECK();
     if (max_splits == 1) {
       // (the value pass has written y and its (max, sum) itself)
@@ -1309,7 +1324,7 @@ int echokv_decode_attn_ex(const echokv_shape* shape, const echokv_layer_cache* a
     if (!workspace || workspace_bytes < need) return ECHOKV_ERR_WORKSPACE;
     if ((uintptr_t)workspace % 256) return ECHOKV_ERR_WORKSPACE;
     return absorbed_impl(dm, value_only, anchor, target, w_k, w_v, q, has_extras ? extras : nullptr, out,
-                         lse_out, (char*)workspace, (hipStream_t)hip_stream);
+                         lse_out, (char*)workspace, workspace_bytes, (hipStream_t)hip_stream);
   }
   if ((shape->flags & ECHOKV_FLAG_W_PACKED) &&
       (dm.r != 0 || (shape->flags & ECHOKV_FLAG_UNFUSED) || !dm.bf16 || !fused_decode_supported<bf16_t>(dm.d, dm.G)))

@@ -1,0 +1,57 @@
+"""GPU parity of the absorbed modes on short sequences: the 32-token score kernel (edges of its tiles, partial
+128-dim stages, fewer stages than waves, the grid size at which it ends), value splits below 1024 tokens with and
+without statistics of their own, and the plan that a workspace without room for them falls back to."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_22910_amd import binding as ek
+from paper_2603_22910_amd import synth
+from paper_2603_22910_amd.harness import DeviceWorkload
+
+import oracle_ref as ref
+from test_gpu_parity import check, host, make_dw
+
+pytestmark = pytest.mark.gpu
+
+CASES = [                                      # H_q, H_kv, d, m, lengths
+    (8, 4, 128, 128, (31, 32, 33, 129)),       # edges of 32-token tiles and of slots
+    (6, 3, 64, 64, (100, 1)),                  # D = 192, m = 64: two partial stages of three
+    (40, 5, 128, 64, (200,)),                  # 40 query heads: the second block of 32 is mostly empty
+    (2, 2, 64, 64, (32768,)),                  # 1024 workgroups of the 32-token kernel: its last grid
+    (2, 2, 64, 64, (32769,)),
+    (32, 8, 128, 512, (1500, 700)),            # several splits of 128 tokens per sequence
+]
+MODES = [pytest.param(ek.FLAG_ABSORBED, id="absorbed"), pytest.param(ek.FLAG_ABSORB_V, id="absorb_v")]
+
+
+@pytest.mark.parametrize("flags", MODES)
+@pytest.mark.parametrize("H_q,H_kv,d,m,lens", CASES)
+def test_short_absorbed_against_the_oracle(H_q, H_kv, d, m, lens, flags):
+    inp = synth.generate(synth.Workload("absorbed", "bf16", H_q, H_kv, d, m, seed=74, seq_lens=lens))
+    out, lse = make_dw(inp, flags).decode()
+    torch.cuda.synchronize()
+    o_ref, l_ref = ref.decode_ref(inp)
+    check(host(out), o_ref, "bf16", f"{H_q} {H_kv} {d} {m} {lens}")
+    assert np.abs(host(lse) - l_ref).max() <= 2e-2
+
+
+@pytest.mark.parametrize("flags", MODES)
+def test_workspace_of_splits_of_1024_tokens_is_still_accepted(flags):
+    H_q, D, m, L, nseq = 16, 1024, 512, 1500, 2
+    inp = synth.generate(synth.Workload("absorbed_ws", "bf16", H_q, 8, 128, m, seed=75, seq_lens=(L,) * nseq))
+    dw = DeviceWorkload(inp, flags=flags)
+    a256 = lambda x: (x + 255) // 256 * 256
+    d_in, slots, splits, pad = D + m, nseq * 12, nseq * 2, 32            # 12 slots of 128 and 2 splits of 1024 tokens each
+    need = (a256(nseq * pad * d_in * 2) + a256(pad * slots * 128 * 4) + a256(splits * pad * 2 * 4) + a256(splits * pad * d_in * 4)
+            + a256(nseq * H_q * d_in * 4) + a256(6 * nseq * H_q * 128 * 4) + a256(nseq * H_q * 2 * 4)
+            + a256(nseq * H_q * 128 * 4) + a256(nseq * H_q * 2 * 4))
+    dw.workspace = dw.workspace[:need]
+    out, lse = dw.decode()
+    torch.cuda.synchronize()
+    o_ref, _ = ref.decode_ref(inp)
+    check(host(out), o_ref, "bf16", "workspace without room for splits of 128 tokens")
+    dw.workspace = dw.workspace[:need - 256]
+    with pytest.raises(ek.EchoKVError) as e:
+        dw.decode()
+    assert e.value.code == ek.ERR_WORKSPACE
