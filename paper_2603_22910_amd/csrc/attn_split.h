@@ -363,4 +363,72 @@ __device__ __forceinline__ void score_stream_workgroup(const Streams<bf16_t>& st
   else row_scores_body<HD, 1, NWAVES>(st.ret, s_out, s_ld, meta.s, b, chunk, y);
 }
 
+// ---------------------------------------------------------------------------
+// Rotary embedding of key rows ahead of the prefill attention kernels (Sec. "Network
+// Architecture": caches hold pre-rotation keys): row j of src [rows, n_heads * d] (pitch
+// ld_src) is rotated to position j, feature i of a head pairing with i + d/2, and written
+// to dst (pitch ld_dst; dst may be src).  One thread per 8 + 8 paired features and turn, the loads of all turns ahead.
+// ---------------------------------------------------------------------------
+struct RopeRows {
+  const bf16_t* src = nullptr; bf16_t* dst = nullptr;
+  int64_t ld_src = 0, ld_dst = 0;
+  int32_t n_heads = 0, d = 0, rows = 0;
+  const float* cos = nullptr; const float* sin = nullptr;      // [>= rows, d / 2]
+};
+// The first (HI = false) or second half's 8 features from both halves' and 8 table entries of their angle.
+template <bool HI>
+__device__ __forceinline__ uint4 rope8(uint4 lo, uint4 hi, const float4 (&cos)[2], const float4 (&sin)[2]) {
+  float a[8], b[8], r[8];
+  unpack_bf16x8(lo, a);
+  unpack_bf16x8(hi, b);
+#pragma unroll
+  for (int i = 0; i < 8; i += 4) {
+    const float4 c4 = cos[i / 4], s4 = sin[i / 4];
+    const float c[4] = {c4.x, c4.y, c4.z, c4.w}, s[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[i + e] = HI ? b[i + e] * c[e] + a[i + e] * s[e] : a[i + e] * c[e] - b[i + e] * s[e];
+  }
+  uint32_t w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = (uint32_t)f32_to_bf16(r[2 * i]) | ((uint32_t)f32_to_bf16(r[2 * i + 1]) << 16);
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+constexpr int kRopeTurns = 4;
+__host__ __device__ inline int64_t rope_workgroups(const RopeRows& a, int threads) {
+  const int64_t per = (int64_t)threads * kRopeTurns;
+  return ((int64_t)a.rows * a.n_heads * (a.d / 16) + per - 1) / per;
+}
+template <int NT>
+__device__ __forceinline__ void rope_workgroup(const RopeRows& a, int wg) {
+  const int cpr = a.d / 16, half = a.d / 2, per_row = a.n_heads * cpr;
+  const int64_t n = (int64_t)per_row * a.rows;
+  uint4 lo[kRopeTurns], hi[kRopeTurns];
+  float4 cs[kRopeTurns][2], sn[kRopeTurns][2];
+  bf16_t* dp[kRopeTurns];
+  const int64_t idx0 = (int64_t)wg * kRopeTurns * NT + threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < kRopeTurns; ++u) {
+    const int64_t idx = min(idx0 + u * NT, n - 1);
+    const int row = (int)(idx / per_row), rem = (int)(idx % per_row), head = rem / cpr, c = rem % cpr;
+    const bf16_t* sp = a.src + (int64_t)row * a.ld_src + head * a.d + c * 8;
+    lo[u] = *reinterpret_cast<const uint4*>(sp);
+    hi[u] = *reinterpret_cast<const uint4*>(sp + half);
+    const int64_t e = (int64_t)row * half + c * 8;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      cs[u][i] = *reinterpret_cast<const float4*>(a.cos + e + 4 * i);
+      sn[u][i] = *reinterpret_cast<const float4*>(a.sin + e + 4 * i);
+    }
+    dp[u] = a.dst + (int64_t)row * a.ld_dst + head * a.d + c * 8;
+  }
+#pragma unroll
+  for (int u = 0; u < kRopeTurns; ++u) {
+    if (idx0 + u * NT >= n) return;
+    *reinterpret_cast<uint4*>(dp[u]) = rope8<false>(lo[u], hi[u], cs[u], sn[u]);
+    *reinterpret_cast<uint4*>(dp[u] + half) = rope8<true>(lo[u], hi[u], cs[u], sn[u]);
+  }
+}
+
+__global__ __launch_bounds__(256) inline void rope_rows_kernel(RopeRows a) { rope_workgroup<256>(a, blockIdx.x); }
+
 }  // namespace echokv

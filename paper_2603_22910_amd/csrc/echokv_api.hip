@@ -602,10 +602,23 @@ int prefill_impl(const Dims& dm, const echokv_layer_cache* an, const echokv_laye
   float* pml = (float*)(ws + wp.off_pml);
   T* kh = (T*)(ws + wp.off_kh);
   T* vh = (T*)(ws + wp.off_vh);
-  if (n_rec_heads > 0) {
-    const T* wk; const T* wv;
-    int rc = effective_weights<T>(dm, w_k, w_v, ws, wp, &wk, &wv, st);
-    if (rc) return rc;
+  // rotary embedding ahead of the MFMA attention kernels, which then run unchanged: the predicted keys are rotated
+  // where they are stored, the retained ones into a copy behind the plan, in one launch
+  RopeRows rope;
+  if constexpr (sizeof(T) == 2) {
+    if (rope_cos && prefill_mfma_supported<T>(dm.d)) {
+      rope.src = (const T*)tg->k + row0 * dm.m; rope.dst = (T*)(ws + prefill_krot_offset(dm, Ltot, T_q));
+      rope.ld_src = rope.ld_dst = dm.m; rope.n_heads = n_ret_heads; rope.d = dm.d; rope.rows = Ltot;
+      rope.cos = rope_cos; rope.sin = rope_sin;
+    }
+  }
+  if (n_rec_heads > 0 || rope.cos) {
+    const T* wk = nullptr; const T* wv = nullptr;
+    if (n_rec_heads > 0) {
+      int rcw = effective_weights<T>(dm, w_k, w_v, ws, wp, &wk, &wv, st);
+      if (rcw) return rcw;
+    }
+    int rc;
     ProfScope prof;
     rc = prof.begin(1, st);
     if (rc) return rc;
@@ -613,7 +626,7 @@ int prefill_impl(const Dims& dm, const echokv_layer_cache* an, const echokv_laye
     mt.n = 1; mt.start[0] = row0; mt.len[0] = Ltot; mt.sbase[0] = 0; mt.sbase[1] = slots_for(Ltot);
     if (recon_mfma_supported<T>()) {
       rc = launch_recon_mfma<T>(dm.D, dm.m, dm.d_out_v, (const T*)an->k, (const T*)an->v,
-                                (const T*)tg->k, (const T*)tg->v, wk, wv, kh, vh, dm.d_out_v, 0, mt, st);
+                                (const T*)tg->k, (const T*)tg->v, wk, wv, kh, vh, dm.d_out_v, 0, mt, st, 0, false, rope);
       if (rc) return rc;
     } else {
       GemmArgs<T> g;
@@ -634,16 +647,7 @@ int prefill_impl(const Dims& dm, const echokv_layer_cache* an, const echokv_laye
     if (rcp) return rcp;
     const T* k_ret = (const T*)tg->k + row0 * dm.m;
     if constexpr (sizeof(T) == 2) {
-      if (rope_cos) {
-        // rotary embedding: the predicted keys are rotated in place in the workspace, the
-        // retained ones into a copy next to them; the attention kernels then run unchanged
-        T* krot = (T*)(ws + prefill_krot_offset(dm, Ltot, T_q));
-        int rc = launch_rope_rows(kh, dm.d_out_v, kh, dm.d_out_v, n_rec_heads, dm.d, Ltot, rope_cos, rope_sin, st);
-        if (rc) return rc;
-        rc = launch_rope_rows(k_ret, dm.m, krot, dm.m, n_ret_heads, dm.d, Ltot, rope_cos, rope_sin, st);
-        if (rc) return rc;
-        if (n_ret_heads > 0) k_ret = krot;
-      }
+      if (rope.cos && n_ret_heads > 0) k_ret = rope.dst;
     }
     float* sp_o = (float*)(ws + prefill_split_offset(dm, Ltot, T_q));
     float* sp_ml = sp_o + (size_t)T_q * dm.H_q * prefill_kv_splits(T_q, Ltot, dm.H_q) * dm.d;

@@ -401,10 +401,16 @@ __global__ __launch_bounds__(NTHREADS) void fused_kscores_kernel(Args a, Streams
 // activation it is the first layer of the one-hidden-layer predictor
 // (Appendix "Prediction Network Architecture").
 // The accumulators go through LDS so that rows leave in 16-byte pieces, 512 contiguous bytes per wave and row.
+// With rotary tables (a.rope_cos, heads of a.H_q dims) K_hat is rotated to its tokens' positions on that way; further workgroups
+// rotate the retained keys (`rope`).
 template <int ACT, bool OUT32 = false>   // activation before rounding: 0 none, 1 ReLU, 2 SiLU; OUT32: fp32 output
-__global__ __launch_bounds__(NTHREADS) void recon_mfma_kernel(Args a, SeqMeta meta) {
+__global__ __launch_bounds__(NTHREADS) void recon_mfma_kernel(Args a, SeqMeta meta, RopeRows rope) {
   __shared__ __attribute__((aligned(1024))) char st[2 * kStage];
-  const int which = blockIdx.y;
+  const int which = blockIdx.y, n_fused = (a.n_tiles + 7) / 8 * 8;
+  if ((int)blockIdx.x >= n_fused) {
+    if (which == 0) rope_workgroup<NTHREADS>(rope, blockIdx.x - n_fused);
+    return;
+  }
   Pipe<false> pipe;
   const Tile t = make_tile<false>(a, meta, pipe, st, 1, which);
   if (!t.ok) return;
@@ -454,6 +460,36 @@ __global__ __launch_bounds__(NTHREADS) void recon_mfma_kernel(Args a, SeqMeta me
   __syncthreads();
   const int c = threadIdx.x & 31, n = t.n0 + c * 8;
   if (n >= a.d_out) return;
+  if (which == 0 && a.rope_cos) {
+    const int half = a.H_q / 2, hc = half / 8;       // chunk c pairs with c +- hc
+    const bool hi = (c & hc) != 0;
+    const int f = n % half;                          // table entry of the chunk's first dim
+    // four rows' table entries at a time: one by one each waits for its own
+    constexpr int STEP = NTHREADS / 32, UN = 4;
+    const int je = min(BM, t.L - t.j0);
+#pragma nounroll
+    for (int j0 = threadIdx.x >> 5; j0 < je; j0 += UN * STEP) {
+      float4 cs[UN][2], sn[UN][2];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const int64_t e = (int64_t)(t.j0 + min(j0 + u * STEP, je - 1)) * half + f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          cs[u][i] = *reinterpret_cast<const float4*>(a.rope_cos + e + 4 * i);
+          sn[u][i] = *reinterpret_cast<const float4*>(a.rope_sin + e + 4 * i);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const int j = j0 + u * STEP;
+        if (j >= je) break;
+        const char* row = st + j * 512;
+        const uint4 x = *reinterpret_cast<const uint4*>(row + ((c ^ (j & 31)) << 4)), y = *reinterpret_cast<const uint4*>(row + ((c ^ hc ^ (j & 31)) << 4));
+        *reinterpret_cast<uint4*>(out + (orow0 + j) * a.ldo + a.col0 + n) = hi ? rope8<true>(y, x, cs[u], sn[u]) : rope8<false>(x, y, cs[u], sn[u]);
+      }
+    }
+    return;
+  }
   for (int j = threadIdx.x >> 5; j < BM && t.j0 + j < t.L; j += NTHREADS / 32)
     *reinterpret_cast<u32x4_t*>(out + (orow0 + j) * a.ldo + a.col0 + n) =
         *reinterpret_cast<const u32x4_t*>(st + j * 512 + ((c ^ (j & 31)) << 4));
@@ -552,28 +588,41 @@ inline int launch_fused_kscores(int H_q, int H_kv, int d, int m, int d_out, int 
 }
 
 // K_hat and V_hat of the sequences in `mt` -> out_k / out_v [rows, ldo] at
-// column col0, output row = sbase[b]*kSlotTokens + j.  d_out = width of W.
+// column col0, output row = sbase[b]*kSlotTokens + j.  d_out = width of W (0: only the rows of `rope`).  With
+// rope.cos K_hat is rotated by token position, heads of rope.d dims, and rope's own rows (the retained keys) are as well, these
+// by workgroups of the product's launch.  K_hat on its way out of the product if that has kRopeTiles workgroups and more, by a
+// launch behind it otherwise: the tables' loads are then a latency at the end of a tile that nothing covers.  In a prefill
+// of 64 queries behind 16000 tokens (252 workgroups) 165 us with two launches behind the product, 154 on its way out; 900 behind 20000
+// (328) 495 and 465; 500 behind 7000 (120) 171 and 168; 100 behind 3000 (52) 78.8 and 80.8; 2000 alone (32) 116 and 120.
+constexpr int kRopeTiles = 120;
 template <typename T>
 inline int launch_recon_mfma(int D, int m, int d_out, const T* ka, const T* va, const T* kr, const T* vr,
                              const T* wk, const T* wv, T* out_k, T* out_v, int64_t ldo, int col0,
-                             SeqMeta& mt, hipStream_t st, int act = 0, bool out_f32 = false) {
+                             SeqMeta& mt, hipStream_t st, int act = 0, bool out_f32 = false,
+                             const RopeRows& rope = RopeRows()) {
   if constexpr (sizeof(T) != 2) {
     return 6;
   } else {
     fused::Args a;
     a.xa[0] = ka; a.xa[1] = va; a.xr[0] = kr; a.xr[1] = vr; a.w[0] = wk; a.w[1] = wv;
     a.q = nullptr; a.part_o = nullptr; a.part_ml = nullptr;
-    a.rope_cos = a.rope_sin = nullptr; a.n_sink = a.n_recent = 0; a.s_out = nullptr; a.s_ld = 0;
+    a.rope_cos = rope.cos; a.rope_sin = rope.sin; a.n_sink = a.n_recent = 0; a.s_out = nullptr; a.s_ld = 0;
     a.out[0] = out_k; a.out[1] = out_v; a.ldo = ldo; a.col0 = col0;
-    a.D = D; a.m = m; a.d_out = d_out; a.H_q = 0; a.G = 1; a.n_ret_heads = 0; a.scale = 0.f;
+    a.D = D; a.m = m; a.d_out = d_out; a.H_q = rope.d; a.G = 1; a.n_ret_heads = 0; a.scale = 0.f;
     a.n_col_tiles = (a.d_out + fused::BN - 1) / fused::BN;
     a.n_tiles = fused_fill_tiles(mt) * a.n_col_tiles;
-    const int grid = ((a.n_tiles + 7) / 8) * 8;
-    const dim3 g(grid, 2), blk(fused::NTHREADS);
-    if (out_f32) hipLaunchKernelGGL((fused::recon_mfma_kernel<0, true>), g, blk, 0, st, a, mt);
-    else if (act == 1) hipLaunchKernelGGL(fused::recon_mfma_kernel<1>, g, blk, 0, st, a, mt);
-    else if (act == 2) hipLaunchKernelGGL(fused::recon_mfma_kernel<2>, g, blk, 0, st, a, mt);
-    else hipLaunchKernelGGL(fused::recon_mfma_kernel<0>, g, blk, 0, st, a, mt);
+    const bool behind = rope.cos && a.n_tiles > 0 && 2 * a.n_tiles < kRopeTiles;
+    if (behind) a.rope_cos = a.rope_sin = nullptr;
+    const dim3 g((unsigned)((a.n_tiles + 7) / 8 * 8 + rope_workgroups(rope, fused::NTHREADS)), 2), blk(fused::NTHREADS);
+    if (out_f32) hipLaunchKernelGGL((fused::recon_mfma_kernel<0, true>), g, blk, 0, st, a, mt, rope);
+    else if (act == 1) hipLaunchKernelGGL(fused::recon_mfma_kernel<1>, g, blk, 0, st, a, mt, rope);
+    else if (act == 2) hipLaunchKernelGGL(fused::recon_mfma_kernel<2>, g, blk, 0, st, a, mt, rope);
+    else hipLaunchKernelGGL(fused::recon_mfma_kernel<0>, g, blk, 0, st, a, mt, rope);
+    if (behind) {                            // (one sequence, rows from 0)
+      RopeRows r = rope;
+      r.src = r.dst = out_k + col0; r.ld_src = r.ld_dst = ldo; r.n_heads = d_out / rope.d;
+      hipLaunchKernelGGL(rope_rows_kernel, dim3((unsigned)rope_workgroups(r, 256)), dim3(256), 0, st, r);
+    }
     if (hipGetLastError() != hipSuccess) return 7;
     return 0;
   }

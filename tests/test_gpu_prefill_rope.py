@@ -1,0 +1,33 @@
+"""GPU parity of the prefill path's rotary embedding: predicted keys rotated on their way out of the predictor
+product (from 120 of its workgroups on) and by a launch behind it (below), retained keys by workgroups of the product's
+launch, also where no head is predicted; every output element against the fp64 oracle."""
+import pytest
+import torch
+
+from paper_2603_22910_amd import synth
+
+import oracle_ref as ref
+from test_gpu_parity import check, host, make_dw
+
+pytestmark = pytest.mark.gpu
+
+CASES = [                                # H_q, H_kv, d, m, tokens, queries
+    (4, 2, 128, 128, 15104, 9),          # 59 token tiles x 1 column tile, twice: 118 workgroups
+    (4, 2, 128, 128, 15105, 9),          # 120: rotated on the way out; one row in the last tile
+    (8, 4, 64, 64, 15300, 5),            # heads of 64, 192 predicted dims
+    (12, 6, 64, 0, 7700, 33),            # no retained head; the second column tile is half empty
+    (4, 2, 64, 128, 700, 70),            # no predicted head: the launch rotates retained keys only
+    (4, 4, 128, 256, 5, 5),
+]
+
+
+@pytest.mark.parametrize("H_q,H_kv,d,m,plen,pq", CASES)
+def test_prefill_rope_routes(H_q, H_kv, d, m, plen, pq):
+    w = synth.Workload("prefill_rope", "bf16", H_q, H_kv, d, m, seed=76, seq_lens=(8,), prefill_len=plen, prefill_q=pq)
+    inp = synth.generate(w)
+    dw = make_dw(inp, 0)
+    rope = synth.rope_tables(d, plen)
+    out, _ = dw.prefill_ex(rope)
+    torch.cuda.synchronize()
+    o_ref, _ = ref.prefill_paper_ref(inp, rope)
+    check(host(out), o_ref, "bf16", f"{H_q} {H_kv} {d} {m} {plen} {pq}")
