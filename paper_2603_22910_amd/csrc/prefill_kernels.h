@@ -645,7 +645,7 @@ template <typename T> inline bool prefill_mfma_supported(int d) {
   return sizeof(T) == 2 && (d == 64 || d == 128);
 }
 
-// Key shares for a chunk of T_q queries over Ltot cached tokens (1 = no split).  Chunks of
+// Key shares the workspace has room for with a chunk of T_q queries over Ltot cached tokens (1 = no split).  Chunks of
 // kMinQueries queries and more fill the chip by themselves.  A shorter chunk has at most three query
 // blocks per head; with a long context in front of it each (head, block) is cut into shares of at
 // least 8 key tiles until about three workgroups per compute unit exist.
@@ -656,6 +656,23 @@ inline int prefill_kv_splits(int T_q, int64_t Ltot, int H_q) {
   int S = (int)std::min<int64_t>(prefill::dma::kMaxSplits, tiles / 8);
   S = std::min(S, (768 + wgs - 1) / wgs);
   return std::max(S, 1);
+}
+// Key shares taken: of the 2 .. prefill_kv_splits possible ones those that cost least.  A workgroup fills a compute unit, so the
+// chip runs them in rounds of 256; one costs its key tiles and about six more for its start and end, and each share's
+// partials (written, read and joined) about one tile per 9000 (query, head) pairs.  All possible shares -> these: 500
+// queries of 32 heads behind 7000 tokens 8 -> 4 shares, 168 -> 153 us; 768 behind 3232 127 -> 106; 1000 behind 3000 151 -> 126; 900 behind 20000
+// 8 -> 5 shares, 466 -> 458; 600 behind 12000 239 -> 221; 400 behind 30000 438 -> 419; one block of queries (300 behind 7000, 64 behind 16000): the same.
+inline int prefill_kv_shares(int T_q, int64_t Ltot, int H_q) {
+  const int cap = prefill_kv_splits(T_q, Ltot, H_q);
+  const int wgs = (T_q + prefill::dma::BQ - 1) / prefill::dma::BQ * H_q;
+  const float tiles = (float)((Ltot + prefill::BKV - 1) / prefill::BKV), share = (float)T_q * (float)H_q / 9000.f;
+  int best = cap;
+  float best_cost = 0.f;
+  for (int S = cap; S >= 2; --S) {
+    const float cost = (float)((wgs * S + 255) / 256) * (tiles / (float)S + 6.f) + (float)S * share;
+    if (S == cap || cost < best_cost) { best = S; best_cost = cost; }
+  }
+  return best;
 }
 // fp32 words the partials of such a launch take: (d + 2) per (query, head, share)
 inline size_t prefill_split_floats(int T_q, int64_t Ltot, int H_q, int d) {
@@ -684,7 +701,7 @@ inline int launch_prefill_mfma(int H_q, int H_kv, int d, int m, int d_out, int n
     // so do short chunks in front of a long context, split over the keys so that the grid still
     // fills the chip
     const int64_t span = (int64_t)(q_pos0 + T_q) * (m > d_out ? m : d_out) * 2;
-    const int S = span < (int64_t)1 << 31 ? prefill_kv_splits(T_q, q_pos0 + T_q, H_q) : 1;
+    const int S = span < (int64_t)1 << 31 ? prefill_kv_shares(T_q, q_pos0 + T_q, H_q) : 1;
     if (S > 1) {
       if (!part_o || !part_ml) return 5;
       a.kv_splits = S; a.part_o = part_o; a.part_ml = part_ml;

@@ -31,3 +31,14 @@ def test_prefill_rope_routes(H_q, H_kv, d, m, plen, pq):
     torch.cuda.synchronize()
     o_ref, _ = ref.prefill_paper_ref(inp, rope)
     check(host(out), o_ref, "bf16", f"{H_q} {H_kv} {d} {m} {plen} {pq}")
+
+
+@pytest.mark.parametrize("plen,pq", [(3700, 385), (4500, 800), (6000, 1023)])
+def test_prefill_key_shares_below_the_limit(plen, pq):
+    """Two and three query blocks of 32 heads: fewer key shares than the workspace has room for."""
+    w = synth.Workload("prefill_shares", "bf16", 32, 4, 64, 64, seed=77, seq_lens=(8,), prefill_len=plen, prefill_q=pq)
+    inp = synth.generate(w)
+    out, _ = make_dw(inp, 0).prefill()
+    torch.cuda.synchronize()
+    o_ref, _ = ref.prefill_ref(inp)
+    check(host(out), o_ref, "bf16", f"{plen} {pq}")
