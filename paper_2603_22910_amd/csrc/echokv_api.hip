@@ -831,20 +831,36 @@ bool absorbed_supported(const Dims& dm, uint32_t flags) {
 // 700 tokens.  So the time goes like ceil(workgroups / 256) * (split + 700), and the split that
 // minimises it is taken: measured over 16 split sizes on three layer shapes this model orders
 // them as the clock does (8 KV heads of 128, 32768 tokens: 3328 tokens, 240 workgroups, 8 % faster than 1024).
-// Splits below 1024 tokens (2 x 1500 tokens, d_in 1536: the value pass 22 -> 10 us with 128) only as far as the workspace holds
-// their partial sums: its bound counts on 1024.
+// Splits below 1024 tokens only as far as the workspace holds their partial sums: its bound counts on 1024.  For these the cost of the
+// launches counts too: several splits per sequence need y_sum (worth about 300 tokens), splits of up to 128 tokens no statistics
+// launch (250); a split is not longer than the longest sequence, and every block of 32 query heads is a row of workgroups of its own.
+// 2 x 1500 tokens, d_in 1536: the value pass 22 -> 10 us with 128; 16 x 1000, 64 heads, d_in 1920: 79 us in one split each, 89 in
+// two, 115 with 128; 16 x 700: 72, 80 and 97; 16 x 700, 32 heads, d_in 1536: 56.6 in one split, 55.2 with 384, 62 with 128.
 int abs_split_tokens(const Dims& dm, const SeqMeta& mt, int64_t slots, size_t ws_bytes) {
-  const int nct = abs_col_tiles(dm.D) + abs_col_tiles(dm.m);
+  const int nct = abs_col_tiles(dm.D) + abs_col_tiles(dm.m), nhb = (dm.H_q + absorbed::kHB - 1) / absorbed::kHB;
   const size_t fixed = abs_pre_bytes(dm) + abs_win_bytes(dm, mt.n);
+  int max_len = 0;
+  for (int b = 0; b < mt.n; ++b) max_len = std::max(max_len, mt.len[b]);
+  auto splits_of = [&](int ts) {
+    int64_t n = 0;
+    for (int b = 0; b < mt.n; ++b) n += (mt.len[b] + ts - 1) / ts;
+    return n;
+  };
   int best = 1024;
   int64_t best_cost = -1;
-  for (int ts = kSlotTokens; ts <= 32768; ts += kSlotTokens) {
-    int64_t splits = 0;
-    for (int b = 0; b < mt.n; ++b) splits += (mt.len[b] + ts - 1) / ts;
-    if (ts < 1024 && fixed + plan_absorbed(dm, mt.n, slots, splits).total > ws_bytes) continue;
-    const int64_t turns = (splits * nct + 255) / 256;
-    const int64_t cost = turns * (ts + 700);
+  for (int ts = 1024; ts <= 32768; ts += kSlotTokens) {
+    const int64_t cost = (splits_of(ts) * nct + 255) / 256 * (ts + 700);
     if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ts; }
+  }
+  auto whole_cost = [&](int ts) {
+    return (splits_of(ts) * nct * nhb + 255) / 256 * (std::min(ts, max_len) + 700) + (max_len > ts ? 300 : 0) -
+           (ts <= absorbed::kPvStatsTokens ? 250 : 0);
+  };
+  best_cost = whole_cost(best);
+  for (int ts = 1024 - kSlotTokens; ts > 0; ts -= kSlotTokens) {
+    if (fixed + plan_absorbed(dm, mt.n, slots, splits_of(ts)).total > ws_bytes) break;      // (shorter ones need more)
+    const int64_t cost = whole_cost(ts);
+    if (cost < best_cost) { best_cost = cost; best = ts; }
   }
   return best;
 }

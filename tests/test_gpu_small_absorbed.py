@@ -1,6 +1,6 @@
 """GPU parity of the absorbed modes on short sequences: the 32-token score kernel (edges of its tiles, partial
 128-dim stages, fewer stages than waves, the grid size at which it ends), value splits below 1024 tokens with and
-without statistics of their own, and the plan that a workspace without room for them falls back to."""
+without statistics of their own, their number, and the plan that a workspace without room for them falls back to."""
 import numpy as np
 import pytest
 import torch
@@ -55,3 +55,36 @@ def test_workspace_of_splits_of_1024_tokens_is_still_accepted(flags):
     with pytest.raises(ek.EchoKVError) as e:
         dw.decode()
     assert e.value.code == ek.ERR_WORKSPACE
+
+
+def workspace_end(H_q, d, d_in, lens, splits):
+    """Bytes of workspace that a call with `splits` splits of the value pass writes up to."""
+    a256 = lambda x: (x + 255) // 256 * 256
+    n, pad, slots = len(lens), (H_q + 31) // 32 * 32, sum((L + 127) // 128 for L in lens)
+    slices = max(1, min(64, d_in // 256))
+    slices = -(-d_in // (-(-(-(-d_in // slices)) // 64) * 64))
+    return (a256(n * pad * d_in * 2) + a256(pad * slots * 512) + a256(splits * pad * 8) + a256(splits * pad * d_in * 4)
+            + a256(n * H_q * d_in * 4) + a256(slices * n * H_q * d * 4) + n * H_q * 8)
+
+
+SPLITS = [                                       # H_q, H_kv, m, sequences, length, tokens per split
+    (64, 8, 896, 16, 700, 1024),                 # one split each: 256 workgroups already, no launch to join them
+    (64, 8, 896, 16, 1000, 1024),
+    (32, 8, 512, 16, 1000, 512),
+    (32, 8, 512, 2, 1500, 128),
+    (32, 8, 512, 1, 128, 128),                   # one split that works out its own statistics
+]
+
+
+@pytest.mark.parametrize("H_q,H_kv,m,n,L,ts", SPLITS)
+def test_tokens_per_split(H_q, H_kv, m, n, L, ts):
+    inp = synth.generate(synth.Workload("absorbed_splits", "bf16", H_q, H_kv, 128, m, seed=79, seq_lens=(L,) * n))
+    dw = DeviceWorkload(inp, flags=ek.FLAG_ABSORBED)
+    dw.workspace = torch.full((dw.workspace.numel() + (64 << 20),), 0xA5, dtype=torch.uint8, device=dw.dev)   # room for every choice
+    out, _ = dw.decode()
+    torch.cuda.synchronize()
+    o_ref, _ = ref.decode_ref(inp)
+    check(host(out), o_ref, "bf16", f"{H_q} {H_kv} {m} {n} {L}")
+    end = int((dw.workspace != 0xA5).nonzero().max()) + 1
+    want = workspace_end(H_q, 128, H_kv * 128 + m, (L,) * n, n * -(-L // ts))
+    assert want - 8 < end <= want
