@@ -813,10 +813,11 @@ size_t absorbed_ws_bytes(const Dims& dm, int batch, int64_t total_tokens) {
   return abs_pre_bytes(dm) + plan_absorbed(dm, n, total_tokens / kSlotTokens + n, total_tokens / 1024 + n).total +
          abs_win_bytes(dm, n);
 }
-// 32-token workgroups of the score pass up to one and a half rounds of them: 3 x 4000 tokens with d_in 5120 (378) 110 -> 107 us,
-// 4 x 3000 with d_in 1536 (376) 54.5 -> 53.5, 2 x 8192 (512) the same.  Beyond, the 128-token kernel fills the chip too, with a quarter
-// of the reads of the absorbed queries: 8 x 4096 with d_in 6144 (1024) 210 us against 225.
-constexpr int64_t kAbsSmallWgs = 384;
+// 32-token workgroups of the score pass as long as they are one round (slots x 4 x blocks of 32 heads; 128-token / 32-token kernel, whole
+// calls in us): 128 of them 67.4 / 61.1, 256 99.5 / 93.0, 52.7 / 50.2 and 72.2 / 72.7, 384 54.5 / 53.5 and 110 / 107 with three
+// or four long sequences, but 88.1 / 93.3, 56.6 / 57.6 and 52.7 / 53.3 with 16 short ones, 512 65.8 / 68.7 and 61.9 / 64.3.  Beyond, the
+// 128-token kernel fills the chip too, with a quarter of the reads of the absorbed queries: 8 x 4096 with d_in 6144 (1024) 210 / 225.
+constexpr int64_t kAbsSmallWgs = 256;
 constexpr uint32_t kAbsModes = ECHOKV_FLAG_ABSORBED | ECHOKV_FLAG_ABSORB_V;
 bool absorbed_supported(const Dims& dm, uint32_t flags) {
   if (!dm.bf16 || (flags & (ECHOKV_FLAG_UNFUSED | ECHOKV_FLAG_W_PACKED | ECHOKV_FLAG_STAGED | ECHOKV_FLAG_W_AUGMENTED))) return false;
