@@ -834,14 +834,16 @@ bool absorbed_supported(const Dims& dm, uint32_t flags) {
 // them as the clock does (8 KV heads of 128, 32768 tokens: 3328 tokens, 240 workgroups, 8 % faster than 1024).
 // Splits below 1024 tokens only as far as the workspace holds their partial sums: its bound counts on 1024.  For these the cost of the
 // launches counts too: several splits per sequence need y_sum (worth about 300 tokens), splits of up to 128 tokens no statistics
-// launch (250); a split is not longer than the longest sequence, and every block of 32 query heads is a row of workgroups of its own.
+// launch (250); a turn lasts as long as the mean split, and all turns at least as long as the longest; and every block of 32 query heads
+// is a row of workgroups of its own.
 // 2 x 1500 tokens, d_in 1536: the value pass 22 -> 10 us with 128; 16 x 1000, 64 heads, d_in 1920: 79 us in one split each, 89 in
 // two, 115 with 128; 16 x 700: 72, 80 and 97; 16 x 700, 32 heads, d_in 1536: 56.6 in one split, 55.2 with 384, 62 with 128.
 int abs_split_tokens(const Dims& dm, const SeqMeta& mt, int64_t slots, size_t ws_bytes) {
   const int nct = abs_col_tiles(dm.D) + abs_col_tiles(dm.m), nhb = (dm.H_q + absorbed::kHB - 1) / absorbed::kHB;
   const size_t fixed = abs_pre_bytes(dm) + abs_win_bytes(dm, mt.n);
   int max_len = 0;
-  for (int b = 0; b < mt.n; ++b) max_len = std::max(max_len, mt.len[b]);
+  int64_t tokens = 0;
+  for (int b = 0; b < mt.n; ++b) { max_len = std::max(max_len, mt.len[b]); tokens += mt.len[b]; }
   auto splits_of = [&](int ts) {
     int64_t n = 0;
     for (int b = 0; b < mt.n; ++b) n += (mt.len[b] + ts - 1) / ts;
@@ -854,7 +856,8 @@ int abs_split_tokens(const Dims& dm, const SeqMeta& mt, int64_t slots, size_t ws
     if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ts; }
   }
   auto whole_cost = [&](int ts) {
-    return (splits_of(ts) * nct * nhb + 255) / 256 * (std::min(ts, max_len) + 700) + (max_len > ts ? 300 : 0) -
+    const int64_t n = splits_of(ts), turns = (n * nct * nhb + 255) / 256;
+    return std::max<int64_t>(turns * (tokens / n + 700), std::min(ts, max_len) + 700) + (max_len > ts ? 300 : 0) -
            (ts <= absorbed::kPvStatsTokens ? 250 : 0);
   };
   best_cost = whole_cost(best);
