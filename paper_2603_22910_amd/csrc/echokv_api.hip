@@ -807,11 +807,13 @@ size_t abs_pre_bytes(const Dims& dm) { return plan_ws(dm, 0, 0).total; }
 size_t abs_win_bytes(const Dims& dm, int nseq) {
   return align_up((size_t)nseq * dm.H_q * dm.d * 4) + align_up((size_t)nseq * dm.H_q * 2 * 4);
 }
-// upper bound for any launch group of a batch holding total_tokens tokens
+// upper bound for any launch group of a batch holding total_tokens tokens, short splits of the value pass included
+constexpr int64_t kAbsShortWgs = 512;
 size_t absorbed_ws_bytes(const Dims& dm, int batch, int64_t total_tokens) {
   const int n = std::min(batch, kMaxSeqPerLaunch);
-  return abs_pre_bytes(dm) + plan_absorbed(dm, n, total_tokens / kSlotTokens + n, total_tokens / 1024 + n).total +
-         abs_win_bytes(dm, n);
+  const int per_split = (abs_col_tiles(dm.D) + abs_col_tiles(dm.m)) * ((dm.H_q + absorbed::kHB - 1) / absorbed::kHB);
+  const int64_t splits = std::max(total_tokens / 1024 + n, std::min(total_tokens / kSlotTokens + n, kAbsShortWgs / per_split));
+  return abs_pre_bytes(dm) + plan_absorbed(dm, n, total_tokens / kSlotTokens + n, splits).total + abs_win_bytes(dm, n);
 }
 // 32-token workgroups of the score pass as long as they are one round (slots x 4 x blocks of 32 heads; 128-token / 32-token kernel, whole
 // calls in us): 128 of them 67.4 / 61.1, 256 99.5 / 93.0, 52.7 / 50.2 and 72.2 / 72.7, 384 54.5 / 53.5 and 110 / 107 with three
@@ -832,7 +834,8 @@ bool absorbed_supported(const Dims& dm, uint32_t flags) {
 // 700 tokens.  So the time goes like ceil(workgroups / 256) * (split + 700), and the split that
 // minimises it is taken: measured over 16 split sizes on three layer shapes this model orders
 // them as the clock does (8 KV heads of 128, 32768 tokens: 3328 tokens, 240 workgroups, 8 % faster than 1024).
-// Splits below 1024 tokens only as far as the workspace holds their partial sums: its bound counts on 1024.  For these the cost of the
+// Splits below 1024 tokens only where longer ones leave compute units idle, in at most two turns (kAbsShortWgs: what the workspace
+// query makes room for), and as far as the workspace holds their partial sums.  For these the cost of the
 // launches counts too: several splits per sequence need y_sum (worth about 300 tokens), splits of up to 128 tokens no statistics
 // launch (250); a turn lasts as long as the mean split, and all turns at least as long as the longest; and every block of 32 query heads
 // is a row of workgroups of its own.
@@ -860,8 +863,9 @@ int abs_split_tokens(const Dims& dm, const SeqMeta& mt, int64_t slots, size_t ws
     return std::max<int64_t>(turns * (tokens / n + 700), std::min(ts, max_len) + 700) + (max_len > ts ? 300 : 0) -
            (ts <= absorbed::kPvStatsTokens ? 250 : 0);
   };
+  if (splits_of(best) * nct * nhb > 256) return best;
   best_cost = whole_cost(best);
-  for (int ts = 1024 - kSlotTokens; ts > 0; ts -= kSlotTokens) {
+  for (int ts = 1024 - kSlotTokens; ts > 0 && splits_of(ts) * nct * nhb <= kAbsShortWgs; ts -= kSlotTokens) {
     if (fixed + plan_absorbed(dm, mt.n, slots, splits_of(ts)).total > ws_bytes) break;      // (shorter ones need more)
     const int64_t cost = whole_cost(ts);
     if (cost < best_cost) { best_cost = cost; best = ts; }

@@ -368,6 +368,17 @@ def test_decode_path_query(lib):
     assert ek.workspace_bytes(big, 2, 5000) >= ek.workspace_bytes(small, 2, 5000) > 5000 * 512 * 2 * 2
 
 
+def test_absorbed_workspace_has_room_for_short_splits(lib):
+    """Few predicted dims: nothing but the absorbed plan asks for workspace.  4 x 700 tokens, 64 heads, d_in 1920: splits of the
+    value pass of 256 tokens (12 x 2 blocks of heads x 8 column tiles: one round of workgroups), fp32 sums of [64, 1920] each."""
+    sh = ek.make_shape(64, 8, 128, 896, "bf16", flags=ek.FLAG_ABSORBED)
+    n, slots, pad, d_in = 4, 24, 64, 1920
+    need = (n * pad * d_in * 2 + pad * slots * 128 * 4 + 12 * pad * 2 * 4 + 12 * pad * d_in * 4 + n * 64 * d_in * 4
+            + 6 * n * 64 * 128 * 4 + n * 64 * 2 * 4 + n * 64 * 128 * 4 + n * 64 * 2 * 4)
+    assert ek.workspace_bytes(sh, n, n * 700) >= need
+    assert ek.workspace_bytes(sh, n, n * 700) <= need + (16 << 20)
+
+
 def test_compress_in_place_argument_rules(lib):
     sh = ek.make_shape(8, 8, 64, 256, "bf16")
     full = ek.LayerCache(FAKE, FAKE, 512, 512, [0, 256], [0, 0], [256, 256])     # no valid rows: nothing launched

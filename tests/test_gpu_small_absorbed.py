@@ -74,15 +74,18 @@ SPLITS = [                                       # H_q, H_kv, m, sequences, leng
     (64, 8, 896, 16, 1000, 1024),
     (32, 8, 512, 16, 1000, 512),
     (32, 8, 512, 2, 1500, 128),
+    (64, 8, 896, 4, 700, 256),                   # few predicted dims: only the absorbed plan asks for workspace
     (32, 8, 512, 1, 128, 128),                   # one split that works out its own statistics
 ]
 
 
+@pytest.mark.parametrize("more", [pytest.param(0, id="asked"), pytest.param(64 << 20, id="larger")])
 @pytest.mark.parametrize("H_q,H_kv,m,n,L,ts", SPLITS)
-def test_tokens_per_split(H_q, H_kv, m, n, L, ts):
+def test_tokens_per_split(H_q, H_kv, m, n, L, ts, more):
+    """The same in the workspace that was asked for and in a larger one."""
     inp = synth.generate(synth.Workload("absorbed_splits", "bf16", H_q, H_kv, 128, m, seed=79, seq_lens=(L,) * n))
     dw = DeviceWorkload(inp, flags=ek.FLAG_ABSORBED)
-    dw.workspace = torch.full((dw.workspace.numel() + (64 << 20),), 0xA5, dtype=torch.uint8, device=dw.dev)   # room for every choice
+    dw.workspace = torch.full((dw.workspace.numel() + more,), 0xA5, dtype=torch.uint8, device=dw.dev)
     out, _ = dw.decode()
     torch.cuda.synchronize()
     o_ref, _ = ref.decode_ref(inp)
