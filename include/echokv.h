@@ -200,7 +200,11 @@ int echokv_augment_weights(const echokv_shape *shape, const void *w_k, const voi
  * context (2 (D - m) values per token), a rotated copy of the retained keys,
  * and, for chunks under 1024 queries in front of a long context, the fp32
  * partial results of the launch split over the keys (at most 8 shares of
- * d + 2 words per query and head).  Returns 0 on a bad shape. */
+ * d + 2 words per query and head).  Returns 0 on a bad shape.
+ * echokv_decode_attn also accepts less, down to what the request itself needs at
+ * least (its own sequence lengths, one partial per 128 tokens); it may then take
+ * kernels that split the context differently, and the result differs in rounding
+ * from the same call with the workspace asked for here. */
 size_t echokv_workspace_bytes(const echokv_shape *shape, int32_t batch,
                               int64_t total_tokens, int32_t max_q);
 
@@ -238,8 +242,9 @@ int echokv_decode_path(const echokv_shape *shape, int32_t *path_out);
 
 /* echokv_decode_attn for callers that cannot allocate device memory and have no
  * workspace to hand over: code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc.  Same arguments, same kernels, same result as
- * echokv_decode_attn (shape->flags honoured alike), but the split partials (and
+ * harnesses that forbid hipMalloc.  Same arguments, same kernels, same result, bit
+ * for bit, as echokv_decode_attn with the workspace that echokv_workspace_bytes
+ * asks for (shape->flags honoured alike), but the split partials (and
  * whatever else the chosen path keeps in its workspace) live in a fixed buffer
  * of ECHOKV_STATIC_SCRATCH_BYTES inside the library's device image instead of a
  * caller-owned workspace.  The call allocates and frees nothing.

@@ -176,6 +176,13 @@ struct ProfScope {
 #define HIP_TRY(expr) do { if ((expr) != hipSuccess) return ECHOKV_ERR_HIP; } while (0)
 #define LAUNCH_CHECK() do { if (hipGetLastError() != hipSuccess) return ECHOKV_ERR_HIP; } while (0)
 
+// Workspace that a choice of kernels may count on beyond the least it needs (small decode problems, short absorbed splits).  A
+// request that the fixed scratch can serve never uses more than that scratch holds: echokv_decode_attn_static then makes the same
+// choices, and gives the same bits, as a call with the workspace that echokv_workspace_bytes asks for.
+size_t choice_bytes(size_t ws_bytes, size_t least) {
+  return least <= kStaticScratchBytes ? std::min(ws_bytes, kStaticScratchBytes) : ws_bytes;
+}
+
 // Fill tbase for a tile size; returns the tile count.
 int fill_tiles(SeqMeta& mt, int tile_tokens) {
   int acc = 0;
@@ -1352,7 +1359,7 @@ int echokv_decode_attn_ex(const echokv_shape* shape, const echokv_layer_cache* a
     if (!workspace || workspace_bytes < need) return ECHOKV_ERR_WORKSPACE;
     if ((uintptr_t)workspace % 256) return ECHOKV_ERR_WORKSPACE;
     return absorbed_impl(dm, value_only, anchor, target, w_k, w_v, q, has_extras ? extras : nullptr, out,
-                         lse_out, (char*)workspace, workspace_bytes, (hipStream_t)hip_stream);
+                         lse_out, (char*)workspace, choice_bytes(workspace_bytes, need), (hipStream_t)hip_stream);
   }
   if ((shape->flags & ECHOKV_FLAG_W_PACKED) &&
       (dm.r != 0 || (shape->flags & ECHOKV_FLAG_UNFUSED) || !dm.bf16 || !fused_decode_supported<bf16_t>(dm.d, dm.G)))
@@ -1364,9 +1371,10 @@ int echokv_decode_attn_ex(const echokv_shape* shape, const echokv_layer_cache* a
   if (!workspace || workspace_bytes < need) return ECHOKV_ERR_WORKSPACE;
   if ((uintptr_t)workspace % 256) return ECHOKV_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
+  const size_t room = choice_bytes(workspace_bytes, need);
   const echokv_decode_extras* ex = has_extras ? extras : nullptr;
-  return dm.bf16 ? decode_impl<bf16_t>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, workspace_bytes, st)
-                 : decode_impl<float>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, workspace_bytes, st);
+  return dm.bf16 ? decode_impl<bf16_t>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, room, st)
+                 : decode_impl<float>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, room, st);
 }
 
 int echokv_decode_attn(const echokv_shape* shape, const echokv_layer_cache* anchor,

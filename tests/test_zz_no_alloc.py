@@ -50,6 +50,12 @@ def test_static_scratch_split_head_and_gqa():
     both_ways(synth.Workload("static_split_head_small", "bf16", 32, 8, 128, 64, seed=12, seq_lens=(130,)))
 
 
+def test_static_scratch_makes_the_choices_of_the_workspace_call():
+    # 240 partials of 32 tokens, 280 heads of 130 words each, are 35 MB, one per 128 tokens 9 MB: the call fits the scratch, the
+    # kernel for small problems does not, and the call with a workspace must not take it either
+    both_ways(synth.Workload("static_choice", "bf16", 280, 35, 128, 4352, seed=13, seq_lens=(7680,)))
+
+
 def test_static_scratch_limit_is_an_error_and_touches_nothing():
     # the unfused path keeps K-hat / V-hat of every token in its workspace: far beyond the limit here
     w = synth.CONFIGS[1].scaled(seq_lens=(40000,))
