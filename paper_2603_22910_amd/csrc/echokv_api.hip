@@ -304,13 +304,32 @@ int merge_launch(const Dims& dm, const float* po, const float* pml, void* out, f
 }
 
 // ---- small problems: everything but the merge in one launch (fused_decode_small.h) ------------
-// Workgroups up to which the small kernel is the faster one.  Measured (us, 32 / 64 tokens per workgroup /
-// 256 x 256 kernel): 188 workgroups of 32 tokens 24.7 / 29.5 / 86, 252 of them 32.5 / 29.8 / 86; 504 workgroups of
-// 64 tokens (three layers) 84 / 63 / 87, 202 / 159 / 223, 60 / 45 / 60; 752 of them 120 / 89 / 89, 295 / 233 / 227,
-// 84 / 62 / 61.  fp32 (16 / 32 tokens / 256 x 256): 128 workgroups of 16 16.6 / 22 / 464; 1000 of 32 tokens 79 / 71 / 510,
+// bf16, workgroups of the product at most; between these and few, the times of both kernels are estimated
+// (small_is_faster).  32 tokens per workgroup below kSmallFewWgs of them (32 / 64 tokens, us: 188 of 32 24.7 / 29.5, 252 32.5 / 29.8).
+// fp32 (16 / 32 tokens / 256 x 256): 128 workgroups of 16 16.6 / 22 / 464; 1000 of 32 tokens 79 / 71 / 510,
 // growing by 71 per 1000 while the large kernel stays at 510 until its tiles fill the chip.
 constexpr int kSmallFewWgs = 240, kSmallMaxWgs = 704, kSmallMaxWgsF32 = 6144;
 inline int small_col_tile(const Dims& dm) { return dm.bf16 ? 128 : dm.d; }
+// Times of a bf16 call in us, with tb token blocks of 16 per workgroup and with the 256 x 256 kernel: launch and merge, rounds of
+// workgroups of the product, and the rows of the retained heads, which the units stream at about 6.5 TB/s; in the
+// large kernel's launch half of that hides behind the product.  A round of the small kernel is between a whole and a partial one
+// (its workgroups end at different times); the large kernel needs one round for up to 256 tiles, of 1.0 us per k-tile
+// and pass, or 0.72 where all columns of a tile fit one half of it.  Against the clock (64-token / 256 x 256 kernel, us): 8 KV heads,
+// one predicted, 8 x 2000 tokens 43.7 / 57.4, 8 x 3200 73.7 / 59.6, 8 x 5568 137 / 93; two, 8 x 1600 54.6 / 74.2, 8 x 2048 65.6 / 75.1,
+// 8 x 2752 90.9 / 75.4; four with 32 heads (d_in 7680) 222 / 277 at 8 x 1024, 297 / 280 at 8 x 1344; 7 query heads per KV head, one
+// predicted of 8, 8 x 1984 (all rows seven times) 96 / 80.  Over 132 such problems the choice costs 0.2 % in the mean, 8 % at most.
+template <typename T>
+bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgroups) {
+  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1;
+  int64_t tokens = 0, t256 = 0;
+  for (int b = 0; b < mt.n; ++b) { tokens += mt.len[b]; t256 += (mt.len[b] + 255) / 256; }
+  const double streams = (double)(tokens * dm.g0 * (dm.G / gt)) * dm.d * 2 * sizeof(T) / 6.5e6;
+  const double rounds = 0.5 * ((double)workgroups / 256 + (double)((workgroups + 255) / 256));
+  const double small = 8 + rounds * (6 + (tb == 2 ? 0.0072 : 0.0112) * dm.d_in) + streams;
+  const int64_t tiles = t256 * ((dm.d_out_v + 255) / 256);
+  const double large = 17 + (double)((tiles + 255) / 256) * 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0) + 0.5 * streams;
+  return small <= large;
+}
 // Token blocks of 16 per workgroup (0: the problem is not small).
 template <typename T>
 int small_token_blocks(const Dims& dm, const SeqMeta& mt) {
@@ -326,8 +345,8 @@ int small_token_blocks(const Dims& dm, const SeqMeta& mt) {
     if (t16 * ct <= 256) return 1;
     return t32 * ct * dm.d / 64 <= kSmallMaxWgsF32 ? 2 : 0;
   }
-  if (t32 * ct <= kSmallFewWgs) return 2;
-  return t64 * ct <= kSmallMaxWgs ? 4 : 0;
+  if (t32 * ct <= kSmallFewWgs) return small_is_faster<T>(dm, mt, 2, t32 * ct) ? 2 : 0;
+  return t64 * ct <= kSmallMaxWgs && small_is_faster<T>(dm, mt, 4, t64 * ct) ? 4 : 0;
 }
 // Partial slots a small launch can need at most, the window's one per sequence included.
 int64_t small_max_slots(const Dims& dm, int batch, int64_t total_tokens) {

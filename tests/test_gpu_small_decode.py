@@ -20,8 +20,8 @@ CASES = [
     (8, 4, 128, 128, "bf16", (31, 32, 33, 1)),          # 3 column tiles, edges of a 32-token tile
     (8, 4, 128, 128, "bf16", (2560,)),                  # 240 workgroups: the last with 32-token tiles
     (8, 4, 128, 128, "bf16", (2561,)),                  # the first with 64-token tiles
-    (8, 4, 128, 128, "bf16", (14976,)),                 # 702 of at most 704 workgroups
-    (8, 4, 128, 128, "bf16", (15000, 64, 65)),          # over it: the 256 x 256 kernel
+    (8, 4, 128, 128, "bf16", (14976,)),                 # 702 of at most 704 workgroups: slower than the 256 x 256 kernel
+    (8, 4, 128, 128, "bf16", (15000, 64, 65)),          # over it
     (10, 5, 64, 128, "bf16", (65, 129, 3)),             # three predicted heads of 64: half of the last tile is empty
     (16, 2, 128, 64, "bf16", (200, 63)),                # split head (r = 64), G = 8
     (4, 1, 64, 0, "bf16", (100,)),                      # d_in = 64: fewer steps than waves, the 256 x 256 kernel
@@ -72,3 +72,29 @@ def test_workspace_of_the_large_kernel_alone_is_still_accepted():
     with pytest.raises(ek.EchoKVError) as e:
         dw.decode()
     assert e.value.code == ek.ERR_WORKSPACE
+
+
+ROUTES = [                                       # H_q, H_kv, d, m, lengths, tokens per partial: 32, 64 or (256 x 256 kernel) 128
+    (8, 4, 128, 128, (2560,), 32),
+    (8, 4, 128, 128, (2561,), 64),
+    (8, 4, 128, 128, (10880,), 64),              # 510 workgroups: two rounds
+    (8, 4, 128, 128, (10881,), 128),             # 513
+    (8, 8, 128, 896, (3200,) * 8, 128),          # 400, each unit streams seven retained heads as well
+    (8, 8, 128, 768, (1600,) * 8, 64),           # 400, six retained heads of half as many tokens
+]
+
+
+@pytest.mark.parametrize("H_q,H_kv,d,m,lens,tok", ROUTES)
+def test_kernel_taken(H_q, H_kv, d, m, lens, tok):
+    """Which kernel ran, by how many partials it left in the workspace."""
+    inp = synth.generate(synth.Workload("small_route", "bf16", H_q, H_kv, d, m, seed=80, seq_lens=lens))
+    dw = DeviceWorkload(inp)
+    dw.workspace.fill_(0xA5)
+    out, _ = dw.decode()
+    torch.cuda.synchronize()
+    o_ref, _ = ref.decode_ref(inp)
+    check(host(out), o_ref, "bf16", f"{H_q} {H_kv} {d} {m} {lens}")
+    end = int((dw.workspace != 0xA5).nonzero().max()) + 1
+    slots = sum(-(-L // tok) for L in lens)      # and one per sequence for a window, not written here
+    want = ((slots + len(lens)) * H_q * d * 4 + 255) // 256 * 256 + slots * H_q * 8
+    assert want - 8 < end <= want
