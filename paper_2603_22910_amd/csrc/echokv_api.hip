@@ -356,12 +356,16 @@ int64_t small_max_slots(const Dims& dm, int batch, int64_t total_tokens) {
   return std::min<int64_t>(total_tokens / (dm.bf16 ? 32 : 16) + n, wgs / ct) + n;
 }
 
+// Streaming workgroups behind the large kernel's: up to 1024 tokens each, longer ones would outlast the last tiles, and at least 512.
+// Each takes a compute unit, and below that its start and its reductions outweigh its rows: with 128 tokens 17 sequences of
+// 2187-13124 tokens, one retained head of 64, 80 us, with 512 55; 8 x 4000, seven heads of 128, 80 and 73.
+constexpr int kStreamMinChunk = 512;
 // Streaming part of a decode call (retained heads, window) as workgroups of the product's launch.  slot_tokens:
-// tokens per partial slot of mt.s.sbase.  Chunks start at one round of a workgroup's rows and double until
+// tokens per partial slot of mt.s.sbase.  Chunks start at min_chunk tokens and double until
 // at most max_wgs workgroups are left or they are max_chunk tokens long.
 template <typename T>
 Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* qq, const echokv_decode_extras* ex,
-                        const KvExtras& kx, float* po, float* pml, int b0, int slot_tokens, int max_wgs, int max_chunk,
+                        const KvExtras& kx, float* po, float* pml, int b0, int slot_tokens, int min_chunk, int max_wgs, int max_chunk,
                         StreamMeta& mt, int* stream_step, int* win_slot0) {
   Streams<T> s;
   const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1, ny = dm.g0 * (dm.G / gt);
@@ -370,7 +374,7 @@ Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* q
   r.q = qq; r.H_q = dm.H_q; r.G = dm.G; r.d = dm.d; r.scale = dm.scale; r.part_o = po; r.part_ml = pml;
   r.slot_tokens = slot_tokens; r.rope_cos = kx.rope_cos; r.rope_sin = kx.rope_sin; r.win = Window{kx.n_sink, kx.n_recent};
   s.win = r;
-  for (r.split_tokens = kSlotTokens;; r.split_tokens *= 2) {
+  for (r.split_tokens = min_chunk;; r.split_tokens *= 2) {
     int acc = 0;
     for (int b = 0; b < mt.s.n; ++b) { mt.cbase[b] = acc; acc += (mt.s.len[b] + r.split_tokens - 1) / r.split_tokens; }
     mt.cbase[mt.s.n] = acc;
@@ -405,7 +409,7 @@ int decode_small(const Dims& dm, int tb, bool packed, const echokv_layer_cache* 
   const int bn = small_col_tile(dm);
   a.n_ttiles = fill_tiles(mt.s, tok); a.n_col_tiles = (dm.d_out_v + bn - 1) / bn;
   a.n_fused = (a.n_ttiles * a.n_col_tiles + 7) / 8 * 8;
-  a.streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, tok, 256, 2048, mt, stream_step, win_slot0);
+  a.streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, tok, kSlotTokens, 256, 2048, mt, stream_step, win_slot0);
   return launch_fused_decode_small<T>(a, mt, tb, packed, st);
 }
 
@@ -470,12 +474,11 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
     if constexpr (sizeof(T) == 2) {
       if (fused && n_rec_heads > 0) {
         // one launch: the product's tiles, then (they fill the units that have no tile left) the streaming
-        // workgroups.  Up to 1024 tokens each: longer ones would outlast the last tiles, shorter ones cost
-        // their reductions.
+        // workgroups.
         StreamMeta sm;
         sm.s = mt;
         int win_slot0 = -1;
-        const Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, 1024, 1024, sm, &stream_step, &win_slot0);
+        const Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, kStreamMinChunk, 1024, 1024, sm, &stream_step, &win_slot0);
         ProfScope prof;
         int rc = prof.begin(0, st);
         if (rc) return rc;
@@ -990,7 +993,7 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
       StreamMeta sm;
       sm.s = mt;
       int stream_step, win_slot0;
-      Streams<T> streams = plan_streams<T>(dm, tg, a.q, ex, kx, win_po, win_pml, b0, kSlotTokens, 1024, 1024, sm, &stream_step, &win_slot0);
+      Streams<T> streams = plan_streams<T>(dm, tg, a.q, ex, kx, win_po, win_pml, b0, kSlotTokens, kStreamMinChunk, 1024, 1024, sm, &stream_step, &win_slot0);
       streams.ret.scale = a.qscale;
       streams.win.win_slot0 = 0;
       rc = launch_fused_kscores<T>(dm.H_q, dm.H_kv, dm.d, dm.m, dm.d_out_v, dm.g0, a.qscale,

@@ -14,13 +14,17 @@ from test_gpu_parity import check, host, make_dw
 
 pytestmark = pytest.mark.gpu
 
-# H_q, H_kv, d, m, lengths.  Chunks of 128 tokens until 1024 workgroups are exceeded.
+# H_q, H_kv, d, m, lengths.  Chunks of 512 tokens, longer ones where 1024 workgroups would be exceeded.
 CASES = [
-    (8, 4, 128, 128, (1100, 129, 1)),         # G = 2, 12 chunks: 8 and 4
-    (12, 4, 64, 64, (900, 31)),               # G = 3: one query head at a time, 9 chunks
-    (16, 4, 64, 128, (1024,)),                # G = 4, two retained heads, 8 chunks, no tail
+    (8, 4, 128, 128, (1100, 129, 1)),         # G = 2, 5 chunks
+    (8, 4, 128, 128, (4500, 600, 1)),         # 12 chunks: 8 and 4
+    (12, 4, 64, 64, (900, 31)),               # G = 3: one query head at a time
+    (12, 4, 64, 64, (4100, 31)),              # 10 chunks
+    (16, 4, 64, 128, (1024,)),                # G = 4, two retained heads
+    (16, 4, 64, 128, (4096,)),                # 8 chunks, no tail
     (32, 4, 128, 256, (257, 255)),            # G = 8: two groups per KV head
-    (8, 8, 64, 512, (17000, 70)),             # every head retained; 134 chunks x 8 heads: chunks of 256 tokens
+    (8, 8, 64, 512, (17000, 70)),             # every head retained; 35 chunks
+    (28, 4, 128, 384, (25000, 70)),           # G = 7: 50 chunks x 21 are too many, 26 of 1024 tokens
 ]
 
 
