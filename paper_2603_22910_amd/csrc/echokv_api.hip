@@ -311,7 +311,7 @@ int merge_launch(const Dims& dm, const float* po, const float* pml, void* out, f
 constexpr int kSmallFewWgs = 240, kSmallMaxWgs = 704, kSmallMaxWgsF32 = 6144;
 inline int small_col_tile(const Dims& dm) { return dm.bf16 ? 128 : dm.d; }
 // Times of a bf16 call in us, with tb token blocks of 16 per workgroup and with the 256 x 256 kernel: launch and merge, rounds of
-// workgroups of the product, and the rows of the retained heads, which the units stream at about 6.5 TB/s; in the
+// workgroups of the product, and the rows of the retained heads, which the units stream at about 6.5 TB/s (with rotary tables half of that); in the
 // large kernel's launch half of that hides behind the product.  A round of the small kernel is between a whole and a partial one
 // (its workgroups end at different times); the large kernel needs one round for up to 256 tiles, of 1.0 us per k-tile
 // and pass, or 0.72 where all columns of a tile fit one half of it.  Against the clock (64-token / 256 x 256 kernel, us): 8 KV heads,
@@ -319,11 +319,11 @@ inline int small_col_tile(const Dims& dm) { return dm.bf16 ? 128 : dm.d; }
 // 8 x 2752 90.9 / 75.4; four with 32 heads (d_in 7680) 222 / 277 at 8 x 1024, 297 / 280 at 8 x 1344; 7 query heads per KV head, one
 // predicted of 8, 8 x 1984 (all rows seven times) 96 / 80.  Over 132 such problems the choice costs 0.2 % in the mean, 8 % at most.
 template <typename T>
-bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgroups) {
+bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgroups, bool rope) {
   const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1;
   int64_t tokens = 0, t256 = 0;
   for (int b = 0; b < mt.n; ++b) { tokens += mt.len[b]; t256 += (mt.len[b] + 255) / 256; }
-  const double streams = (double)(tokens * dm.g0 * (dm.G / gt)) * dm.d * 2 * sizeof(T) / 6.5e6;
+  const double streams = (double)(tokens * dm.g0 * (dm.G / gt)) * dm.d * 2 * sizeof(T) / (rope ? 3.25e6 : 6.5e6);
   const double rounds = 0.5 * ((double)workgroups / 256 + (double)((workgroups + 255) / 256));
   const double small = 8 + rounds * (6 + (tb == 2 ? 0.0072 : 0.0112) * dm.d_in) + streams;
   const int64_t tiles = t256 * ((dm.d_out_v + 255) / 256);
@@ -332,7 +332,7 @@ bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgrou
 }
 // Token blocks of 16 per workgroup (0: the problem is not small).
 template <typename T>
-int small_token_blocks(const Dims& dm, const SeqMeta& mt) {
+int small_token_blocks(const Dims& dm, const SeqMeta& mt, bool rope) {
   if (!fused_decode_supported<T>(dm.d, dm.G) || dm.d_out_v == 0) return 0;
   if (dm.d_in < (sizeof(T) == 2 ? 128 : 64)) return 0;      // every wave needs a step of 32 (fp32: 16) input dims
   // 32-bit byte offsets inside a token tile and inside W
@@ -345,8 +345,8 @@ int small_token_blocks(const Dims& dm, const SeqMeta& mt) {
     if (t16 * ct <= 256) return 1;
     return t32 * ct * dm.d / 64 <= kSmallMaxWgsF32 ? 2 : 0;
   }
-  if (t32 * ct <= kSmallFewWgs) return small_is_faster<T>(dm, mt, 2, t32 * ct) ? 2 : 0;
-  return t64 * ct <= kSmallMaxWgs && small_is_faster<T>(dm, mt, 4, t64 * ct) ? 4 : 0;
+  if (t32 * ct <= kSmallFewWgs) return small_is_faster<T>(dm, mt, 2, t32 * ct, rope) ? 2 : 0;
+  return t64 * ct <= kSmallMaxWgs && small_is_faster<T>(dm, mt, 4, t64 * ct, rope) ? 4 : 0;
 }
 // Partial slots a small launch can need at most, the window's one per sequence included.
 int64_t small_max_slots(const Dims& dm, int batch, int64_t total_tokens) {
@@ -447,7 +447,7 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
     const T* qq = (const T*)q + (int64_t)b0 * dm.H_q * dm.d;
     int stream_step = 1, fused_step = 1;
 
-    const int tb = fused && !(flags & ECHOKV_FLAG_STAGED) ? small_token_blocks<T>(dm, mt) : 0;
+    const int tb = fused && !(flags & ECHOKV_FLAG_STAGED) ? small_token_blocks<T>(dm, mt, kx.rope_cos != nullptr) : 0;
     if (tb > 0) {
       SeqMeta ms = mt;
       const int sl = fill_slots(ms, 16 * tb);
@@ -478,9 +478,10 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
         StreamMeta sm;
         sm.s = mt;
         int win_slot0 = -1;
-        const Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, kStreamMinChunk, 1024, 1024, sm, &stream_step, &win_slot0);
+        Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, kStreamMinChunk, 1024, 1024, sm, &stream_step, &win_slot0);
+        int rc;
         ProfScope prof;
-        int rc = prof.begin(0, st);
+        rc = prof.begin(0, st);
         if (rc) return rc;
         rc = launch_fused_decode<T>(dm.H_q, dm.H_kv, dm.d, dm.m, dm.d_out_v, dm.g0, dm.scale,
                                     (const T*)an->k, (const T*)an->v, (const T*)tg->k, (const T*)tg->v, wk, wv, qq, po,
