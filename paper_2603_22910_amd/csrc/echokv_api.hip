@@ -394,6 +394,23 @@ Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* q
   return s;
 }
 
+// Retained heads of a bf16 call in a launch of their own ahead of the large kernel's: with three and more passes over their rows
+// (one per group of query heads that share a row: 3, 5 or 7 of them per KV head are as many groups) the streams run at 0.65-0.8 of their
+// rate where only eight waves share a unit.  That is made up for by the units that the product's last round leaves idle if they
+// are worth 0.12 of the streams' time.  In the launch / ahead of it, us: 8 KV heads, 7 retained, 8 x 6000 tokens, G = 5 194 / 170, G = 7 243 /
+// 202; 40 x 4000 684 / 601 and 863 / 784, with rope 920 / 732 and 1170 / 919; 2 x 40000 (more idle units) 345 / 378 and 429 / 469.
+bool streams_by_themselves(const Dims& dm, const SeqMeta& mt) {
+  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1, passes = dm.G / gt;
+  if (dm.g0 == 0 || passes < 3) return false;
+  int64_t tokens = 0, tiles = 0;
+  for (int b = 0; b < mt.n; ++b) { tokens += mt.len[b]; tiles += (mt.len[b] + 255) / 256; }
+  tiles *= (dm.d_out_v + 255) / 256;
+  const double tile_us = 9 + 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0);        // see small_is_faster
+  const double idle = (double)((tiles + 255) / 256 * 256 - tiles) * tile_us;
+  const double streams = (double)(tokens * dm.g0 * passes) * dm.d * 4 / 6.5e6 * 256;
+  return idle < 0.12 * streams;
+}
+
 template <typename T>
 int decode_small(const Dims& dm, int tb, bool packed, const echokv_layer_cache* an, const echokv_layer_cache* tg,
                  const T* wk, const T* wv, const T* qq, const echokv_decode_extras* ex, const KvExtras& kx,
@@ -480,6 +497,14 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
         int win_slot0 = -1;
         Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, kStreamMinChunk, 1024, 1024, sm, &stream_step, &win_slot0);
         int rc;
+        if (streams_by_themselves(dm, mt)) {
+          AttnArgs<T> a = streams.ret;
+          a.split_tokens = pick_split_tokens(tokens, n_ret_heads);
+          stream_step = a.split_tokens / kSlotTokens;
+          rc = launch_attn_split<T>(dm, a, mt, n_ret_heads, st);
+          if (rc) return rc;
+          streams.n_ret = 0;
+        }
         ProfScope prof;
         rc = prof.begin(0, st);
         if (rc) return rc;
