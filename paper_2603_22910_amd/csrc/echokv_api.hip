@@ -1019,7 +1019,8 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
       StreamMeta sm;
       sm.s = mt;
       int stream_step, win_slot0;
-      Streams<T> streams = plan_streams<T>(dm, tg, a.q, ex, kx, win_po, win_pml, b0, kSlotTokens, kStreamMinChunk, 1024, 1024, sm, &stream_step, &win_slot0);
+      Streams<T> streams = plan_streams<T>(dm, tg, a.q, ex, kx, win_po, win_pml, b0, kSlotTokens, dm.d_out_v ? kStreamMinChunk : kSlotTokens,
+                                            dm.d_out_v ? 1024 : 4096, 1024, sm, &stream_step, &win_slot0);
       streams.ret.scale = a.qscale;
       streams.win.win_slot0 = 0;
       rc = launch_fused_kscores<T>(dm.H_q, dm.H_kv, dm.d, dm.m, dm.d_out_v, dm.g0, a.qscale,

@@ -395,6 +395,16 @@ __global__ __launch_bounds__(NTHREADS) void fused_kscores_kernel(Args a, Streams
   });
 }
 
+// The same streaming workgroups with no product in front of them (every head is retained): four waves and no tiles, so that
+// a unit holds several.  Whole calls, as workgroups of the product's kernel / so: 2 x 9496-56976 tokens, two heads of 64, 48.8 / 45.1 us, 29 x
+// 53-318 tokens, eight heads of 128 50.5 / 47.4, with rope and window 84 / 76; one sequence of 40000, rope and window 94 / 101 (117 as two launches).
+constexpr int kScoreStreamWaves = 4;
+template <int HD>
+__global__ __launch_bounds__(64 * kScoreStreamWaves) void score_stream_kernel(Streams<bf16_t> streams, StreamMeta smeta, float* s_out, int64_t s_ld) {
+  __shared__ __attribute__((aligned(16))) char smem[stream_smem_bytes<bf16_t, HD, kScoreStreamWaves>()];
+  score_stream_workgroup<HD, kScoreStreamWaves>(streams, smeta, blockIdx.x, s_out, s_ld, smem);
+}
+
 // Stand-alone predictor product (Eq. 3) with the same main loop: K_hat or V_hat
 // (blockIdx.y) of the tile is rounded to bf16 and stored at
 // out[row, col0 + column].  Output row = sbase[b]*kSlotTokens + j.  With an
@@ -575,7 +585,13 @@ inline int launch_fused_kscores(int H_q, int H_kv, int d, int m, int d_out, int 
     a.rope_cos = ex.rope_cos; a.rope_sin = ex.rope_sin; a.n_sink = 0; a.n_recent = 0;
     a.s_out = s_out; a.s_ld = s_ld;
     a.n_col_tiles = (a.d_out + fused::BN - 1) / fused::BN;
-    a.n_tiles = fused_fill_tiles(mt) * a.n_col_tiles;          // (0: every head is retained)
+    a.n_tiles = fused_fill_tiles(mt) * a.n_col_tiles;
+    if (a.n_tiles == 0) {                    // every head is retained
+      const dim3 sg(streams.n_ret + streams.n_win), sb(64 * fused::kScoreStreamWaves);
+      if (d == 128) hipLaunchKernelGGL((fused::score_stream_kernel<128>), sg, sb, 0, st, streams, smt, s_out, s_ld);
+      else hipLaunchKernelGGL((fused::score_stream_kernel<64>), sg, sb, 0, st, streams, smt, s_out, s_ld);
+      return hipGetLastError() != hipSuccess ? 7 : 0;
+    }
     const dim3 g((a.n_tiles + 7) / 8 * 8 + streams.n_ret + streams.n_win), blk(fused::NTHREADS);
     const bool rope = ex.rope_cos != nullptr;
     if (d == 128 && rope) hipLaunchKernelGGL((fused::fused_kscores_kernel<128, true>), g, blk, 0, st, a, streams, smt);
