@@ -456,6 +456,7 @@ __global__ __launch_bounds__(NTHREADS) void recon_mfma_kernel(Args a, SeqMeta me
   // token row: 32 chunks of 16 bytes, chunk ch at ch ^ (token % 32)
 #pragma unroll
   for (int tb = 0; tb < 4; ++tb) {
+    if (t.j0 + t.wt * WM + tb * 16 >= t.L) break;      // (uniform: rows past the end are not stored; their rounding is 2 us of a tile)
     const int j = t.wt * WM + tb * 16 + lc;
 #pragma unroll
     for (int cb = 0; cb < 8; ++cb) {

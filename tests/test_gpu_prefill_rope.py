@@ -18,6 +18,10 @@ CASES = [                                # H_q, H_kv, d, m, tokens, queries
     (12, 6, 64, 0, 7700, 33),            # no retained head; the second column tile is half empty
     (4, 2, 64, 128, 700, 70),            # no predicted head: the launch rotates retained keys only
     (4, 4, 128, 256, 5, 5),
+    (4, 2, 128, 128, 16, 16),            # rows are stored in blocks of 16 as far as the tile's tokens go
+    (4, 2, 128, 128, 17, 9),
+    (4, 2, 64, 0, 272, 20),
+    (4, 2, 64, 0, 273, 20),
 ]
 
 
