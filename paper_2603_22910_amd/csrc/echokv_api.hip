@@ -1019,7 +1019,7 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
       StreamMeta sm;
       sm.s = mt;
       int stream_step, win_slot0;
-      Streams<T> streams = plan_streams<T>(dm, tg, a.q, ex, kx, win_po, win_pml, b0, kSlotTokens, dm.d_out_v ? kStreamMinChunk : kSlotTokens,
+      Streams<T> streams = plan_streams<T>(dm, tg, a.q, ex, kx, win_po, win_pml, b0, kSlotTokens, kStreamMinChunk,
                                             dm.d_out_v ? 1024 : 4096, 1024, sm, &stream_step, &win_slot0);
       streams.ret.scale = a.qscale;
       streams.win.win_slot0 = 0;
