@@ -264,6 +264,21 @@ __device__ __forceinline__ void stream_workgroup(const Streams<T>& st, const Str
   else attn_split_body<T, LPR, 1, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
 }
 
+// The same workgroups in a launch of their own: four waves each, so that a unit holds several.
+constexpr int kStreamWaves = 4;
+template <typename T, int HD>
+__global__ __launch_bounds__(64 * kStreamWaves) void stream_kernel(Streams<T> st, StreamMeta meta) {
+  __shared__ __attribute__((aligned(16))) char smem[stream_smem_bytes<T, HD, kStreamWaves>()];
+  stream_workgroup<T, HD, kStreamWaves, 4>(st, meta, blockIdx.x, smem);
+}
+template <typename T>
+inline int launch_streams(const Streams<T>& s, const StreamMeta& meta, hipStream_t st) {
+  const dim3 grid(s.n_ret + s.n_win), blk(64 * kStreamWaves);
+  if (s.ret.d == 128) hipLaunchKernelGGL((stream_kernel<T, 128>), grid, blk, 0, st, s, meta);
+  else hipLaunchKernelGGL((stream_kernel<T, 64>), grid, blk, 0, st, s, meta);
+  return hipGetLastError() != hipSuccess ? 7 : 0;
+}
+
 // ---------------------------------------------------------------------------
 // Scores only, over heads stored as rows (the target layer's retained heads), one workgroup per chunk and y as in
 // attn_split_body: S^T[h, slot * 128 + j] = scale * q_h . rot_j(k_j) for GT query heads of one KV

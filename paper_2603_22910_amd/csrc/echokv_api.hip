@@ -394,21 +394,27 @@ Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* q
   return s;
 }
 
-// Retained heads of a bf16 call in a launch of their own ahead of the large kernel's: with three and more passes over their rows
-// (one per group of query heads that share a row: 3, 5 or 7 of them per KV head are as many groups) the streams run at 0.65-0.8 of their
-// rate where only eight waves share a unit.  That is made up for by the units that the product's last round leaves idle if they
-// are worth 0.12 of the streams' time.  In the launch / ahead of it, us: 8 KV heads, 7 retained, 8 x 6000 tokens, G = 5 194 / 170, G = 7 243 /
-// 202; 40 x 4000 684 / 601 and 863 / 784, with rope 920 / 732 and 1170 / 919; 2 x 40000 (more idle units) 345 / 378 and 429 / 469.
-bool streams_by_themselves(const Dims& dm, const SeqMeta& mt) {
+// Streams of a bf16 call in a launch of their own ahead of the large kernel's, with several of their workgroups per unit.  As
+// workgroups of that kernel's launch, one per unit, they take about 1.14 times as long, but the units that the product's
+// last round leaves idle work for nothing.  All times in us of one unit: a row and pass (query heads of a KV head that do not share
+// a workgroup pass over its rows again: 3, 5 or 7 of them) and 2 per workgroup; the launch costs 5, and what is less than 3 % of
+// the product is left alone.  In the launch / by themselves, us, 8 KV heads: G = 5, 6 retained, 128 x 300 tokens with window 374 / 261, 7 retained, 40 x
+// 4000 684 / 603, with rope 912 / 790; G = 8, 4 retained, 128 x 300 with window 365 / 302; G = 4, 4 retained, 8 x 6000 (many
+// units idle) 165 / 190; G = 7, 3 of 4 retained, 2 x 40000 170 / 180, 40 x 4000 397 / 353.
+bool streams_by_themselves(const Dims& dm, const SeqMeta& mt, bool rope, const Window& win) {
   const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1, passes = dm.G / gt;
-  if (dm.g0 == 0 || passes < 3) return false;
-  int64_t tokens = 0, tiles = 0;
-  for (int b = 0; b < mt.n; ++b) { tokens += mt.len[b]; tiles += (mt.len[b] + 255) / 256; }
+  int64_t tokens = 0, chunks = 0, tiles = 0;
+  for (int b = 0; b < mt.n; ++b) {
+    tokens += mt.len[b]; chunks += (mt.len[b] + kStreamMinChunk - 1) / kStreamMinChunk; tiles += (mt.len[b] + 255) / 256;
+  }
   tiles *= (dm.d_out_v + 255) / 256;
-  const double tile_us = 9 + 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0);        // see small_is_faster
-  const double idle = (double)((tiles + 255) / 256 * 256 - tiles) * tile_us;
-  const double streams = (double)(tokens * dm.g0 * passes) * dm.d * 4 / 6.5e6 * 256;
-  return idle < 0.12 * streams;
+  const double wgs = (double)passes * (chunks * dm.g0 + (win.on() ? mt.n * dm.H_kv : 0));
+  const double rows = (double)passes * (tokens * dm.g0 + (double)mt.n * dm.H_kv * win.rows());
+  const double streams = 256 * rows * dm.d * 4 / (rope ? 3.25e6 : 6.5e6) + 2 * wgs;
+  const int64_t rounds = (tiles + 255) / 256;
+  const double tile = 9 + 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0);           // see small_is_faster
+  const double idle = (double)(rounds * 256 - tiles) * tile;
+  return (0.14 * streams - 1.14 * idle) / 256 > 5 + 0.03 * (double)rounds * tile;
 }
 
 template <typename T>
@@ -495,15 +501,13 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
         StreamMeta sm;
         sm.s = mt;
         int win_slot0 = -1;
-        Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, kStreamMinChunk, 1024, 1024, sm, &stream_step, &win_slot0);
+        const bool apart = streams_by_themselves(dm, mt, kx.rope_cos != nullptr, win);
+        Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, kStreamMinChunk, apart ? 8192 : 1024, 1024, sm, &stream_step, &win_slot0);
         int rc;
-        if (streams_by_themselves(dm, mt)) {
-          AttnArgs<T> a = streams.ret;
-          a.split_tokens = pick_split_tokens(tokens, n_ret_heads);
-          stream_step = a.split_tokens / kSlotTokens;
-          rc = launch_attn_split<T>(dm, a, mt, n_ret_heads, st);
+        if (apart) {
+          rc = launch_streams<T>(streams, sm, st);
           if (rc) return rc;
-          streams.n_ret = 0;
+          streams.n_ret = streams.n_win = 0;
         }
         ProfScope prof;
         rc = prof.begin(0, st);

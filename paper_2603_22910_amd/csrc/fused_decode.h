@@ -398,11 +398,10 @@ __global__ __launch_bounds__(NTHREADS) void fused_kscores_kernel(Args a, Streams
 // The same streaming workgroups with no product in front of them (every head is retained): four waves and no tiles, so that
 // a unit holds several.  Whole calls, as workgroups of the product's kernel / so: 2 x 9496-56976 tokens, two heads of 64, 48.8 / 45.1 us, 29 x
 // 53-318 tokens, eight heads of 128 50.5 / 47.4, with rope and window 84 / 76; one sequence of 40000, rope and window 94 / 101 (117 as two launches).
-constexpr int kScoreStreamWaves = 4;
 template <int HD>
-__global__ __launch_bounds__(64 * kScoreStreamWaves) void score_stream_kernel(Streams<bf16_t> streams, StreamMeta smeta, float* s_out, int64_t s_ld) {
-  __shared__ __attribute__((aligned(16))) char smem[stream_smem_bytes<bf16_t, HD, kScoreStreamWaves>()];
-  score_stream_workgroup<HD, kScoreStreamWaves>(streams, smeta, blockIdx.x, s_out, s_ld, smem);
+__global__ __launch_bounds__(64 * kStreamWaves) void score_stream_kernel(Streams<bf16_t> streams, StreamMeta smeta, float* s_out, int64_t s_ld) {
+  __shared__ __attribute__((aligned(16))) char smem[stream_smem_bytes<bf16_t, HD, kStreamWaves>()];
+  score_stream_workgroup<HD, kStreamWaves>(streams, smeta, blockIdx.x, s_out, s_ld, smem);
 }
 
 // Stand-alone predictor product (Eq. 3) with the same main loop: K_hat or V_hat
@@ -588,7 +587,7 @@ inline int launch_fused_kscores(int H_q, int H_kv, int d, int m, int d_out, int 
     a.n_col_tiles = (a.d_out + fused::BN - 1) / fused::BN;
     a.n_tiles = fused_fill_tiles(mt) * a.n_col_tiles;
     if (a.n_tiles == 0) {                    // every head is retained
-      const dim3 sg(streams.n_ret + streams.n_win), sb(64 * fused::kScoreStreamWaves);
+      const dim3 sg(streams.n_ret + streams.n_win), sb(64 * kStreamWaves);
       if (d == 128) hipLaunchKernelGGL((fused::score_stream_kernel<128>), sg, sb, 0, st, streams, smt, s_out, s_ld);
       else hipLaunchKernelGGL((fused::score_stream_kernel<64>), sg, sb, 0, st, streams, smt, s_out, s_ld);
       return hipGetLastError() != hipSuccess ? 7 : 0;

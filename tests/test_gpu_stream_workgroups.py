@@ -1,7 +1,7 @@
 """GPU parity of the streaming workgroups behind the predictor product's: retained heads and window of a
 decode call on the kernel for large problems, and retained heads' scores and window of the value-absorbed mode.  Chunk
 counts on both sides of multiples of 8 (their order changes there), every way the query heads of a KV head
-are grouped, rows of 64 and 128 dims, a layer whose heads are all retained, retained heads in a launch of their own; every output element against the fp64 oracle."""
+are grouped, rows of 64 and 128 dims, a layer whose heads are all retained, streams in a launch of their own; every output element against the fp64 oracle."""
 import numpy as np
 import pytest
 import torch
@@ -25,9 +25,9 @@ CASES = [
     (32, 4, 128, 256, (257, 255)),            # G = 8: two groups per KV head
     (8, 8, 64, 512, (17000, 70)),             # every head retained; 35 chunks
     (28, 4, 128, 384, (25000, 70)),           # G = 7: 50 chunks x 21 are too many, 26 of 1024 tokens
-    (20, 4, 128, 128, (32700,)),              # G = 5, 256 tiles: no unit idle, the retained head by itself ahead of them
-    (20, 4, 128, 128, (32700, 60)),           # 258 tiles: in the launch
-    (12, 4, 64, 64, (65200,)),                # G = 3, by itself
+    (56, 8, 128, 768, (300,) * 128),          # G = 7, 256 tiles: no unit idle, the streams in a launch of their own
+    (24, 8, 64, 384, (512,) * 127 + (500,)),  # G = 3: the same
+    (32, 4, 128, 384, (500,) * 128),          # G = 8: only with the window and rotary tables
 ]
 
 
