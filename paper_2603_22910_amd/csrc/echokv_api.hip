@@ -311,10 +311,11 @@ int merge_launch(const Dims& dm, const float* po, const float* pml, void* out, f
 constexpr int kSmallFewWgs = 240, kSmallMaxWgs = 704, kSmallMaxWgsF32 = 6144;
 inline int small_col_tile(const Dims& dm) { return dm.bf16 ? 128 : dm.d; }
 // Times of a bf16 call in us, with tb token blocks of 16 per workgroup and with the 256 x 256 kernel: launch and merge, rounds of
-// workgroups of the product, and the rows of the retained heads, which the units stream at about 6.5 TB/s (with rotary tables half of that); in the
-// large kernel's launch half of that hides behind the product.  A round of the small kernel is between a whole and a partial one
-// (its workgroups end at different times); the large kernel needs one round for up to 256 tiles, of 1.0 us per k-tile
-// and pass, or 0.72 where all columns of a tile fit one half of it.  Against the clock (64-token / 256 x 256 kernel, us): 8 KV heads,
+// workgroups of the product, and the rows of the retained heads, which the units stream at about 6.5 TB/s (with rotary tables
+// half of that; 1.3 times as long in the small kernel with three and more passes over the rows); in the large kernel's launch half
+// of that hides behind the product.  A round of the small kernel is between a whole and a partial one (its workgroups end at different
+// times); the large kernel needs one round for up to 256 tiles, of 1.0 us per k-tile and pass, or 0.72 where all columns of a tile fit
+// one half of it.  Against the clock (64-token / 256 x 256 kernel, us): 8 KV heads,
 // one predicted, 8 x 2000 tokens 43.7 / 57.4, 8 x 3200 73.7 / 59.6, 8 x 5568 137 / 93; two, 8 x 1600 54.6 / 74.2, 8 x 2048 65.6 / 75.1,
 // 8 x 2752 90.9 / 75.4; four with 32 heads (d_in 7680) 222 / 277 at 8 x 1024, 297 / 280 at 8 x 1344; 7 query heads per KV head, one
 // predicted of 8, 8 x 1984 (all rows seven times) 96 / 80.  Over 132 such problems the choice costs 0.2 % in the mean, 8 % at most.
@@ -325,7 +326,7 @@ bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgrou
   for (int b = 0; b < mt.n; ++b) { tokens += mt.len[b]; t256 += (mt.len[b] + 255) / 256; }
   const double streams = (double)(tokens * dm.g0 * (dm.G / gt)) * dm.d * 2 * sizeof(T) / (rope ? 3.25e6 : 6.5e6);
   const double rounds = 0.5 * ((double)workgroups / 256 + (double)((workgroups + 255) / 256));
-  const double small = 8 + rounds * (6 + (tb == 2 ? 0.0072 : 0.0112) * dm.d_in) + streams;
+  const double small = 8 + rounds * (6 + (tb == 2 ? 0.0072 : 0.0112) * dm.d_in) + (dm.G / gt >= 3 ? 1.3 : 1.0) * streams;
   const int64_t tiles = t256 * ((dm.d_out_v + 255) / 256);
   const double large = 17 + (double)((tiles + 255) / 256) * 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0) + 0.5 * streams;
   return small <= large;
