@@ -98,3 +98,32 @@ def test_kernel_taken(H_q, H_kv, d, m, lens, tok):
     slots = sum(-(-L // tok) for L in lens)      # and one per sequence for a window, not written here
     want = ((slots + len(lens)) * H_q * d * 4 + 255) // 256 * 256 + slots * H_q * 8
     assert want - 8 < end <= want
+
+
+LARGE_F32 = [                                    # H_q, H_kv, d, m, lengths
+    (4, 2, 128, 128, (300, 129, 1)),             # G = 2
+    (16, 4, 128, 128, (257, 70)),                # G = 4, three predicted heads: two column tiles, the second half empty
+    (16, 4, 64, 64, (256, 255, 128)),            # G = 4, heads of 64
+    (7, 7, 64, 64, (513, 31)),                   # six predicted heads of 64: both halves of a tile and a second tile
+    (8, 2, 128, 64, (200, 140)),                 # split head
+    (8, 4, 128, 0, (130,)),                      # nothing retained
+]
+
+
+@pytest.mark.parametrize("extras", EXTRAS)
+@pytest.mark.parametrize("H_q,H_kv,d,m,lens", LARGE_F32)
+def test_large_fp32_kernel_on_short_sequences(H_q, H_kv, d, m, lens, extras):
+    """The fp32 256 x 256 kernel, which only very long sequences reach by themselves."""
+    inp = synth.generate(synth.Workload("large_f32", "f32", H_q, H_kv, d, m, seed=81, seq_lens=lens))
+    dw = DeviceWorkload(inp, flags=ek.FLAG_STAGED)
+    if extras:
+        rope = synth.rope_tables(d, max(lens))
+        window = (*synth.window_rows(inp, 4, 24), 4, 24)
+        out, lse = dw.decode_ex(rope, window)
+        o_ref, l_ref = ref.decode_paper_ref(inp, rope, window)
+    else:
+        out, lse = dw.decode()
+        o_ref, l_ref = ref.decode_ref(inp)
+    torch.cuda.synchronize()
+    check(host(out), o_ref, "f32", f"{H_q} {H_kv} {d} {m} {lens}")
+    assert np.abs(host(lse) - l_ref).max() <= 1e-5
