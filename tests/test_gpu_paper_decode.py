@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 
 TOL = {"bf16": (2e-2, 5e-3), "f32": (1e-5, 1e-5)}
 MODES = [pytest.param(0, id="fused"), pytest.param(ek.FLAG_UNFUSED, id="unfused"),
-         pytest.param(-1, id="packed"), pytest.param(ek.FLAG_ABSORB_V, id="absorb_v")]
+         pytest.param(-1, id="packed"), pytest.param(ek.FLAG_ABSORB_V, id="absorb_v"),
+         # the kernel for large problems, whatever the size
+         pytest.param(ek.FLAG_STAGED, id="staged"), pytest.param(-2, id="packed_staged")]
 
 
 def host(t):
@@ -30,12 +32,13 @@ def check(got, want, dtype, what):
 
 def run(w, flags, use_rope, use_window, n_sink=4, n_recent=128):
     inp = synth.generate(w)
-    if flags == -1:
+    if flags < 0:
         if w.dtype != "bf16" or w.d_out == 0 or w.n_retained % w.head_dim:
             pytest.skip("packed weights: bf16 fused path, whole heads only")
         dw = DeviceWorkload(inp)
         dw.pack_weights()
         dw.W_K, dw.W_V = dw.W_K_packed, dw.W_V_packed
+        dw.shape.flags |= ek.FLAG_STAGED if flags == -2 else 0
     else:
         if flags & ek.FLAG_ABSORB_V and w.dtype != "bf16":
             pytest.skip("value-absorbed decode: bf16 caches only")
@@ -61,6 +64,7 @@ EXTRAS = [pytest.param(True, False, id="rope"), pytest.param(False, True, id="wi
     (8, 8, 128, 512, "bf16"),      # MHA, half retained (the 7B-shaped layout, reduced)
     (32, 8, 128, 512, "bf16"),     # GQA 4:1 (the paper's 8 x 128 layout)
     (8, 4, 64, 128, "bf16"),       # head_dim 64
+    (32, 8, 64, 64, "bf16"),       # head_dim 64, GQA 4:1, two column tiles
     (32, 8, 128, 0, "bf16"),       # nothing retained (the paper's ratio-0.5 preset)
     (32, 8, 128, 64, "bf16"),      # half a head retained (the paper's m = 64 preset)
     (8, 8, 64, 256, "f32"),
@@ -71,7 +75,8 @@ def test_decode_extras_shapes(H_q, H_kv, d, m, dtype, flags, use_rope, use_windo
     run(w, flags, use_rope, use_window)
 
 
-@pytest.mark.parametrize("flags", [pytest.param(0, id="fused"), pytest.param(ek.FLAG_ABSORB_V, id="absorb_v")])
+@pytest.mark.parametrize("flags", [pytest.param(0, id="fused"), pytest.param(ek.FLAG_ABSORB_V, id="absorb_v"),
+                                   pytest.param(ek.FLAG_STAGED, id="staged")])
 @pytest.mark.parametrize("L", [1, 3, 4, 5, 131, 132, 133, 134, 259, 260, 261, 400, 1030])
 def test_window_boundaries(L, flags):
     """Lengths around n_sink, n_sink + n_recent and the tile size: everything in the
@@ -142,7 +147,8 @@ def test_window_append_keeps_the_ring_current():
                 assert torch.equal(wv[b, r], full_v[b][p]), (b, p)
 
 
-@pytest.mark.parametrize("flags", [pytest.param(0, id="fused"), pytest.param(ek.FLAG_ABSORB_V, id="absorb_v")])
+@pytest.mark.parametrize("flags", [pytest.param(0, id="fused"), pytest.param(ek.FLAG_ABSORB_V, id="absorb_v"),
+                                   pytest.param(ek.FLAG_STAGED, id="staged")])
 def test_decode_extras_batch_above_one_launch(flags):
     lens = tuple(1 + (53 * i) % 400 for i in range(140))
     w = synth.Workload("px_b140", "bf16", 4, 2, 128, 128, seed=78, seq_lens=lens)

@@ -16,8 +16,9 @@ import oracle_ref as ref
 pytestmark = pytest.mark.gpu
 
 TOL = {"bf16": (2e-2, 5e-3), "f32": (1e-5, 1e-5)}
-PACKED = 1 << 20       # test-only marker: weights re-laid out once by echokv_pack_weights (direct-to-LDS kernel)
+PACKED = 1 << 20       # test-only marker: weights re-laid out once by echokv_pack_weights
 MODES = [pytest.param(0, id="fused"), pytest.param(ek.FLAG_UNFUSED, id="unfused"),
+         pytest.param(ek.FLAG_STAGED, id="staged"),            # the kernel for large problems, whatever the size
          pytest.param(PACKED, id="packed"),
          pytest.param(PACKED | ek.FLAG_STAGED, id="packed_staged"),
          pytest.param(ek.FLAG_ABSORBED, id="absorbed"),

@@ -29,7 +29,7 @@ def random_lens(rng, n):
     return tuple(int(rng.choice(edges)) if rng.random() < 0.5 else int(rng.integers(1, 2600)) for _ in range(n))
 
 
-DECODE_MODES = {"fused": 0, "unfused": ek.FLAG_UNFUSED, "packed": PACKED, "absorbed": ek.FLAG_ABSORBED,
+DECODE_MODES = {"fused": 0, "staged": ek.FLAG_STAGED, "unfused": ek.FLAG_UNFUSED, "packed": PACKED, "absorbed": ek.FLAG_ABSORBED,
                 "absorb_v": ek.FLAG_ABSORB_V}
 
 
