@@ -65,8 +65,9 @@ typedef enum { ECHOKV_BF16 = 0, ECHOKV_F32 = 1 } echokv_dtype;
                                   echokv_pack_weights ([D - m, D + m]); honoured by
                                   echokv_decode_attn on the fused bf16 path, every
                                   other use returns ECHOKV_ERR_UNSUPPORTED */
-#define ECHOKV_FLAG_STAGED 4u  /* with W_PACKED: use the kernel for large problems
-                                  whatever the size (comparison) */
+#define ECHOKV_FLAG_STAGED 4u  /* decode on the fused paths, bf16 and fp32, either weight
+                                  layout: use the kernel for large problems whatever
+                                  the size (comparison); not with the absorbed modes */
 #define ECHOKV_FLAG_ABSORBED 8u /* decode: same output in the other association order
                                   (Eq. 3 is linear): queries are folded into W_K and
                                   the probability-weighted sum of predictor inputs is
@@ -232,8 +233,9 @@ int echokv_decode_attn(const echokv_shape *shape, const echokv_layer_cache *anch
  * exactly as if ECHOKV_FLAG_UNFUSED were set, and echokv_workspace_bytes
  * already accounts for it.  The same call reports the choice made for the
  * other flags.  *path_out is one of ECHOKV_PATH_*. */
-#define ECHOKV_PATH_FUSED 0          /* fused predictor product + attention, row-major W */
-#define ECHOKV_PATH_FUSED_DIRECT 1   /* the same with packed W */
+#define ECHOKV_PATH_FUSED 0          /* fused predictor product + attention: row-major W, and every
+                                        layout with ECHOKV_FLAG_STAGED */
+#define ECHOKV_PATH_FUSED_DIRECT 1   /* the same, packed W without that flag */
 #define ECHOKV_PATH_UNFUSED 2        /* K-hat / V-hat materialised in the workspace, then attended */
 #define ECHOKV_PATH_ABSORBED 3       /* ECHOKV_FLAG_ABSORBED */
 #define ECHOKV_PATH_ABSORB_V 4       /* ECHOKV_FLAG_ABSORB_V */

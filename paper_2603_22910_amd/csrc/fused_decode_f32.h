@@ -2,14 +2,14 @@
 //
 // Same plan as the bf16 kernel (256 tokens x 256 predicted columns per
 // workgroup, K pass with W as the row operand, V pass with X as the row
-// operand, identical accumulator layout and therefore the same attention
-// epilogues), but the predictor product (Eq. 3) runs on v_mfma_f32_32x32x2f32:
-// true fp32 products and fp32 accumulation, as the 1e-5 tolerance of the fp32
-// configuration needs.  An fp32 MFMA operand is ONE value per lane (row or
+// operand), but four waves of 128 x 128, and the predictor product (Eq. 3) runs on
+// v_mfma_f32_32x32x2f32: true fp32 products and fp32 accumulation, as the 1e-5
+// tolerance of the fp32 configuration needs.  Its accumulators are blocks of 32 x 32 where the bf16
+// kernel's are 16 x 16, so the attention epilogues are its own.  An fp32 MFMA operand is ONE value per lane (row or
 // column = lane % 32, k = lane / 32), so both tiles are read from LDS in their
 // natural layouts with scalar reads and W needs no transposition.  The main
-// loop is single-buffered and synchronous: this path exists for correctness on
-// small fp32 problems, not for speed.
+// loop is single-buffered and synchronous: it serves the fp32 problems that are too large
+// for fused_decode_small.h.
 #pragma once
 #include "common.h"
 #include "fused_decode.h"

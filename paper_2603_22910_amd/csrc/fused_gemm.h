@@ -41,7 +41,8 @@
 //
 // The LDS reads of the loop are instructions with waits of their own: in builtin form the compiler puts
 // them behind every outstanding copy (s_waitcnt vmcnt(0)), which would drain the pipeline in every phase.
-// The copies are counted (vmcnt), so the kernels must not spill: the build checks it.
+// The copies are counted (vmcnt), so the kernels must not spill, and nothing may touch a fragment's registers between its
+// request and its wait: the build checks both.
 #pragma once
 #include "common.h"
 

@@ -350,7 +350,7 @@ struct VFrag { short4_t lo[4], hi[4]; };
 // them behind every outstanding global -> LDS copy (s_waitcnt vmcnt(0)), which would drain the
 // ring once per tile.  issue_v requests the fragments of k-step TS; wait_v<N> waits until at
 // most N reads requested after them are outstanding, its operands tie it to the registers it
-// guards.  voff0: this lane's byte offset inside a V tile for k-step 0 and 32-dim block 0; block
+// guards (that nothing touches them in between is checked by the build).  voff0: this lane's byte offset inside a V tile for k-step 0 and 32-dim block 0; block
 // cb is at voff0 ^ (cb << 6) (the swizzle only touches the two chunk-index bits that cb occupies).
 #define ECHOKV_TR(dst, adr, off) "ds_read_b64_tr_b16 " dst ", " adr " offset:" off "\n"
 template <int HD, int TS>
