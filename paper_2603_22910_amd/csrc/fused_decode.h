@@ -607,9 +607,11 @@ inline int launch_fused_kscores(int H_q, int H_kv, int d, int m, int d_out, int 
 // column col0, output row = sbase[b]*kSlotTokens + j.  d_out = width of W (0: only the rows of `rope`).  With
 // rope.cos K_hat is rotated by token position, heads of rope.d dims, and rope's own rows (the retained keys) are as well, these
 // by workgroups of the product's launch.  K_hat on its way out of the product if that has kRopeTiles workgroups and more, by a
-// launch behind it otherwise: the tables' loads are then a latency at the end of a tile that nothing covers.  In a prefill
-// of 64 queries behind 16000 tokens (252 workgroups) 165 us with two launches behind the product, 154 on its way out; 900 behind 20000
-// (328) 495 and 465; 500 behind 7000 (120) 171 and 168; 100 behind 3000 (52) 78.8 and 80.8; 2000 alone (32) 116 and 120.
+// launch behind it otherwise: the tables' loads are then a latency at the end of a tile that nothing covers.  Whole prefill calls of
+// 32 heads over 8 of 128, behind the product / on its way out, us, and the product's workgroups: m = 512, 64 queries behind 16000 tokens (252)
+// 152 / 144, 900 behind 20000 (328) 442 / 441, 500 behind 7000 (120) 139 / 143, 100 behind 3000 (52) 73.5 / 79.8, 2000 alone (32)
+// 115 / 121; m = 64, 64 behind 16000 (504) 175 / 170, 900 behind 20000 (656) 485 / 474, 500 behind 7000 (240) 141 / 143, 100 behind
+// 3000 (104) 68.0 / 73.2.  From 120 to 240 the two are within 3 % of each other.
 constexpr int kRopeTiles = 120;
 template <typename T>
 inline int launch_recon_mfma(int D, int m, int d_out, const T* ka, const T* va, const T* kr, const T* vr,

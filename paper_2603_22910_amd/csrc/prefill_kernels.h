@@ -673,9 +673,10 @@ inline int prefill_kv_splits(int T_q, int64_t Ltot, int H_q) {
 }
 // Key shares taken: of the 2 .. prefill_kv_splits possible ones those that cost least.  A workgroup fills a compute unit, so the
 // chip runs them in rounds of 256; one costs its key tiles and about six more for its start and end, and each share's
-// partials (written, read and joined) about one tile per 9000 (query, head) pairs.  All possible shares -> these: 500
-// queries of 32 heads behind 7000 tokens 8 -> 4 shares, 168 -> 153 us; 768 behind 3232 127 -> 106; 1000 behind 3000 151 -> 126; 900 behind 20000
-// 8 -> 5 shares, 466 -> 458; 600 behind 12000 239 -> 221; 400 behind 30000 438 -> 419; one block of queries (300 behind 7000, 64 behind 16000): the same.
+// partials (written, read and joined) about one tile per 9000 (query, head) pairs.  All possible shares -> these, whole calls of
+// 32 heads over 8 of 128 with m = 512: 500 queries behind 7000 tokens (rope) 8 -> 4 shares, 158 -> 143 us; 768 behind 3232 119 -> 102;
+// 1000 behind 3000 149 -> 124; 900 behind 20000 (rope) 8 -> 5 shares, 449 -> 444; 400 behind 30000 430 -> 410; m = 0, 600 behind 12000
+// 232 -> 214; one block of queries (300 behind 7000, 64 behind 16000): the same.
 // The probabilities are rounded to bf16 relative to the softmax reference, and the key that sets it is rounded without error: fewer
 // shares alone put the output further from its value in 64 bits (0.24 % more error in the mean of 32 such chunks, up to 0.8 %).  So
 // a share takes a new reference wherever one of prefill_kv_splits shares would begin (kv_refs): the probabilities are then the same
