@@ -246,7 +246,8 @@ int echokv_decode_path(const echokv_shape *shape, int32_t *path_out);
  * workspace to hand over: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments, same kernels, same result, bit
  * for bit, as echokv_decode_attn with the workspace that echokv_workspace_bytes
- * asks for (shape->flags honoured alike), but the split partials (and
+ * asks for (shape->flags honoured alike; fp32 caches whose partials per 32 tokens
+ * do not fit the buffer: a slower kernel with other roundings), but the split partials (and
  * whatever else the chosen path keeps in its workspace) live in a fixed buffer
  * of ECHOKV_STATIC_SCRATCH_BYTES inside the library's device image instead of a
  * caller-owned workspace.  The call allocates and frees nothing.

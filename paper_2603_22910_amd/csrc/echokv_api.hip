@@ -177,10 +177,12 @@ struct ProfScope {
 #define LAUNCH_CHECK() do { if (hipGetLastError() != hipSuccess) return ECHOKV_ERR_HIP; } while (0)
 
 // Workspace that a choice of kernels may count on beyond the least it needs (small decode problems, short absorbed splits).  A
-// request that the fixed scratch can serve never uses more than that scratch holds: echokv_decode_attn_static then makes the same
-// choices, and gives the same bits, as a call with the workspace that echokv_workspace_bytes asks for.
-size_t choice_bytes(size_t ws_bytes, size_t least) {
-  return least <= kStaticScratchBytes ? std::min(ws_bytes, kStaticScratchBytes) : ws_bytes;
+// bf16 request that the fixed scratch can serve never uses more than that scratch holds: echokv_decode_attn_static then makes the
+// same choices, and gives the same bits, as a call with the workspace that echokv_workspace_bytes asks for.  Not so in fp32: there
+// the kernel for small problems is three times as fast up to 6144 workgroups, whose partials (40 heads, 10470 + 62822 tokens: 47 MB) are
+// beyond the scratch (975 us against 3240).
+size_t choice_bytes(const Dims& dm, size_t ws_bytes, size_t least) {
+  return dm.bf16 && least <= kStaticScratchBytes ? std::min(ws_bytes, kStaticScratchBytes) : ws_bytes;
 }
 
 // Fill tbase for a tile size; returns the tile count.
@@ -1413,7 +1415,7 @@ int echokv_decode_attn_ex(const echokv_shape* shape, const echokv_layer_cache* a
     if (!workspace || workspace_bytes < need) return ECHOKV_ERR_WORKSPACE;
     if ((uintptr_t)workspace % 256) return ECHOKV_ERR_WORKSPACE;
     return absorbed_impl(dm, value_only, anchor, target, w_k, w_v, q, has_extras ? extras : nullptr, out,
-                         lse_out, (char*)workspace, choice_bytes(workspace_bytes, need), (hipStream_t)hip_stream);
+                         lse_out, (char*)workspace, choice_bytes(dm, workspace_bytes, need), (hipStream_t)hip_stream);
   }
   if ((shape->flags & ECHOKV_FLAG_W_PACKED) &&
       (dm.r != 0 || (shape->flags & ECHOKV_FLAG_UNFUSED) || !dm.bf16 || !fused_decode_supported<bf16_t>(dm.d, dm.G)))
@@ -1425,7 +1427,7 @@ int echokv_decode_attn_ex(const echokv_shape* shape, const echokv_layer_cache* a
   if (!workspace || workspace_bytes < need) return ECHOKV_ERR_WORKSPACE;
   if ((uintptr_t)workspace % 256) return ECHOKV_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
-  const size_t room = choice_bytes(workspace_bytes, need);
+  const size_t room = choice_bytes(dm, workspace_bytes, need);
   const echokv_decode_extras* ex = has_extras ? extras : nullptr;
   return dm.bf16 ? decode_impl<bf16_t>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, room, st)
                  : decode_impl<float>(dm, shape->flags, anchor, target, w_k, w_v, q, ex, out, lse_out, (char*)workspace, room, st);
