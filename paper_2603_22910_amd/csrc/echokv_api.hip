@@ -877,11 +877,18 @@ size_t absorbed_ws_bytes(const Dims& dm, int batch, int64_t total_tokens) {
   const int64_t splits = std::max(total_tokens / 1024 + n, std::min(total_tokens / kSlotTokens + n, kAbsShortWgs / per_split));
   return abs_pre_bytes(dm) + plan_absorbed(dm, n, total_tokens / kSlotTokens + n, splits).total + abs_win_bytes(dm, n);
 }
-// 32-token workgroups of the score pass as long as they are one round (slots x 4 x blocks of 32 heads; 128-token / 32-token kernel, whole
-// calls in us): 128 of them 67.4 / 61.1, 256 99.5 / 93.0, 52.7 / 50.2 and 72.2 / 72.7, 384 54.5 / 53.5 and 110 / 107 with three
-// or four long sequences, but 88.1 / 93.3, 56.6 / 57.6 and 52.7 / 53.3 with 16 short ones, 512 65.8 / 68.7 and 61.9 / 64.3.  Beyond, the
-// 128-token kernel fills the chip too, with a quarter of the reads of the absorbed queries: 8 x 4096 with d_in 6144 (1024) 210 / 225.
-constexpr int64_t kAbsSmallWgs = 256;
+// 32-token workgroups of the score pass (those that have tokens; 128-token / 32-token kernel, whole calls in us) as long as they are one
+// round: 128 of them 67.4 / 61.1, 208 99.5 / 93.0, 52.7 / 50.2 and 72.2 / 72.7; and up to one and a half where the absorbed queries of all
+// sequences stay in an L2 beside the rows (under 1 MB: each workgroup reads as much of them as of its rows): 322 120 / 115, 376 54.5 / 53.5,
+// 378 110 / 107, but 352 88.1 / 93.3 with 4 MB and 56.6 / 57.6 with 1.6; half a round where they are over 8 MB: 230 109 / 115 with 19.
+// Beyond, the 128-token kernel fills the chip too, with a quarter of these reads: 416 65.8 / 68.7, 512 61.9 / 64.3, 1024 210 / 225.
+bool scores_are_small(const Dims& dm, const SeqMeta& mt) {
+  const int64_t pad = (dm.H_q + absorbed::kHB - 1) / absorbed::kHB * absorbed::kHB;
+  int64_t wgs = 0;
+  for (int b = 0; b < mt.n; ++b) wgs += (mt.len[b] + absorbed::kSmallTok - 1) / absorbed::kSmallTok;
+  const int64_t u = mt.n * pad * dm.d_in * 2;
+  return wgs * (pad / absorbed::kHB) <= (u < 1 << 20 ? 384 : u < 8 << 20 ? 256 : 128);
+}
 constexpr uint32_t kAbsModes = ECHOKV_FLAG_ABSORBED | ECHOKV_FLAG_ABSORB_V;
 bool absorbed_supported(const Dims& dm, uint32_t flags) {
   if (!dm.bf16 || (flags & (ECHOKV_FLAG_UNFUSED | ECHOKV_FLAG_W_PACKED | ECHOKV_FLAG_STAGED | ECHOKV_FLAG_W_AUGMENTED))) return false;
@@ -896,40 +903,46 @@ bool absorbed_supported(const Dims& dm, uint32_t flags) {
 // 700 tokens.  So the time goes like ceil(workgroups / 256) * (split + 700), and the split that
 // minimises it is taken: measured over 16 split sizes on three layer shapes this model orders
 // them as the clock does (8 KV heads of 128, 32768 tokens: 3328 tokens, 240 workgroups, 8 % faster than 1024).
-// Splits below 1024 tokens only where longer ones leave compute units idle, in at most two turns (kAbsShortWgs: what the workspace
-// query makes room for), and as far as the workspace holds their partial sums.  For these the cost of the
-// launches counts too: several splits per sequence need y_sum (worth about 300 tokens), splits of up to 128 tokens no statistics
-// launch (250); a turn lasts as long as the mean split, and all turns at least as long as the longest; and every block of 32 query heads
-// is a row of workgroups of its own.
-// 2 x 1500 tokens, d_in 1536: the value pass 22 -> 10 us with 128; 16 x 1000, 64 heads, d_in 1920: 79 us in one split each, 89 in
-// two, 115 with 128; 16 x 700: 72, 80 and 97; 16 x 700, 32 heads, d_in 1536: 56.6 in one split, 55.2 with 384, 62 with 128.
+// Splits below 1024 tokens only up to two workgroups per compute unit (kAbsShortWgs: what the workspace
+// query makes room for), and as far as the workspace holds their partial sums.  Where longer ones are several per sequence too, by the
+// same cost: 2 x 1500 tokens, d_in 1536: the value pass 22 -> 10 us with 128; 64 heads, d_in 1792, 3321 + 12000 tokens: 94 -> 85 with 512.
+// Where a sequence would be one split otherwise, only if the longer ones leave units idle, and the cost of the launches counts: several
+// splits need y_sum (worth about 300 tokens), splits of up to 128 tokens no statistics launch (250); every block of 32 query heads is a
+// row of workgroups of its own; a turn lasts as long as the mean split, and all turns at least as long as the longest.  16 x 1000
+// tokens, 64 heads, d_in 1920: 79 us in one split each, 89 in two, 115 with 128; 16 x 700: 72, 80 and 97; 16 x 700, 32 heads, d_in 1536:
+// 56.6 in one split, 55.2 with 384, 62 with 128.
 int abs_split_tokens(const Dims& dm, const SeqMeta& mt, int64_t slots, size_t ws_bytes) {
   const int nct = abs_col_tiles(dm.D) + abs_col_tiles(dm.m), nhb = (dm.H_q + absorbed::kHB - 1) / absorbed::kHB;
   const size_t fixed = abs_pre_bytes(dm) + abs_win_bytes(dm, mt.n);
   int max_len = 0;
   int64_t tokens = 0;
   for (int b = 0; b < mt.n; ++b) { max_len = std::max(max_len, mt.len[b]); tokens += mt.len[b]; }
+  if (max_len <= absorbed::kPvStatsTokens) return absorbed::kPvStatsTokens;      // (one split each whatever their length)
   auto splits_of = [&](int ts) {
     int64_t n = 0;
     for (int b = 0; b < mt.n; ++b) n += (mt.len[b] + ts - 1) / ts;
     return n;
   };
+  auto turns_cost = [&](int ts) { return (splits_of(ts) * nct + 255) / 256 * (ts + 700); };
   int best = 1024;
-  int64_t best_cost = -1;
-  for (int ts = 1024; ts <= 32768; ts += kSlotTokens) {
-    const int64_t cost = (splits_of(ts) * nct + 255) / 256 * (ts + 700);
-    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ts; }
+  int64_t best_cost = turns_cost(best);
+  for (int ts = 1024 + kSlotTokens; ts <= 32768; ts += kSlotTokens) {
+    const int64_t cost = turns_cost(ts);
+    if (cost < best_cost) { best_cost = cost; best = ts; }
   }
+  const bool several = max_len > best;
   auto whole_cost = [&](int ts) {
     const int64_t n = splits_of(ts), turns = (n * nct * nhb + 255) / 256;
     return std::max<int64_t>(turns * (tokens / n + 700), std::min(ts, max_len) + 700) + (max_len > ts ? 300 : 0) -
            (ts <= absorbed::kPvStatsTokens ? 250 : 0);
   };
-  if (splits_of(best) * nct * nhb > 256) return best;
-  best_cost = whole_cost(best);
+  if (!several) {
+    if (splits_of(best) * nct * nhb > 256) return best;
+    best_cost = whole_cost(best);
+  }
   for (int ts = 1024 - kSlotTokens; ts > 0 && splits_of(ts) * nct * nhb <= kAbsShortWgs; ts -= kSlotTokens) {
     if (fixed + plan_absorbed(dm, mt.n, slots, splits_of(ts)).total > ws_bytes) break;      // (shorter ones need more)
-    const int64_t cost = whole_cost(ts);
+    const int64_t cost = several ? turns_cost(ts) : whole_cost(ts);
     if (cost < best_cost) { best_cost = cost; best = ts; }
   }
   return best;
@@ -1015,7 +1028,7 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
       else hipLaunchKernelGGL((absorbed::absorb_q_kernel<64>), qg, dim3(256), 0, st, a, n);
       LAUNCH_CHECK();
       // small grids: 32-token workgroups; few of 128 tokens: one per compute unit with a deeper pipeline; many: two per compute unit
-      if ((int64_t)slots * nhb * absorbed::kSmallSlots <= kAbsSmallWgs) hipLaunchKernelGGL(absorbed::scores_small_kernel, dim3(slots * absorbed::kSmallSlots, nhb), dim3(absorbed::kSmallWaves * 64), 0, st, a, mt);
+      if (scores_are_small(dm, mt)) hipLaunchKernelGGL(absorbed::scores_small_kernel, dim3(slots * absorbed::kSmallSlots, nhb), dim3(absorbed::kSmallWaves * 64), 0, st, a, mt);
       else if ((int64_t)slots * nhb <= 384) hipLaunchKernelGGL(absorbed::scores_kernel<4>, dim3(slots, nhb), dim3(256), 0, st, a, mt);
       else hipLaunchKernelGGL(absorbed::scores_kernel<2>, dim3(slots, nhb), dim3(256), 0, st, a, mt);
       LAUNCH_CHECK();

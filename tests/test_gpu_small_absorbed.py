@@ -18,10 +18,12 @@ CASES = [                                      # H_q, H_kv, d, m, lengths
     (8, 4, 128, 128, (31, 32, 33, 129)),       # edges of 32-token tiles and of slots
     (6, 3, 64, 64, (100, 1)),                  # D = 192, m = 64: two partial stages of three
     (40, 5, 128, 64, (200,)),                  # 40 query heads: the second block of 32 is mostly empty
-    (2, 2, 64, 64, (8192,)),                   # 256 workgroups of the 32-token kernel: its last grid
+    (2, 2, 64, 64, (8192,)),                   # 256 workgroups of the 32-token kernel: one round
     (2, 2, 64, 64, (8193,)),
-    (2, 2, 64, 64, (12288,)),
+    (2, 2, 64, 64, (12288,)),                  # 384: its last grid
     (2, 2, 64, 64, (12289,)),
+    (8, 8, 128, 512, (20,) * 128 + (65,)),     # 129 sequences, two launch groups, one 32-token workgroup each but the last
+    (40, 5, 128, 128, (25,) * 40 + (130,)),    # blocks of heads; the queries of 41 sequences are over 1 MB
     (32, 8, 128, 512, (1500, 700)),            # several splits of 128 tokens per sequence
 ]
 MODES = [pytest.param(ek.FLAG_ABSORBED, id="absorbed"), pytest.param(ek.FLAG_ABSORB_V, id="absorb_v")]
