@@ -313,20 +313,21 @@ int merge_launch(const Dims& dm, const float* po, const float* pml, void* out, f
 constexpr int kSmallFewWgs = 240, kSmallMaxWgs = 704, kSmallMaxWgsF32 = 6144;
 inline int small_col_tile(const Dims& dm) { return dm.bf16 ? 128 : dm.d; }
 // Times of a bf16 call in us, with tb token blocks of 16 per workgroup and with the 256 x 256 kernel: launch and merge, rounds of
-// workgroups of the product, and the rows of the retained heads, which the units stream at about 6.5 TB/s (with rotary tables
-// half of that; 1.3 times as long in the small kernel with three and more passes over the rows); in the large kernel's launch half
-// of that hides behind the product.  A round of the small kernel is between a whole and a partial one (its workgroups end at different
+// workgroups of the product, and the rows of the retained heads and the window, which the units stream at about 6.5 TB/s (with rotary tables
+// half of that; 1.3 times as long in the small kernel with three and more passes over the rows) and 2 us of a unit per sequence, head and
+// pass; in the large kernel's launch half of that hides behind the product.  A round of the small kernel is between a whole and a partial one (its workgroups end at different
 // times); the large kernel needs one round for up to 256 tiles, of 1.0 us per k-tile and pass, or 0.72 where all columns of a tile fit
 // one half of it.  Against the clock (64-token / 256 x 256 kernel, us): 8 KV heads,
 // one predicted, 8 x 2000 tokens 43.7 / 57.4, 8 x 3200 73.7 / 59.6, 8 x 5568 137 / 93; two, 8 x 1600 54.6 / 74.2, 8 x 2048 65.6 / 75.1,
 // 8 x 2752 90.9 / 75.4; four with 32 heads (d_in 7680) 222 / 277 at 8 x 1024, 297 / 280 at 8 x 1344; 7 query heads per KV head, one
 // predicted of 8, 8 x 1984 (all rows seven times) 96 / 80.  Over 132 such problems the choice costs 0.2 % in the mean, 8 % at most.
 template <typename T>
-bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgroups, bool rope) {
-  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1;
+bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgroups, bool rope, const Window& win) {
+  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1, win_heads = win.on() ? dm.H_kv : 0;
   int64_t tokens = 0, t256 = 0;
   for (int b = 0; b < mt.n; ++b) { tokens += mt.len[b]; t256 += (mt.len[b] + 255) / 256; }
-  const double streams = (double)(tokens * dm.g0 * (dm.G / gt)) * dm.d * 2 * sizeof(T) / (rope ? 3.25e6 : 6.5e6);
+  const double rows = (double)(dm.G / gt) * (tokens * dm.g0 + (double)mt.n * win_heads * win.rows());
+  const double streams = rows * dm.d * 2 * sizeof(T) / (rope ? 3.25e6 : 6.5e6) + 2.0 / 256 * (dm.G / gt) * mt.n * (dm.g0 + win_heads);
   const double rounds = 0.5 * ((double)workgroups / 256 + (double)((workgroups + 255) / 256));
   const double small = 8 + rounds * (6 + (tb == 2 ? 0.0072 : 0.0112) * dm.d_in) + (dm.G / gt >= 3 ? 1.3 : 1.0) * streams;
   const int64_t tiles = t256 * ((dm.d_out_v + 255) / 256);
@@ -335,7 +336,7 @@ bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgrou
 }
 // Token blocks of 16 per workgroup (0: the problem is not small).
 template <typename T>
-int small_token_blocks(const Dims& dm, const SeqMeta& mt, bool rope) {
+int small_token_blocks(const Dims& dm, const SeqMeta& mt, bool rope, const Window& win) {
   if (!fused_decode_supported<T>(dm.d, dm.G) || dm.d_out_v == 0) return 0;
   if (dm.d_in < (sizeof(T) == 2 ? 128 : 64)) return 0;      // every wave needs a step of 32 (fp32: 16) input dims
   // 32-bit byte offsets inside a token tile and inside W
@@ -348,8 +349,8 @@ int small_token_blocks(const Dims& dm, const SeqMeta& mt, bool rope) {
     if (t16 * ct <= 256) return 1;
     return t32 * ct * dm.d / 64 <= kSmallMaxWgsF32 ? 2 : 0;
   }
-  if (t32 * ct <= kSmallFewWgs) return small_is_faster<T>(dm, mt, 2, t32 * ct, rope) ? 2 : 0;
-  return t64 * ct <= kSmallMaxWgs && small_is_faster<T>(dm, mt, 4, t64 * ct, rope) ? 4 : 0;
+  if (t32 * ct <= kSmallFewWgs) return small_is_faster<T>(dm, mt, 2, t32 * ct, rope, win) ? 2 : 0;
+  return t64 * ct <= kSmallMaxWgs && small_is_faster<T>(dm, mt, 4, t64 * ct, rope, win) ? 4 : 0;
 }
 // Partial slots a small launch can need at most, the window's one per sequence included.
 int64_t small_max_slots(const Dims& dm, int batch, int64_t total_tokens) {
@@ -359,13 +360,13 @@ int64_t small_max_slots(const Dims& dm, int batch, int64_t total_tokens) {
   return std::min<int64_t>(total_tokens / (dm.bf16 ? 32 : 16) + n, wgs / ct) + n;
 }
 
-// Streaming workgroups behind the large kernel's: up to 1024 tokens each, longer ones would outlast the last tiles, and at least 512.
-// Each takes a compute unit, and below that its start and its reductions outweigh its rows: with 128 tokens 17 sequences of
+// Streaming workgroups behind the large kernel's: up to 1024 tokens each, longer ones would outlast the last tiles, and at least 512
+// if there are more than 256.  Each takes a compute unit, and below that its start and its reductions outweigh its rows: with 128 tokens 17 sequences of
 // 2187-13124 tokens, one retained head of 64, 80 us, with 512 55; 8 x 4000, seven heads of 128, 80 and 73.
 constexpr int kStreamMinChunk = 512;
 // Streaming part of a decode call (retained heads, window) as workgroups of the product's launch.  slot_tokens:
-// tokens per partial slot of mt.s.sbase.  Chunks start at min_chunk tokens and double until
-// at most max_wgs workgroups are left or they are max_chunk tokens long.
+// tokens per partial slot of mt.s.sbase.  Chunks start at one round of a workgroup's rows and double until at most one round of
+// workgroups is left, or max_wgs of them and min_chunk tokens, or they are max_chunk tokens long.
 template <typename T>
 Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* qq, const echokv_decode_extras* ex,
                         const KvExtras& kx, float* po, float* pml, int b0, int slot_tokens, int min_chunk, int max_wgs, int max_chunk,
@@ -377,12 +378,13 @@ Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* q
   r.q = qq; r.H_q = dm.H_q; r.G = dm.G; r.d = dm.d; r.scale = dm.scale; r.part_o = po; r.part_ml = pml;
   r.slot_tokens = slot_tokens; r.rope_cos = kx.rope_cos; r.rope_sin = kx.rope_sin; r.win = Window{kx.n_sink, kx.n_recent};
   s.win = r;
-  for (r.split_tokens = min_chunk;; r.split_tokens *= 2) {
+  for (r.split_tokens = kSlotTokens;; r.split_tokens *= 2) {
     int acc = 0;
     for (int b = 0; b < mt.s.n; ++b) { mt.cbase[b] = acc; acc += (mt.s.len[b] + r.split_tokens - 1) / r.split_tokens; }
     mt.cbase[mt.s.n] = acc;
     s.n_ret_chunks = acc;
-    if ((int64_t)acc * ny <= max_wgs || r.split_tokens >= max_chunk) break;
+    const int64_t wgs = (int64_t)acc * ny;
+    if (wgs <= 256 || (wgs <= max_wgs && r.split_tokens >= min_chunk) || r.split_tokens >= max_chunk) break;
   }
   s.n_ret = s.n_ret_chunks * ny;
   *stream_step = r.split_tokens / slot_tokens;
@@ -473,7 +475,7 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
     const T* qq = (const T*)q + (int64_t)b0 * dm.H_q * dm.d;
     int stream_step = 1, fused_step = 1;
 
-    const int tb = fused && !(flags & ECHOKV_FLAG_STAGED) ? small_token_blocks<T>(dm, mt, kx.rope_cos != nullptr) : 0;
+    const int tb = fused && !(flags & ECHOKV_FLAG_STAGED) ? small_token_blocks<T>(dm, mt, kx.rope_cos != nullptr, win) : 0;
     if (tb > 0) {
       SeqMeta ms = mt;
       const int sl = fill_slots(ms, 16 * tb);

@@ -14,16 +14,17 @@ from test_gpu_parity import check, host, make_dw
 
 pytestmark = pytest.mark.gpu
 
-# H_q, H_kv, d, m, lengths.  Chunks of 512 tokens, longer ones where 1024 workgroups would be exceeded.
+# H_q, H_kv, d, m, lengths.  Chunks of 128 tokens up to 256 workgroups, of 512 up to 1024, then longer ones.
 CASES = [
-    (8, 4, 128, 128, (1100, 129, 1)),         # G = 2, 5 chunks
-    (8, 4, 128, 128, (4500, 600, 1)),         # 12 chunks: 8 and 4
-    (12, 4, 64, 64, (900, 31)),               # G = 3: one query head at a time
-    (12, 4, 64, 64, (4100, 31)),              # 10 chunks
-    (16, 4, 64, 128, (1024,)),                # G = 4, two retained heads
-    (16, 4, 64, 128, (4096,)),                # 8 chunks, no tail
+    (8, 4, 128, 128, (1100, 129, 1)),         # G = 2, 12 chunks: 8 and 4
+    (8, 4, 128, 128, (4500, 600, 1)),         # 42 chunks: 40 and 2
+    (12, 4, 64, 64, (900, 31)),               # G = 3: one query head at a time, 9 chunks
+    (12, 4, 64, 64, (4100, 31)),              # 34 chunks
+    (16, 4, 64, 128, (1024,)),                # G = 4, two retained heads, 8 chunks, no tail
+    (16, 4, 64, 128, (4096,)),                # 32 chunks x 2 heads
     (32, 4, 128, 256, (257, 255)),            # G = 8: two groups per KV head
-    (8, 8, 64, 512, (17000, 70)),             # every head retained; 35 chunks
+    (8, 8, 64, 512, (17000, 70)),             # every head retained; 134 chunks x 8 heads are too many: 35 of 512 tokens, 280 workgroups
+    (16, 4, 64, 128, (17000, 70)),            # 134 x 2: just over one round, 35 x 2
     (28, 4, 128, 384, (25000, 70)),           # G = 7: 50 chunks x 21 are too many, 26 of 1024 tokens
     (56, 8, 128, 768, (300,) * 128),          # G = 7, 256 tiles: no unit idle, the streams in a launch of their own
     (24, 8, 64, 384, (512,) * 127 + (500,)),  # G = 3: the same
