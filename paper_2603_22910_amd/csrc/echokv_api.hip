@@ -406,10 +406,18 @@ Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* q
 // the product is left alone.  In the launch / by themselves, us, 8 KV heads: G = 5, 6 retained, 128 x 300 tokens with window 374 / 261, 7 retained, 40 x
 // 4000 684 / 603, with rope 912 / 790; G = 8, 4 retained, 128 x 300 with window 365 / 302; G = 4, 4 retained, 8 x 6000 (many
 // units idle) 165 / 190; G = 7, 3 of 4 retained, 2 x 40000 170 / 180, 40 x 4000 397 / 353.
-bool streams_by_themselves(const Dims& dm, const SeqMeta& mt, bool rope, const Window& win) {
+// With 5 or 7 passes over sequences of up to 8192 tokens the launches of attn_split_kernel, head after head, are faster than
+// that (the product's launch takes 1.25 times as long, not 1.14) while the rows stay in the last cache or there are rotary tables to
+// wait for.  Launch of their own in the order of chunks / head after head: G = 5, 6 of 8 retained, 48 x 800 with rope and window 238 /
+// 207, 7 of 8, 8 x 6000 190 / 171, 40 x 4000 with rope 790 / 720; but G = 7, 40 x 4000 without rope 353 / 411, 2 x 40000 with it 253 / 358.
+// G = 3, 3 of 4, 8 x 6000 with rope and window: in the product's launch 87, head after head 98.
+enum class StreamsIn { kProduct, kChunkOrder, kHeadOrder };
+StreamsIn place_of_streams(const Dims& dm, const SeqMeta& mt, bool rope, const Window& win) {
   const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1, passes = dm.G / gt;
   int64_t tokens = 0, chunks = 0, tiles = 0;
+  int max_len = 0;
   for (int b = 0; b < mt.n; ++b) {
+    max_len = std::max(max_len, mt.len[b]);
     tokens += mt.len[b]; chunks += (mt.len[b] + kStreamMinChunk - 1) / kStreamMinChunk; tiles += (mt.len[b] + 255) / 256;
   }
   tiles *= (dm.d_out_v + 255) / 256;
@@ -419,7 +427,10 @@ bool streams_by_themselves(const Dims& dm, const SeqMeta& mt, bool rope, const W
   const int64_t rounds = (tiles + 255) / 256;
   const double tile = 9 + 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0);           // see small_is_faster
   const double idle = (double)(rounds * 256 - tiles) * tile;
-  return (0.14 * streams - 1.14 * idle) / 256 > 5 + 0.03 * (double)rounds * tile;
+  const bool head_order = passes >= 5 && max_len <= 8192 && (rope || tokens * dm.m * 4 <= (int64_t)200 << 20);
+  const double faster = head_order ? 0.25 : 0.14;
+  if ((faster * streams - (1 + faster) * idle) / 256 <= 5 + 0.03 * (double)rounds * tile) return StreamsIn::kProduct;
+  return head_order ? StreamsIn::kHeadOrder : StreamsIn::kChunkOrder;
 }
 
 template <typename T>
@@ -506,14 +517,22 @@ int decode_impl(const Dims& dm, uint32_t flags, const echokv_layer_cache* an,
         StreamMeta sm;
         sm.s = mt;
         int win_slot0 = -1;
-        const bool apart = streams_by_themselves(dm, mt, kx.rope_cos != nullptr, win);
-        Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, kStreamMinChunk, apart ? 8192 : 1024, 1024, sm, &stream_step, &win_slot0);
-        int rc;
-        if (apart) {
+        const StreamsIn place = place_of_streams(dm, mt, kx.rope_cos != nullptr, win);
+        Streams<T> streams = plan_streams<T>(dm, tg, qq, ex, kx, po, pml, b0, kSlotTokens, kStreamMinChunk, place == StreamsIn::kProduct ? 1024 : 8192, 1024, sm, &stream_step, &win_slot0);
+        int rc = ECHOKV_OK;
+        if (place == StreamsIn::kChunkOrder) {
           rc = launch_streams<T>(streams, sm, st);
-          if (rc) return rc;
-          streams.n_ret = streams.n_win = 0;
+        } else if (place == StreamsIn::kHeadOrder) {
+          if (n_ret_heads > 0) {
+            AttnArgs<T> a = streams.ret;
+            a.split_tokens = pick_split_tokens(tokens, n_ret_heads);
+            stream_step = a.split_tokens / kSlotTokens;
+            rc = launch_attn_split<T>(dm, a, mt, n_ret_heads, st);
+          }
+          if (!rc && win.on()) rc = launch_window_attn<T>(dm, ex, kx, qq, po, pml, b0, win_slot0, mt, st);
         }
+        if (rc) return rc;
+        if (place != StreamsIn::kProduct) streams.n_ret = streams.n_win = 0;
         ProfScope prof;
         rc = prof.begin(0, st);
         if (rc) return rc;

@@ -1,7 +1,7 @@
 """GPU parity of the streaming workgroups behind the predictor product's: retained heads and window of a
 decode call on the kernel for large problems, and retained heads' scores and window of the value-absorbed mode.  Chunk
 counts on both sides of multiples of 8 (their order changes there), every way the query heads of a KV head
-are grouped, rows of 64 and 128 dims, a layer whose heads are all retained, streams in a launch of their own; every output element against the fp64 oracle."""
+are grouped, rows of 64 and 128 dims, a layer whose heads are all retained, streams in launches of their own, by chunks or head after head; every output element against the fp64 oracle."""
 import numpy as np
 import pytest
 import torch
@@ -26,8 +26,8 @@ CASES = [
     (8, 8, 64, 512, (17000, 70)),             # every head retained; 134 chunks x 8 heads are too many: 35 of 512 tokens, 280 workgroups
     (16, 4, 64, 128, (17000, 70)),            # 134 x 2: just over one round, 35 x 2
     (28, 4, 128, 384, (25000, 70)),           # G = 7: 50 chunks x 21 are too many, 26 of 1024 tokens
-    (56, 8, 128, 768, (300,) * 128),          # G = 7, 256 tiles: no unit idle, the streams in a launch of their own
-    (24, 8, 64, 384, (512,) * 127 + (500,)),  # G = 3: the same
+    (56, 8, 128, 768, (300,) * 128),          # G = 7, 256 tiles: no unit idle, the streams ahead of the product, head after head
+    (24, 8, 64, 384, (512,) * 127 + (500,)),  # G = 3: the same by chunks
     (32, 4, 128, 384, (500,) * 128),          # G = 8: only with the window and rotary tables
 ]
 
