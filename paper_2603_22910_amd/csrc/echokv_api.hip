@@ -676,7 +676,7 @@ template <typename T>
 int prefill_impl(const Dims& dm, const echokv_layer_cache* an, const echokv_layer_cache* tg,
                  const void* w_k, const void* w_v, int seq, const void* q, int T_q, int q_pos0,
                  const float* rope_cos, const float* rope_sin, void* out, float* lse, char* ws,
-                 hipStream_t st) {
+                 size_t ws_bytes, hipStream_t st) {
   const int n_ret_heads = dm.g0, n_rec_heads = dm.H_kv - n_ret_heads;
   const int Ltot = q_pos0 + T_q;
   const int64_t row0 = an->seq_start[seq];
@@ -732,11 +732,11 @@ int prefill_impl(const Dims& dm, const echokv_layer_cache* an, const echokv_laye
     if constexpr (sizeof(T) == 2) {
       if (rope.cos && n_ret_heads > 0) k_ret = rope.dst;
     }
-    float* sp_o = (float*)(ws + prefill_split_offset(dm, Ltot, T_q));
-    float* sp_ml = sp_o + (size_t)T_q * dm.H_q * prefill_kv_splits(T_q, Ltot, dm.H_q) * dm.d;
+    const size_t part = prefill_split_offset(dm, Ltot, T_q);
     rcp = launch_prefill_mfma<T>(dm.H_q, dm.H_kv, dm.d, dm.m, dm.d_out_v, dm.g0, dm.scale, dm.out_bf16,
                                  k_ret, (const T*)tg->v + row0 * dm.m,
-                                 kh, vh, (const T*)q, T_q, q_pos0, out, lse, st, sp_o, sp_ml);
+                                 kh, vh, (const T*)q, T_q, q_pos0, out, lse, st,
+                                 (float*)(ws + part), (ws_bytes - part) / 4);
     if (rcp) return rcp;
     return prof.end();
   }
@@ -1145,7 +1145,10 @@ size_t echokv_workspace_bytes(const echokv_shape* shape, int32_t batch, int64_t 
   size_t need = decode_ws_bytes(dm, batch, total_tokens, true);
   if ((shape->flags & kAbsModes) && absorbed_supported(dm, shape->flags))
     need = std::max(need, absorbed_ws_bytes(dm, batch, total_tokens));
-  if (max_q >= 1) need = std::max(need, prefill_ws_bytes(dm, total_tokens, max_q));
+  if (max_q >= 1) {
+    need = std::max(need, prefill_ws_bytes(dm, total_tokens, max_q));
+    if (dm.bf16) need = std::max(need, prefill_split_offset(dm, total_tokens, max_q) + align_up(prefill_most_split_floats(max_q, dm.H_q, dm.d) * 4));
+  }
   return need;
 }
 
@@ -1774,8 +1777,8 @@ int echokv_prefill_attn_ex(const echokv_shape* shape, const echokv_layer_cache* 
   if (!workspace || workspace_bytes < need) return ECHOKV_ERR_WORKSPACE;
   if ((uintptr_t)workspace % 256) return ECHOKV_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
-  return dm.bf16 ? prefill_impl<bf16_t>(dm, anchor, target, w_k, w_v, seq, q, T_q, q_pos0, rope_cos, rope_sin, out, lse_out, (char*)workspace, st)
-                 : prefill_impl<float>(dm, anchor, target, w_k, w_v, seq, q, T_q, q_pos0, rope_cos, rope_sin, out, lse_out, (char*)workspace, st);
+  return dm.bf16 ? prefill_impl<bf16_t>(dm, anchor, target, w_k, w_v, seq, q, T_q, q_pos0, rope_cos, rope_sin, out, lse_out, (char*)workspace, workspace_bytes, st)
+                 : prefill_impl<float>(dm, anchor, target, w_k, w_v, seq, q, T_q, q_pos0, rope_cos, rope_sin, out, lse_out, (char*)workspace, workspace_bytes, st);
 }
 
 int echokv_prefill_attn(const echokv_shape* shape, const echokv_layer_cache* anchor,

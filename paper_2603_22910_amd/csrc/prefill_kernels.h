@@ -30,7 +30,7 @@ struct Args {
   const bf16_t* k_hat; const bf16_t* v_hat;   // predicted heads, row 0 = token 0, stride d_out
   const bf16_t* q;                            // [T_q, H_q, d]
   void* out; float* lse;                      // [T_q, H_q, d], [T_q, H_q]
-  int32_t H_q, G, m, d_out, n_ret_heads, T_q, q_pos0, out_bf16;
+  int32_t H_q, H_kv, G, m, d_out, n_ret_heads, T_q, q_pos0, out_bf16;
   float scale;
   // split over the keys (long-chunk kernel only; kv_splits == 1: off): workgroup z of a (head,
   // query block) takes one share of the block's key tiles and writes its unnormalised partial
@@ -258,8 +258,10 @@ __global__ __launch_bounds__(NTHREADS, 2) void prefill_attn_kernel(Args a) {
 
 
 // ---------------------------------------------------------------------------------------
-// Long chunks: 384 queries x one head per workgroup of twelve waves (32 queries each, three
-// waves per SIMD: what hides the latencies here is other waves), K and V tiles of 64 keys
+// Long chunks and short ones behind a long context: 384 rows of one KV head per workgroup of twelve waves (32 rows each, three
+// waves per SIMD: what hides the latencies here is other waves).  A row is a (query, query head of the group) pair: a block
+// holds all heads of its queries, so that G heads share the tiles they read, few queries fill a block G times better and causality
+// cuts a block's keys G times finer (one head per block -> this with the shares below, see prefill_kv_shares).  K and V tiles of 64 keys are
 // copied global -> LDS by the buffer-load-to-LDS path into a ring of four stages (three tiles in
 // flight, no staging registers, no address arithmetic per element), both stored row-major
 // [key][dim].  The V^T fragments the second product needs are read with the LDS transpose
@@ -279,7 +281,7 @@ typedef short short4_t __attribute__((ext_vector_type(4)));
 // the first NCOPY waves issue the copies (a tile is 16 or 32 one-KB copies per operand)
 constexpr int NST = 4, NCOPY = 8, NWAVES = 12, NTHREADS = 64 * NWAVES, BQ = 32 * NWAVES;
 constexpr int kMinQueries = 1024;      // shorter chunks: split over the keys if the context is long, else the four-wave kernel
-constexpr int kMaxSplits = 8;
+constexpr int kMaxSplits = 8, kMaxShares = 32, kMinShareTiles = 3;      // see prefill_kv_splits, prefill_kv_shares
 // A new reference lies at most this many base-2 units below the one before it: the sums grow by less than 2^(7 * 16), and what
 // is that far below the former keys has no weight beside them.
 constexpr float kRefDrop = 16.0f;
@@ -382,6 +384,12 @@ __device__ __forceinline__ void wait_v(VFrag& f) {
     asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(f.lo[0]), "+v"(f.lo[1]), "+v"(f.hi[0]), "+v"(f.hi[1]) : "n"(N));
 }
 
+// Row of the [T_q, H_q] tensors that row r (query r / G, head r % G of the group) of a KV head stands for.
+__device__ __forceinline__ int64_t row_of(const Args& a, int kvh, int r) {
+  const int qi = r / a.G;
+  return (int64_t)qi * a.H_q + kvh * a.G + (r - qi * a.G);
+}
+
 template <int HD, bool SPLIT>
 __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
   using C = Cfg<HD>;
@@ -389,14 +397,13 @@ __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int lr = lane & 31, lh = lane >> 5;
-  const int h = blockIdx.x;                       // grid = (heads, query blocks), longest blocks of all heads first
-  // Query blocks are counted from the END of the chunk: block y covers queries
-  // [T_q - (y + 1) BQ, T_q - y BQ).  If T_q is not a multiple of BQ the block that is only partly
-  // filled is then the first (shortest, cheapest) one and not the last (longest) one; its queries
-  // below 0 repeat query 0 and are not written back.
-  const int i0 = a.T_q - ((int)blockIdx.y + 1) * BQ;
+  const int blk = (int)(blockIdx.x / (unsigned)a.H_kv), kvh = (int)(blockIdx.x % (unsigned)a.H_kv);      // longest blocks of all KV heads first
+  // Row r = query r / G, query head r % G of the KV head's group.  Row blocks are counted from the END of the
+  // chunk: block k covers rows [T_q G - (k + 1) BQ, T_q G - k BQ).  If T_q G is not a multiple of BQ the block
+  // that is only partly filled is then the first (shortest, cheapest) one and not the last (longest) one; its
+  // rows below 0 repeat row 0 and are not written back, and a wave that has no others only copies.
+  const int i0 = a.T_q * a.G - (blk + 1) * BQ;
   const int Ltot = a.q_pos0 + a.T_q;
-  const int kvh = h / a.G;
   const bf16_t* kbase; const bf16_t* vbase; uint32_t ld2;
   if (kvh < a.n_ret_heads) { kbase = a.k_ret + kvh * HD; vbase = a.v_ret + kvh * HD; ld2 = (uint32_t)a.m * 2; }
   else { const int c = (kvh - a.n_ret_heads) * HD; kbase = a.k_hat + c; vbase = a.v_hat + c; ld2 = (uint32_t)a.d_out * 2; }
@@ -408,12 +415,11 @@ __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
   cp.rk = fused::make_rsrc(kbase); cp.rv = fused::make_rsrc(vbase);
   cp.ld2 = ld2; cp.last = Ltot - 1; cp.wave_u = wave_u;
 
-  // ---- this lane's query (clamped; clamped duplicates are not written back)
-  const int qi = i0 + wave_u * 32 + lr;
-  const int qic = max(qi, 0);                     // (qi < T_q always: blocks end at T_q - y BQ)
+  // ---- this lane's row (clamped; clamped duplicates are not written back)
+  const int row0 = i0 + wave_u * 32;              // (below T_q G always: blocks end at T_q G - k BQ)
   bf16x8_t qf[C::KSTEPS];
   {
-    const bf16_t* qp = a.q + ((int64_t)qic * a.H_q + h) * HD + lh * 8;
+    const bf16_t* qp = a.q + row_of(a, kvh, max(row0 + lr, 0)) * HD + lh * 8;
 #pragma unroll
     for (int kk = 0; kk < C::KSTEPS; ++kk) qf[kk] = *reinterpret_cast<const bf16x8_t*>(qp + kk * 16);
   }
@@ -427,9 +433,9 @@ __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
     for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
   const float scale2 = a.scale * 1.44269504088896340736f;    // softmax in base 2
-  const int qpos_min = a.q_pos0 + max(i0 + wave_u * 32, 0);
-  const int qpos_max = a.q_pos0 + max(i0 + wave_u * 32 + 31, 0);
-  const int kv_end = min(Ltot, a.q_pos0 + i0 + BQ);   // keys any query of the block sees (i0 + BQ <= T_q)
+  const int qpos_min = a.q_pos0 + max(row0, 0) / a.G;
+  const int qpos_max = a.q_pos0 + max(row0 + 31, 0) / a.G;
+  const int kv_end = a.q_pos0 + (i0 + BQ - 1) / a.G + 1;   // keys any row of the block sees
   const int ntiles_blk = (kv_end + BKV - 1) / BKV;
   // SPLIT: this workgroup's share [t_first, ntiles) of the block's key tiles
   int t_first = 0, ntiles = ntiles_blk;
@@ -458,7 +464,7 @@ __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
   // Two loops (tiles that reach a query of this wave, then tiles wholly past them where the
   // wave only keeps copying and meeting the others) instead of a skip inside one: no values
   // to merge between the paths.
-  const int nact = min(ntiles, qpos_max / BKV + 1);
+  const int nact = row0 + 31 < 0 ? t_first : min(ntiles, qpos_max / BKV + 1);
   dma_tile<HD, SPLIT ? 1 : 0>(smem, cp, t_first); dma_tile<HD, SPLIT ? 1 : 0>(smem, cp, t_first + 1); dma_tile<HD, SPLIT ? 1 : 0>(smem, cp, t_first + 2);
   int t = t_first;
   for (; t < nact; ++t) {
@@ -486,7 +492,7 @@ __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
     // ---- online softmax, lane-local (keys: mb*32 + 8*(r/4) + 4*lh + r%4), base 2, scale folded in
     if (kv0 + BKV - 1 > qpos_min) {   // rare (diagonal tiles): the lane's query position is worked out afresh
       const int ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-      const int qp = a.q_pos0 + max(i0 + wave_u * 32 + (ln & 31), 0);
+      const int qp = a.q_pos0 + max(row0 + (ln & 31), 0) / a.G;
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
@@ -561,15 +567,15 @@ __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
     dma_tile<HD, SPLIT ? 1 : 0>(smem, cp, t + 3);
   }
   wait_loads_and_barrier<0>();         // the ring's last copies have landed before the workgroup ends
-  // ---- finish: this lane holds query qi, head dims cb*32 + 8*(r/4) + 4*lh + r%4
+  // ---- finish: this lane holds row row0 + lane % 32, head dims cb*32 + 8*(r/4) + 4*lh + r%4
   //      (The lane index is read afresh so that nothing of the set-up stays in registers over the loop.)
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   const int lh_e = lane_e >> 5;
-  const int qi_e = i0 + wave_u * 32 + (lane_e & 31);
-  if (qi_e < 0) return;
+  if (row0 + (lane_e & 31) < 0) return;
+  const int64_t orow = row_of(a, kvh, row0 + (lane_e & 31));
   if constexpr (SPLIT) {        // unnormalised partial of this share: (max, sum, O)
-    const int64_t pr = ((int64_t)qi_e * a.H_q + h) * a.kv_splits + blockIdx.z;
+    const int64_t pr = orow * a.kv_splits + blockIdx.z;
 #pragma unroll
     for (int cb = 0; cb < C::CB; ++cb)
 #pragma unroll
@@ -580,7 +586,7 @@ __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
     return;
   }
   const float inv = 1.0f / l_tot;
-  const int64_t ob = ((int64_t)qi_e * a.H_q + h) * HD;
+  const int64_t ob = orow * HD;
 #pragma unroll
   for (int cb = 0; cb < C::CB; ++cb)
 #pragma unroll
@@ -598,7 +604,7 @@ __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
       }
     }
   if (a.lse && lh_e == 0)
-    a.lse[(int64_t)qi_e * a.H_q + h] = (m_run * scale2 + __log2f(l_tot)) * 0.69314718055994530942f;
+    a.lse[orow] = (m_run * scale2 + __log2f(l_tot)) * 0.69314718055994530942f;
 }
 
 // Joins the key shares of a split launch: exact re-association of the softmax-weighted sums.
@@ -612,9 +618,11 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(Args a, int HD) {
   const int c = (int)(idx % q4) * 4;
   const float* ml = a.part_ml + row * a.kv_splits * 2;
   float M = -INFINITY;
+#pragma unroll 4
   for (int s = 0; s < a.kv_splits; ++s) M = fmaxf(M, ml[2 * s]);     // share 0 holds key 0: finite
   float l = 0.f;
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
   for (int s = 0; s < a.kv_splits; ++s) {
     const float ms = ml[2 * s];
     const float w = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - M);
@@ -659,9 +667,9 @@ template <typename T> inline bool prefill_mfma_supported(int d) {
   return sizeof(T) == 2 && (d == 64 || d == 128);
 }
 
-// Key shares the workspace has room for with a chunk of T_q queries over Ltot cached tokens (1 = no split).  Chunks of
-// kMinQueries queries and more fill the chip by themselves.  A shorter chunk has at most three query
-// blocks per head; with a long context in front of it each (head, block) is cut into shares of at
+// Key shares a chunk of T_q queries over Ltot cached tokens has room for in the least workspace of such a call (1 = no split).
+// Chunks of kMinQueries queries and more fill the chip by themselves.  A shorter chunk has few blocks of rows
+// per KV head; with a long context in front of it each (KV head, block) is cut into shares of at
 // least 8 key tiles until about three workgroups per compute unit exist.
 inline int prefill_kv_splits(int T_q, int64_t Ltot, int H_q) {
   if (T_q >= prefill::dma::kMinQueries) return 1;
@@ -671,25 +679,45 @@ inline int prefill_kv_splits(int T_q, int64_t Ltot, int H_q) {
   S = std::min(S, (768 + wgs - 1) / wgs);
   return std::max(S, 1);
 }
-// Key shares taken: of the 2 .. prefill_kv_splits possible ones those that cost least.  A workgroup fills a compute unit, so the
-// chip runs them in rounds of 256; one costs its key tiles and about six more for its start and end, and each share's
-// partials (written, read and joined) about one tile per 9000 (query, head) pairs.  All possible shares -> these, whole calls of
-// 32 heads over 8 of 128 with m = 512: 500 queries behind 7000 tokens (rope) 8 -> 4 shares, 158 -> 143 us; 768 behind 3232 119 -> 102;
-// 1000 behind 3000 149 -> 124; 900 behind 20000 (rope) 8 -> 5 shares, 449 -> 444; 400 behind 30000 430 -> 410; m = 0, 600 behind 12000
-// 232 -> 214; one block of queries (300 behind 7000, 64 behind 16000): the same.
+// (KV head, block of rows) pairs of a chunk.
+inline int64_t prefill_blocks(int T_q, int H_q, int H_kv) {
+  return ((int64_t)T_q * (H_q / H_kv) + prefill::dma::BQ - 1) / prefill::dma::BQ * H_kv;
+}
+// Workgroups that a split chunk may have where prefill_kv_splits makes no room for as many shares: one round, three from kMinQueries
+// queries on (which it does not split at all).
+inline int prefill_share_wgs(int T_q) { return T_q < prefill::dma::kMinQueries ? 256 : 768; }
+// Key shares taken: those that cost least, of as many as the room for partials (words) allows and at least 2 where
+// prefill_kv_splits makes room for them.  A workgroup fills a compute unit; one costs its key tiles and about six more for its start and
+// end, and each share's partials (written, read and joined) about one tile per 9000 (query, head) pairs.  Equal workgroups
+// run in rounds of 256; where causality makes them unequal the units' mean load counts, and the longest one.
+// One head of up to 384 queries per workgroup and 2 .. 8 shares, none from 1024 queries on -> these rows and shares, whole calls in us,
+// 32 heads over 8 of 128: 16 queries behind 24000 tokens 209 -> 116, 64 behind 16000 (rope) 169 -> 121, 500 behind 7000 (m = 64, rope)
+// 144 -> 127, 900 behind 20000 (rope) 443 -> 372, 1200 behind 12000 (m = 64) 497 -> 331, 4096 behind 24000 (m = 64) 1996 -> 1750, 1500 alone
+// 94 -> 86, 8192 alone 548 -> 547; 32 over 32: 1500 behind 8000 825 -> 720, 1100 behind 24000 1860 -> 1470, 2500 alone 203 -> 203.  With 8
+// tiles per share at least, 100 behind 3000 took 72 us and 200 behind 1000 72; with 3 67 and 65.
 // The probabilities are rounded to bf16 relative to the softmax reference, and the key that sets it is rounded without error: fewer
 // shares alone put the output further from its value in 64 bits (0.24 % more error in the mean of 32 such chunks, up to 0.8 %).  So
 // a share takes a new reference wherever one of prefill_kv_splits shares would begin (kv_refs): the probabilities are then the same
 // as with all the shares.
-inline int prefill_kv_shares(int T_q, int64_t Ltot, int H_q) {
+inline int prefill_kv_shares(int T_q, int q_pos0, int H_q, int H_kv, int d, size_t words) {
+  using namespace prefill;
+  const int64_t Ltot = (int64_t)q_pos0 + T_q;
   const int cap = prefill_kv_splits(T_q, Ltot, H_q);
-  const int wgs = (T_q + prefill::dma::BQ - 1) / prefill::dma::BQ * H_q;
-  const float tiles = (float)((Ltot + prefill::BKV - 1) / prefill::BKV), share = (float)T_q * (float)H_q / 9000.f;
-  int best = cap;
+  if (cap == 1 && T_q < dma::kMinQueries) return 1;
+  const int G = H_q / H_kv;
+  const int64_t wgs = prefill_blocks(T_q, H_q, H_kv), tiles = (Ltot + BKV - 1) / BKV;
+  const int64_t first_rows = ((int64_t)T_q * G - 1) % dma::BQ + 1, first = (q_pos0 + (first_rows + G - 1) / G + BKV - 1) / BKV;
+  int64_t most = std::min<int64_t>({dma::kMaxShares, tiles / dma::kMinShareTiles, std::max<int64_t>(prefill_share_wgs(T_q) / wgs, 1)});
+  most = std::max<int64_t>(cap, std::min<int64_t>(most, (int64_t)(words / ((size_t)T_q * H_q * (d + 2)))));
+  const float share = (float)T_q * (float)H_q / 9000.f;
+  const float longest = (float)tiles, mean = 0.5f * (float)(tiles + first), alike = (float)first / (float)tiles;
+  int best = 1;
   float best_cost = 0.f;
-  for (int S = cap; S >= 2; --S) {
-    const float cost = (float)((wgs * S + 255) / 256) * (tiles / (float)S + 6.f) + (float)S * share;
-    if (S == cap || cost < best_cost) { best = S; best_cost = cost; }
+  for (int S = (int)std::max<int64_t>(most, 1); S >= (cap > 1 ? 2 : 1); --S) {
+    const float n = (float)(wgs * S), each = mean / (float)S + 6.f;
+    const float load = n * each / 256.f, rounds = (float)((wgs * S + 255) / 256) * each;
+    const float cost = std::max(load + alike * (rounds - load), longest / (float)S + 6.f) + (S > 1 ? (float)S * share : 0.f);
+    if (best_cost == 0.f || cost < best_cost) { best = S; best_cost = cost; }
   }
   return best;
 }
@@ -697,6 +725,10 @@ inline int prefill_kv_shares(int T_q, int64_t Ltot, int H_q) {
 inline size_t prefill_split_floats(int T_q, int64_t Ltot, int H_q, int d) {
   const int S = prefill_kv_splits(T_q, Ltot, H_q);
   return S > 1 ? (size_t)T_q * H_q * S * (d + 2) : 0;
+}
+// ... and the most that any chunk of up to max_q queries can make use of
+inline size_t prefill_most_split_floats(int max_q, int H_q, int d) {
+  return std::min<size_t>((size_t)max_q * H_q * prefill::dma::kMaxShares, (size_t)prefill_share_wgs(max_q) * prefill::dma::BQ) * (d + 2);
 }
 
 // k_ret / v_ret: retained cache at the sequence's first row (stride m);
@@ -706,27 +738,27 @@ inline int launch_prefill_mfma(int H_q, int H_kv, int d, int m, int d_out, int n
                                float scale, bool out_bf16,
                                const T* k_ret, const T* v_ret, const T* k_hat, const T* v_hat,
                                const T* q, int T_q, int q_pos0, void* out, float* lse,
-                               hipStream_t st, float* part_o = nullptr, float* part_ml = nullptr) {
+                               hipStream_t st, float* part, size_t part_words) {
   if constexpr (sizeof(T) != 2) {
     return 6;
   } else {
     prefill::Args a;
     a.k_ret = k_ret; a.v_ret = v_ret; a.k_hat = k_hat; a.v_hat = v_hat; a.q = q;
     a.out = out; a.lse = lse;
-    a.H_q = H_q; a.G = H_q / H_kv; a.m = m; a.d_out = d_out; a.n_ret_heads = n_ret_heads;
+    a.H_q = H_q; a.H_kv = H_kv; a.G = H_q / H_kv; a.m = m; a.d_out = d_out; a.n_ret_heads = n_ret_heads;
     a.T_q = T_q; a.q_pos0 = q_pos0; a.out_bf16 = out_bf16 ? 1 : 0; a.scale = scale;
     a.kv_splits = a.kv_refs = 1; a.ref_drop = 0.f; a.part_o = nullptr; a.part_ml = nullptr;
     // long chunks take the twelve-wave kernel with the LDS ring (its 32-bit row offsets must fit);
     // so do short chunks in front of a long context, split over the keys so that the grid still
     // fills the chip
     const int64_t span = (int64_t)(q_pos0 + T_q) * (m > d_out ? m : d_out) * 2;
-    const int S = span < (int64_t)1 << 31 ? prefill_kv_shares(T_q, q_pos0 + T_q, H_q) : 1;
+    const int S = span < (int64_t)1 << 31 ? prefill_kv_shares(T_q, q_pos0, H_q, H_kv, d, part_words) : 1;
+    const dim3 dgrid((unsigned)prefill_blocks(T_q, H_q, H_kv), 1, S), dblk(prefill::dma::NTHREADS);
     if (S > 1) {
-      if (!part_o || !part_ml) return 5;
-      a.kv_splits = S; a.kv_refs = prefill_kv_splits(T_q, q_pos0 + T_q, H_q);
-      a.ref_drop = prefill::dma::kRefDrop / (scale * 1.44269504088896340736f); a.part_o = part_o; a.part_ml = part_ml;
-      const dim3 grid(H_q, (T_q + prefill::dma::BQ - 1) / prefill::dma::BQ, S), blk(prefill::dma::NTHREADS);
-      int rc = d == 128 ? prefill::dma::launch<128, true>(grid, blk, st, a) : prefill::dma::launch<64, true>(grid, blk, st, a);
+      a.kv_splits = S; a.kv_refs = std::max(S, prefill_kv_splits(T_q, q_pos0 + T_q, H_q));
+      a.ref_drop = prefill::dma::kRefDrop / (scale * 1.44269504088896340736f); a.part_o = part;
+      a.part_ml = part + (size_t)T_q * H_q * S * d;
+      int rc = d == 128 ? prefill::dma::launch<128, true>(dgrid, dblk, st, a) : prefill::dma::launch<64, true>(dgrid, dblk, st, a);
       if (rc) return rc;
       const unsigned mb = (unsigned)(((int64_t)T_q * H_q * (d / 4) + 255) / 256);
       if (out_bf16) hipLaunchKernelGGL((prefill::dma::prefill_merge_kernel<bf16_t>), dim3(mb), dim3(256), 0, st, a, d);
@@ -734,8 +766,7 @@ inline int launch_prefill_mfma(int H_q, int H_kv, int d, int m, int d_out, int n
       return hipGetLastError() != hipSuccess ? 7 : 0;
     }
     if (T_q >= prefill::dma::kMinQueries && span < (int64_t)1 << 31) {
-      const dim3 grid(H_q, (T_q + prefill::dma::BQ - 1) / prefill::dma::BQ), blk(prefill::dma::NTHREADS);
-      return d == 128 ? prefill::dma::launch<128, false>(grid, blk, st, a) : prefill::dma::launch<64, false>(grid, blk, st, a);
+      return d == 128 ? prefill::dma::launch<128, false>(dgrid, dblk, st, a) : prefill::dma::launch<64, false>(dgrid, dblk, st, a);
     }
     dim3 grid(H_q, (T_q + prefill::BQ - 1) / prefill::BQ);
     if (d == 128) hipLaunchKernelGGL((prefill::prefill_attn_kernel<128>), grid, dim3(prefill::NTHREADS), 0, st, a);
