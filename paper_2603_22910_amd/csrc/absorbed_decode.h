@@ -453,6 +453,7 @@ struct PvIo {
   int nrows, nsteps;
   int lh8;
   int vlo, vhi;      // rows [vlo, vhi) of the split count (the others are past the end or in the window)
+  uint32_t vn;       // how many that are
 };
 
 __device__ __forceinline__ void pv_fetch(PvStage& st, const PvIo& io, int step) {
@@ -479,11 +480,10 @@ __device__ __forceinline__ void pv_mma(floatx16_t (&acc)[8], const PvStage& st, 
   for (int i = 0; i < 4; ++i) {
     const float s0 = __uint_as_float(st.s[i >> 1][(2 * i) & 3]);
     const float s1 = __uint_as_float(st.s[i >> 1][(2 * i + 1) & 3]);
-    const float p0 = (t0 + 2 * i >= io.vlo && t0 + 2 * i < io.vhi) ? exp2f(s0 - M) : 0.f;
-    const float p1 = (t0 + 2 * i + 1 >= io.vlo && t0 + 2 * i + 1 < io.vhi) ? exp2f(s1 - M) : 0.f;
-    const bf16_t h0 = f32_to_bf16(p0), h1 = f32_to_bf16(p1);
-    pw[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-    pl[i] = (uint32_t)f32_to_bf16(p0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(p1 - bf16_to_f32(h1)) << 16);
+    const bool in0 = (uint32_t)(t0 + 2 * i - io.vlo) < io.vn, in1 = (uint32_t)(t0 + 2 * i + 1 - io.vlo) < io.vn;
+    const float p0 = __builtin_amdgcn_exp2f(in0 ? s0 - M : -INFINITY), p1 = __builtin_amdgcn_exp2f(in1 ? s1 - M : -INFINITY);
+    pw[i] = pack_bf16(p0, p1);
+    pl[i] = pack_bf16(p0 - __uint_as_float(pw[i] << 16), p1 - __uint_as_float(pw[i] & 0xffff0000u));
   }
   const bf16x8_t pa = __builtin_bit_cast(bf16x8_t, pw);
   const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, pl);
@@ -530,6 +530,7 @@ __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta me
   io.soff0 = ((uint32_t)lr * (uint32_t)a.s_ld + (uint32_t)lh * 8) * 4;
   io.nrows = nrows; io.nsteps = (nrows + 15) / 16; io.lh8 = lh * 8;
   io.vlo = max(0, a.win.lo(L) - t_begin); io.vhi = min(nrows, a.win.hi(L) - t_begin);
+  io.vn = (uint32_t)max(0, io.vhi - io.vlo);
   const int head = hb * kHB + lr;
   float* const mls = a.ml + ((int64_t)sp * a.H_pad + hb * kHB) * 2;      // this block of heads
   float M;                                        // the split's own maximum
@@ -572,11 +573,16 @@ __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta me
   const int nw = (n - wave + kPvWaves - 1) / kPvWaves;
   pv_fetch(s0, io, wave);
   for (int it = 0; it < nw; it += 2) {
+    // (a stage's loads all leave ahead of the other's products: dealt out between these, they are waited for at once)
     const int st = wave + it * kPvWaves;
     pv_fetch(s1, io, st + kPvWaves);
+    __builtin_amdgcn_sched_barrier(0);
     pv_mma(acc, s0, io, st, M);
+    __builtin_amdgcn_sched_barrier(0);
     pv_fetch(s0, io, st + 2 * kPvWaves);
+    __builtin_amdgcn_sched_barrier(0);
     pv_mma(acc, s1, io, st + kPvWaves, M);
+    __builtin_amdgcn_sched_barrier(0);
   }
 
   // tree reduction over the 4 waves: {2, 3} -> {0, 1}, then 1 -> 0
@@ -756,14 +762,9 @@ __global__ __launch_bounds__(256) void out_partial_kernel(Args a, int nseq) {
     u32x4_t hi, lo;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-      uint32_t h2[2], l2[2];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const float v = live ? yv[2 * p + q] : 0.f;
-        const bf16_t hb = f32_to_bf16(v);
-        h2[q] = hb; l2[q] = f32_to_bf16(v - bf16_to_f32(hb));
-      }
-      hi[p] = h2[0] | (h2[1] << 16); lo[p] = l2[0] | (l2[1] << 16);
+      const float v0 = live ? yv[2 * p] : 0.f, v1 = live ? yv[2 * p + 1] : 0.f;
+      hi[p] = pack_bf16(v0, v1);
+      lo[p] = pack_bf16(v0 - __uint_as_float(hi[p] << 16), v1 - __uint_as_float(hi[p] & 0xffff0000u));
     }
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {

@@ -405,7 +405,7 @@ __device__ __forceinline__ uint4 rope8(uint4 lo, uint4 hi, const float4 (&cos)[2
   }
   uint32_t w[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = (uint32_t)f32_to_bf16(r[2 * i]) | ((uint32_t)f32_to_bf16(r[2 * i + 1]) << 16);
+  for (int i = 0; i < 4; ++i) w[i] = pack_bf16(r[2 * i], r[2 * i + 1]);
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 constexpr int kRopeTurns = 4;

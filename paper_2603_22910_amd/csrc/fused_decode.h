@@ -404,6 +404,40 @@ __global__ __launch_bounds__(64 * kStreamWaves) void score_stream_kernel(Streams
   score_stream_workgroup<HD, kStreamWaves>(streams, smeta, blockIdx.x, s_out, s_ld, smem);
 }
 
+// K_hat of the tile rotated to its tokens' positions, as store(tile row, column block, four values).  A lane holds dims 16 cb + 4 (lane /
+// 16) + r of a head together with their partners HD / 32 blocks further on; the table entries of the next block of 16 tokens are
+// requested ahead of this one's rotation.
+template <int HD, class Store>
+__device__ __forceinline__ void rotate_tile(const Args& a, const Tile& t, const Acc& acc, Store store) {
+  constexpr int HPW = WN / HD, CBH = HD / 16, HB = CBH / 2;
+  const int c = t.lane & 15, o = t.lane >> 4, j0 = t.wt * WM;
+  float4 cs[2][HB], sn[2][HB];
+  auto load = [&](int tb) __attribute__((always_inline)) {
+    const int64_t at = (int64_t)min(t.j0 + j0 + tb * 16 + c, t.L - 1) * (HD / 2) + 4 * o;
+#pragma unroll
+    for (int cb = 0; cb < HB; ++cb) {
+      cs[tb & 1][cb] = *reinterpret_cast<const float4*>(a.rope_cos + at + cb * 16);
+      sn[tb & 1][cb] = *reinterpret_cast<const float4*>(a.rope_sin + at + cb * 16);
+    }
+  };
+  load(0);
+#pragma unroll
+  for (int tb = 0; tb < 4; ++tb) {
+    if (t.j0 + j0 + tb * 16 >= t.L) break;               // (uniform: rows past the end are not stored)
+    if (tb < 3) load(tb + 1);
+#pragma unroll
+    for (int cb = 0; cb < HB; ++cb) {
+      const float4 cq = cs[tb & 1][cb], sq = sn[tb & 1][cb];
+#pragma unroll
+      for (int hw = 0; hw < HPW; ++hw) {
+        const floatx4_t x = acc.v[hw * CBH + cb][tb], y = acc.v[hw * CBH + cb + HB][tb];
+        store(j0 + tb * 16 + c, hw * CBH + cb, x[0] * cq.x - y[0] * sq.x, x[1] * cq.y - y[1] * sq.y, x[2] * cq.z - y[2] * sq.z, x[3] * cq.w - y[3] * sq.w);
+        store(j0 + tb * 16 + c, hw * CBH + cb + HB, y[0] * cq.x + x[0] * sq.x, y[1] * cq.y + x[1] * sq.y, y[2] * cq.z + x[2] * sq.z, y[3] * cq.w + x[3] * sq.w);
+      }
+    }
+  }
+}
+
 // Stand-alone predictor product (Eq. 3) with the same main loop: K_hat or V_hat
 // (blockIdx.y) of the tile is rounded to bf16 and stored at
 // out[row, col0 + column].  Output row = sbase[b]*kSlotTokens + j.  With an
@@ -453,53 +487,28 @@ __global__ __launch_bounds__(NTHREADS) void recon_mfma_kernel(Args a, SeqMeta me
     return;
   }
   // token row: 32 chunks of 16 bytes, chunk ch at ch ^ (token % 32)
+  auto store = [&](int j, int cb, float x0, float x1, float x2, float x3) __attribute__((always_inline)) {
+    const int ch = t.wc * 16 + cb * 2 + (lo >> 1);
+    const u32x2_t w = {pack_bf16(x0, x1), pack_bf16(x2, x3)};
+    *reinterpret_cast<u32x2_t*>(st + j * 512 + ((ch ^ (j & 31)) << 4) + (lo & 1) * 8) = w;
+  };
+  if (which == 0 && a.rope_cos) {
+    if (a.H_q == 128) rotate_tile<128>(a, t, acc, store);
+    else rotate_tile<64>(a, t, acc, store);
+  } else {
 #pragma unroll
-  for (int tb = 0; tb < 4; ++tb) {
-    if (t.j0 + t.wt * WM + tb * 16 >= t.L) break;      // (uniform: rows past the end are not stored; their rounding is 2 us of a tile)
-    const int j = t.wt * WM + tb * 16 + lc;
+    for (int tb = 0; tb < 4; ++tb) {
+      if (t.j0 + t.wt * WM + tb * 16 >= t.L) break;      // (uniform: rows past the end are not stored)
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) {
-      const int ch = t.wc * 16 + cb * 2 + (lo >> 1);
-      const floatx4_t v = acc.v[cb][tb];
-      u32x2_t w;
-      w[0] = (uint32_t)f32_to_bf16(act(v[0])) | ((uint32_t)f32_to_bf16(act(v[1])) << 16);
-      w[1] = (uint32_t)f32_to_bf16(act(v[2])) | ((uint32_t)f32_to_bf16(act(v[3])) << 16);
-      *reinterpret_cast<u32x2_t*>(st + j * 512 + ((ch ^ (j & 31)) << 4) + (lo & 1) * 8) = w;
+      for (int cb = 0; cb < 8; ++cb) {
+        const floatx4_t v = acc.v[cb][tb];
+        store(t.wt * WM + tb * 16 + lc, cb, act(v[0]), act(v[1]), act(v[2]), act(v[3]));
+      }
     }
   }
   __syncthreads();
   const int c = threadIdx.x & 31, n = t.n0 + c * 8;
   if (n >= a.d_out) return;
-  if (which == 0 && a.rope_cos) {
-    const int half = a.H_q / 2, hc = half / 8;       // chunk c pairs with c +- hc
-    const bool hi = (c & hc) != 0;
-    const int f = n % half;                          // table entry of the chunk's first dim
-    // four rows' table entries at a time: one by one each waits for its own
-    constexpr int STEP = NTHREADS / 32, UN = 4;
-    const int je = min(BM, t.L - t.j0);
-#pragma nounroll
-    for (int j0 = threadIdx.x >> 5; j0 < je; j0 += UN * STEP) {
-      float4 cs[UN][2], sn[UN][2];
-#pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const int64_t e = (int64_t)(t.j0 + min(j0 + u * STEP, je - 1)) * half + f;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          cs[u][i] = *reinterpret_cast<const float4*>(a.rope_cos + e + 4 * i);
-          sn[u][i] = *reinterpret_cast<const float4*>(a.rope_sin + e + 4 * i);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const int j = j0 + u * STEP;
-        if (j >= je) break;
-        const char* row = st + j * 512;
-        const uint4 x = *reinterpret_cast<const uint4*>(row + ((c ^ (j & 31)) << 4)), y = *reinterpret_cast<const uint4*>(row + ((c ^ hc ^ (j & 31)) << 4));
-        *reinterpret_cast<uint4*>(out + (orow0 + j) * a.ldo + a.col0 + n) = hi ? rope8<true>(y, x, cs[u], sn[u]) : rope8<false>(x, y, cs[u], sn[u]);
-      }
-    }
-    return;
-  }
   for (int j = threadIdx.x >> 5; j < BM && t.j0 + j < t.L; j += NTHREADS / 32)
     *reinterpret_cast<u32x4_t*>(out + (orow0 + j) * a.ldo + a.col0 + n) =
         *reinterpret_cast<const u32x4_t*>(st + j * 512 + ((c ^ (j & 31)) << 4));
@@ -608,10 +617,10 @@ inline int launch_fused_kscores(int H_q, int H_kv, int d, int m, int d_out, int 
 // rope.cos K_hat is rotated by token position, heads of rope.d dims, and rope's own rows (the retained keys) are as well, these
 // by workgroups of the product's launch.  K_hat on its way out of the product if that has kRopeTiles workgroups and more, by a
 // launch behind it otherwise: the tables' loads are then a latency at the end of a tile that nothing covers.  Whole prefill calls of
-// 32 heads over 8 of 128, behind the product / on its way out, us, and the product's workgroups: m = 512, 64 queries behind 16000 tokens (252)
-// 152 / 144, 900 behind 20000 (328) 442 / 441, 500 behind 7000 (120) 139 / 143, 100 behind 3000 (52) 73.5 / 79.8, 2000 alone (32)
-// 115 / 121; m = 64, 64 behind 16000 (504) 175 / 170, 900 behind 20000 (656) 485 / 474, 500 behind 7000 (240) 141 / 143, 100 behind
-// 3000 (104) 68.0 / 73.2.  From 120 to 240 the two are within 3 % of each other.
+// 32 heads over 8 of 128, behind the product / on its way out, us, and the product's workgroups: m = 512, 16 queries behind 500 tokens (12)
+// 53.7 / 56.6, 100 behind 3000 (52) 66.5 / 69.4, 2000 alone (32) 98.5 / 101.5; m = 64, 100 behind 3000 (104) 61.0 / 62.7.  From 120 to 240
+// the two were within 3 % of each other, and with 252 and more the product's way out ahead by 2 - 5 %, when the rotation was done on rounded
+// rows from LDS, whose table loads four by four took 13 us of a 50 us product (500 behind 7000, m = 64: now 37).
 constexpr int kRopeTiles = 120;
 template <typename T>
 inline int launch_recon_mfma(int D, int m, int d_out, const T* ka, const T* va, const T* kr, const T* vr,

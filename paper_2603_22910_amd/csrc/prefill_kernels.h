@@ -244,8 +244,8 @@ __global__ __launch_bounds__(NTHREADS, 2) void prefill_attn_kernel(Args a) {
         const float x2 = oacc[cb][r4 * 4 + 2] * inv, x3 = oacc[cb][r4 * 4 + 3] * inv;
         if (a.out_bf16) {
           uint2 w;
-          w.x = (uint32_t)f32_to_bf16(x0) | ((uint32_t)f32_to_bf16(x1) << 16);
-          w.y = (uint32_t)f32_to_bf16(x2) | ((uint32_t)f32_to_bf16(x3) << 16);
+          w.x = pack_bf16(x0, x1);
+          w.y = pack_bf16(x2, x3);
           *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(a.out) + ob + c) = w;
         } else {
           *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + ob + c) = make_float4(x0, x1, x2, x3);
@@ -596,8 +596,8 @@ __global__ __launch_bounds__(NTHREADS) void prefill_attn_dma_kernel(Args a) {
       const float x2 = oacc[cb][r4 * 4 + 2] * inv, x3 = oacc[cb][r4 * 4 + 3] * inv;
       if (a.out_bf16) {
         uint2 w;
-        w.x = (uint32_t)f32_to_bf16(x0) | ((uint32_t)f32_to_bf16(x1) << 16);
-        w.y = (uint32_t)f32_to_bf16(x2) | ((uint32_t)f32_to_bf16(x3) << 16);
+        w.x = pack_bf16(x0, x1);
+        w.y = pack_bf16(x2, x3);
         *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(a.out) + ob + c) = w;
       } else {
         *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + ob + c) = make_float4(x0, x1, x2, x3);
@@ -634,8 +634,8 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(Args a, int HD) {
   TO* out = reinterpret_cast<TO*>(a.out) + row * HD + c;
   if constexpr (sizeof(TO) == 2) {
     uint2 w2;
-    w2.x = (uint32_t)f32_to_bf16(o.x * inv) | ((uint32_t)f32_to_bf16(o.y * inv) << 16);
-    w2.y = (uint32_t)f32_to_bf16(o.z * inv) | ((uint32_t)f32_to_bf16(o.w * inv) << 16);
+    w2.x = pack_bf16(o.x * inv, o.y * inv);
+    w2.y = pack_bf16(o.z * inv, o.w * inv);
     *reinterpret_cast<uint2*>(out) = w2;
   } else {
     *reinterpret_cast<float4*>(out) = make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
