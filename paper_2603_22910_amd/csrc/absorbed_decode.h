@@ -177,7 +177,15 @@ __device__ __forceinline__ StageDesc stage_desc(const ScoreIo& io, int t) {
   return d;
 }
 
+// Cache rows that one workgroup reads and nobody after it are loaded as non-temporal: they leave the L2 to what is read again.
+// Whole calls without / with it in the value pass / in both passes, us, d_in 6144, 32 heads: 4 x 3500 tokens 126 / 126 / 118, 4 x 8000 196 /
+// 194 / 180, 16 x 8000 623 / 612 / 581; d_in 5120, 4 x 32768 538 / 520 / 502; d_in 1536: 4 x 8000 75.8 / 71.7 / 70.9, 4 x 14000 102 / 101 / 96, 4 x
+// 50000 273 / 270 / 274, 4 x 4000 58 / 53 / 58.  So in the value pass, and in the score pass, which reads a row in pieces of 256
+// bytes, for anchor rows of 4 KB and more.  With more than 32 query heads the rows are read once per 32: without; and without in
+// splits of up to 128 tokens (2 x 1500 34.6 / 35.2, 1 x 300 of d_in 6144 49.3 / 50.2).
+constexpr int kNonTemporal = 2;              // cache policy operand of the buffer loads: nt
 // this wave's 10 direct-to-LDS loads of stage t: X rows 32 w .. 32 w + 31, U rows 8 w .. 8 w + 7
+template <bool NT>
 __device__ __forceinline__ void score_issue(char* buf, const ScoreIo& io, int t, int wave, int lane) {
   const StageDesc d = stage_desc(io, t);
   const rsrc_t rx = make_rsrc(d.anchor ? io.pa : io.pr);
@@ -190,7 +198,7 @@ __device__ __forceinline__ void score_issue(char* buf, const ScoreIo& io, int t,
     const int chunk = min(slot ^ (row & 15), nchunk - 1);            // a partial stage repeats its last chunk
     const uint32_t voff = __umul24((uint32_t)min(row, io.last), ld2) + (uint32_t)chunk * 16;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (ECHOKV_LDS void*)(buf + (wave * 32 + 4 * i) * kRowBytes),
-                                             16, voff, d.k0 * 2, 0, 0);
+                                             16, voff, d.k0 * 2, 0, NT ? kNonTemporal : 0);
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -234,7 +242,7 @@ __device__ __forceinline__ void score_wait_read() {
   asm volatile("" ::: "memory");
 }
 
-template <int NST>
+template <int NST, bool NT>
 __device__ __forceinline__ void score_stage(floatx16_t& acc, char* buf, const ScoreIo& io, int t,
                                             int wave, int lane, bool head_ok) {
   const int lr = lane & 31, lh = lane >> 5;
@@ -251,7 +259,7 @@ __device__ __forceinline__ void score_stage(floatx16_t& acc, char* buf, const Sc
     uf[s] = *reinterpret_cast<const u32x4_t*>(urow + off);
   }
   score_wait_read();                            // every wave holds its fragments: the buffer is free
-  score_issue(buf, io, t + NST, wave, lane);
+  score_issue<NT>(buf, io, t + NST, wave, lane);
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
     u32x4_t uu = uf[s];
@@ -261,7 +269,7 @@ __device__ __forceinline__ void score_stage(floatx16_t& acc, char* buf, const Sc
   }
 }
 
-template <int NST>      // LDS stages: 2 (80 KB, two workgroups per compute unit) or 4 (160 KB, for small grids)
+template <int NST, bool NT>      // LDS stages: 2 (80 KB, two workgroups per compute unit) or 4 (160 KB, for small grids)
 __global__ __launch_bounds__(256, NST == 2 ? 2 : 1) void scores_kernel(Args a, SeqMeta meta) {
   __shared__ __attribute__((aligned(1024))) char lds[NST * kStageBytes];
   const int slot = blockIdx.x, hb = blockIdx.y;
@@ -289,10 +297,10 @@ __global__ __launch_bounds__(256, NST == 2 ? 2 : 1) void scores_kernel(Args a, S
   // stage t lives in buffer t % NST; stages past the last one repeat it with U counted as
   // zero, so every wave runs the same barriers
 #pragma unroll
-  for (int i = 0; i < NST; ++i) score_issue(lds + i * kStageBytes, io, i, wave, lane);
+  for (int i = 0; i < NST; ++i) score_issue<NT>(lds + i * kStageBytes, io, i, wave, lane);
   for (int t = 0; t < io.ns; t += NST) {
 #pragma unroll
-    for (int i = 0; i < NST; ++i) score_stage<NST>(acc, lds + i * kStageBytes, io, t + i, wave, lane, head_ok);
+    for (int i = 0; i < NST; ++i) score_stage<NST, NT>(acc, lds + i * kStageBytes, io, t + i, wave, lane, head_ok);
   }
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the look-ahead loads land before the block's LDS is released
@@ -456,13 +464,14 @@ struct PvIo {
   uint32_t vn;       // how many that are
 };
 
+template <bool NT>
 __device__ __forceinline__ void pv_fetch(PvStage& st, const PvIo& io, int step) {
   step = min(step, io.nsteps - 1);
   const int t0 = step * 16 + io.lh8;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const uint32_t row = (uint32_t)min(t0 + e, io.nrows - 1);
-    st.x[e] = __builtin_amdgcn_raw_buffer_load_b128(io.rx, __umul24(row, io.pitch2) + io.colb, 0, 0);
+    st.x[e] = __builtin_amdgcn_raw_buffer_load_b128(io.rx, __umul24(row, io.pitch2) + io.colb, 0, NT ? kNonTemporal : 0);
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -504,7 +513,7 @@ __device__ __forceinline__ void pv_mma(floatx16_t (&acc)[8], const PvStage& st, 
 // kPvStatsTokens scores from L2 cost each workgroup less than a launch in front of them all (2 x 1500 tokens 38.9 -> 38.0 us);
 // with 384 tokens they cost more (2 x 8192: 53.7 -> 56.7).
 constexpr int kPvStatsTokens = 128;
-template <bool STATS>
+template <bool STATS, bool NT>
 __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta meta) {
   __shared__ float red[2][128][64];       // 64 KB: two waves' accumulators
   __shared__ float s_ml[STATS ? kHB : 1][2];
@@ -571,15 +580,15 @@ __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta me
   PvStage s0, s1;
   const int n = io.nsteps;
   const int nw = (n - wave + kPvWaves - 1) / kPvWaves;
-  pv_fetch(s0, io, wave);
+  pv_fetch<NT>(s0, io, wave);
   for (int it = 0; it < nw; it += 2) {
     // (a stage's loads all leave ahead of the other's products: dealt out between these, they are waited for at once)
     const int st = wave + it * kPvWaves;
-    pv_fetch(s1, io, st + kPvWaves);
+    pv_fetch<NT>(s1, io, st + kPvWaves);
     __builtin_amdgcn_sched_barrier(0);
     pv_mma(acc, s0, io, st, M);
     __builtin_amdgcn_sched_barrier(0);
-    pv_fetch(s0, io, st + 2 * kPvWaves);
+    pv_fetch<NT>(s0, io, st + 2 * kPvWaves);
     __builtin_amdgcn_sched_barrier(0);
     pv_mma(acc, s1, io, st + kPvWaves, M);
     __builtin_amdgcn_sched_barrier(0);

@@ -1050,8 +1050,12 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
       LAUNCH_CHECK();
       // small grids: 32-token workgroups; few of 128 tokens: one per compute unit with a deeper pipeline; many: two per compute unit
       if (scores_are_small(dm, mt)) hipLaunchKernelGGL(absorbed::scores_small_kernel, dim3(slots * absorbed::kSmallSlots, nhb), dim3(absorbed::kSmallWaves * 64), 0, st, a, mt);
-      else if ((int64_t)slots * nhb <= 384) hipLaunchKernelGGL(absorbed::scores_kernel<4>, dim3(slots, nhb), dim3(256), 0, st, a, mt);
-      else hipLaunchKernelGGL(absorbed::scores_kernel<2>, dim3(slots, nhb), dim3(256), 0, st, a, mt);
+      else {
+        const bool nt = nhb == 1 && dm.D >= 2048, few = (int64_t)slots * nhb <= 384;
+        const auto scores = few ? (nt ? absorbed::scores_kernel<4, true> : absorbed::scores_kernel<4, false>)
+                                : (nt ? absorbed::scores_kernel<2, true> : absorbed::scores_kernel<2, false>);
+        hipLaunchKernelGGL(scores, dim3(slots, nhb), dim3(256), 0, st, a, mt);
+      }
       LAUNCH_CHECK();
     } else {
       // scores of the retained heads straight from the target cache, of the predicted heads from the fused
@@ -1073,13 +1077,13 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
     a.single_split = max_splits == 1 ? 1 : 0;
     const dim3 pg(splits * pl.n_col_tiles, nhb), pb(absorbed::kPvWaves * 64);
     if (ts <= absorbed::kPvStatsTokens) {
-      hipLaunchKernelGGL(absorbed::pv_kernel<true>, pg, pb, 0, st, a, mt);
+      hipLaunchKernelGGL((absorbed::pv_kernel<true, false>), pg, pb, 0, st, a, mt);
     } else {
       // few long pieces: more threads on each
       if ((int64_t)dm.H_q * splits < 1024 && ts >= 2048) hipLaunchKernelGGL(absorbed::softmax_stats_kernel<1024>, dim3(dm.H_q, splits), dim3(1024), 0, st, a, mt);
       else hipLaunchKernelGGL(absorbed::softmax_stats_kernel<256>, dim3(dm.H_q, splits), dim3(256), 0, st, a, mt);
       LAUNCH_CHECK();
-      hipLaunchKernelGGL(absorbed::pv_kernel<false>, pg, pb, 0, st, a, mt);
+      hipLaunchKernelGGL((nhb == 1 ? absorbed::pv_kernel<false, true> : absorbed::pv_kernel<false, false>), pg, pb, 0, st, a, mt);
     }
     LAUNCH_CHECK();
     if (max_splits == 1) {
