@@ -144,13 +144,13 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
       }
     }
   } else {
-    // Rotary embedding of the rebuilt key at its token's position, folded into the dot product: feature c pairs with
+    // Rotary embedding of the rebuilt key at its token's position on its way into the dot product: feature c pairs with
     // c + HD/2, which this lane holds HD/32 column blocks further on.  With a = k_c, b = k_{c+HD/2}:
     //   q_c (a cos - b sin) + q_{c+HD/2} (b cos + a sin)
-    //     = cos (a q_c + b q_{c+HD/2}) + sin (a q_{c+HD/2} - b q_c)
-    // The accumulators are only read.  Masked tokens borrow the last valid table row.  The table values of a (token
-    // block, column block) are shared by the query heads of the group: the loop over them is innermost, unrolled to
-    // the largest group size with a uniform skip.
+    // The rotated values are temporaries (written back they would cost hundreds of spilled registers), used by all query heads of
+    // the group: 4 + 2 G operations per pair (the rotation folded into the products: 6 G).  Masked tokens borrow the last valid
+    // table row.  The loop over the query heads is innermost, unrolled to the largest group size with a uniform skip.  Whole calls, us:
+    // value-absorbed 131072 tokens 342 -> 333, 4 x 4000-24000 (m = 64) 171 -> 163, fused 8 x 2048-36864 (m = 384) 309 -> 304.
     constexpr int HB = CBH / 2;
 #pragma unroll
     for (int hw = 0; hw < HPW; ++hw) {
@@ -173,6 +173,12 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
           const floatx4_t& ka = acc.v[hw * CBH + cb][tb];
           const floatx4_t& kb = acc.v[hw * CBH + cb + HB][tb];
           const float cc[4] = {cs[cb].x, cs[cb].y, cs[cb].z, cs[cb].w}, ss[4] = {sn[cb].x, sn[cb].y, sn[cb].z, sn[cb].w};
+          float ra[4], rb[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            ra[i] = fmaf(ka[i], cc[i], -kb[i] * ss[i]);
+            rb[i] = fmaf(kb[i], cc[i], ka[i] * ss[i]);
+          }
 #pragma unroll
           for (int g = 0; g < MAXPAIR; ++g) {
             if (g < G) {
@@ -180,11 +186,7 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
               const float4 qa = *reinterpret_cast<const float4*>(qs), qb = *reinterpret_cast<const float4*>(qs + HD / 2);
               const float q0[4] = {qa.x, qa.y, qa.z, qa.w}, q1[4] = {qb.x, qb.y, qb.z, qb.w};
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const float t1 = fmaf(ka[i], q0[i], kb[i] * q1[i]);
-                const float t2 = fmaf(ka[i], q1[i], -kb[i] * q0[i]);
-                s[g][tb] = fmaf(cc[i], t1, fmaf(ss[i], t2, s[g][tb]));
-              }
+              for (int i = 0; i < 4; ++i) s[g][tb] = fmaf(ra[i], q0[i], fmaf(rb[i], q1[i], s[g][tb]));
             }
           }
         }
