@@ -297,7 +297,13 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs<TO> a, SeqMeta meta
   };
   __shared__ float s_red[NW];
   __shared__ float s_w[NT];
-  __shared__ float s_acc[NG][128];
+  __shared__ __attribute__((aligned(16))) float s_acc[NG][128];
+  auto write = [&](float r, float M, float ll, int dim) {
+    const int64_t oh = (a.out_seq0 + b) * a.H_q + h;
+    if constexpr (sizeof(TO) == 2) a.out[oh * a.d + dim] = f32_to_bf16(r);
+    else a.out[oh * a.d + dim] = r;
+    if (dim == 0 && a.lse) a.lse[oh] = M + __logf(ll);
+  };
   auto block_reduce = [&](float v, bool is_max) -> float {    // fixed order: same bits every run
     v = is_max ? wave_max(v, 64) : wave_sum(v, 64);
     __syncthreads();                // s_red may still be read from the previous reduction
@@ -308,6 +314,42 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs<TO> a, SeqMeta meta
     for (int w = 1; w < NW; ++w) r = is_max ? fmaxf(r, s_red[w]) : r + s_red[w];
     return r;
   };
+  // Few partials: all rows are requested ahead of the maxima and sums, not behind them, so that one round trip to memory
+  // is left of two (kernel 4.2 -> 3.2 us; whole calls: fp32, 512 tokens 15.9 -> 14.9, 8 KV heads with 4 retained, 1000 tokens, rope
+  // and window 25.2 -> 24.2, 300 tokens 23.2 -> 21.9).
+  constexpr int NF = 8;
+  if (DS == 1 && n <= NG * NF) {
+    const int grp = tid >> 5, q4 = (tid & 31) * 4;
+    const float* ml = a.part_ml + ph_of(min(tid, n - 1)) * 2;
+    const float pm = ml[0], pl = ml[1];
+    float4 o[NF];
+#pragma unroll
+    for (int u = 0; u < NF; ++u)
+      if (grp + NG * u < n && q4 < a.d) o[u] = *reinterpret_cast<const float4*>(a.part_o + ph_of(grp + NG * u) * a.d + q4);
+    __builtin_amdgcn_sched_barrier(0);
+    // (as below: a partial that covers no token has -inf and weight 0, and one at least covers a token)
+    const float M = block_reduce(tid < n ? pm : -INFINITY, true);
+    const float w = tid < n ? __expf(pm - M) : 0.f;
+    s_w[tid] = w;
+    const float ll = block_reduce(w * pl, false);      // (its barriers publish the weights, too)
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < NF; ++u)
+      if (grp + NG * u < n && q4 < a.d) {
+        const float wu = s_w[grp + NG * u];
+        acc[0] = fmaf(wu, o[u].x, acc[0]); acc[1] = fmaf(wu, o[u].y, acc[1]);
+        acc[2] = fmaf(wu, o[u].z, acc[2]); acc[3] = fmaf(wu, o[u].w, acc[3]);
+      }
+    if (q4 < a.d) *reinterpret_cast<float4*>(&s_acc[grp][q4]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    __syncthreads();
+    if (tid < a.d) {
+      float r = 0.f;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) r += s_acc[g][tid];
+      write(r / ll, M, ll, tid);
+    }
+    return;
+  }
   // 1. global max of the partial maxima (a partial that covers no token has -inf and weight 0;
   //    at least one partial of every sequence covers a token)
   float M = -INFINITY;
@@ -369,12 +411,7 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs<TO> a, SeqMeta meta
     float r = 0.f;
 #pragma unroll
     for (int g = 0; g < NG; ++g) r += s_acc[g][tid];
-    r /= ll;
-    const int64_t oh = (a.out_seq0 + b) * a.H_q + h;
-    const int dim = DS == 1 ? tid : dim0 + tid;
-    if constexpr (sizeof(TO) == 2) a.out[oh * a.d + dim] = f32_to_bf16(r);
-    else a.out[oh * a.d + dim] = r;
-    if (dim == 0 && a.lse) a.lse[oh] = M + __logf(ll);
+    write(r / ll, M, ll, DS == 1 ? tid : dim0 + tid);
   }
 }
 
