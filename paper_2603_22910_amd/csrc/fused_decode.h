@@ -116,9 +116,10 @@ __device__ __forceinline__ float add_rows(float v) {
 // After the K pass: acc[cb][tb] holds K_hat^T.  A lane owns dims 16 cb + 4 (lane / 16) + r of the wave's 128 columns for
 // the tokens 16 tb + lane % 16.  `tail(s, hw, g)` receives the scores (Eq. 7) of head hw of the wave's tile and
 // query head g of its group: s[tb], the same in all four lanes of a token.
-// qw: the queries of the wave's first head; jw0: its first token.
-template <int HD, bool ROPE, class Tail>
-__device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int lane, int jw0, int L, const KExtra& x, Tail tail) {
+// qw: the queries of the wave's first head; table(tb, cb, cs, sn): rotary table entries of the lane's token of block
+// tb, dims 16 cb + 4 (lane / 16) ... .
+template <int HD, bool ROPE, class Table, class Tail>
+__device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int lane, Table table, Tail tail) {
   constexpr int HPW = WN / HD, CBH = HD / 16;
   const int c = lane & 15, o = lane >> 4;
   if constexpr (!ROPE) {
@@ -150,7 +151,8 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
     // The rotated values are temporaries (written back they would cost hundreds of spilled registers), used by all query heads of
     // the group: 4 + 2 G operations per pair (the rotation folded into the products: 6 G).  Masked tokens borrow the last valid
     // table row.  The loop over the query heads is innermost, unrolled to the largest group size with a uniform skip.  Whole calls, us:
-    // value-absorbed 131072 tokens 342 -> 333, 4 x 4000-24000 (m = 64) 171 -> 163, fused 8 x 2048-36864 (m = 384) 309 -> 304.
+    // value-absorbed 131072 tokens 342 -> 333, 4 x 4000-24000 (m = 64) 171 -> 163, fused 8 x 2048-36864 (m = 384) 309 -> 304.  The queries of
+    // a column block are read once for the four token blocks: 343 -> 336 and (60000 tokens, twice the predicted dims) 219 -> 208.
     constexpr int HB = CBH / 2;
 #pragma unroll
     for (int hw = 0; hw < HPW; ++hw) {
@@ -160,34 +162,32 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
 #pragma unroll
         for (int tb = 0; tb < 4; ++tb) s[g][tb] = 0.f;
 #pragma unroll
-      for (int tb = 0; tb < 4; ++tb) {
-        const int64_t row = (int64_t)min(jw0 + tb * 16 + c, L - 1) * (HD / 2) + 4 * o;
-        float4 cs[HB], sn[HB];
+      for (int cb = 0; cb < HB; ++cb) {
+        float4 cs[4], sn[4];
 #pragma unroll
-        for (int cb = 0; cb < HB; ++cb) {
-          cs[cb] = *reinterpret_cast<const float4*>(x.cos + row + cb * 16);
-          sn[cb] = *reinterpret_cast<const float4*>(x.sin + row + cb * 16);
-        }
+        for (int tb = 0; tb < 4; ++tb) table(tb, cb, cs[tb], sn[tb]);
+        float ra[4][4], rb[4][4];
 #pragma unroll
-        for (int cb = 0; cb < HB; ++cb) {
+        for (int tb = 0; tb < 4; ++tb) {
           const floatx4_t& ka = acc.v[hw * CBH + cb][tb];
           const floatx4_t& kb = acc.v[hw * CBH + cb + HB][tb];
-          const float cc[4] = {cs[cb].x, cs[cb].y, cs[cb].z, cs[cb].w}, ss[4] = {sn[cb].x, sn[cb].y, sn[cb].z, sn[cb].w};
-          float ra[4], rb[4];
+          const float cc[4] = {cs[tb].x, cs[tb].y, cs[tb].z, cs[tb].w}, ss[4] = {sn[tb].x, sn[tb].y, sn[tb].z, sn[tb].w};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            ra[i] = fmaf(ka[i], cc[i], -kb[i] * ss[i]);
-            rb[i] = fmaf(kb[i], cc[i], ka[i] * ss[i]);
+            ra[tb][i] = fmaf(ka[i], cc[i], -kb[i] * ss[i]);
+            rb[tb][i] = fmaf(kb[i], cc[i], ka[i] * ss[i]);
           }
+        }
 #pragma unroll
-          for (int g = 0; g < MAXPAIR; ++g) {
-            if (g < G) {
-              const float* qs = qw + (hw * G + g) * HD + cb * 16 + 4 * o;
-              const float4 qa = *reinterpret_cast<const float4*>(qs), qb = *reinterpret_cast<const float4*>(qs + HD / 2);
-              const float q0[4] = {qa.x, qa.y, qa.z, qa.w}, q1[4] = {qb.x, qb.y, qb.z, qb.w};
+        for (int g = 0; g < MAXPAIR; ++g) {
+          if (g < G) {
+            const float* qs = qw + (hw * G + g) * HD + cb * 16 + 4 * o;
+            const float4 qa = *reinterpret_cast<const float4*>(qs), qb = *reinterpret_cast<const float4*>(qs + HD / 2);
+            const float q0[4] = {qa.x, qa.y, qa.z, qa.w}, q1[4] = {qb.x, qb.y, qb.z, qb.w};
 #pragma unroll
-              for (int i = 0; i < 4; ++i) s[g][tb] = fmaf(ra[i], q0[i], fmaf(rb[i], q1[i], s[g][tb]));
-            }
+            for (int tb = 0; tb < 4; ++tb)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) s[g][tb] = fmaf(ra[tb][i], q0[i], fmaf(rb[tb][i], q1[i], s[g][tb]));
           }
         }
         asm volatile("" ::: "memory");       // keep the table loads of later rounds from piling up
@@ -202,6 +202,38 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
         }
     }
   }
+}
+
+// Table entries of a lane from memory: token block tb, dims 16 cb + 4 (lane / 16) ...; jw0: the wave's first token.
+template <int HD>
+__device__ __forceinline__ void table_from_memory(const KExtra& x, int jw0, int L, int lane, int tb, int cb, float4& cs, float4& sn) {
+  const int64_t at = (int64_t)min(jw0 + tb * 16 + (lane & 15), L - 1) * (HD / 2) + 4 * (lane >> 4) + cb * 16;
+  cs = *reinterpret_cast<const float4*>(x.cos + at);
+  sn = *reinterpret_cast<const float4*>(x.sin + at);
+}
+// ... and through LDS, where there is room for the tables of the tile's 256 tokens (the score kernel's stages, once its only pass is
+// done): loaded from memory a lane's 16 bytes lie in another row than its neighbour's but three, and the address unit takes
+// a row per clock.  Whole calls, value-absorbed, four query heads per KV head, from memory / so, us: 131072 tokens 347 / 343, 60000 with
+// twice the predicted dims 223 / 219.  Per 64 tokens cos rows, then sin rows, of HD / 8 16-byte chunks; chunk ch of row r
+// sits at ch ^ (r % (HD / 8)): no bank conflicts.  The two waves of a token group copy one table each.
+template <int HD>
+__device__ __forceinline__ void tables_to_lds(char* smem, const KExtra& x, int jw0, int L, int wt, int wc, int lane) {
+  constexpr int CH = HD / 8, RPC = 64 / CH;               // chunks of a row, rows of a copy
+  const int jb = min(jw0, L - 1), last = L - 1 - jb;
+  const rsrc_t src = make_rsrc((wc ? x.sin : x.cos) + (int64_t)jb * (HD / 2));
+#pragma unroll
+  for (int i = 0; i < WM / RPC; ++i) {
+    const int r = i * RPC + lane / CH;
+    copy_to_lds(src, smem + (2 * wt + wc) * (WM * CH * 16) + i * 1024, (uint32_t)(min(r, last) * (HD * 2) + ((lane % CH) ^ (r % CH)) * 16), 0);
+  }
+}
+template <int HD>
+__device__ __forceinline__ void table_from_lds(const char* smem, int wt, int lane, int tb, int cb, float4& cs, float4& sn) {
+  constexpr int CH = HD / 8;
+  const int r = tb * 16 + (lane & 15);
+  const char* at = smem + 2 * wt * (WM * CH * 16) + r * (CH * 16) + ((((cb << 2) | (lane >> 4)) ^ (r % CH)) << 4);
+  cs = *reinterpret_cast<const float4*>(at);
+  sn = *reinterpret_cast<const float4*>(at + WM * CH * 16);
 }
 
 // Softmax numerators of one (head, query head) pair over the wave's 64 tokens -> pp, (max, sum) -> ml.
@@ -301,7 +333,10 @@ __global__ __launch_bounds__(NTHREADS) void fused_decode_kernel(Args a, Streams<
   pipe.template pass<true>(acc, 0);
   const KExtra x = make_kextra(a.rope_cos, a.rope_sin, a.n_sink, a.n_recent, t.L);
   if (pipe.active)
-    k_scores<HD, ROPE>(acc, &sm.e.q[t.wc * HPW * a.G * HD], a.G, t.lane, jw0, t.L, x,
+    k_scores<HD, ROPE>(acc, &sm.e.q[t.wc * HPW * a.G * HD], a.G, t.lane,
+                       [&](int tb, int cb, float4& cs, float4& sn) __attribute__((always_inline)) {
+                         table_from_memory<HD>(x, jw0, t.L, t.lane, tb, cb, cs, sn);
+                       },
                        [&](float (&s)[4], int hw, int g) __attribute__((always_inline)) {
                          score_tail(s, sm.e.p[t.wave][hw * a.G + g], sm.e.ml[t.wave][hw * a.G + g], t.lane, jw0, x);
                        });
@@ -380,15 +415,23 @@ __global__ __launch_bounds__(NTHREADS) void fused_kscores_kernel(Args a, Streams
   pipe.first_landed();
   Acc acc;
   pipe.template pass<true>(acc, 0);
-  wait_copies<0>();                        // the copies past the end land before the workgroup's LDS is released
   const int jw0 = t.j0 + t.wt * WM;
+  const KExtra x = make_kextra(a.rope_cos, a.rope_sin, 0, 0, t.L);
+  if constexpr (ROPE) {
+    pipe.drain();                          // the stages are free
+    tables_to_lds<HD>(sm.st, x, jw0, t.L, t.wt, t.wc, t.lane);
+    pipe.drain();
+  } else {
+    wait_copies<0>();                      // the copies past the end land before the workgroup's LDS is released
+  }
   if (jw0 >= t.L || !pipe.active) return;
   constexpr int HPW = WN / HD;
   const int kvh0 = a.n_ret_heads + (t.n0 + t.wc * WN) / HD;       // first KV head of this wave's columns
   const int H_kv = a.H_q / a.G;
   float* srow = a.s_out + (int64_t)meta.sbase[t.b] * kSlotTokens + jw0 + t.lane;
-  const KExtra x = make_kextra(a.rope_cos, a.rope_sin, 0, 0, t.L);
-  k_scores<HD, ROPE>(acc, &sm.e.q[t.wc * HPW * a.G * HD], a.G, t.lane, jw0, t.L, x, [&](float (&s)[4], int hw, int g) __attribute__((always_inline)) {
+  k_scores<HD, ROPE>(acc, &sm.e.q[t.wc * HPW * a.G * HD], a.G, t.lane, [&](int tb, int cb, float4& cs, float4& sn) __attribute__((always_inline)) {
+    table_from_lds<HD>(sm.st, t.wt, t.lane, tb, cb, cs, sn);
+  }, [&](float (&s)[4], int hw, int g) __attribute__((always_inline)) {
     if (HPW > 1 && kvh0 + hw >= H_kv) return;
     const int o = t.lane >> 4;             // lane <- token lane
     const float s0 = s[0], s1 = s[1], s2 = s[2], s3 = s[3];
