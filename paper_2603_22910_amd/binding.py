@@ -1,4 +1,4 @@
-"""ctypes binding over libechokv.so: argument marshalling only.
+"""Binding over libechokv.so (ctypes; the entry points of a decode loop through _hostcall.so): argument marshalling only.
 
 Function names mirror the C ABI in include/echokv.h.  Tensors are torch tensors
 used as device buffers; `stream` defaults to torch's current HIP stream.  There
@@ -13,6 +13,8 @@ from typing import List, Optional, Sequence
 import numpy as np
 
 _LIB = None
+_call = None             # _hostcall.call and the addresses it is given, set by load()
+_APPEND = _WINDOW_APPEND = _DECODE = _DECODE_EX = 0
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libechokv.so")
 
 OK, ERR_NULL, ERR_SHAPE, ERR_DTYPE, ERR_CAPACITY, ERR_WORKSPACE, ERR_UNSUPPORTED, ERR_HIP, ERR_STATIC_LIMIT = range(9)
@@ -63,7 +65,7 @@ class DecodeExtras(C.Structure):
 
 def load() -> C.CDLL:
     """Load libechokv.so (built in-tree by build.build_library)."""
-    global _LIB
+    global _LIB, _call, _APPEND, _WINDOW_APPEND, _DECODE, _DECODE_EX
     if _LIB is not None:
         return _LIB
     path = os.environ.get("ECHOKV_LIB", LIB_PATH)   # A/B builds of the same ABI
@@ -147,6 +149,11 @@ def load() -> C.CDLL:
     lib.echokv_profile_read_channel.argtypes = [C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
     lib.echokv_profile_stream_read.restype = C.c_int
     lib.echokv_profile_stream_read.argtypes = [C.c_void_p, C.c_size_t, C.c_int32, C.POINTER(C.c_double)]
+    from . import _hostcall
+    address = lambda f: C.cast(f, C.c_void_p).value
+    _APPEND, _WINDOW_APPEND = address(lib.echokv_cache_append), address(lib.echokv_window_append)
+    _DECODE, _DECODE_EX = address(lib.echokv_decode_attn), address(lib.echokv_decode_attn_ex)
+    _call = _hostcall.call
     _LIB = lib
     return lib
 
@@ -217,8 +224,8 @@ def _ptr(t) -> Optional[int]:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         # The current stream's handle without a Stream object around it (2 us less per call; an append of one token to
-        # 32 sequences, three calls that the host bounds, 28 -> 18 us with this and plain addresses for the host
-        # arrays); before the first use of the GPU by the public way, which starts it.
+        # 32 sequences, three calls that the host bounds, 28 -> 20 us with this and plain addresses for the host
+        # arrays, 16 with the calls through _hostcall); before the first use of the GPU by the public way, which starts it.
         import torch
         if torch.cuda.is_initialized():
             return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
@@ -226,6 +233,12 @@ def _stream(stream) -> Optional[int]:
     if isinstance(stream, int):
         return stream or None
     return int(stream.cuda_stream) or None
+
+
+def _shape(shape: Shape) -> Shape:
+    if not isinstance(shape, Shape):
+        raise TypeError(f"expected a Shape, got {type(shape).__name__}")
+    return shape
 
 
 def _check(rc: int, where: str):
@@ -239,10 +252,8 @@ def workspace_bytes(shape: Shape, batch: int, total_tokens: int, max_q: int = 0)
 
 def cache_append(shape: Shape, dst: LayerCache, k_new, v_new, n_new: Sequence[int], stream=None):
     n = np.ascontiguousarray(n_new, dtype=np.int32)
-    c = dst.as_c()
-    _check(load().echokv_cache_append(C.byref(shape), C.byref(c), _ptr(k_new), _ptr(v_new),
-                                      n.ctypes.data, _stream(stream)),
-           "echokv_cache_append")
+    load()
+    _check(_call(_APPEND, _shape(shape), dst.as_c(), _ptr(k_new), _ptr(v_new), n, _stream(stream)), "echokv_cache_append")
 
 
 def cache_compress(shape: Shape, full: LayerCache, dst: LayerCache, stream=None):
@@ -261,11 +272,10 @@ def reconstruct(shape: Shape, anchor: LayerCache, target: LayerCache, w_k, w_v, 
 
 def decode_attn(shape: Shape, anchor: LayerCache, target: LayerCache, w_k, w_v, q, out,
                 lse_out, workspace, stream=None):
-    a, t = anchor.as_c(), target.as_c()
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().echokv_decode_attn(C.byref(shape), C.byref(a), C.byref(t), _ptr(w_k), _ptr(w_v),
-                                     _ptr(q), _ptr(out), _ptr(lse_out), _ptr(workspace), nbytes,
-                                     _stream(stream)), "echokv_decode_attn")
+    load()
+    _check(_call(_DECODE, _shape(shape), anchor.as_c(), target.as_c(), _ptr(w_k), _ptr(w_v), _ptr(q), _ptr(out),
+                 _ptr(lse_out), _ptr(workspace), nbytes, _stream(stream)), "echokv_decode_attn")
 
 
 def decode_path(shape: Shape) -> int:
@@ -287,17 +297,15 @@ def decode_attn_static(shape: Shape, anchor: LayerCache, target: LayerCache, w_k
 def decode_attn_ex(shape: Shape, anchor: LayerCache, target: LayerCache, w_k, w_v, q, out,
                    lse_out, workspace, rope=None, window=None, stream=None):
     """rope = (cos, sin) device fp32 [positions, d/2]; window = (win_k, win_v, n_sink, n_recent)."""
-    a, t = anchor.as_c(), target.as_c()
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     ex = DecodeExtras()
     if rope is not None:
         ex.rope_cos, ex.rope_sin, ex.rope_positions = _ptr(rope[0]), _ptr(rope[1]), int(rope[0].shape[0])
     if window is not None:
         ex.win_k, ex.win_v, ex.n_sink, ex.n_recent = _ptr(window[0]), _ptr(window[1]), int(window[2]), int(window[3])
-    _check(load().echokv_decode_attn_ex(C.byref(shape), C.byref(a), C.byref(t), _ptr(w_k), _ptr(w_v),
-                                        _ptr(q), C.byref(ex), _ptr(out), _ptr(lse_out),
-                                        _ptr(workspace), nbytes, _stream(stream)),
-           "echokv_decode_attn_ex")
+    load()
+    _check(_call(_DECODE_EX, _shape(shape), anchor.as_c(), target.as_c(), _ptr(w_k), _ptr(w_v), _ptr(q), ex, _ptr(out),
+                 _ptr(lse_out), _ptr(workspace), nbytes, _stream(stream)), "echokv_decode_attn_ex")
 
 
 def mlp_workspace_bytes(shape: Shape, batch: int, total_tokens: int, hidden: int) -> int:
@@ -333,11 +341,9 @@ def window_append(shape: Shape, win_k, win_v, n_sink: int, n_recent: int, seq_le
                   v_new, n_new, stream=None):
     before = np.ascontiguousarray(seq_len_before, dtype=np.int32)
     nn = np.ascontiguousarray(n_new, dtype=np.int32)
-    _check(load().echokv_window_append(C.byref(shape), _ptr(win_k), _ptr(win_v), int(n_sink),
-                                       int(n_recent), len(nn),
-                                       before.ctypes.data, _ptr(k_new),
-                                       _ptr(v_new), nn.ctypes.data,
-                                       _stream(stream)), "echokv_window_append")
+    load()
+    _check(_call(_WINDOW_APPEND, _shape(shape), _ptr(win_k), _ptr(win_v), int(n_sink), int(n_recent), len(nn), before,
+                 _ptr(k_new), _ptr(v_new), nn, _stream(stream)), "echokv_window_append")
 
 
 def prefill_attn(shape: Shape, anchor: LayerCache, target: LayerCache, w_k, w_v, seq: int, q,

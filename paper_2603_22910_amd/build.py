@@ -7,11 +7,13 @@ import re
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libechokv.so")
+HOSTCALL_PATH = os.path.join(HERE, "_hostcall.so")      # the Python binding's way into the library
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -66,7 +68,21 @@ def build_library(verbose: bool = False, extra_flags=()) -> str:
         raise RuntimeError("scratch memory (spills or stack objects) in kernels that count their own loads: "
                            + ", ".join(f"{k} ({n})" for k, n in spilled))
     os.replace(LIB_PATH + ".tmp", LIB_PATH)
+    build_hostcall(verbose)
     return LIB_PATH
+
+
+def build_hostcall(verbose: bool = False) -> str:
+    cmd = [shutil.which("gcc") or "cc", "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+           "-o", HOSTCALL_PATH + ".tmp", os.path.join(CSRC, "hostcall.c")]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("building _hostcall.so failed")
+    os.replace(HOSTCALL_PATH + ".tmp", HOSTCALL_PATH)
+    return HOSTCALL_PATH
 
 
 def check_spills(remarks: str):
