@@ -199,12 +199,13 @@ int echokv_augment_weights(const echokv_shape *shape, const void *w_k, const voi
  * whose visible context (q_pos0 + T_q) is at most total_tokens.  max_q == 0:
  * decode only.  The prefill part holds the predicted dims of the whole visible
  * context (2 (D - m) values per token), a rotated copy of the retained keys,
- * and, for chunks under 1024 queries in front of a long context, the fp32
- * partial results of the launch split over the keys (at most 8 shares of
- * d + 2 words per query and head).  Returns 0 on a bad shape.
+ * and the fp32 partial results of a launch split over the keys (d + 2 words per
+ * query, head and share; the shares of 768 blocks of 384 (query, head) rows at
+ * most, below 1024 queries of 256 or 8 shares each).  Returns 0 on a bad shape.
  * echokv_decode_attn also accepts less, down to what the request itself needs at
- * least (its own sequence lengths, one partial per 128 tokens); it may then take
- * kernels that split the context differently, and the result differs in rounding
+ * least (its own sequence lengths, one partial per 128 tokens), and so does
+ * echokv_prefill_attn (at most 8 shares, none from 1024 queries on); they may then
+ * split the context differently, and the result differs in rounding
  * from the same call with the workspace asked for here. */
 size_t echokv_workspace_bytes(const echokv_shape *shape, int32_t batch,
                               int64_t total_tokens, int32_t max_q);

@@ -32,8 +32,8 @@ struct Args {
   void* out; float* lse;                      // [T_q, H_q, d], [T_q, H_q]
   int32_t H_q, H_kv, G, m, d_out, n_ret_heads, T_q, q_pos0, out_bf16;
   float scale;
-  // split over the keys (long-chunk kernel only; kv_splits == 1: off): workgroup z of a (head,
-  // query block) takes one share of the block's key tiles and writes its unnormalised partial
+  // split over the keys (twelve-wave kernel only; kv_splits == 1: off): workgroup z of a (KV head,
+  // block of rows) takes one share of the block's key tiles and writes its unnormalised partial
   // instead of the output; prefill_merge_kernel joins the shares.
   int32_t kv_splits, kv_refs;                 // kv_refs >= kv_splits: see prefill_kv_shares
   float ref_drop;                             // kRefDrop in units of the unscaled scores
