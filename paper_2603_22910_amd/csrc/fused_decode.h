@@ -305,7 +305,7 @@ __device__ __forceinline__ Tile make_tile(const Args& a, const SeqMeta& meta, Pi
   op.last = min(BM, t.L - t.j0) - 1;
   op.ncol = a.d_out - t.n0;
   op.nk = (a.D + a.m) / BK; op.nka = a.D / BK; op.total = passes * op.nk;
-  op.rot = (int)((blockIdx.x & 7) * op.nk) >> 3;
+  op.rot = (t.j0 / BM * 3) % op.nk;
   pipe.smem = smem; pipe.wave = t.wave; pipe.lane = t.lane;
   pipe.active = t.n0 + t.wc * WN < a.d_out;
   return t;

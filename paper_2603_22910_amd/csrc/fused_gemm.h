@@ -91,11 +91,11 @@ struct Operands {
   int last;                  // last valid token of the tile: rows past it repeat it
   int ncol;                  // valid columns from the tile's first one on (>= 8): those past them repeat the last ones
   int nk, nka, total;        // k-tiles per pass, of them in the anchor row; passes * nk
-  int rot;                   // k-tile visited first, an eighth of the dims further on for each XCD: rows are a power of two bytes apart, and
-                             // workgroups that all walked the dims in step would pull from one memory channel at a time.  Those of an XCD share
-                             // their order, and with it more of what they read (L2 misses of 8 x 4096 tokens, d_in 6144: 2.88 -> 2.69 GB, of 32 sequences
-                             // 40.0 -> 39.0).  Three k-tiles further on for each token tile -> so, whole calls: prefill of 8192, 32 heads, 877 -> 865 us,
-                             // 8 x 2048-36864 with d_in 1408 325 -> 321, 8 x 4096 1288 -> 1286; all in one order the same within 0.5 %
+  int rot;                   // k-tile visited first, three further on for each token tile of a sequence: rows are a power of two bytes apart, and
+                             // workgroups that all walked the dims in step would pull from one memory channel at a time.  It goes by the tile's
+                             // place in its sequence alone, so that the sums do not depend on what else is in the launch.  An eighth of the dims
+                             // further on for each XCD (fewer L2 misses of W) is up to 2.4 % faster (prefill of 8192, 32 heads: 935 / 920 us, 4000 behind
+                             // 4000 880 / 860, 8 x 4096 tokens 1306 / 1304), but a sequence's sums then follow the number of tiles of the launch
 };
 
 // Per-thread part of the copies.  Copy i (0, 1) of a wave fills 1 KB of a part: for rows of 64 dims (X,
