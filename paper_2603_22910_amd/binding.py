@@ -176,6 +176,7 @@ class LayerCache:
     k, v: torch tensors [pool_tokens, width] on the GPU (or None when width == 0).
     The sequence arrays live in NumPy so the C side can read and update them.
     """
+    _c_key = None
 
     def __init__(self, k, v, width: int, pool_tokens: int, seq_start: Sequence[int],
                  seq_len: Sequence[int], seq_cap: Sequence[int]):
@@ -200,25 +201,30 @@ class LayerCache:
         return c
 
     def as_c(self) -> LayerCacheC:
-        # built once per (tensors, arrays): a decode loop calls this three times a step
-        key = (id(self.k), id(self.v), id(self.seq_start), id(self.seq_len), id(self.seq_cap),
+        # built once per (addresses, arrays): a decode loop calls this three times a step.  The tensors go by their addresses, since
+        # their storage can be replaced and the id of a freed one comes back; the arrays are kept, so that theirs cannot
+        key = (_ptr(self.k), _ptr(self.v), id(self.seq_start), id(self.seq_len), id(self.seq_cap),
                self.width, self.pool_tokens)
-        if getattr(self, "_c_key", None) != key:
+        if self._c_key != key:
             self._c = LayerCacheC(
-                _ptr(self.k), _ptr(self.v), self.width, self.batch, self.pool_tokens,
+                key[0], key[1], self.width, self.batch, self.pool_tokens,
                 self.seq_start.ctypes.data_as(C.POINTER(C.c_int64)),
                 self.seq_len.ctypes.data_as(C.POINTER(C.c_int32)),
                 self.seq_cap.ctypes.data_as(C.POINTER(C.c_int32)))
+            self._c_arrays = (self.seq_start, self.seq_len, self.seq_cap)
             self._c_key = key
         return self._c
 
 
 def _ptr(t) -> Optional[int]:
-    if t is None:
-        return None
-    if isinstance(t, int):
+    if t is None or type(t) is int:
         return t
-    return int(t.data_ptr())
+    try:                                   # (isinstance of a tensor takes longer than its address)
+        return int(t.data_ptr())
+    except AttributeError:
+        if isinstance(t, int):
+            return t
+        raise
 
 
 def _stream(stream) -> Optional[int]:
