@@ -1,4 +1,5 @@
-"""Binding over libechokv.so (ctypes; the entry points of a decode loop through _hostcall.so): argument marshalling only.
+"""Binding over libechokv.so: argument marshalling only.  By ctypes; the entry points of a decode loop through the C module _hostcall
+where it is built for the running Python.
 
 Function names mirror the C ABI in include/echokv.h.  Tensors are torch tensors
 used as device buffers; `stream` defaults to torch's current HIP stream.  There
@@ -7,13 +8,14 @@ is no fallback: if the library is missing or a call fails, an exception is raise
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import List, Optional, Sequence
 
 import numpy as np
 
 _LIB = None
-_call = None             # _hostcall.call and the addresses it is given, set by load()
+_call = None             # _hostcall.call or call_by_ctypes, and the addresses it is given, set by load()
 _APPEND = _WINDOW_APPEND = _DECODE = _DECODE_EX = 0
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libechokv.so")
 
@@ -61,6 +63,29 @@ class DecodeExtras(C.Structure):
     _fields_ = [("rope_cos", C.c_void_p), ("rope_sin", C.c_void_p), ("rope_positions", C.c_int32),
                 ("n_sink", C.c_int32), ("n_recent", C.c_int32), ("win_k", C.c_void_p),
                 ("win_v", C.c_void_p)]
+
+
+def call_by_ctypes(address: int, *args) -> int:
+    """_hostcall.call: integers, None (a null pointer), ctypes structures and contiguous NumPy arrays (their addresses)."""
+    if not 1 <= len(args) <= 14:
+        raise TypeError("call(address, *args) with 1 to 14 arguments")
+    if not address:
+        raise ValueError("null entry point")
+    values = []
+    for a in args:
+        if isinstance(a, np.ndarray):
+            if not a.flags.c_contiguous:
+                raise ValueError("ndarray is not C-contiguous")
+            a = a.ctypes.data
+        elif a is not None and not isinstance(a, int):
+            a = C.addressof(a)
+        values.append(a or 0)
+    return _entry_point(address, len(values))(*values)
+
+
+@functools.lru_cache(maxsize=16)
+def _entry_point(address: int, n: int):
+    return C.CFUNCTYPE(C.c_int, *[C.c_int64] * n)(address)
 
 
 def load() -> C.CDLL:
@@ -149,11 +174,14 @@ def load() -> C.CDLL:
     lib.echokv_profile_read_channel.argtypes = [C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
     lib.echokv_profile_stream_read.restype = C.c_int
     lib.echokv_profile_stream_read.argtypes = [C.c_void_p, C.c_size_t, C.c_int32, C.POINTER(C.c_double)]
-    from . import _hostcall
+    try:
+        from ._hostcall import call
+    except ImportError:                    # not built for this Python: the same calls, 3.5 us slower each
+        call = call_by_ctypes
     address = lambda f: C.cast(f, C.c_void_p).value
     _APPEND, _WINDOW_APPEND = address(lib.echokv_cache_append), address(lib.echokv_window_append)
     _DECODE, _DECODE_EX = address(lib.echokv_decode_attn), address(lib.echokv_decode_attn_ex)
-    _call = _hostcall.call
+    _call = call
     _LIB = lib
     return lib
 

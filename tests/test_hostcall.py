@@ -1,16 +1,51 @@
 """The binding's call helper: what it passes for each kind of argument, and what it refuses."""
 import ctypes as C
+import os
+import subprocess
+import sys
+import sysconfig
 
 import numpy as np
 import pytest
 
 from paper_2603_22910_amd import binding as ek
+from paper_2603_22910_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def call():
-    ek.load()
-    return ek._call
+@pytest.fixture(scope="module", params=["_hostcall", "ctypes"])
+def call(request):
+    if not os.path.exists(ek.LIB_PATH):
+        build.build_library()
+    if request.param == "ctypes":
+        return ek.call_by_ctypes
+    if not os.path.exists(build.HOSTCALL_PATH) and build.build_hostcall() is None:
+        pytest.skip("no C compiler or no Python.h")
+    from paper_2603_22910_amd import _hostcall
+    return _hostcall.call
+
+
+def test_library_loads_without_the_helper():
+    """Every entry point is there where the helper is not: the rest of the binding never needs it, a decode loop's calls go by ctypes."""
+    code = ("import sys; sys.modules['paper_2603_22910_amd._hostcall'] = None\n"
+            "from paper_2603_22910_amd import binding as ek\n"
+            "print(ek.status_string(0))\n"
+            "c = ek.LayerCache(1 << 20, 1 << 20, 512, 64, [0], [60], [64])\n"
+            "try: ek.cache_append(ek.make_shape(8, 8, 64, 256, 'f32'), c, 1 << 20, 1 << 20, [5], stream=0)\n"
+            "except ek.EchoKVError as e: print(e.code == ek.ERR_CAPACITY, ek._call is ek.call_by_ctypes)\n")
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert out.returncode == 0, out.stderr
+    assert out.stdout.split() == ["ok", "True", "True"]
+
+
+def test_helper_is_built_for_one_python_and_not_a_need_of_the_build(monkeypatch, tmp_path, capsys):
+    assert build.HOSTCALL_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    monkeypatch.setattr(build, "HOSTCALL_PATH", str(tmp_path / "_hostcall.so"))
+    for compiler in ("/bin/false", "/no/such/compiler"):
+        monkeypatch.setattr(build.shutil, "which", lambda _: compiler)
+        assert build.build_hostcall() is None
+        assert "not built" in capsys.readouterr().err
 
 
 @pytest.mark.parametrize("n", range(1, 15))
