@@ -41,8 +41,10 @@ def test_rows_and_shares(H_q, H_kv, d, m, plen, pq):
 
 @pytest.mark.parametrize("plen,pq", [(6200, 16), (1500, 1030)])
 def test_least_workspace(plen, pq):
-    """The least workspace that is accepted has no room for more shares than the former rule took: fewer are taken."""
+    """The number of shares follows from the workspace's size: nothing is written past its end, from the least one that is accepted to
+    one just short of what the launch would use, and with all of it that tail is written."""
     inp, dw = run(8, 2, 64, 64, plen, pq)
+    o_ref = ref.prefill_ref(inp)[0]
     full, need, lo = dw.workspace, dw.workspace.numel(), 0
     while need - lo > 256:
         mid = (need + lo) // 512 * 256
@@ -53,7 +55,17 @@ def test_least_workspace(plen, pq):
         except ek.EchoKVError:
             lo = mid
     assert need < full.numel()
-    dw.workspace = full[:need]
-    out, _ = dw.prefill()
-    torch.cuda.synchronize()
-    check(host(out), ref.prefill_ref(inp)[0], "bf16", f"least workspace {need} of {full.numel()}")
+
+    def tail_written(size, begin):
+        full[begin:] = 0xA5
+        dw.workspace = full[:size]
+        dw.out_prefill.fill_(float("nan"))
+        out, _ = dw.prefill()
+        torch.cuda.synchronize()
+        check(host(out), o_ref, "bf16", f"workspace {size} of {full.numel()}")
+        return not bool((full[begin:] == 0xA5).all())
+
+    assert tail_written(full.numel(), need)
+    for eighth in range(8):
+        size = need + (full.numel() - need) * eighth // 2048 * 256
+        assert not tail_written(size, size), size
