@@ -513,9 +513,17 @@ __device__ __forceinline__ void pv_mma(floatx16_t (&acc)[8], const PvStage& st, 
 // kPvStatsTokens scores from L2 cost each workgroup less than a launch in front of them all (2 x 1500 tokens 38.9 -> 38.0 us);
 // with 384 tokens they cost more (2 x 8192: 53.7 -> 56.7).
 constexpr int kPvStatsTokens = 128;
-template <bool STATS, bool NT>
-__global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta meta) {
-  __shared__ float red[STATS ? 4 : 2][128][64];       // 64 KB: two waves' accumulators; STATS: all four
+// QUARTERS: with STATS, the epilogue over all four waves' sums.  Its 128 KB of LDS leave a compute unit to one workgroup, so it is taken
+// as long as they are no more than the units; beyond, two workgroups of 64 KB stand beside each other and the statistics, loads and
+// sums of one beside the products of the other.  Tree / quarters, whole calls in us and workgroups, d_in 1536: 2 x 1500 tokens (144)
+// 34.2 / 34.0, 16 x 100 (96) 37.2 / 35.9, 20 x 128 (120) 38.8 / 37.4, 32 x 100 (192) 43.2 / 41.8, 43 x 100 (258) 49.8 / 54.1,
+// 64 x 100 (384) 60.2 / 64.0; d_in 6144: 10 x 128 (240) 62.6 / 60.3, 16 x 100 (384) 69.7 / 73.3, 64 x 100 (1536) 148 / 160, 128 x 128
+// (3072) 256 / 282
+constexpr int kPvQuartersWgs = 256;
+template <bool STATS, bool NT, bool QUARTERS>
+__global__ __launch_bounds__(kPvWaves * 64, QUARTERS ? 1 : 2) void pv_kernel(Args a, SeqMeta meta) {
+  static_assert(!QUARTERS || STATS, "the quarters' epilogue reads the statistics from LDS");
+  __shared__ float red[QUARTERS ? 4 : 2][128][64];       // two waves' accumulators; QUARTERS: all four
   __shared__ float s_ml[STATS ? kHB : 1][2];
   const int ct = blockIdx.x % a.n_col_tiles, sp = blockIdx.x / a.n_col_tiles, hb = blockIdx.y;
   const int b = find_seq(meta.tbase, meta.n, sp);
@@ -594,18 +602,17 @@ __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta me
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  if constexpr (STATS) {
-    // few rows: the waves leave everything in LDS and each adds up and writes a quarter of the heads, in the order of the tree
-    // below: one barrier instead of three with waves at rest (whole calls, 2 x 1500 tokens 34.1 -> 33.4 us, 16 x 100 37.2 -> 35.3).  Taken
-    // back: the rows requested ahead of the statistics (no change)
+  if constexpr (QUARTERS) {
+    // the waves leave everything in LDS and each adds up and writes a quarter of the heads, in the order of the tree below: one barrier
+    // instead of three with waves at rest.  Taken back: the rows requested ahead of the statistics (no change)
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) red[wave][i * 16 + r][lane] = acc[i][r];
     __syncthreads();
     if (a.single_split && ct == 0 && wave == 0 && lh == 0 && head < a.H_q) {     // the split is the sequence: its (max, sum) is final
-      a.y_ml[((int64_t)b * a.H_q + head) * 2] = s_ml[STATS ? lr : 0][0];
-      a.y_ml[((int64_t)b * a.H_q + head) * 2 + 1] = s_ml[STATS ? lr : 0][1];
+      a.y_ml[((int64_t)b * a.H_q + head) * 2] = s_ml[lr][0];
+      a.y_ml[((int64_t)b * a.H_q + head) * 2 + 1] = s_ml[lr][1];
     }
     if (!col_ok) return;
 #pragma unroll
@@ -614,11 +621,11 @@ __global__ __launch_bounds__(kPvWaves * 64, 2) void pv_kernel(Args a, SeqMeta me
       float v[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        v[i] = (red[0][i * 16 + r][lane] + red[STATS ? 2 : 0][i * 16 + r][lane]) + (red[STATS ? 1 : 0][i * 16 + r][lane] + red[STATS ? 3 : 0][i * 16 + r][lane]);
+        v[i] = (red[0][i * 16 + r][lane] + red[2][i * 16 + r][lane]) + (red[1][i * 16 + r][lane] + red[3][i * 16 + r][lane]);
       float* dst = a.ypart + ((int64_t)sp * a.H_pad + ha) * a.d_in + (anchor ? 0 : a.D) + col;
       if (a.single_split) {       // normalised, straight into y (what y_sum would make of one split)
         if (ha >= a.H_q) continue;
-        const float l = s_ml[STATS ? hr : 0][1];
+        const float l = s_ml[hr][1];
         const float inv = l > 0.f ? 1.f / l : 0.f;        // l == 0: every counted token sits in the window
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] *= inv;

@@ -1077,13 +1077,14 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
     a.single_split = max_splits == 1 ? 1 : 0;
     const dim3 pg(splits * pl.n_col_tiles, nhb), pb(absorbed::kPvWaves * 64);
     if (ts <= absorbed::kPvStatsTokens) {
-      hipLaunchKernelGGL((absorbed::pv_kernel<true, false>), pg, pb, 0, st, a, mt);
+      const bool quarters = (int64_t)splits * pl.n_col_tiles * nhb <= absorbed::kPvQuartersWgs;
+      hipLaunchKernelGGL((quarters ? absorbed::pv_kernel<true, false, true> : absorbed::pv_kernel<true, false, false>), pg, pb, 0, st, a, mt);
     } else {
       // few long pieces: more threads on each
       if ((int64_t)dm.H_q * splits < 1024 && ts >= 2048) hipLaunchKernelGGL(absorbed::softmax_stats_kernel<1024>, dim3(dm.H_q, splits), dim3(1024), 0, st, a, mt);
       else hipLaunchKernelGGL(absorbed::softmax_stats_kernel<256>, dim3(dm.H_q, splits), dim3(256), 0, st, a, mt);
       LAUNCH_CHECK();
-      hipLaunchKernelGGL((nhb == 1 ? absorbed::pv_kernel<false, true> : absorbed::pv_kernel<false, false>), pg, pb, 0, st, a, mt);
+      hipLaunchKernelGGL((nhb == 1 ? absorbed::pv_kernel<false, true, false> : absorbed::pv_kernel<false, false, false>), pg, pb, 0, st, a, mt);
     }
     LAUNCH_CHECK();
     if (max_splits == 1) {

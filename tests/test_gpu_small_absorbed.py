@@ -41,6 +41,19 @@ def test_short_absorbed_against_the_oracle(H_q, H_kv, d, m, lens, flags):
 
 
 @pytest.mark.parametrize("flags", MODES)
+def test_sums_of_few_and_many_value_workgroups(flags):
+    """Up to 256 workgroups of the value pass each wave adds up a quarter of the heads, past that the sums meet in a tree: the same bits.
+    Three column tiles: 255 workgroups of 85 sequences, 258 of 86."""
+    inp = synth.generate(synth.Workload("absorbed_sums", "bf16", 8, 4, 128, 128, seed=84, seq_lens=tuple(100 + i % 29 for i in range(86))))
+    dw = DeviceWorkload(inp, out_dtype="f32", flags=flags)
+    many = dw.decode()[0].clone()
+    check(host(many), ref.decode_ref(inp)[0], "bf16", "86 sequences")
+    dw.anchor, dw.target = dw.anchor_all.view(0, 85), dw.target_all.view(0, 85)
+    few = dw.decode()[0]
+    assert torch.equal(few[:85], many[:85])
+
+
+@pytest.mark.parametrize("flags", MODES)
 def test_workspace_of_splits_of_1024_tokens_is_still_accepted(flags):
     H_q, D, m, L, nseq = 16, 1024, 512, 1500, 2
     inp = synth.generate(synth.Workload("absorbed_ws", "bf16", H_q, 8, 128, m, seed=75, seq_lens=(L,) * nseq))
