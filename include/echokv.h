@@ -204,9 +204,10 @@ int echokv_augment_weights(const echokv_shape *shape, const void *w_k, const voi
  * most, below 1024 queries of 256 or 8 shares each).  Returns 0 on a bad shape.
  * echokv_decode_attn also accepts less, down to what the request itself needs at
  * least (its own sequence lengths, one partial per 128 tokens), and so does
- * echokv_prefill_attn (at most 8 shares, none from 1024 queries on); they may then
- * split the context differently, and the result differs in rounding
- * from the same call with the workspace asked for here. */
+ * echokv_prefill_attn (room for the partials of 8 shares of min(T_q, 1023)
+ * queries at most; as many shares are taken as fit); they may then split the
+ * context differently, and the result differs in rounding from the same call
+ * with the workspace asked for here. */
 size_t echokv_workspace_bytes(const echokv_shape *shape, int32_t batch,
                               int64_t total_tokens, int32_t max_q);
 
@@ -218,7 +219,9 @@ size_t echokv_workspace_bytes(const echokv_shape *shape, int32_t batch,
  *   out     : device [batch, H_q, d] in shape->out_dtype
  *   lse_out : device [batch, H_q] fp32 log-sum-exp of the scaled scores, or NULL
  * anchor and target must describe the same sequences (equal batch, seq_len).
- * Every seq_len[b] must be >= 1. */
+ * Every seq_len[b] must be >= 1.  Kernels and splits of the context are chosen
+ * by the sizes of the whole call: the result of a sequence may differ in
+ * rounding with the other sequences of the batch. */
 int echokv_decode_attn(const echokv_shape *shape, const echokv_layer_cache *anchor,
                        const echokv_layer_cache *target, const void *w_k,
                        const void *w_v, const void *q, void *out, float *lse_out,
@@ -391,7 +394,8 @@ int echokv_prefill_attn(const echokv_shape *shape, const echokv_layer_cache *anc
  * q_pos0 + T_q.  A prefill chunk reads the compressed cache only: extras with
  * window pointers are refused (ECHOKV_ERR_UNSUPPORTED).  extras == NULL or no
  * tables: the same as echokv_prefill_attn.  Same workspace size.  (bf16: the
- * rotated keys are rounded to bf16 once more before the attention products.) */
+ * attention products take the rotated keys rounded to bf16; predicted ones are
+ * rotated in fp32 ahead of that, or in a small call out of bf16.) */
 int echokv_prefill_attn_ex(const echokv_shape *shape, const echokv_layer_cache *anchor,
                            const echokv_layer_cache *target, const void *w_k,
                            const void *w_v, int32_t seq, const void *q, int32_t T_q,

@@ -180,8 +180,9 @@ __device__ __forceinline__ StageDesc stage_desc(const ScoreIo& io, int t) {
 // Cache rows that one workgroup reads and nobody after it are loaded as non-temporal: they leave the L2 to what is read again.
 // Whole calls without / with it in the value pass / in both passes, us, d_in 6144, 32 heads: 4 x 3500 tokens 126 / 126 / 118, 4 x 8000 196 /
 // 194 / 180, 16 x 8000 623 / 612 / 581; d_in 5120, 4 x 32768 538 / 520 / 502; d_in 1536: 4 x 8000 75.8 / 71.7 / 70.9, 4 x 14000 102 / 101 / 96, 4 x
-// 50000 273 / 270 / 274, 4 x 4000 58 / 53 / 58.  So in the value pass, and in the score pass, which reads a row in pieces of 256
-// bytes, for anchor rows of 4 KB and more.  With more than 32 query heads the rows are read once per 32: without; and without in
+// 50000 273 / 270 / 274, 4 x 4000 58 / 53 / 58; d_in 3072 of 16 KV heads: 4 x 3500 75.1 / 72.4 / 71.5, 4 x 8000 106 / 106 / 101, d_in 2048 of
+// them: 63.8 / 58.4 / 59.5 and 86.5 / 84.1 / 79.5; d_in 2304 of 12: 68.6 / 60.2 / 64.5 and 92.6 / 91.5 / 87.0.  So in the value pass, and in
+// the score pass, which reads a row in pieces of 256 bytes, for anchor rows of 4 KB (16 KV heads of 128) and more.  With more than 32 query heads the rows are read once per 32: without; and without in
 // splits of up to 128 tokens (2 x 1500 34.6 / 35.2, 1 x 300 of d_in 6144 49.3 / 50.2).
 constexpr int kNonTemporal = 2;              // cache policy operand of the buffer loads: nt
 // this wave's 10 direct-to-LDS loads of stage t: X rows 32 w .. 32 w + 31, U rows 8 w .. 8 w + 7

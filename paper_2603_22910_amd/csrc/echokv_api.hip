@@ -1115,10 +1115,9 @@ size_t decode_ws_bytes(const Dims& dm, int batch, int64_t total_tokens, bool unf
 size_t prefill_ws_bytes(const Dims& dm, int64_t Ltot, int max_q) {
   const bool mfma = dm.bf16 && prefill_mfma_supported<bf16_t>(dm.d);
   if (!mfma) return prefill_krot_offset(dm, Ltot, max_q);
-  // the partials of the largest split launch any chunk of up to max_q queries can take: the
-  // number of shares only changes where the number of query blocks does
+  // the partials of prefill_kv_splits shares of any chunk of up to max_q queries (their number only changes
+  // where the number of query blocks does); longer chunks than kMinQueries - 1 use the same room
   size_t split = 0;
-  // (chunks of kMinQueries queries and more are not split)
   for (int tq : {std::min(max_q, prefill::dma::kMinQueries - 1), prefill::dma::BQ, 2 * prefill::dma::BQ})
     if (tq <= max_q) split = std::max(split, prefill_split_floats(tq, Ltot, dm.H_q, dm.d) * 4);
   return prefill_split_offset(dm, Ltot, max_q) + align_up(split);

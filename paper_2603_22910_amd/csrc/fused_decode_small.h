@@ -273,13 +273,14 @@ __device__ __forceinline__ float add_halves(float x) {
 }
 
 // Shares of the scaled scores (Eq. 7) of the wave's K_hat share -> sm.s[kq].  A lane holds, per token
-// block and column group, 4 * VW consecutive columns of one head.  Rotary embedding: the rotation of
+// block and column group, 4 * VW consecutive columns of one head.  Rotary embedding (fp32; bf16: rope_score_shares): the rotation of
 // the key is moved onto the query, q'_c = q_c cos + q_{c + d/2} sin (c < d/2), q_c cos - q_{c - d/2} sin.
 // The loop over the query heads stays a loop: every workgroup runs this code once, and unrolled its
 // instructions alone take longer to fetch than to execute.
 template <typename T, int HD, int TB, bool ROPE>
 __device__ __forceinline__ void score_shares(Acc<T, HD, TB>& acc, Smem<TB>& sm, int G,
                                              int kq, int lane, const f32x4_t* tables) {
+  static_assert(!ROPE || sizeof(T) == 4, "bf16 with rotary tables: rope_score_shares");
   using C = Cfg<T, HD>;
   using R = RopeTile<HD, TB>;
   constexpr int RUN = 4 * C::VW;               // columns of a lane and group

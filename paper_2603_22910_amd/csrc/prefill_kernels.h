@@ -280,7 +280,7 @@ typedef short short4_t __attribute__((ext_vector_type(4)));
 
 // the first NCOPY waves issue the copies (a tile is 16 or 32 one-KB copies per operand)
 constexpr int NST = 4, NCOPY = 8, NWAVES = 12, NTHREADS = 64 * NWAVES, BQ = 32 * NWAVES;
-constexpr int kMinQueries = 1024;      // shorter chunks: split over the keys if the context is long, else the four-wave kernel
+constexpr int kMinQueries = 1024;      // shorter chunks behind fewer than 16 key tiles: the four-wave kernel (see prefill_kv_shares)
 constexpr int kMaxSplits = 8, kMaxShares = 32, kMinShareTiles = 3;      // see prefill_kv_splits, prefill_kv_shares
 // A new reference lies at most this many base-2 units below the one before it: the sums grow by less than 2^(7 * 16), and what
 // is that far below the former keys has no weight beside them.
@@ -667,10 +667,10 @@ template <typename T> inline bool prefill_mfma_supported(int d) {
   return sizeof(T) == 2 && (d == 64 || d == 128);
 }
 
-// Key shares a chunk of T_q queries over Ltot cached tokens has room for in the least workspace of such a call (1 = no split).
-// Chunks of kMinQueries queries and more fill the chip by themselves.  A shorter chunk has few blocks of rows
-// per KV head; with a long context in front of it each (KV head, block) is cut into shares of at
-// least 8 key tiles until about three workgroups per compute unit exist.
+// Key shares that the least workspace of a call has room for, with a chunk of T_q < kMinQueries queries over Ltot cached tokens (1: it
+// runs unsplit): one head of 384 queries to a workgroup, cut into shares of at least 8 key tiles until about three workgroups per
+// compute unit exist.  From kMinQueries queries on 1: nothing is asked for, but the least workspace of such a chunk holds the partials of
+// one of kMinQueries - 1 queries, and prefill_kv_shares uses what room there is.
 inline int prefill_kv_splits(int T_q, int64_t Ltot, int H_q) {
   if (T_q >= prefill::dma::kMinQueries) return 1;
   const int wgs = (T_q + prefill::dma::BQ - 1) / prefill::dma::BQ * H_q;
@@ -684,7 +684,7 @@ inline int64_t prefill_blocks(int T_q, int H_q, int H_kv) {
   return ((int64_t)T_q * (H_q / H_kv) + prefill::dma::BQ - 1) / prefill::dma::BQ * H_kv;
 }
 // Workgroups that a split chunk may have where prefill_kv_splits makes no room for as many shares: one round, three from kMinQueries
-// queries on (which it does not split at all).
+// queries on.
 inline int prefill_share_wgs(int T_q) { return T_q < prefill::dma::kMinQueries ? 256 : 768; }
 // Key shares taken: those that cost least, of as many as the room for partials (words) allows and at least 2 where
 // prefill_kv_splits makes room for them.  A workgroup fills a compute unit; one costs its key tiles and about six more for its start and
@@ -697,8 +697,10 @@ inline int prefill_share_wgs(int T_q) { return T_q < prefill::dma::kMinQueries ?
 // tiles per share at least, 100 behind 3000 took 72 us and 200 behind 1000 72; with 3 67 and 65.
 // The probabilities are rounded to bf16 relative to the softmax reference, and the key that sets it is rounded without error: fewer
 // shares alone put the output further from its value in 64 bits (0.24 % more error in the mean of 32 such chunks, up to 0.8 %).  So
-// a share takes a new reference wherever one of prefill_kv_splits shares would begin (kv_refs): the probabilities are then the same
-// as with all the shares.
+// a share takes a new reference where it begins and wherever one of prefill_kv_splits shares would begin (kv_refs).  With more shares than
+// that, and from kMinQueries queries on, the references are the shares' own, as many as there are: how the probabilities round
+// follows the number of shares, and with it the room.  Error against 64 bits of 60 chunks of 16 - 2400 queries behind 100 - 9000 tokens, one
+// head to a block and at most 8 shares -> this: 0.04 - 0.4 % less in the mean of each kind (5 % with rotary tables and the MHA layer), 0.3 % more at most.
 inline int prefill_kv_shares(int T_q, int q_pos0, int H_q, int H_kv, int d, size_t words) {
   using namespace prefill;
   const int64_t Ltot = (int64_t)q_pos0 + T_q;

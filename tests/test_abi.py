@@ -112,7 +112,7 @@ def test_workspace_covers_a_prefill_chunk_only_when_asked():
     # a short chunk in front of a long context is split over the keys: room for 8 shares of
     # (d + 2) fp32 words per query and head on top of what one query needs
     assert short - one >= 499 * 32 * 8 * 130 * 4 * 0.9
-    # chunks of 1024 queries and more are not split, but a caller may still pass shorter ones
+    # a workspace for longer chunks serves shorter ones, too
     assert long_ - one >= 1023 * 32 * 8 * 130 * 4 * 0.9
     # a prefill call checks the size it needs for its own chunk: a decode-sized workspace is refused
     a = ek.LayerCache(FAKE, FAKE, 1024, 32768, [0], [20000], [32768])

@@ -275,7 +275,7 @@ def run_prefill_case(w, flags=0):
     return inp, dw
 
 
-# chunks of 1024 queries and more take the kernel variant with 64 queries per wave
+# chunks of 1024 queries and more, or behind 16 key tiles and more, take the twelve-wave kernel
 @pytest.mark.parametrize("plen,pq", [(400, 400), (400, 150), (130, 1), (257, 256), (64, 64),
                                      (1300, 1100), (1024, 1024), (1500, 1025)])
 def test_prefill_small(plen, pq):

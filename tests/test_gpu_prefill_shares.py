@@ -1,4 +1,4 @@
-"""Prefill chunks split over the keys: the bf16 probabilities are the same whatever the number of key shares the launch takes."""
+"""Prefill chunks split over the keys: fewer key shares than a workspace of eight has room for cost no precision."""
 import pytest
 import torch
 
@@ -13,9 +13,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("plen,pq", [(7680, 500), (7680, 390)])
 def test_probabilities_do_not_depend_on_the_shares_taken(plen, pq):
-    """Eight possible shares of 15 key tiles of 64 in both query blocks (120 and 114 tiles), four taken.  Keys of one of
-    the eight have one score, so that its probabilities are exactly 1 relative to its own reference; relative to the reference
-    of a longer share they would be rounded to bf16, 2^-9 of them.  What is left are fp32 sums of 7680 terms: 1e-5, the
+    """Eight possible shares of 15 key tiles of 64; five shares are taken of 500 queries (11 blocks of 384 rows per KV head), seven of 390
+    (9 blocks).  Keys of one of the eight have one score, so that its probabilities are exactly 1 relative to its own reference; relative
+    to the reference of a longer share they would be rounded to bf16, 2^-9 of them.  (A share that begins inside one of the eight has the
+    same reference there: how other scores would round in it is not seen.)  What is left are fp32 sums of 7680 terms: 1e-5, the
     tolerance of fp32 inputs."""
     w = synth.Workload("shares", "bf16", 32, 4, 64, 256, seed=78, seq_lens=(8,), prefill_len=plen, prefill_q=pq)
     inp = synth.generate(w)                     # m = D: nothing is predicted, the keys are the stored ones
