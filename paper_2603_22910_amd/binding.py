@@ -231,11 +231,14 @@ class LayerCache:
     def as_c(self) -> LayerCacheC:
         # built once per (addresses, arrays): a decode loop calls this three times a step.  The tensors go by their addresses, since
         # their storage can be replaced and the id of a freed one comes back; the arrays are kept, so that theirs cannot
-        key = (_ptr(self.k), _ptr(self.v), id(self.seq_start), id(self.seq_len), id(self.seq_cap),
-               self.width, self.pool_tokens)
+        try:
+            k, v = self.k.data_ptr(), self.v.data_ptr()      # (0.2 us less than through _ptr)
+        except AttributeError:
+            k, v = _ptr(self.k), _ptr(self.v)
+        key = (k, v, id(self.seq_start), id(self.seq_len), id(self.seq_cap), self.width, self.pool_tokens)
         if self._c_key != key:
             self._c = LayerCacheC(
-                key[0], key[1], self.width, self.batch, self.pool_tokens,
+                k, v, self.width, self.batch, self.pool_tokens,
                 self.seq_start.ctypes.data_as(C.POINTER(C.c_int64)),
                 self.seq_len.ctypes.data_as(C.POINTER(C.c_int32)),
                 self.seq_cap.ctypes.data_as(C.POINTER(C.c_int32)))
