@@ -204,7 +204,7 @@ class LayerCache:
     k, v: torch tensors [pool_tokens, width] on the GPU (or None when width == 0).
     The sequence arrays live in NumPy so the C side can read and update them.
     """
-    _c_key = None
+    _c_of = (None,) * 7      # what the C view was made of
 
     def __init__(self, k, v, width: int, pool_tokens: int, seq_start: Sequence[int],
                  seq_len: Sequence[int], seq_cap: Sequence[int]):
@@ -229,21 +229,21 @@ class LayerCache:
         return c
 
     def as_c(self) -> LayerCacheC:
-        # built once per (addresses, arrays): a decode loop calls this three times a step.  The tensors go by their addresses, since
-        # their storage can be replaced and the id of a freed one comes back; the arrays are kept, so that theirs cannot
+        # built once per (addresses, arrays, sizes): a decode loop calls this three times a step.  The tensors go by their addresses,
+        # since their storage can be replaced and the id of a freed one comes back
         try:
             k, v = self.k.data_ptr(), self.v.data_ptr()      # (0.2 us less than through _ptr)
         except AttributeError:
             k, v = _ptr(self.k), _ptr(self.v)
-        key = (k, v, id(self.seq_start), id(self.seq_len), id(self.seq_cap), self.width, self.pool_tokens)
-        if self._c_key != key:
+        k0, v0, start, length, cap, width, pool = self._c_of
+        if (k != k0 or v != v0 or self.seq_start is not start or self.seq_len is not length or self.seq_cap is not cap
+                or self.width != width or self.pool_tokens != pool):
             self._c = LayerCacheC(
                 k, v, self.width, self.batch, self.pool_tokens,
                 self.seq_start.ctypes.data_as(C.POINTER(C.c_int64)),
                 self.seq_len.ctypes.data_as(C.POINTER(C.c_int32)),
                 self.seq_cap.ctypes.data_as(C.POINTER(C.c_int32)))
-            self._c_arrays = (self.seq_start, self.seq_len, self.seq_cap)
-            self._c_key = key
+            self._c_of = (k, v, self.seq_start, self.seq_len, self.seq_cap, self.width, self.pool_tokens)
         return self._c
 
 
