@@ -102,4 +102,19 @@ __device__ __forceinline__ float row_sum(float v) {
   return v;
 }
 
+// Maximum / sum over all 64 lanes, in every lane, without the LDS crossbar: inside the rows of 16 lanes as above, then the rows.
+template <class F>
+__device__ __forceinline__ float wave_reduce64(float v, F f) {
+  v = f(v, dpp_move<0xB1>(v));
+  v = f(v, dpp_move<0x4E>(v));
+  v = f(v, dpp_move<0x141>(v));
+  v = f(v, dpp_move<0x140>(v));
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+__device__ __forceinline__ float wave_max64(float v) { return wave_reduce64(v, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float wave_sum64(float v) { return wave_reduce64(v, [](float a, float b) { return a + b; }); }
+
 }  // namespace echokv

@@ -30,6 +30,7 @@ namespace echokv {
 namespace fused {
 
 constexpr int MAXPAIR = 8;   // (head in wave tile, query head in group) pairs per wave
+constexpr int kVectorHeads = 2;   // up to so many query heads per KV head the epilogues use the vector unit, beyond it fma_heads
 
 struct Args {
   const bf16_t* xa[2];   // anchor cache K, V      [pool, D]
@@ -105,43 +106,73 @@ __device__ __forceinline__ KExtra make_kextra(const float* cos, const float* sin
   return x;
 }
 
-// Sum over the 16-lane rows of a wave: rows (0, 1) and (2, 3), then (0, 2) and (1, 3).
-__device__ __forceinline__ float add_rows(float v) {
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+// Sums over the four 16-lane rows of a wave (rows 0 + 1 and 2 + 3, then both) of four values: row i ends up with the sums of the
+// i-th.  Six instructions; with every row holding all four sums it would be sixteen and a selection.
+__device__ __forceinline__ float sum_rows(float a, float b, float c, float d) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(c), __float_as_uint(d), false, false);
+  const float ab = __uint_as_float(p[0]) + __uint_as_float(p[1]), cd = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(ab), __float_as_uint(cd), false, false);
   return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
+// Four query heads against a lane's own values on the matrix pipe: v_mfma_f32_4x4x1 has 16 blocks of four lanes, and with row i of
+// A = query head i, d[i] += a of the block's lane i * this lane's b, in fp32.  8 cycles for what takes the vector unit
+// 4 per head, which meanwhile rotates the keys of the SIMD's other wave.
+__device__ __forceinline__ floatx4_t fma_heads(float a, float b, floatx4_t d) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, d, 0, 0, 0); }
+
 // After the K pass: acc[cb][tb] holds K_hat^T.  A lane owns dims 16 cb + 4 (lane / 16) + r of the wave's 128 columns for
 // the tokens 16 tb + lane % 16.  `tail(s, hw, g)` receives the scores (Eq. 7) of head hw of the wave's tile and
-// query head g of its group: s[tb], the same in all four lanes of a token.
+// query head g of its group: that of the wave's token `lane`.
 // qw: the queries of the wave's first head; table(tb, cb, cs, sn): rotary table entries of the lane's token of block
 // tb, dims 16 cb + 4 (lane / 16) ... .
 template <int HD, bool ROPE, class Table, class Tail>
 __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int lane, Table table, Tail tail) {
   constexpr int HPW = WN / HD, CBH = HD / 16;
-  const int c = lane & 15, o = lane >> 4;
+  const int o = lane >> 4;
   if constexpr (!ROPE) {
+    if (G <= kVectorHeads) {
+#pragma unroll
+      for (int hw = 0; hw < HPW; ++hw) {
+#pragma nounroll
+        for (int g = 0; g < G; ++g) {
+          const float* qs = qw + (hw * G + g) * HD + 4 * o;
+          float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int cb = 0; cb < CBH; ++cb) {
+            const float4 qv = *reinterpret_cast<const float4*>(qs + cb * 16);
+#pragma unroll
+            for (int tb = 0; tb < 4; ++tb) {
+              const floatx4_t& k = acc.v[hw * CBH + cb][tb];
+              s[tb] = fmaf(qv.x, k[0], s[tb]); s[tb] = fmaf(qv.y, k[1], s[tb]);
+              s[tb] = fmaf(qv.z, k[2], s[tb]); s[tb] = fmaf(qv.w, k[3], s[tb]);
+            }
+          }
+          tail(sum_rows(s[0], s[1], s[2], s[3]), hw, g);
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int hw = 0; hw < HPW; ++hw) {
 #pragma nounroll
-      for (int g = 0; g < G; ++g) {
-        const float* qs = qw + (hw * G + g) * HD + 4 * o;
-        float s[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int g0 = 0; g0 < G; g0 += 4) {
+        const float* qs = qw + (hw * G + min(g0 + (lane & 3), G - 1)) * HD + 4 * o;      // (heads past the last repeat it)
+        floatx4_t s[4];
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb) s[tb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int cb = 0; cb < CBH; ++cb) {
-          const float4 qv = *reinterpret_cast<const float4*>(qs + cb * 16);
+          const float4 q4 = *reinterpret_cast<const float4*>(qs + cb * 16);
+          const float qv[4] = {q4.x, q4.y, q4.z, q4.w};
 #pragma unroll
-          for (int tb = 0; tb < 4; ++tb) {
-            const floatx4_t& k = acc.v[hw * CBH + cb][tb];
-            s[tb] = fmaf(qv.x, k[0], s[tb]); s[tb] = fmaf(qv.y, k[1], s[tb]);
-            s[tb] = fmaf(qv.z, k[2], s[tb]); s[tb] = fmaf(qv.w, k[3], s[tb]);
-          }
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int tb = 0; tb < 4; ++tb) s[tb] = fma_heads(qv[r], acc.v[hw * CBH + cb][tb][r], s[tb]);
         }
 #pragma unroll
-        for (int tb = 0; tb < 4; ++tb) s[tb] = add_rows(s[tb]);
-        tail(s, hw, g);
+        for (int i = 0; i < 4; ++i)
+          if (g0 + i < G) tail(sum_rows(s[0][i], s[1][i], s[2][i], s[3][i]), hw, g0 + i);
       }
     }
   } else {
@@ -149,18 +180,18 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
     // c + HD/2, which this lane holds HD/32 column blocks further on.  With a = k_c, b = k_{c+HD/2}:
     //   q_c (a cos - b sin) + q_{c+HD/2} (b cos + a sin)
     // The rotated values are temporaries (written back they would cost hundreds of spilled registers), used by all query heads of
-    // the group: 4 + 2 G operations per pair (the rotation folded into the products: 6 G).  Masked tokens borrow the last valid
-    // table row.  The loop over the query heads is innermost, unrolled to the largest group size with a uniform skip.  Whole calls, us:
-    // value-absorbed 131072 tokens 342 -> 333, 4 x 4000-24000 (m = 64) 171 -> 163, fused 8 x 2048-36864 (m = 384) 309 -> 304.  The queries of
-    // a column block are read once for the four token blocks: 343 -> 336 and (60000 tokens, twice the predicted dims) 219 -> 208.
-    constexpr int HB = CBH / 2;
+    // the group.  Masked tokens borrow the last valid table row.
+    constexpr int HB = CBH / 2, NG = MAXPAIR / (4 * HPW);      // groups of four query heads at most
 #pragma unroll
     for (int hw = 0; hw < HPW; ++hw) {
-      float s[MAXPAIR][4];
+      floatx4_t s[NG][4];
+      const float* qs[NG];
 #pragma unroll
-      for (int g = 0; g < MAXPAIR; ++g)
+      for (int n = 0; n < NG; ++n) {
+        qs[n] = qw + (hw * G + min(4 * n + (lane & 3), G - 1)) * HD + 4 * o;
 #pragma unroll
-        for (int tb = 0; tb < 4; ++tb) s[g][tb] = 0.f;
+        for (int tb = 0; tb < 4; ++tb) s[n][tb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+      }
 #pragma unroll
       for (int cb = 0; cb < HB; ++cb) {
         float4 cs[4], sn[4];
@@ -179,27 +210,27 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
           }
         }
 #pragma unroll
-        for (int g = 0; g < MAXPAIR; ++g) {
-          if (g < G) {
-            const float* qs = qw + (hw * G + g) * HD + cb * 16 + 4 * o;
-            const float4 qa = *reinterpret_cast<const float4*>(qs), qb = *reinterpret_cast<const float4*>(qs + HD / 2);
+        for (int n = 0; n < NG; ++n) {
+          if (4 * n < G) {
+            const float4 qa = *reinterpret_cast<const float4*>(qs[n] + cb * 16), qb = *reinterpret_cast<const float4*>(qs[n] + cb * 16 + HD / 2);
             const float q0[4] = {qa.x, qa.y, qa.z, qa.w}, q1[4] = {qb.x, qb.y, qb.z, qb.w};
 #pragma unroll
-            for (int tb = 0; tb < 4; ++tb)
+            for (int i = 0; i < 4; ++i) {
 #pragma unroll
-              for (int i = 0; i < 4; ++i) s[g][tb] = fmaf(ra[tb][i], q0[i], fmaf(rb[tb][i], q1[i], s[g][tb]));
+              for (int tb = 0; tb < 4; ++tb) s[n][tb] = fma_heads(q0[i], ra[tb][i], s[n][tb]);
+#pragma unroll
+              for (int tb = 0; tb < 4; ++tb) s[n][tb] = fma_heads(q1[i], rb[tb][i], s[n][tb]);
+            }
           }
         }
         asm volatile("" ::: "memory");       // keep the table loads of later rounds from piling up
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int g = 0; g < MAXPAIR; ++g)
-        if (g < G) {
+      for (int n = 0; n < NG; ++n)
 #pragma unroll
-          for (int tb = 0; tb < 4; ++tb) s[g][tb] = add_rows(s[g][tb]);
-          tail(s[g], hw, g);
-        }
+        for (int i = 0; i < 4; ++i)
+          if (4 * n + i < G) tail(sum_rows(s[n][0][i], s[n][1][i], s[n][2][i], s[n][3][i]), hw, 4 * n + i);
     }
   }
 }
@@ -236,41 +267,66 @@ __device__ __forceinline__ void table_from_lds(const char* smem, int wt, int lan
   sn = *reinterpret_cast<const float4*>(at + WM * CH * 16);
 }
 
-// Softmax numerators of one (head, query head) pair over the wave's 64 tokens -> pp, (max, sum) -> ml.
-__device__ __forceinline__ void score_tail(const float (&s)[4], float* pp, float* ml, int lane, int jw0, const KExtra& x) {
-  // lane <- token lane: the row of 16 lanes o takes block o
-  const int o = lane >> 4;
-  const float s0 = s[0], s1 = s[1], s2 = s[2], s3 = s[3];
-  float v = o == 0 ? s0 : o == 1 ? s1 : o == 2 ? s2 : s3;
+// Softmax numerators of one (head, query head) pair over the wave's 64 tokens -> pp, (max, sum) -> ml.  v: score of token `lane`.
+__device__ __forceinline__ void score_tail(float v, float* pp, float* ml, int lane, int jw0, const KExtra& x) {
   const int tok = jw0 + lane;
   if (tok < x.lo || tok >= x.hi) v = -INFINITY;
-  const float mx = wave_max(v, 64);
+  const float mx = wave_max64(v);
   const float p = v == -INFINITY ? 0.f : __expf(v - mx);
   pp[lane] = p;
-  const float sum = wave_sum(p, 64);
+  const float sum = wave_sum64(p);
   if (lane == 0) { ml[0] = mx; ml[1] = sum; }
 }
 
-// After the V pass: acc[cb][tb] holds V_hat; a lane owns tokens 16 tb + 4 (lane / 16) + r of dim 16 cb + lane % 16.  sum_j p_j v_hat_j
-// of one (head, query head) pair over the wave's tokens: dim 16 cb + lane % 16 in o[cb], the same in all four rows.
-template <int HD>
-__device__ __forceinline__ void value_sum(Acc& acc, const float* pp, int hw, int lane, float (&out)[HD / 16]) {
+// After the V pass: acc[cb][tb] holds V_hat; a lane owns tokens 16 tb + 4 (lane / 16) + r of dim 16 cb + lane % 16.  Hands out sum_j p_j
+// v_hat_j over the wave's tokens for head hw of its tile as put(g, dim, value), every (g, dim) in one lane.  pp: the
+// numerators [pair][WT] of the head's first query head.
+template <int HD, class Put>
+__device__ __forceinline__ void value_sums(const Acc& acc, const float* pp, int hw, int G, int lane, Put put) {
   constexpr int CBH = HD / 16;
-  const int o = lane >> 4;
+  const int c = lane & 15, o = lane >> 4;
+  if (G <= kVectorHeads) {
+#pragma nounroll
+    for (int g = 0; g < G; ++g) {
+      float out[CBH];
 #pragma unroll
-  for (int cb = 0; cb < CBH; ++cb) out[cb] = 0.f;
+      for (int cb = 0; cb < CBH; ++cb) out[cb] = 0.f;
 #pragma unroll
-  for (int tb = 0; tb < 4; ++tb) {
-    const float4 p = *reinterpret_cast<const float4*>(pp + tb * 16 + 4 * o);
+      for (int tb = 0; tb < 4; ++tb) {
+        const float4 p = *reinterpret_cast<const float4*>(pp + g * WM + tb * 16 + 4 * o);
+#pragma unroll
+        for (int cb = 0; cb < CBH; ++cb) {
+          const floatx4_t& v = acc.v[hw * CBH + cb][tb];
+          out[cb] = fmaf(p.x, v[0], out[cb]); out[cb] = fmaf(p.y, v[1], out[cb]);
+          out[cb] = fmaf(p.z, v[2], out[cb]); out[cb] = fmaf(p.w, v[3], out[cb]);
+        }
+      }
+#pragma unroll
+      for (int cb = 0; cb < CBH; cb += 4) put(g, cb * 16 + lane, sum_rows(out[cb], out[cb + 1], out[cb + 2], out[cb + 3]));
+    }
+    return;
+  }
+#pragma nounroll
+  for (int g0 = 0; g0 < G; g0 += 4) {
+    const float* ps = pp + min(g0 + (lane & 3), G - 1) * WM + 4 * o;
+    floatx4_t out[CBH];
+#pragma unroll
+    for (int cb = 0; cb < CBH; ++cb) out[cb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int tb = 0; tb < 4; ++tb) {
+      const float4 p4 = *reinterpret_cast<const float4*>(ps + tb * 16);
+      const float p[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int cb = 0; cb < CBH; ++cb) out[cb] = fma_heads(p[r], acc.v[hw * CBH + cb][tb][r], out[cb]);
+    }
 #pragma unroll
     for (int cb = 0; cb < CBH; ++cb) {
-      const floatx4_t& v = acc.v[hw * CBH + cb][tb];
-      out[cb] = fmaf(p.x, v[0], out[cb]); out[cb] = fmaf(p.y, v[1], out[cb]);
-      out[cb] = fmaf(p.z, v[2], out[cb]); out[cb] = fmaf(p.w, v[3], out[cb]);
+      const float v = sum_rows(out[cb][0], out[cb][1], out[cb][2], out[cb][3]);
+      if (g0 + o < G) put(g0 + o, cb * 16 + c, v);
     }
   }
-#pragma unroll
-  for (int cb = 0; cb < CBH; ++cb) out[cb] = add_rows(out[cb]);
 }
 
 // What a workgroup is about: its tile and the operands of its product.
@@ -337,61 +393,49 @@ __global__ __launch_bounds__(NTHREADS) void fused_decode_kernel(Args a, Streams<
                        [&](int tb, int cb, float4& cs, float4& sn) __attribute__((always_inline)) {
                          table_from_memory<HD>(x, jw0, t.L, t.lane, tb, cb, cs, sn);
                        },
-                       [&](float (&s)[4], int hw, int g) __attribute__((always_inline)) {
+                       [&](float s, int hw, int g) __attribute__((always_inline)) {
                          score_tail(s, sm.e.p[t.wave][hw * a.G + g], sm.e.ml[t.wave][hw * a.G + g], t.lane, jw0, x);
                        });
   // ---- V_hat = X W_V
   pipe.template pass<false>(acc, pipe.op.nk);
   pipe.drain();
-  // ---- the waves 2 s and 2 s + 1 (same columns) hold the halves of a 128-token slot: the odd one hands its
-  //      sums over in LDS, both relative to the larger of the two maxima
-  float* xo = reinterpret_cast<float*>(sm.st) + (t.wave >> 1) * (MAXPAIR * 128);
-  const int H_kv = a.H_q / a.G, kvh0 = a.n_ret_heads + (t.n0 + t.wc * WN) / HD;
-  const int c = t.lane & 15;
-  const bool writes = t.lane < 16;
-  auto weight = [&](int pair) __attribute__((always_inline)) {
-    const float m0 = sm.e.ml[t.wave & ~1][pair][0], m1 = sm.e.ml[t.wave | 1][pair][0], m = fmaxf(m0, m1);
-    const float mine = (t.wave & 1) ? m1 : m0;
+  // ---- the waves 2 s and 2 s + 1 (same columns) hold the halves of a 128-token slot: all put their sums, relative to the larger of
+  //      the two maxima, into LDS, and all threads add the halves up on the way out.  (The odd wave's handed over first and
+  //      the even one's added to them, half of the SIMDs had nothing to do in either half.)
+  float (*xo)[MAXPAIR * 128] = reinterpret_cast<float (*)[MAXPAIR * 128]>(sm.st);
+  const int H_kv = a.H_q / a.G;
+  auto rescale = [&](int wave, int pair, float& m) __attribute__((always_inline)) {      // of a wave's sums, and the larger maximum
+    const float mine = sm.e.ml[wave][pair][0];
+    m = fmaxf(mine, sm.e.ml[wave ^ 1][pair][0]);
     return mine == -INFINITY ? 0.f : __expf(mine - m);
   };
-  auto sums = [&](auto&& out) __attribute__((always_inline)) {
+  if (pipe.active && t.j0 + (t.wt & ~1) * WM < t.L) {                // (the slot has a token)
 #pragma unroll
-    for (int hw = 0; hw < HPW; ++hw) {
-      if (kvh0 + hw >= H_kv) continue;
-#pragma nounroll
-      for (int g = 0; g < a.G; ++g) {
-        float o[CBH];
-        value_sum<HD>(acc, sm.e.p[t.wave][hw * a.G + g], hw, t.lane, o);
-        const float w = weight(hw * a.G + g);
-#pragma unroll
-        for (int cb = 0; cb < CBH; ++cb) o[cb] *= w;
-        out(o, hw, g);
-      }
-    }
-  };
-  const bool have = pipe.active && t.j0 + (t.wt & ~1) * WM < t.L;      // the slot has a token
-  if (have && (t.wave & 1))
-    sums([&](float (&o)[CBH], int hw, int g) __attribute__((always_inline)) {
-#pragma unroll
-      for (int cb = 0; cb < CBH; ++cb)
-        if (writes) xo[(hw * a.G + g) * HD + cb * 16 + c] = o[cb];
-    });
+    for (int hw = 0; hw < HPW; ++hw)
+      value_sums<HD>(acc, sm.e.p[t.wave][hw * a.G], hw, a.G, t.lane, [&](int g, int dim, float v) __attribute__((always_inline)) {
+        const int pair = hw * a.G + g;
+        float m;
+        xo[t.wave][pair * HD + dim] = v * rescale(t.wave, pair, m);
+      });
+  }
   __syncthreads();
-  if (!have || (t.wave & 1)) return;
-  const int64_t slot = meta.sbase[t.b] + jw0 / kSlotTokens;
-  sums([&](float (&o)[CBH], int hw, int g) __attribute__((always_inline)) {
-    const int pair = hw * a.G + g;
-    const int64_t ph = slot * a.H_q + (kvh0 + hw) * a.G + g;
+  // a wave takes the pairs wave, wave + 8, ... of all (slot, column half, pair)
+  const int npair = HPW * a.G;
+  for (int i = t.wave; i < 4 * npair; i += NWAVES) {
+    const int quarter = i / npair, pair = i - quarter * npair, s = quarter & 1, wc = quarter >> 1, w0 = 4 * wc + 2 * s;
+    const int jw = t.j0 + 2 * s * WM, kvh = a.n_ret_heads + (t.n0 + wc * WN) / HD + pair / a.G;
+    if (jw >= t.L || t.n0 + wc * WN >= a.d_out || kvh >= H_kv) continue;
+    const int64_t ph = (int64_t)(meta.sbase[t.b] + jw / kSlotTokens) * a.H_q + kvh * a.G + pair % a.G;
 #pragma unroll
-    for (int cb = 0; cb < CBH; ++cb)
-      if (writes) a.part_o[ph * HD + cb * 16 + c] = o[cb] + xo[pair * HD + cb * 16 + c];
+    for (int dim = 0; dim < HD; dim += 64)
+      a.part_o[ph * HD + dim + t.lane] = xo[w0][pair * HD + dim + t.lane] + xo[w0 + 1][pair * HD + dim + t.lane];
     if (t.lane == 0) {
-      const float m0 = sm.e.ml[t.wave][pair][0], m1 = sm.e.ml[t.wave | 1][pair][0], m = fmaxf(m0, m1);
+      float m;
+      const float l0 = sm.e.ml[w0][pair][1] * rescale(w0, pair, m);
       a.part_ml[ph * 2] = m;
-      a.part_ml[ph * 2 + 1] = (m0 == -INFINITY ? 0.f : sm.e.ml[t.wave][pair][1] * __expf(m0 - m)) +
-                              (m1 == -INFINITY ? 0.f : sm.e.ml[t.wave | 1][pair][1] * __expf(m1 - m));
+      a.part_ml[ph * 2 + 1] = l0 + sm.e.ml[w0 + 1][pair][1] * rescale(w0 + 1, pair, m);
     }
-  });
+  }
 }
 
 // Key half of the fused kernel on its own: K_hat^T of the tile, then the scaled scores of
@@ -431,11 +475,8 @@ __global__ __launch_bounds__(NTHREADS) void fused_kscores_kernel(Args a, Streams
   float* srow = a.s_out + (int64_t)meta.sbase[t.b] * kSlotTokens + jw0 + t.lane;
   k_scores<HD, ROPE>(acc, &sm.e.q[t.wc * HPW * a.G * HD], a.G, t.lane, [&](int tb, int cb, float4& cs, float4& sn) __attribute__((always_inline)) {
     table_from_lds<HD>(sm.st, t.wt, t.lane, tb, cb, cs, sn);
-  }, [&](float (&s)[4], int hw, int g) __attribute__((always_inline)) {
+  }, [&](float v, int hw, int g) __attribute__((always_inline)) {
     if (HPW > 1 && kvh0 + hw >= H_kv) return;
-    const int o = t.lane >> 4;             // lane <- token lane
-    const float s0 = s[0], s1 = s[1], s2 = s[2], s3 = s[3];
-    const float v = o == 0 ? s0 : o == 1 ? s1 : o == 2 ? s2 : s3;
     if (jw0 + t.lane < t.L) srow[(int64_t)((kvh0 + hw) * a.G + g) * a.s_ld] = v;
   });
 }
