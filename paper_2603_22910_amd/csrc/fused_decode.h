@@ -29,7 +29,7 @@ namespace echokv {
 
 namespace fused {
 
-constexpr int MAXPAIR = 8;   // (head in wave tile, query head in group) pairs per wave
+constexpr int MAXPAIR = 8;   // query heads per 128 columns: (128 / head dim) * G at most
 constexpr int kVectorHeads = 2;   // up to so many query heads per KV head the epilogues use the vector unit, beyond it fma_heads
 
 struct Args {
@@ -53,15 +53,15 @@ struct Args {
   int64_t s_ld;
 };
 
-// LDS state of the attention epilogues; WT = tokens of a wave.
-template <int NW, int WT> struct EpiSmem {
-  float q[BN * MAXPAIR];               // [(head in tile * G + g)][d], pre-scaled
-  float p[NW][MAXPAIR][WT];            // per wave and pair: softmax numerators of its tokens
-  float ml[NW][MAXPAIR][2];            // per wave and pair: max and sum
+// LDS state of the attention epilogues; a pair: (head of the tile, query head of its group).
+struct EpiSmem {
+  float q[BN * MAXPAIR];               // [pair][d], pre-scaled
+  float p[4][2 * MAXPAIR][WM];         // per 64 tokens and pair: score shares of one wave, then softmax numerators
+  float ml[4][2 * MAXPAIR][2];         // max and sum
 };
 struct Smem {
   char st[2 * kStage];
-  EpiSmem<NWAVES, WM> e;
+  EpiSmem e;
 };
 
 // Workgroup id -> (token tile, column tile).  Consecutive workgroup ids go to
@@ -76,19 +76,23 @@ __device__ __forceinline__ bool tile_of_block(const Args& a, int& ttile, int& ct
   return true;
 }
 
-// Queries of the tile's heads -> LDS as fp32, pre-scaled by the softmax scale.
-template <int HD, int NT, typename T>
-__device__ __forceinline__ void load_queries(float* eq, const T* q, int b, int H_q, int G,
-                                             int kvh0, float scale, int tid) {
-  const int H_kv = H_q / G;
-  for (int idx = tid; idx < (BN / HD) * G * HD; idx += NT) {
-    const int c = idx % HD, pg = idx / HD;       // pg = head_in_tile * G + g
-    const int kvh = kvh0 + pg / G;
-    float v = 0.f;
-    if (kvh < H_kv) v = Elem<T>::to_f32(q[((int64_t)b * H_q + kvh * G + pg % G) * HD + c]) * scale;
-    eq[pg * HD + c] = v;
+// Queries of the tile's nh heads -> LDS as fp32, pre-scaled by the softmax scale: [pair][HD], as they lie in memory.  Requested ahead of the
+// first copies (behind them their wait would be for those as well) and stored once these are on their way.
+struct Queries {
+  static constexpr int N = BN * MAXPAIR / NTHREADS;
+  bf16_t v[N];
+  int n;
+  __device__ __forceinline__ void load(const bf16_t* q, int n_, int tid) {
+    n = n_;
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = q[min(i * NTHREADS + tid, n - 1)];
   }
-}
+  __device__ __forceinline__ void store(float* eq, float scale, int tid) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (i * NTHREADS + tid < n) eq[i * NTHREADS + tid] = bf16_to_f32(v[i]) * scale;
+  }
+};
 
 // Extras of the score epilogue: rotary tables (null: none) and the token range [lo, hi) of the
 // sequence that counts (tokens outside are masked: past the end, or held by the window).
@@ -121,88 +125,65 @@ __device__ __forceinline__ float sum_rows(float a, float b, float c, float d) {
 // 4 per head, which meanwhile rotates the keys of the SIMD's other wave.
 __device__ __forceinline__ floatx4_t fma_heads(float a, float b, floatx4_t d) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, d, 0, 0, 0); }
 
-// After the K pass: acc[cb][tb] holds K_hat^T.  A lane owns dims 16 cb + 4 (lane / 16) + r of the wave's 128 columns for
-// the tokens 16 tb + lane % 16.  `tail(s, hw, g)` receives the scores (Eq. 7) of head hw of the wave's tile and
-// query head g of its group: that of the wave's token `lane`.
-// qw: the queries of the wave's first head; table(tb, cb, cs, sn): rotary table entries of the lane's token of block
-// tb, dims 16 cb + 4 (lane / 16) ... .
-template <int HD, bool ROPE, class Table, class Tail>
-__device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int lane, Table table, Tail tail) {
-  constexpr int HPW = WN / HD, CBH = HD / 16;
+// A wave's share of the tile's heads (see column_of): N heads, of each CBH blocks of 16 columns; blocks b and b + HB are rotation partners.
+template <int HD, bool SPLIT> struct Part {
+  static constexpr int N = (SPLIT ? BN : WN) / HD, CBH = 8 / N, HB = CBH / 2;
+  __device__ static __forceinline__ int head(int wc, int hw) { return SPLIT ? hw : wc * N + hw; }      // of the tile
+  __device__ static __forceinline__ int dim(int b, int wc) { return SPLIT ? b / HB * (HD / 2) + wc * (HD / 4) + b % HB * 16 : 16 * b; }
+  __device__ static constexpr __forceinline__ int block(int hw, int b) { return SPLIT ? b / HB * 4 + hw * HB + b % HB : hw * CBH + b; }      // of the accumulators
+};
+
+// After the K pass: acc[cb][tb] holds K_hat^T.  A lane owns rows 4 (lane / 16) + r of the wave's column blocks for
+// the tokens 16 tb + lane % 16.  Hands out the scores (Eq. 7) of the tile's nh heads as tail(v, pair), v: that of the wave's token `lane`.
+// SPLIT: the two waves of 64 tokens exchange half of their shares through share[pair][token], and wave column wc hands
+// out the pairs with (hw + g) % 2 = wc; all waves of the workgroup come here.
+// q: [pair][HD]; table(tb, hb, cs, sn): rotary table entries of the lane's token of block tb for the dims of block hb.
+template <int HD, bool ROPE, bool SPLIT, class Table, class Tail>
+__device__ __forceinline__ void k_scores(const Acc& acc, const float* q, float (*share)[WM], int nh, int G, int wc, int lane, Table table, Tail tail) {
+  using P = Part<HD, SPLIT>;
+  constexpr int CBH = P::CBH, HB = P::HB, MG = MAXPAIR * HD / 128;      // MG: query heads per KV head at most
   const int o = lane >> 4;
-  if constexpr (!ROPE) {
-    if (G <= kVectorHeads) {
+  uint32_t mine[P::N][MG / 2];               // SPLIT: shares of the pairs that this wave hands out
 #pragma unroll
-      for (int hw = 0; hw < HPW; ++hw) {
-#pragma nounroll
-        for (int g = 0; g < G; ++g) {
-          const float* qs = qw + (hw * G + g) * HD + 4 * o;
-          float s[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int hw = 0; hw < P::N; ++hw)
 #pragma unroll
-          for (int cb = 0; cb < CBH; ++cb) {
-            const float4 qv = *reinterpret_cast<const float4*>(qs + cb * 16);
-#pragma unroll
-            for (int tb = 0; tb < 4; ++tb) {
-              const floatx4_t& k = acc.v[hw * CBH + cb][tb];
-              s[tb] = fmaf(qv.x, k[0], s[tb]); s[tb] = fmaf(qv.y, k[1], s[tb]);
-              s[tb] = fmaf(qv.z, k[2], s[tb]); s[tb] = fmaf(qv.w, k[3], s[tb]);
-            }
-          }
-          tail(sum_rows(s[0], s[1], s[2], s[3]), hw, g);
-        }
-      }
-      return;
+    for (int i = 0; i < MG / 2; ++i) mine[hw][i] = 0;
+  auto out = [&](float v, int hw, int g) __attribute__((always_inline)) {
+    if constexpr (SPLIT) {
+      // (as if / else of two stores the compiler selects between their addresses, and the array would lie in scratch memory)
+      const uint32_t own = 0u - (uint32_t)(((hw + g) & 1) == wc);
+      mine[hw][g / 2] = (own & __float_as_uint(v)) | (~own & mine[hw][g / 2]);
+      if (!own) share[hw * G + g][lane] = v;
+    } else {
+      tail(v, P::head(wc, hw) * G + g);
     }
+  };
+  const float* qw = q + P::head(wc, 0) * G * HD + P::dim(0, wc) + 4 * o;
 #pragma unroll
-    for (int hw = 0; hw < HPW; ++hw) {
-#pragma nounroll
-      for (int g0 = 0; g0 < G; g0 += 4) {
-        const float* qs = qw + (hw * G + min(g0 + (lane & 3), G - 1)) * HD + 4 * o;      // (heads past the last repeat it)
-        floatx4_t s[4];
-#pragma unroll
-        for (int tb = 0; tb < 4; ++tb) s[tb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int cb = 0; cb < CBH; ++cb) {
-          const float4 q4 = *reinterpret_cast<const float4*>(qs + cb * 16);
-          const float qv[4] = {q4.x, q4.y, q4.z, q4.w};
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int tb = 0; tb < 4; ++tb) s[tb] = fma_heads(qv[r], acc.v[hw * CBH + cb][tb][r], s[tb]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (g0 + i < G) tail(sum_rows(s[0][i], s[1][i], s[2][i], s[3][i]), hw, g0 + i);
-      }
-    }
-  } else {
-    // Rotary embedding of the rebuilt key at its token's position on its way into the dot product: feature c pairs with
-    // c + HD/2, which this lane holds HD/32 column blocks further on.  With a = k_c, b = k_{c+HD/2}:
-    //   q_c (a cos - b sin) + q_{c+HD/2} (b cos + a sin)
-    // The rotated values are temporaries (written back they would cost hundreds of spilled registers), used by all query heads of
-    // the group.  Masked tokens borrow the last valid table row.
-    constexpr int HB = CBH / 2, NG = MAXPAIR / (4 * HPW);      // groups of four query heads at most
-#pragma unroll
-    for (int hw = 0; hw < HPW; ++hw) {
+  for (int hw = 0; hw < P::N; ++hw) {
+    if (P::head(wc, hw) >= nh) continue;
+    if constexpr (ROPE) {
+      // Rotary embedding of the rebuilt key at its token's position on its way into the dot product: feature c pairs with
+      // c + HD/2.  With a = k_c, b = k_{c+HD/2}:
+      //   q_c (a cos - b sin) + q_{c+HD/2} (b cos + a sin)
+      // The rotated values are temporaries (written back they would cost hundreds of spilled registers), used by all query heads of
+      // the group.  Masked tokens borrow the last valid table row.
+      constexpr int NG = MG / 4;             // groups of four query heads at most
       floatx4_t s[NG][4];
-      const float* qs[NG];
 #pragma unroll
-      for (int n = 0; n < NG; ++n) {
-        qs[n] = qw + (hw * G + min(4 * n + (lane & 3), G - 1)) * HD + 4 * o;
+      for (int n = 0; n < NG; ++n)
 #pragma unroll
         for (int tb = 0; tb < 4; ++tb) s[n][tb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-      }
 #pragma unroll
-      for (int cb = 0; cb < HB; ++cb) {
-        float4 cs[4], sn[4];
-#pragma unroll
-        for (int tb = 0; tb < 4; ++tb) table(tb, cb, cs[tb], sn[tb]);
+      for (int hb = 0; hb < HB; ++hb) {
         float ra[4][4], rb[4][4];
 #pragma unroll
         for (int tb = 0; tb < 4; ++tb) {
-          const floatx4_t& ka = acc.v[hw * CBH + cb][tb];
-          const floatx4_t& kb = acc.v[hw * CBH + cb + HB][tb];
-          const float cc[4] = {cs[tb].x, cs[tb].y, cs[tb].z, cs[tb].w}, ss[4] = {sn[tb].x, sn[tb].y, sn[tb].z, sn[tb].w};
+          float4 cs, sn;
+          table(tb, hb, cs, sn);
+          const floatx4_t& ka = acc.v[P::block(hw, hb)][tb];
+          const floatx4_t& kb = acc.v[P::block(hw, hb + HB)][tb];
+          const float cc[4] = {cs.x, cs.y, cs.z, cs.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             ra[tb][i] = fmaf(ka[i], cc[i], -kb[i] * ss[i]);
@@ -212,7 +193,8 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
 #pragma unroll
         for (int n = 0; n < NG; ++n) {
           if (4 * n < G) {
-            const float4 qa = *reinterpret_cast<const float4*>(qs[n] + cb * 16), qb = *reinterpret_cast<const float4*>(qs[n] + cb * 16 + HD / 2);
+            const float* qs = qw + (hw * G + min(4 * n + (lane & 3), G - 1)) * HD + hb * 16;
+            const float4 qa = *reinterpret_cast<const float4*>(qs), qb = *reinterpret_cast<const float4*>(qs + HD / 2);
             const float q0[4] = {qa.x, qa.y, qa.z, qa.w}, q1[4] = {qb.x, qb.y, qb.z, qb.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -223,25 +205,84 @@ __device__ __forceinline__ void k_scores(Acc& acc, const float* qw, int G, int l
             }
           }
         }
-        asm volatile("" ::: "memory");       // keep the table loads of later rounds from piling up
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!SPLIT) {
+          asm volatile("" ::: "memory");       // keep the table reads of later rounds from piling up
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
 #pragma unroll
       for (int n = 0; n < NG; ++n)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (4 * n + i < G) tail(sum_rows(s[n][0][i], s[n][1][i], s[n][2][i], s[n][3][i]), hw, 4 * n + i);
+          if (4 * n + i < G) out(sum_rows(s[n][0][i], s[n][1][i], s[n][2][i], s[n][3][i]), hw, 4 * n + i);
+    } else if (G <= kVectorHeads) {
+#pragma nounroll
+      for (int g = 0; g < G; ++g) {
+        const float* qs = qw + (hw * G + g) * HD;
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < CBH; ++b) {
+          const float4 qv = *reinterpret_cast<const float4*>(qs + P::dim(b, 0));
+#pragma unroll
+          for (int tb = 0; tb < 4; ++tb) {
+            const floatx4_t& k = acc.v[P::block(hw, b)][tb];
+            s[tb] = fmaf(qv.x, k[0], s[tb]); s[tb] = fmaf(qv.y, k[1], s[tb]);
+            s[tb] = fmaf(qv.z, k[2], s[tb]); s[tb] = fmaf(qv.w, k[3], s[tb]);
+          }
+        }
+        out(sum_rows(s[0], s[1], s[2], s[3]), hw, g);
+      }
+    } else {
+#pragma nounroll
+      for (int g0 = 0; g0 < G; g0 += 4) {
+        const float* qs = qw + (hw * G + min(g0 + (lane & 3), G - 1)) * HD;      // (heads past the last repeat it)
+        floatx4_t s[4];
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb) s[tb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < CBH; ++b) {
+          const float4 q4 = *reinterpret_cast<const float4*>(qs + P::dim(b, 0));
+          const float qv[4] = {q4.x, q4.y, q4.z, q4.w};
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int tb = 0; tb < 4; ++tb) s[tb] = fma_heads(qv[r], acc.v[P::block(hw, b)][tb][r], s[tb]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (g0 + i < G) out(sum_rows(s[0][i], s[1][i], s[2][i], s[3][i]), hw, g0 + i);
+      }
+    }
+  }
+  if constexpr (SPLIT) {
+    static_assert(ROPE, "the loops over the query heads have to be unrolled");
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (the copies in flight stay in flight)
+    barrier();
+#pragma unroll
+    for (int hw = 0; hw < P::N; ++hw) {
+      if (hw >= nh) continue;
+#pragma unroll
+      for (int g = 0; g < MG; ++g)
+        if (g < G && ((hw + g) & 1) == wc) tail(__uint_as_float(mine[hw][g / 2]) + share[hw * G + g][lane], hw * G + g);
     }
   }
 }
 
-// Table entries of a lane from memory: token block tb, dims 16 cb + 4 (lane / 16) ...; jw0: the wave's first token.
-template <int HD>
-__device__ __forceinline__ void table_from_memory(const KExtra& x, int jw0, int L, int lane, int tb, int cb, float4& cs, float4& sn) {
-  const int64_t at = (int64_t)min(jw0 + tb * 16 + (lane & 15), L - 1) * (HD / 2) + 4 * (lane >> 4) + cb * 16;
-  cs = *reinterpret_cast<const float4*>(x.cos + at);
-  sn = *reinterpret_cast<const float4*>(x.sin + at);
-}
+// Table entries of a lane from memory (SPLIT): all it needs of its four tokens, requested at once.
+template <int HD> struct TableRegs {
+  static constexpr int HB = Part<HD, true>::HB;
+  float4 cs[HB][4], sn[HB][4];
+  __device__ __forceinline__ void load(const KExtra& x, int jw0, int L, int wc, int lane) {
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+      for (int tb = 0; tb < 4; ++tb) {
+        const int64_t at = (int64_t)min(jw0 + tb * 16 + (lane & 15), L - 1) * (HD / 2) + wc * (HD / 4) + hb * 16 + 4 * (lane >> 4);
+        cs[hb][tb] = *reinterpret_cast<const float4*>(x.cos + at);
+        sn[hb][tb] = *reinterpret_cast<const float4*>(x.sin + at);
+      }
+  }
+};
 // ... and through LDS, where there is room for the tables of the tile's 256 tokens (the score kernel's stages, once its only pass is
 // done): loaded from memory a lane's 16 bytes lie in another row than its neighbour's but three, and the address unit takes
 // a row per clock.  Whole calls, value-absorbed, four query heads per KV head, from memory / so, us: 131072 tokens 347 / 343, 60000 with
@@ -259,10 +300,10 @@ __device__ __forceinline__ void tables_to_lds(char* smem, const KExtra& x, int j
   }
 }
 template <int HD>
-__device__ __forceinline__ void table_from_lds(const char* smem, int wt, int lane, int tb, int cb, float4& cs, float4& sn) {
+__device__ __forceinline__ void table_from_lds(const char* smem, int wt, int lane, int tb, int hb, float4& cs, float4& sn) {
   constexpr int CH = HD / 8;
   const int r = tb * 16 + (lane & 15);
-  const char* at = smem + 2 * wt * (WM * CH * 16) + r * (CH * 16) + ((((cb << 2) | (lane >> 4)) ^ (r % CH)) << 4);
+  const char* at = smem + 2 * wt * (WM * CH * 16) + r * (CH * 16) + (((hb * 4 + (lane >> 4)) ^ (r % CH)) << 4);
   cs = *reinterpret_cast<const float4*>(at);
   sn = *reinterpret_cast<const float4*>(at + WM * CH * 16);
 }
@@ -278,53 +319,66 @@ __device__ __forceinline__ void score_tail(float v, float* pp, float* ml, int la
   if (lane == 0) { ml[0] = mx; ml[1] = sum; }
 }
 
-// After the V pass: acc[cb][tb] holds V_hat; a lane owns tokens 16 tb + 4 (lane / 16) + r of dim 16 cb + lane % 16.  Hands out sum_j p_j
-// v_hat_j over the wave's tokens for head hw of its tile as put(g, dim, value), every (g, dim) in one lane.  pp: the
-// numerators [pair][WT] of the head's first query head.
-template <int HD, class Put>
-__device__ __forceinline__ void value_sums(const Acc& acc, const float* pp, int hw, int G, int lane, Put put) {
-  constexpr int CBH = HD / 16;
+// After the V pass: acc[cb][tb] holds V_hat; a lane owns tokens 16 tb + 4 (lane / 16) + r of column lane % 16 of the wave's blocks.  Hands out
+// sum_j p_j v_hat_j over the wave's 64 tokens for its dims of the tile's nh heads as put(pair, dim, value), every (pair, dim) in one
+// lane.  p: the numerators [pair][WM].
+template <int HD, bool SPLIT, class Put>
+__device__ __forceinline__ void value_sums(const Acc& acc, const float (*p)[WM], int nh, int G, int wc, int lane, Put put) {
+  using P = Part<HD, SPLIT>;
+  constexpr int CBH = P::CBH, NH = CBH < 4 ? 4 / CBH : 1;        // heads of four blocks
   const int c = lane & 15, o = lane >> 4;
-  if (G <= kVectorHeads) {
+#pragma unroll
+  for (int n0 = 0; n0 < 8; n0 += 4) {          // blocks n0 ... n0 + 3, heads after heads
+    const int hw0 = n0 / CBH;
+    if (P::head(wc, hw0) >= nh) continue;
+    if (G <= kVectorHeads) {
 #pragma nounroll
-    for (int g = 0; g < G; ++g) {
-      float out[CBH];
+      for (int g = 0; g < G; ++g) {
+        float out[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int cb = 0; cb < CBH; ++cb) out[cb] = 0.f;
+        for (int tb = 0; tb < 4; ++tb)
 #pragma unroll
-      for (int tb = 0; tb < 4; ++tb) {
-        const float4 p = *reinterpret_cast<const float4*>(pp + g * WM + tb * 16 + 4 * o);
+          for (int i = 0; i < 4; ++i) {
+            const int hw = (n0 + i) / CBH;
+            const float4 pv = *reinterpret_cast<const float4*>(&p[P::head(wc, hw) * G + g][tb * 16 + 4 * o]);
+            const floatx4_t& v = acc.v[P::block(hw, (n0 + i) % CBH)][tb];
+            out[i] = fmaf(pv.x, v[0], out[i]); out[i] = fmaf(pv.y, v[1], out[i]);
+            out[i] = fmaf(pv.z, v[2], out[i]); out[i] = fmaf(pv.w, v[3], out[i]);
+          }
+        const int head = P::head(wc, (n0 + o) / CBH);        // (row o of 16 lanes has block n0 + o)
+        const float v = sum_rows(out[0], out[1], out[2], out[3]);
+        if (head < nh) put(head * G + g, P::dim((n0 + o) % CBH, wc) + c, v);
+      }
+    } else {
+#pragma nounroll
+      for (int g0 = 0; g0 < G; g0 += 4) {
+        const int gl = min(g0 + (lane & 3), G - 1);
+        floatx4_t out[4];
 #pragma unroll
-        for (int cb = 0; cb < CBH; ++cb) {
-          const floatx4_t& v = acc.v[hw * CBH + cb][tb];
-          out[cb] = fmaf(p.x, v[0], out[cb]); out[cb] = fmaf(p.y, v[1], out[cb]);
-          out[cb] = fmaf(p.z, v[2], out[cb]); out[cb] = fmaf(p.w, v[3], out[cb]);
+        for (int i = 0; i < 4; ++i) out[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb) {
+          float pv[NH][4];
+#pragma unroll
+          for (int j = 0; j < NH; ++j) {
+            const float4 p4 = *reinterpret_cast<const float4*>(&p[P::head(wc, hw0 + j) * G + gl][tb * 16 + 4 * o]);
+            pv[j][0] = p4.x; pv[j][1] = p4.y; pv[j][2] = p4.z; pv[j][3] = p4.w;
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int hw = (n0 + i) / CBH;
+              out[i] = fma_heads(pv[hw - hw0][r], acc.v[P::block(hw, (n0 + i) % CBH)][tb][r], out[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int head = P::head(wc, (n0 + i) / CBH);
+          const float v = sum_rows(out[i][0], out[i][1], out[i][2], out[i][3]);
+          if (head < nh && g0 + o < G) put(head * G + g0 + o, P::dim((n0 + i) % CBH, wc) + c, v);
         }
       }
-#pragma unroll
-      for (int cb = 0; cb < CBH; cb += 4) put(g, cb * 16 + lane, sum_rows(out[cb], out[cb + 1], out[cb + 2], out[cb + 3]));
-    }
-    return;
-  }
-#pragma nounroll
-  for (int g0 = 0; g0 < G; g0 += 4) {
-    const float* ps = pp + min(g0 + (lane & 3), G - 1) * WM + 4 * o;
-    floatx4_t out[CBH];
-#pragma unroll
-    for (int cb = 0; cb < CBH; ++cb) out[cb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int tb = 0; tb < 4; ++tb) {
-      const float4 p4 = *reinterpret_cast<const float4*>(ps + tb * 16);
-      const float p[4] = {p4.x, p4.y, p4.z, p4.w};
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int cb = 0; cb < CBH; ++cb) out[cb] = fma_heads(p[r], acc.v[hw * CBH + cb][tb][r], out[cb]);
-    }
-#pragma unroll
-    for (int cb = 0; cb < CBH; ++cb) {
-      const float v = sum_rows(out[cb][0], out[cb][1], out[cb][2], out[cb][3]);
-      if (g0 + o < G) put(g0 + o, cb * 16 + c, v);
     }
   }
 }
@@ -334,8 +388,8 @@ struct Tile {
   int b, L, j0, n0, wave, lane, wt, wc;
   bool ok;
 };
-template <bool PACKED>
-__device__ __forceinline__ Tile make_tile(const Args& a, const SeqMeta& meta, Pipe<PACKED>& pipe, char* smem, int passes, int which) {
+template <bool PACKED, bool SPLIT>
+__device__ __forceinline__ Tile make_tile(const Args& a, const SeqMeta& meta, Pipe<PACKED, SPLIT>& pipe, char* smem, int passes, int which, int head_dim) {
   Tile t;
   int ttile, ctile;
   t.ok = tile_of_block(a, ttile, ctile);
@@ -355,7 +409,7 @@ __device__ __forceinline__ Tile make_tile(const Args& a, const SeqMeta& meta, Pi
     const int s = passes == 2 ? p : which;
     op.xa[p] = a.xa[s] + row0 * a.D; op.xr[p] = a.xr[s] + row0 * a.m; op.w[p] = a.w[s] + woff;
   }
-  op.D = a.D; op.m = a.m; op.d_out = a.d_out;
+  op.D = a.D; op.m = a.m; op.d_out = a.d_out; op.run = head_dim / 4;
   // rows past the end of the sequence are clamped onto its last valid token, columns past d_out onto
   // the last valid ones, so that what is masked or skipped later is finite
   op.last = min(BM, t.L - t.j0) - 1;
@@ -363,7 +417,7 @@ __device__ __forceinline__ Tile make_tile(const Args& a, const SeqMeta& meta, Pi
   op.nk = (a.D + a.m) / BK; op.nka = a.D / BK; op.total = passes * op.nk;
   op.rot = (t.j0 / BM * 3) % op.nk;
   pipe.smem = smem; pipe.wave = t.wave; pipe.lane = t.lane;
-  pipe.active = t.n0 + t.wc * WN < a.d_out;
+  pipe.half = op.ncol <= (SPLIT ? WN : t.wc * WN);
   return t;
 }
 
@@ -376,56 +430,51 @@ __global__ __launch_bounds__(NTHREADS) void fused_decode_kernel(Args a, Streams<
     return;
   }
   const SeqMeta& meta = smeta.s;
-  constexpr int HPW = WN / HD, CBH = HD / 16;
-  Pipe<PACKED> pipe;
-  const Tile t = make_tile<PACKED>(a, meta, pipe, sm.st, 2, 0);
+  constexpr bool SPLIT = ROPE;
+  Pipe<PACKED, SPLIT> pipe;
+  const Tile t = make_tile(a, meta, pipe, sm.st, 2, 0, HD);
   if (!t.ok) return;
+  const int kvh0 = a.n_ret_heads + t.n0 / HD, nh = min(BN / HD, (a.d_out - t.n0) / HD);      // first KV head, heads of the tile
+  Queries queries;
+  queries.load(a.q + ((int64_t)t.b * a.H_q + kvh0 * a.G) * HD, nh * a.G * HD, threadIdx.x);
   pipe.begin();
-  load_queries<HD, NTHREADS>(sm.e.q, a.q, t.b, a.H_q, a.G, a.n_ret_heads + t.n0 / HD, a.scale, threadIdx.x);
+  queries.store(sm.e.q, a.scale, threadIdx.x);
   pipe.first_landed();                             // (publishes the queries as well)
   const int jw0 = t.j0 + t.wt * WM;                // first token of this wave
   Acc acc;
   // ---- K_hat^T = W_K^T X^T; the last two tiles of the pass request the first two of the V pass
   pipe.template pass<true>(acc, 0);
   const KExtra x = make_kextra(a.rope_cos, a.rope_sin, a.n_sink, a.n_recent, t.L);
-  if (pipe.active)
-    k_scores<HD, ROPE>(acc, &sm.e.q[t.wc * HPW * a.G * HD], a.G, t.lane,
-                       [&](int tb, int cb, float4& cs, float4& sn) __attribute__((always_inline)) {
-                         table_from_memory<HD>(x, jw0, t.L, t.lane, tb, cb, cs, sn);
-                       },
-                       [&](float s, int hw, int g) __attribute__((always_inline)) {
-                         score_tail(s, sm.e.p[t.wave][hw * a.G + g], sm.e.ml[t.wave][hw * a.G + g], t.lane, jw0, x);
-                       });
+  TableRegs<HD> tables;
+  if constexpr (ROPE) tables.load(x, jw0, t.L, t.wc, t.lane);
+  k_scores<HD, ROPE, SPLIT>(acc, sm.e.q, sm.e.p[t.wt], nh, a.G, t.wc, t.lane,
+                            [&](int tb, int hb, float4& cs, float4& sn) __attribute__((always_inline)) { cs = tables.cs[hb][tb]; sn = tables.sn[hb][tb]; },
+                            [&](float s, int pair) __attribute__((always_inline)) {
+                              score_tail(s, sm.e.p[t.wt][pair], sm.e.ml[t.wt][pair], t.lane, jw0, x);
+                            });
   // ---- V_hat = X W_V
   pipe.template pass<false>(acc, pipe.op.nk);
   pipe.drain();
-  // ---- the waves 2 s and 2 s + 1 (same columns) hold the halves of a 128-token slot: all put their sums, relative to the larger of
-  //      the two maxima, into LDS, and all threads add the halves up on the way out.  (The odd wave's handed over first and
+  // ---- the token groups 2 s and 2 s + 1 are the halves of a 128-token slot: all waves put their sums, relative to the larger of
+  //      the two maxima, into LDS, and all threads add the halves up on the way out.  (The odd group's handed over first and
   //      the even one's added to them, half of the SIMDs had nothing to do in either half.)
-  float (*xo)[MAXPAIR * 128] = reinterpret_cast<float (*)[MAXPAIR * 128]>(sm.st);
-  const int H_kv = a.H_q / a.G;
-  auto rescale = [&](int wave, int pair, float& m) __attribute__((always_inline)) {      // of a wave's sums, and the larger maximum
-    const float mine = sm.e.ml[wave][pair][0];
-    m = fmaxf(mine, sm.e.ml[wave ^ 1][pair][0]);
-    return mine == -INFINITY ? 0.f : __expf(mine - m);
+  float (*xo)[2 * MAXPAIR * 128] = reinterpret_cast<float (*)[2 * MAXPAIR * 128]>(sm.st);
+  auto rescale = [&](int wt, int pair, float& m) __attribute__((always_inline)) {      // of a group's sums, and the larger maximum
+    const float own = sm.e.ml[wt][pair][0];
+    m = fmaxf(own, sm.e.ml[wt ^ 1][pair][0]);
+    return own == -INFINITY ? 0.f : __expf(own - m);
   };
-  if (pipe.active && t.j0 + (t.wt & ~1) * WM < t.L) {                // (the slot has a token)
-#pragma unroll
-    for (int hw = 0; hw < HPW; ++hw)
-      value_sums<HD>(acc, sm.e.p[t.wave][hw * a.G], hw, a.G, t.lane, [&](int g, int dim, float v) __attribute__((always_inline)) {
-        const int pair = hw * a.G + g;
-        float m;
-        xo[t.wave][pair * HD + dim] = v * rescale(t.wave, pair, m);
-      });
-  }
+  if (t.j0 + (t.wt & ~1) * WM < t.L)               // (the slot has a token)
+    value_sums<HD, SPLIT>(acc, sm.e.p[t.wt], nh, a.G, t.wc, t.lane, [&](int pair, int dim, float v) __attribute__((always_inline)) {
+      float m;
+      xo[t.wt][pair * HD + dim] = v * rescale(t.wt, pair, m);
+    });
   __syncthreads();
-  // a wave takes the pairs wave, wave + 8, ... of all (slot, column half, pair)
-  const int npair = HPW * a.G;
-  for (int i = t.wave; i < 4 * npair; i += NWAVES) {
-    const int quarter = i / npair, pair = i - quarter * npair, s = quarter & 1, wc = quarter >> 1, w0 = 4 * wc + 2 * s;
-    const int jw = t.j0 + 2 * s * WM, kvh = a.n_ret_heads + (t.n0 + wc * WN) / HD + pair / a.G;
-    if (jw >= t.L || t.n0 + wc * WN >= a.d_out || kvh >= H_kv) continue;
-    const int64_t ph = (int64_t)(meta.sbase[t.b] + jw / kSlotTokens) * a.H_q + kvh * a.G + pair % a.G;
+  const int npair = nh * a.G;
+  for (int i = t.wave; i < 2 * npair; i += NWAVES) {
+    const int s = i >= npair, pair = i - s * npair, w0 = 2 * s, jw = t.j0 + w0 * WM;
+    if (jw >= t.L) continue;
+    const int64_t ph = (int64_t)(meta.sbase[t.b] + jw / kSlotTokens) * a.H_q + kvh0 * a.G + pair;
 #pragma unroll
     for (int dim = 0; dim < HD; dim += 64)
       a.part_o[ph * HD + dim + t.lane] = xo[w0][pair * HD + dim + t.lane] + xo[w0 + 1][pair * HD + dim + t.lane];
@@ -451,11 +500,14 @@ __global__ __launch_bounds__(NTHREADS) void fused_kscores_kernel(Args a, Streams
     return;
   }
   const SeqMeta& meta = smeta.s;
-  Pipe<false> pipe;
-  const Tile t = make_tile<false>(a, meta, pipe, sm.st, 1, 0);
+  Pipe<false, false> pipe;
+  const Tile t = make_tile(a, meta, pipe, sm.st, 1, 0, HD);
   if (!t.ok) return;
+  const int kvh0 = a.n_ret_heads + t.n0 / HD, nh = min(BN / HD, (a.d_out - t.n0) / HD);      // first KV head, heads of the tile
+  Queries queries;
+  queries.load(a.q + ((int64_t)t.b * a.H_q + kvh0 * a.G) * HD, nh * a.G * HD, threadIdx.x);
   pipe.begin();
-  load_queries<HD, NTHREADS>(sm.e.q, a.q, t.b, a.H_q, a.G, a.n_ret_heads + t.n0 / HD, a.scale, threadIdx.x);
+  queries.store(sm.e.q, a.scale, threadIdx.x);
   pipe.first_landed();
   Acc acc;
   pipe.template pass<true>(acc, 0);
@@ -468,16 +520,12 @@ __global__ __launch_bounds__(NTHREADS) void fused_kscores_kernel(Args a, Streams
   } else {
     wait_copies<0>();                      // the copies past the end land before the workgroup's LDS is released
   }
-  if (jw0 >= t.L || !pipe.active) return;
-  constexpr int HPW = WN / HD;
-  const int kvh0 = a.n_ret_heads + (t.n0 + t.wc * WN) / HD;       // first KV head of this wave's columns
-  const int H_kv = a.H_q / a.G;
-  float* srow = a.s_out + (int64_t)meta.sbase[t.b] * kSlotTokens + jw0 + t.lane;
-  k_scores<HD, ROPE>(acc, &sm.e.q[t.wc * HPW * a.G * HD], a.G, t.lane, [&](int tb, int cb, float4& cs, float4& sn) __attribute__((always_inline)) {
-    table_from_lds<HD>(sm.st, t.wt, t.lane, tb, cb, cs, sn);
-  }, [&](float v, int hw, int g) __attribute__((always_inline)) {
-    if (HPW > 1 && kvh0 + hw >= H_kv) return;
-    if (jw0 + t.lane < t.L) srow[(int64_t)((kvh0 + hw) * a.G + g) * a.s_ld] = v;
+  float* srow = a.s_out + (int64_t)kvh0 * a.G * a.s_ld + (int64_t)meta.sbase[t.b] * kSlotTokens + jw0 + t.lane;
+  if (jw0 >= t.L) return;
+  k_scores<HD, ROPE, false>(acc, sm.e.q, nullptr, nh, a.G, t.wc, t.lane, [&](int tb, int hb, float4& cs, float4& sn) __attribute__((always_inline)) {
+    table_from_lds<HD>(sm.st, t.wt, t.lane, tb, hb, cs, sn);
+  }, [&](float v, int pair) __attribute__((always_inline)) {
+    if (jw0 + t.lane < t.L) srow[(int64_t)pair * a.s_ld] = v;
   });
 }
 
@@ -490,20 +538,21 @@ __global__ __launch_bounds__(64 * kStreamWaves) void score_stream_kernel(Streams
   score_stream_workgroup<HD, kStreamWaves>(streams, smeta, blockIdx.x, s_out, s_ld, smem);
 }
 
-// K_hat of the tile rotated to its tokens' positions, as store(tile row, column block, four values).  A lane holds dims 16 cb + 4 (lane /
-// 16) + r of a head together with their partners HD / 32 blocks further on; the table entries of the next block of 16 tokens are
-// requested ahead of this one's rotation.
+// K_hat of the tile rotated to its tokens' positions, as store(tile row, column block, four values).  A lane holds dims of a head together
+// with their partners, and the table entries serve every head of the tile; those of the next block of 16 tokens are requested ahead
+// of this one's rotation.
 template <int HD, class Store>
 __device__ __forceinline__ void rotate_tile(const Args& a, const Tile& t, const Acc& acc, Store store) {
-  constexpr int HPW = WN / HD, CBH = HD / 16, HB = CBH / 2;
+  using P = Part<HD, true>;
+  constexpr int HB = P::HB;
   const int c = t.lane & 15, o = t.lane >> 4, j0 = t.wt * WM;
   float4 cs[2][HB], sn[2][HB];
   auto load = [&](int tb) __attribute__((always_inline)) {
-    const int64_t at = (int64_t)min(t.j0 + j0 + tb * 16 + c, t.L - 1) * (HD / 2) + 4 * o;
+    const int64_t at = (int64_t)min(t.j0 + j0 + tb * 16 + c, t.L - 1) * (HD / 2) + t.wc * (HD / 4) + 4 * o;
 #pragma unroll
-    for (int cb = 0; cb < HB; ++cb) {
-      cs[tb & 1][cb] = *reinterpret_cast<const float4*>(a.rope_cos + at + cb * 16);
-      sn[tb & 1][cb] = *reinterpret_cast<const float4*>(a.rope_sin + at + cb * 16);
+    for (int hb = 0; hb < HB; ++hb) {
+      cs[tb & 1][hb] = *reinterpret_cast<const float4*>(a.rope_cos + at + hb * 16);
+      sn[tb & 1][hb] = *reinterpret_cast<const float4*>(a.rope_sin + at + hb * 16);
     }
   };
   load(0);
@@ -512,13 +561,13 @@ __device__ __forceinline__ void rotate_tile(const Args& a, const Tile& t, const 
     if (t.j0 + j0 + tb * 16 >= t.L) break;               // (uniform: rows past the end are not stored)
     if (tb < 3) load(tb + 1);
 #pragma unroll
-    for (int cb = 0; cb < HB; ++cb) {
-      const float4 cq = cs[tb & 1][cb], sq = sn[tb & 1][cb];
+    for (int hb = 0; hb < HB; ++hb) {
+      const float4 cq = cs[tb & 1][hb], sq = sn[tb & 1][hb];
 #pragma unroll
-      for (int hw = 0; hw < HPW; ++hw) {
-        const floatx4_t x = acc.v[hw * CBH + cb][tb], y = acc.v[hw * CBH + cb + HB][tb];
-        store(j0 + tb * 16 + c, hw * CBH + cb, x[0] * cq.x - y[0] * sq.x, x[1] * cq.y - y[1] * sq.y, x[2] * cq.z - y[2] * sq.z, x[3] * cq.w - y[3] * sq.w);
-        store(j0 + tb * 16 + c, hw * CBH + cb + HB, y[0] * cq.x + x[0] * sq.x, y[1] * cq.y + x[1] * sq.y, y[2] * cq.z + x[2] * sq.z, y[3] * cq.w + x[3] * sq.w);
+      for (int hw = 0; hw < P::N; ++hw) {
+        const floatx4_t x = acc.v[P::block(hw, hb)][tb], y = acc.v[P::block(hw, hb + HB)][tb];
+        store(j0 + tb * 16 + c, P::block(hw, hb), x[0] * cq.x - y[0] * sq.x, x[1] * cq.y - y[1] * sq.y, x[2] * cq.z - y[2] * sq.z, x[3] * cq.w - y[3] * sq.w);
+        store(j0 + tb * 16 + c, P::block(hw, hb + HB), y[0] * cq.x + x[0] * sq.x, y[1] * cq.y + x[1] * sq.y, y[2] * cq.z + x[2] * sq.z, y[3] * cq.w + x[3] * sq.w);
       }
     }
   }
@@ -540,8 +589,9 @@ __global__ __launch_bounds__(NTHREADS) void recon_mfma_kernel(Args a, SeqMeta me
     if (which == 0) rope_workgroup<NTHREADS>(rope, blockIdx.x - n_fused);
     return;
   }
-  Pipe<false> pipe;
-  const Tile t = make_tile<false>(a, meta, pipe, st, 1, which);
+  Pipe<false, true> pipe;
+  const int head_dim = a.H_q == 64 ? 64 : 128;      // (which columns go to which wave matters to the rotation only)
+  const Tile t = make_tile(a, meta, pipe, st, 1, which, head_dim);
   if (!t.ok) return;
   pipe.begin();
   pipe.first_landed();
@@ -549,6 +599,7 @@ __global__ __launch_bounds__(NTHREADS) void recon_mfma_kernel(Args a, SeqMeta me
   pipe.template pass<true>(acc, 0);
   pipe.drain();
   const int lc = t.lane & 15, lo = t.lane >> 4;
+  auto column = [&](int cb) __attribute__((always_inline)) { return column_of<true>(head_dim / 4, t.wc, cb >> 2, (cb & 3) * 16); };
   auto act = [](float v) {
     if constexpr (ACT == 1) return fmaxf(v, 0.f);
     else if constexpr (ACT == 2) return v / (1.f + __expf(-v));
@@ -563,7 +614,7 @@ __global__ __launch_bounds__(NTHREADS) void recon_mfma_kernel(Args a, SeqMeta me
       if (t.j0 + j >= t.L) continue;
 #pragma unroll
       for (int cb = 0; cb < 8; ++cb) {
-        const int n = t.n0 + t.wc * WN + cb * 16 + lo * 4;
+        const int n = t.n0 + column(cb) + lo * 4;
         const floatx4_t v = acc.v[cb][tb];
         if (n < a.d_out)
           *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + (orow0 + j) * a.ldo + a.col0 + n) =
@@ -574,7 +625,7 @@ __global__ __launch_bounds__(NTHREADS) void recon_mfma_kernel(Args a, SeqMeta me
   }
   // token row: 32 chunks of 16 bytes, chunk ch at ch ^ (token % 32)
   auto store = [&](int j, int cb, float x0, float x1, float x2, float x3) __attribute__((always_inline)) {
-    const int ch = t.wc * 16 + cb * 2 + (lo >> 1);
+    const int ch = column(cb) / 8 + (lo >> 1);
     const u32x2_t w = {pack_bf16(x0, x1), pack_bf16(x2, x3)};
     *reinterpret_cast<u32x2_t*>(st + j * 512 + ((ch ^ (j & 31)) << 4) + (lo & 1) * 8) = w;
   };

@@ -205,10 +205,28 @@ struct Args {
   int32_t n_sink, n_recent;                         // uncompressed window (0, 0: none)
 };
 
+// Queries of the tile's heads -> LDS as fp32, pre-scaled by the softmax scale.
+template <int HD, int NT, typename T>
+__device__ __forceinline__ void load_queries(float* eq, const T* q, int b, int H_q, int G, int kvh0, float scale, int tid) {
+  const int H_kv = H_q / G;
+  for (int idx = tid; idx < (BN / HD) * G * HD; idx += NT) {
+    const int c = idx % HD, pg = idx / HD;       // pg = head_in_tile * G + g
+    const int kvh = kvh0 + pg / G;
+    float v = 0.f;
+    if (kvh < H_kv) v = Elem<T>::to_f32(q[((int64_t)b * H_q + kvh * G + pg % G) * HD + c]) * scale;
+    eq[pg * HD + c] = v;
+  }
+}
+
+struct EpiSmem {
+  float q[fused::BN * fused::MAXPAIR];               // [(head in tile * G + g)][d], pre-scaled
+  float p[4][fused::MAXPAIR][WM];                    // per wave and pair: softmax numerators of its tokens
+  float ml[4][fused::MAXPAIR][2];                    // per wave and pair: max and sum
+};
 struct Smem {
   float x[BM * XP];
   float w[BK * BN];
-  fused::EpiSmem<4, WM> e;
+  EpiSmem e;
 };
 
 template <bool SWAP>
@@ -280,7 +298,7 @@ __global__ __launch_bounds__(NTHREADS) void fused_decode_f32_kernel(Args a, SeqM
   const int wt = wave >> 1, wc = wave & 1;
   const int last = min(BM, L - j0) - 1;
   const int64_t row0 = meta.start[b] + j0;
-  fused::load_queries<HD, NTHREADS>(sm.e.q, a.q, b, a.H_q, a.G, a.n_ret_heads + n0 / HD, a.scale, tid);
+  load_queries<HD, NTHREADS>(sm.e.q, a.q, b, a.H_q, a.G, a.n_ret_heads + n0 / HD, a.scale, tid);
   floatx16_t acc[4][4];
   gemm_pass<true>(acc, sm, a, a.xa[0] + row0 * a.D, a.xr[0] + row0 * a.m, a.w[0] + n0, last, n0, tid);
   const int jw0 = j0 + wt * WM;

@@ -2,8 +2,8 @@
 // kernel, its score-only half and the stand-alone product.
 //
 // One workgroup of eight waves owns 256 tokens x 256 predicted columns; wave w (wt = w % 4, wc = w / 4)
-// holds 64 tokens x 128 columns (whole heads) in 128 accumulators, so two waves share a SIMD and cover
-// each other's barriers, LDS round trips and issue slots.  With one wave of 128 x 128 per SIMD the matrix
+// holds 64 tokens x 128 columns (whole heads, or SPLIT: half the dims of every head of the tile) in 128 accumulators, so two waves
+// share a SIMD and cover each other's barriers, LDS round trips and issue slots.  With one wave of 128 x 128 per SIMD the matrix
 // pipe was busy 69 % of the time whatever the operands' way into LDS; an MFMA and six other
 // instructions of one wave take 40 cycles, of two waves 32.
 // The chip is power-limited under this loop, and of the two MFMA shapes the smaller one costs less: a loop of
@@ -88,6 +88,7 @@ struct Operands {
   const bf16_t* xr[2];       // ... in the retained cache, pitch m
   const bf16_t* w[2];        // first column of the tile: row-major W + n0, or packed W + n0 * d_in
   int D, m, d_out;           // d_out: pitch of row-major W
+  int run;                   // head dim / 4 (SPLIT)
   int last;                  // last valid token of the tile: rows past it repeat it
   int ncol;                  // valid columns from the tile's first one on (>= 8): those past them repeat the last ones
   int nk, nka, total;        // k-tiles per pass, of them in the anchor row; passes * nk
@@ -111,8 +112,24 @@ struct Copies {
 // Row-major W, dim k: bits 2 and 3 of the chunk from k % 4, bit 1 from k / 8 % 2.
 __device__ __forceinline__ int w_swizzle(int k) { return ((k & 3) << 2) | (((k >> 3) & 1) << 1); }
 
-template <bool PACKED>
-__device__ __forceinline__ void make_copies(Copies& c, const Operands& op, int wave, int lane) {
+// Column of the tile that is column x (0 ... 63) of wave column wc in W part h.  Plain: the wave column has the columns 128 wc ..., part h
+// 64 of them, and a wave whose columns do not exist only copies.  SPLIT (run = head dim / 4): part 0 holds the first halves of the heads' dims, part 1
+// the second ones, and of either half the wave columns take a run each: a dim and its rotation partner stay in one lane, and a wave reads
+// half a token's rotary table entries for all heads of the tile instead of all of them for one.  Where the tile
+// has no columns past 128 both parts' columns x < 32 then fit into one (half): both waves of a SIMD work on them, and there is no second part.
+// The two waves of 64 tokens have to add their scores up, which costs as much as it brings where there are no tables to load: fused
+// decode, plain / SPLIT, us: 8 x 2048-36864 tokens, 32 heads over 8, m = 384, rope 294 / 288, 2 x 40000, m = 512, rope 286 / 279, but 4 x 2000-12000, m =
+// 384, no rope 131 / 137, and with the tables through LDS (the score kernel) 325 / 327.
+// (Whole heads as parts would do the same without a second mapping for half, but rows of row-major W are mostly a multiple of 4 KB apart:
+// with 256 bytes of each in a part instead of two times 128 a multi-head decode took 1.3 % longer.)
+template <bool SPLIT>
+__device__ __forceinline__ int column_of(int run, int wc, int h, int x) {
+  return SPLIT ? x / run * (4 * run) + h * (2 * run) + wc * run + x % run : wc * 128 + h * 64 + x;
+}
+
+template <bool PACKED, bool SPLIT>
+__device__ __forceinline__ void make_copies(Copies& c, const Operands& op, bool half, int wave, int lane) {
+  auto column = [&](int wc, int h, int x) { return SPLIT && half ? column_of<SPLIT>(op.run, wc, x >> 5, x & 31) : column_of<SPLIT>(op.run, wc, h, x); };
   // part row r <-> token 64 (r / 32) + 32 h + r % 32: wave wt reads rows 32 wt .. of either part
   const int r0 = 16 * wave + (lane >> 3);
   c.xrow = (uint32_t)((r0 >> 5) * 64 + (r0 & 31));
@@ -122,7 +139,7 @@ __device__ __forceinline__ void make_copies(Copies& c, const Operands& op, int w
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const int r = r0 + 8 * i, n = min((r >> 6) * 128 + h * 64 + (r & 63), op.ncol - 1);
+        const int r = r0 + 8 * i, n = min(column(r >> 6, h, r & 63), op.ncol - 1);
         c.w[h][i] = (uint32_t)n * (uint32_t)((op.D + op.m) * 2) + (c.ch ^ (i * 64));
       }
   } else {
@@ -130,7 +147,7 @@ __device__ __forceinline__ void make_copies(Copies& c, const Operands& op, int w
     const int ch = (lane & 15) ^ w_swizzle(k);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int n = min((ch >> 3) * 128 + h * 64 + (ch & 7) * 8, op.ncol - 8);
+      const int n = min(column(ch >> 3, h, (ch & 7) * 8), op.ncol - 8);
       c.w[h][0] = (uint32_t)k * (uint32_t)(op.d_out * 2) + (uint32_t)n * 2;
       c.w[h][1] = 0;
     }
@@ -260,12 +277,14 @@ __device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0)
 // Sixteen MFMAs of one (W half, X half), with the phase's LDS reads in up to three parts (read(0 .. 2)) and
 // its two copies (copy(0 .. 1)) with whatever scalar work there is dealt out between them: the two waves of a SIMD run in
 // step, so a burst of other instructions leaves the matrix pipe idle, while a few behind every MFMA are free.
-template <bool SWAP, bool PACKED, class Read, class Copy>
+// HALF: the columns of both parts in one.
+template <bool SWAP, bool PACKED, bool HALF = false, class Read, class Copy>
 __device__ __forceinline__ void mma16(Acc& acc, const WFrag<PACKED>& w, const XFrag& x, int wh, int xh, Read read, Copy copy) {
+  auto block = [&](int b) __attribute__((always_inline)) { return HALF ? 4 * (b >> 1) + (b & 1) : 4 * wh + b; };
   auto mma = [&](int i) __attribute__((always_inline)) {
     const int kk = i >> 3, t = (i >> 2) & 1, b = i & 3;
     const bf16x8_t wf = frag(w, kk, b), xf = __builtin_bit_cast(bf16x8_t, x.v[kk][t]);
-    floatx4_t& d = acc.v[4 * wh + b][2 * xh + t];
+    floatx4_t& d = acc.v[block(b)][2 * xh + t];
     d = SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, xf, d, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, wf, d, 0, 0, 0);
   };
 #pragma unroll
@@ -273,7 +292,7 @@ __device__ __forceinline__ void mma16(Acc& acc, const WFrag<PACKED>& w, const XF
     keep_order();
     mma(i);
     mma(i + 1);
-    asm volatile("" : "+v"(acc.v[4 * wh + (i & 3)][2 * xh + ((i >> 2) & 1)]), "+v"(acc.v[4 * wh + (i & 3) + 1][2 * xh + ((i >> 2) & 1)]));
+    asm volatile("" : "+v"(acc.v[block(i & 3)][2 * xh + ((i >> 2) & 1)]), "+v"(acc.v[block((i & 3) + 1)][2 * xh + ((i >> 2) & 1)]));
     keep_order();
     read(i >> 1);
   }
@@ -291,7 +310,7 @@ __device__ __forceinline__ void mma16(Acc& acc, const WFrag<PACKED>& w, const XF
   }
   keep_order();
 #pragma unroll
-  for (int b = 0; b < 4; ++b) asm volatile("" : "+v"(acc.v[4 * wh + b][2 * xh]), "+v"(acc.v[4 * wh + b][2 * xh + 1]));
+  for (int b = 0; b < 4; ++b) asm volatile("" : "+v"(acc.v[block(b)][2 * xh]), "+v"(acc.v[block(b)][2 * xh + 1]));
 }
 
 __device__ __forceinline__ void barrier() {
@@ -302,17 +321,17 @@ __device__ __forceinline__ void barrier() {
 template <int N> __device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // State of a workgroup's product that outlives a pass.
-template <bool PACKED> struct Pipe {
+template <bool PACKED, bool SPLIT> struct Pipe {
   Operands op;
   Copies cp;
   Lanes<PACKED> ln;
   char* smem;
   int wave, lane;
-  bool active;               // this wave's columns exist: otherwise it only copies and meets the others
+  bool half;                 // no columns past 128.  SPLIT: of the tile, W1 is neither copied nor multiplied; plain: this wave's do not exist
 
-  // Requests k-tile 0 and all of k-tile 1 but its W1 (phase 1 of tile 0 does).  op, smem, wave, lane, active are set.
+  // Requests k-tile 0 and all of k-tile 1 but its W1 (phase 1 of tile 0 does).  op, smem, wave, lane, half are set.
   __device__ __forceinline__ void begin() {
-    make_copies<PACKED>(cp, op, wave, lane);
+    make_copies<PACKED, SPLIT>(cp, op, half, wave, lane);
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const Src s = source_of<PACKED>(op, t);
@@ -320,8 +339,9 @@ template <bool PACKED> struct Pipe {
       for (int part = 0; part < 4 - t; ++part)       // Xa, W0, Xb, W1: the order in which they are waited for
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
+          if (SPLIT && part == 3 && half) continue;
           if (part & 1) copy_w<PACKED>(smem, op, cp, s, t, part >> 1, i, wave);
-          else copy_x(smem, op, cp, s, t, t ^ (part >> 1), i, wave);
+          else copy_x(smem, op, cp, s, t, (SPLIT && half ? 0 : t) ^ (part >> 1), i, wave);
         }
     }
   }
@@ -383,6 +403,62 @@ template <bool PACKED> struct Pipe {
     }
     src = s2;
   }
+  // SPLIT, a tile with no columns past 128: two phases, X0 and X1, the copies a tile and a half ahead as well.  W0's fragments of the
+  // next tile are read beside the second phase into the registers that W1's would take.  1.1 us per tile where 256 columns take
+  // 1.6 (with 128 columns to each of four waves and the others only copying 1.17; with the parts in a ring of eight, two tiles
+  // ahead, 1.27: twice the scalar instructions).
+  //   phase 1  MFMA W0 X0 | read X1            | copy X0, W0 of tile t+2 -> wait for X0 W0 of t+1, barrier
+  //   phase 2  MFMA W0 X1 | read W0, X0 of t+1 | copy X1 of tile t+2     -> wait for X1 of t+1, barrier
+  template <bool SWAP>
+  __device__ __forceinline__ void half_tile(Acc& acc, XFrag (&x)[2], WFrag<PACKED>& w, WFrag<PACKED>& next, int t, Src& s2) {
+    const int st = t & 1;
+    Src s3;                                  // of tile t + 3; s2: of tile t + 2
+    mma16<SWAP, PACKED, true>(acc, w, x[0], 0, 0, [&](int i) __attribute__((always_inline)) {
+      if (i == 0) read_x<1>(x[1], ln.x);
+    }, [&](int i) __attribute__((always_inline)) {
+      copy_x(smem, op, cp, s2, st, 0, i, wave);
+      copy_w<PACKED>(smem, op, cp, s2, st, 0, i, wave);
+    });
+    wait_x(x[1]);
+    wait_copies<6>();
+    barrier();
+    ln.next_stage();
+    mma16<SWAP, PACKED, true>(acc, w, x[1], 0, 1, [&](int i) __attribute__((always_inline)) {
+      if (i == 0) { read_w<0, 0>(next, ln); read_w<0, 1>(next, ln); }
+      if (i == 1) { read_w<0, 2>(next, ln); read_w<0, 3>(next, ln); }
+      if (i == 2) read_x<0>(x[0], ln.x);
+    }, [&](int i) __attribute__((always_inline)) {
+      copy_x(smem, op, cp, s2, st, 1, i, wave);
+      if (i == 1) {
+        int t3 = t + 3;
+        asm volatile("" : "+s"(t3));
+        s3 = source_of<PACKED>(op, t3);
+      }
+    });
+    wait_w(next);
+    wait_x(x[0]);
+    wait_copies<6>();
+    barrier();
+    s2 = s3;
+  }
+  template <bool SWAP>
+  __device__ __forceinline__ void half_tiles(Acc& acc, int t0) {
+    XFrag x[2];
+    WFrag<PACKED> w0, w1;
+    read_x<0>(x[0], ln.x);
+    read_w<0, 0>(w0, ln); read_w<0, 1>(w0, ln); read_w<0, 2>(w0, ln); read_w<0, 3>(w0, ln);
+    wait_w(w0);
+    wait_x(x[0]);
+    barrier();                               // X0, W0 of the first tile are free
+    const int t1 = t0 + op.nk;
+    int t = t0;
+    Src s2 = source_of<PACKED>(op, t0 + 2);
+    for (; t + 1 < t1; t += 2) {
+      half_tile<SWAP>(acc, x, w0, w1, t, s2);
+      half_tile<SWAP>(acc, x, w1, w0, t + 1, s2);
+    }
+    if (t < t1) half_tile<SWAP>(acc, x, w0, w1, t, s2);
+  }
   template <bool SWAP, bool IDLE>
   __device__ __forceinline__ void tiles(Acc& acc, int t0) {
     XFrag x[2];
@@ -415,10 +491,15 @@ template <bool PACKED> struct Pipe {
     // between two passes would be spilled
     int l = lane;
     asm volatile("" : "+v"(l));
-    make_copies<PACKED>(cp, op, wave, l);
+    make_copies<PACKED, SPLIT>(cp, op, half, wave, l);
     ln.init(smem + (t0 & 1) * kStage, wave & 3, wave >> 2, l);
-    if (active) tiles<SWAP, false>(acc, t0);
-    else tiles<SWAP, true>(acc, t0);
+    if constexpr (SPLIT) {
+      if (half) half_tiles<SWAP>(acc, t0);
+      else tiles<SWAP, false>(acc, t0);
+    } else {
+      if (half) tiles<SWAP, true>(acc, t0);
+      else tiles<SWAP, false>(acc, t0);
+    }
   }
   // (own LDS writes done, this wave's copies of tile 0 landed, everyone's after the barrier)
   __device__ __forceinline__ void first_landed() {
