@@ -70,11 +70,180 @@ struct AttnArgs {
 template <typename T, int LPR, int GT, int NWAVES>
 constexpr int attn_split_smem_bytes() { return NWAVES * GT * (2 + LPR * Elem<T>::kVec) * 4; }
 
+// Tokens and rows of one workgroup's chunk.
+struct ChunkRows {
+  int64_t row0;             // pool row of token 0
+  int beg, end;             // the compressed rows outside the window, or all window rows
+  bool window;
+  template <typename T>
+  __device__ __forceinline__ ChunkRows(const AttnArgs<T>& a, const SeqMeta& meta, int b, int chunk, int L) {
+    window = a.row_mode == 3;
+    row0 = a.row_mode == 0 ? meta.start[b]
+         : a.row_mode == 1 ? (int64_t)meta.sbase[b] * kSlotTokens
+         : window ? (int64_t)(a.seq0 + b) * a.win.rows() : 0;
+    beg = window ? 0 : max(chunk * a.split_tokens, a.win.lo(L));
+    end = window ? a.win.rows() : min(a.win.hi(L), chunk * a.split_tokens + a.split_tokens);
+  }
+};
+// The waves' sums of GT query heads, in LDS relative to their maxima, added up and written as one partial.
+template <int GT, int NWAVES, int ROW, typename T>
+__device__ __forceinline__ void write_chunk_partial(const AttnArgs<T>& a, const SeqMeta& meta, int b, int chunk, int qh0,
+                                                    const float (*s_m)[GT], const float (*s_l)[GT], const float (*s_o)[GT][ROW]) {
+  __syncthreads();
+  const int slot = a.row_mode == 3 ? a.win_slot0 + b : meta.sbase[b] + chunk * (a.split_tokens / a.slot_tokens);
+  for (int idx = threadIdx.x; idx < GT * a.d; idx += 64 * NWAVES) {
+    const int g = idx / a.d, c = idx % a.d;
+    float M = s_m[0][g];
+#pragma unroll
+    for (int w = 1; w < NWAVES; ++w) M = fmaxf(M, s_m[w][g]);
+    float l = 0.f, acc = 0.f;
+#pragma unroll
+    for (int w = 0; w < NWAVES; ++w) {
+      const float e = (s_m[w][g] == -INFINITY) ? 0.f : __expf(s_m[w][g] - M);
+      l += s_l[w][g] * e; acc += s_o[w][g][c] * e;
+    }
+    const int64_t ph = (int64_t)slot * a.H_q + qh0 + g;
+    a.part_o[ph * a.d + c] = acc;
+    if (c == 0) { a.part_ml[ph * 2] = M; a.part_ml[ph * 2 + 1] = l; }
+  }
+}
+
+// Sums over the four lanes of a quad of four values: lane i of it ends up with the sum of the i-th.
+__device__ __forceinline__ float sum_quad4(float t0, float t1, float t2, float t3, int lane) {
+  const bool odd = lane & 1, high = lane & 2;
+  const float a0 = (odd ? t1 : t0) + dpp_move<0xB1>(odd ? t0 : t1), a1 = (odd ? t3 : t2) + dpp_move<0xB1>(odd ? t2 : t3);
+  return (high ? a1 : a0) + dpp_move<0x4E>(high ? a0 : a1);
+}
+
+// attn_split_body for four query heads of a KV head and bf16 rows of 128 dims.  What bounds it: with rotary tables, the vector unit: a row is 16
+// lanes of 8 dims, and scores, softmax and value sums of four heads in each of them were 200 instructions per row.  Here lane % 4
+// stands for the query head wherever a value is the same for all lanes of a row: the scores' sums end there (11 instructions instead of 16), the
+// softmax is worked out once per quad instead of four times, the values are multiplied four heads at a time by v_mfma_f32_4x4x1
+// (fma_heads), rotation partners, eight lanes away, come by row rotation instead of through LDS.
+// Whole calls, 32 heads over 8, before / so, us: 8 x 2048-36864 tokens, 3 heads retained, rope and window 292 / 285, 2 x 40000, 4 retained, the same
+// 283 / 274, without rope 260 / 248, 8 x 6000, 7 retained, rope 135 / 120; 64 heads over 8, 4 x 5000, 4 retained, rope 93.9 / 83.6.  Rows of
+// 64 dims, whose quads are two to a row, lose what they win (4 x 5000 tokens 23.8 / 24.6): attn_split_body.
+template <int NWAVES, int UN>
+__device__ __forceinline__ void attn_split_body4(const AttnArgs<bf16_t>& a, const SeqMeta& meta, int b, int chunk, int y, char* smem) {
+  constexpr int GT = 4, LPR = 16, RPW = 64 / LPR, NRG = NWAVES * RPW;
+  const int L = meta.len[b];
+  const int gchunks = a.G / GT, hl = y / gchunks;
+  const int qh0 = (a.head0 + hl) * a.G + (y % gchunks) * GT;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rl = lane / LPR, li = lane % LPR;
+  const ChunkRows rows(a, meta, b, chunk, L);
+  const int col = a.col0 + hl * a.d + li * 8;
+  const bool rope = a.rope_cos != nullptr;
+  const int hc = (li % (LPR / 2)) * 8;            // this lane's first column in the d/2-wide tables
+  const float sgn = (li < LPR / 2) ? -1.f : 1.f;
+  float qv[GT][8];
+#pragma unroll
+  for (int g = 0; g < GT; ++g) {
+    load16<bf16_t>(a.q + ((int64_t)b * a.H_q + qh0 + g) * a.d + li * 8, qv[g]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) qv[g][i] *= a.scale;
+  }
+  float mx = -INFINITY, sm = 0.f;                 // of query head lane % 4, this lane's row group
+  floatx4_t o[8];                                 // [dim][query head]
+#pragma unroll
+  for (int i = 0; i < 8; ++i) o[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  // (uniform: MFMAs take all lanes, so row groups past the end go on with rows that count for nothing)
+  for (int jb = rows.beg + wave * RPW; jb < rows.end; jb += NRG * UN) {
+    uint4 kr[UN], vr[UN];
+    int pos[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int j = jb + rl + u * NRG, jj = min(j, rows.end - 1);
+      kr[u] = *reinterpret_cast<const uint4*>(a.k + (rows.row0 + jj) * a.ld + col);
+      vr[u] = *reinterpret_cast<const uint4*>(a.v + (rows.row0 + jj) * a.ld + col);
+      pos[u] = rows.window ? a.win.pos_of(jj, L) : jj;
+      if (j >= rows.end) pos[u] = -1;
+    }
+    float sc[UN], mn = mx;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      float k[8];
+      unpack_bf16x8(kr[u], k);
+      if (rope) {        // feature i pairs with i + d/2, held by the lane LPR / 2 away
+        const int64_t at = (int64_t)max(pos[u], 0) * (a.d / 2) + hc;
+        float cs[8], sn[8];
+#pragma unroll
+        for (int i = 0; i < 8; i += 4) {
+          const float4 c4 = *reinterpret_cast<const float4*>(a.rope_cos + at + i), s4 = *reinterpret_cast<const float4*>(a.rope_sin + at + i);
+          cs[i] = c4.x; cs[i + 1] = c4.y; cs[i + 2] = c4.z; cs[i + 3] = c4.w;
+          sn[i] = s4.x; sn[i + 1] = s4.y; sn[i + 2] = s4.z; sn[i + 3] = s4.w;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float other = dpp_move<0x128>(k[i]);      // rotate the row by 8
+          k[i] = fmaf(k[i], cs[i], sgn * other * sn[i]);
+        }
+      }
+      float t[GT];
+#pragma unroll
+      for (int g = 0; g < GT; ++g) {
+        t[g] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[g] = fmaf(qv[g][i], k[i], t[g]);
+      }
+      float s = sum_quad4(t[0], t[1], t[2], t[3], lane);
+      s += dpp_move<0x124>(s);                    // rotate the row by 4, by 8
+      s += dpp_move<0x128>(s);
+      sc[u] = pos[u] >= 0 ? s : -INFINITY;
+      mn = fmaxf(mn, sc[u]);
+    }
+    const float ref = mn == -INFINITY ? 0.f : mn;
+    const float corr = __expf(mx - ref);          // mx = -inf at the start: 0, and o, sm are 0
+    float p[UN], ps = 0.f;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) { p[u] = __expf(sc[u] - ref); ps += p[u]; }     // a dead row: exp(-inf) = 0
+    sm = sm * corr + ps;
+    mx = mn;
+    const float c0 = dpp_move<0x00>(corr), c1 = dpp_move<0x55>(corr), c2 = dpp_move<0xAA>(corr), c3 = dpp_move<0xFF>(corr);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { o[i][0] *= c0; o[i][1] *= c1; o[i][2] *= c2; o[i][3] *= c3; }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      float v[8];
+      const uint32_t m = pos[u] >= 0 ? ~0u : 0u;  // (0 times what a dead row holds may not be 0)
+      unpack_bf16x8(make_uint4(vr[u].x & m, vr[u].y & m, vr[u].z & m, vr[u].w & m), v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[i] = fma_heads(p[u], v[i], o[i]);
+    }
+  }
+  // merge the row groups: first inside the wave, then across waves in LDS
+  float (*s_m)[GT] = reinterpret_cast<float (*)[GT]>(smem);
+  float (*s_l)[GT] = s_m + NWAVES;
+  float (*s_o)[GT][LPR * 8] = reinterpret_cast<float (*)[GT][LPR * 8]>(s_l + NWAVES);
+  float M = mx;
+#pragma unroll
+  for (int off = LPR; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+  const float w = mx == -INFINITY ? 0.f : __expf(mx - M);
+  float l = sm * w;
+#pragma unroll
+  for (int off = LPR; off < 64; off <<= 1) l += __shfl_xor(l, off, 64);
+  if (lane < GT) { s_m[wave][lane] = M; s_l[wave][lane] = l; }
+  const float w0 = dpp_move<0x00>(w), w1 = dpp_move<0x55>(w), w2 = dpp_move<0xAA>(w), w3 = dpp_move<0xFF>(w);
+  float r[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    r[i] = sum_rows(o[i][0] * w0, o[i][1] * w1, o[i][2] * w2, o[i][3] * w3);      // row g of 16 lanes: query head g
+  }
+  float* dst = &s_o[wave][lane >> 4][li * 8];
+  *reinterpret_cast<float4*>(dst) = make_float4(r[0], r[1], r[2], r[3]);
+  *reinterpret_cast<float4*>(dst + 4) = make_float4(r[4], r[5], r[6], r[7]);
+  write_chunk_partial<GT, NWAVES, LPR * 8>(a, meta, b, chunk, qh0, s_m, s_l, s_o);
+}
+
 // One workgroup of NWAVES waves: chunk `chunk` of sequence b, y = KV head * (G / GT) + group of query heads.
 // UN: rows of a row group in flight (4; 8 where few waves share a compute unit).
 template <typename T, int LPR, int GT, int NWAVES, int UN = 4>
 __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqMeta& meta, int b, int chunk,
                                                 int y, char* smem) {
+  if constexpr (GT == 4 && LPR == 16 && sizeof(T) == 2) {
+    attn_split_body4<NWAVES, UN>(a, meta, b, chunk, y, smem);
+    return;
+  }
   constexpr int VEC = Elem<T>::kVec;
   constexpr int RPW = 64 / LPR;        // row groups per wave
   constexpr int NRG = NWAVES * RPW;    // row groups per block
@@ -85,14 +254,11 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqM
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rg = wave * RPW + lane / LPR;        // row group in block
   const int li = lane % LPR;                     // lane within row
-  const bool wmode = a.row_mode == 3;
-  const int64_t row0 = a.row_mode == 0 ? meta.start[b]
-                     : a.row_mode == 1 ? (int64_t)meta.sbase[b] * kSlotTokens
-                     : wmode ? (int64_t)(a.seq0 + b) * a.win.rows() : 0;
+  const ChunkRows rows(a, meta, b, chunk, L);
+  const bool wmode = rows.window;
+  const int64_t row0 = rows.row0;
   const int col = a.col0 + hl * a.d + li * VEC;
-  // tokens of this chunk: the compressed rows outside the window, or all window rows
-  const int jbeg = wmode ? 0 : max(chunk * a.split_tokens, a.win.lo(L));
-  const int jend = wmode ? a.win.rows() : min(a.win.hi(L), chunk * a.split_tokens + a.split_tokens);
+  const int jbeg = rows.beg, jend = rows.end;
   const bool rope = a.rope_cos != nullptr;
   const int hc = (li % (LPR / 2)) * VEC;          // this lane's first column in the d/2-wide tables
 
@@ -196,23 +362,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqM
     }
     if (lane == 0) { s_m[wave][g] = M; s_l[wave][g] = l; }
   }
-  __syncthreads();
-  const int slot = wmode ? a.win_slot0 + b : meta.sbase[b] + chunk * (a.split_tokens / a.slot_tokens);
-  for (int idx = threadIdx.x; idx < GT * a.d; idx += 64 * NWAVES) {
-    const int g = idx / a.d, c = idx % a.d;
-    float M = s_m[0][g];
-#pragma unroll
-    for (int w = 1; w < NWAVES; ++w) M = fmaxf(M, s_m[w][g]);
-    float l = 0.f, acc = 0.f;
-#pragma unroll
-    for (int w = 0; w < NWAVES; ++w) {
-      const float e = (s_m[w][g] == -INFINITY) ? 0.f : __expf(s_m[w][g] - M);
-      l += s_l[w][g] * e; acc += s_o[w][g][c] * e;
-    }
-    const int64_t ph = (int64_t)slot * a.H_q + qh0 + g;
-    a.part_o[ph * a.d + c] = acc;
-    if (c == 0) { a.part_ml[ph * 2] = M; a.part_ml[ph * 2 + 1] = l; }
-  }
+  write_chunk_partial<GT, NWAVES, LPR * VEC>(a, meta, b, chunk, qh0, s_m, s_l, s_o);
 }
 template <typename T, int LPR, int GT>
 __global__ __launch_bounds__(256) void attn_split_kernel(AttnArgs<T> a, SeqMeta meta) {

@@ -110,21 +110,6 @@ __device__ __forceinline__ KExtra make_kextra(const float* cos, const float* sin
   return x;
 }
 
-// Sums over the four 16-lane rows of a wave (rows 0 + 1 and 2 + 3, then both) of four values: row i ends up with the sums of the
-// i-th.  Six instructions; with every row holding all four sums it would be sixteen and a selection.
-__device__ __forceinline__ float sum_rows(float a, float b, float c, float d) {
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(c), __float_as_uint(d), false, false);
-  const float ab = __uint_as_float(p[0]) + __uint_as_float(p[1]), cd = __uint_as_float(q[0]) + __uint_as_float(q[1]);
-  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(ab), __float_as_uint(cd), false, false);
-  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
-}
-
-// Four query heads against a lane's own values on the matrix pipe: v_mfma_f32_4x4x1 has 16 blocks of four lanes, and with row i of
-// A = query head i, d[i] += a of the block's lane i * this lane's b, in fp32.  8 cycles for what takes the vector unit
-// 4 per head, which meanwhile rotates the keys of the SIMD's other wave.
-__device__ __forceinline__ floatx4_t fma_heads(float a, float b, floatx4_t d) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, d, 0, 0, 0); }
-
 // A wave's share of the tile's heads (see column_of): N heads, of each CBH blocks of 16 columns; blocks b and b + HB are rotation partners.
 template <int HD, bool SPLIT> struct Part {
   static constexpr int N = (SPLIT ? BN : WN) / HD, CBH = 8 / N, HB = CBH / 2;

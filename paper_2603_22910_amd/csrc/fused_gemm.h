@@ -50,7 +50,6 @@ namespace echokv {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
 #ifndef ECHOKV_LDS
 #define ECHOKV_LDS __attribute__((address_space(3)))
 #endif
