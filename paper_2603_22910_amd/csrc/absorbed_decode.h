@@ -428,9 +428,9 @@ __global__ __launch_bounds__(NT) void softmax_stats_kernel(Args a, SeqMeta meta)
 #pragma unroll
   for (int c = 1; c < 4; ++c) ml_merge(M[0], l[0], M[c], l[c]);
   // over the wave, then over the waves
-  const float Mw = wave_max(M[0], 64);
+  const float Mw = wave_max64(M[0]);
   float lw = M[0] == -INFINITY ? 0.f : l[0] * exp2f(M[0] - Mw);
-  lw = wave_sum(lw, 64);
+  lw = wave_sum64(lw);
   if (lane == 0) { s_m[wave] = Mw; s_l[wave] = lw; }
   __syncthreads();
   if (tid == 0) {
@@ -565,8 +565,9 @@ __global__ __launch_bounds__(kPvWaves * 64, QUARTERS ? 1 : 2) void pv_kernel(Arg
         for (int e = 0; e < 4; ++e)
           if (j + e >= io.vlo && j + e < io.vhi) ml_push(m0, l0, xs[e]);
       }
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) ml_merge(m0, l0, __shfl_xor(m0, o, 64), __shfl_xor(l0, o, 64));
+    ml_merge(m0, l0, dpp_move<0xB1>(m0), dpp_move<0xB1>(l0));        // neighbours, pairs, quads (see row_sum)
+    ml_merge(m0, l0, dpp_move<0x4E>(m0), dpp_move<0x4E>(l0));
+    ml_merge(m0, l0, dpp_move<0x141>(m0), dpp_move<0x141>(l0));
     if ((tid & 7) == 0) {
       s_ml[h][0] = m0; s_ml[h][1] = l0;
       if (ct == 0 && hs) { mls[2 * h] = m0; mls[2 * h + 1] = l0; }
@@ -705,9 +706,52 @@ __global__ __launch_bounds__(256) void y_sum_kernel(Args a, SeqMeta meta) {
   __shared__ float4 s_acc[SG][CQ];
   const float* mlp = a.ml + ((int64_t)s0 * a.H_pad + h) * 2;
   const int64_t mls = (int64_t)a.H_pad * 2;
+  // Few splits: every wave works out all weights itself, and the rows are requested ahead of them: one round trip to memory
+  // and one barrier instead of three and four.  Whole calls, with the wave reductions on the vector unit, us: d_in 1536, 2 x 1500 tokens 33.9 -> 33.5,
+  // 8 x 300-4000 56.2 -> 54.9, 40000 86.6 -> 85.3, value-absorbed 4 x 1000-9000 with rope and window 101.4 -> 100.0; d_in 5120, 300 tokens 47.8 -> 46.6.
+  constexpr int NF = SG == 1 ? 8 : 16;
+  if (ns <= SG * NF) {
+    const float* ml = mlp + min(lane, ns - 1) * mls;
+    const float pm = lane < ns ? ml[0] : -INFINITY, pl = ml[1];
+    const float* yp = a.ypart + ((int64_t)s0 * a.H_pad + h) * a.d_in + k;
+    const int64_t yps = (int64_t)a.H_pad * a.d_in;
+    float4 v[NF];
+#pragma unroll
+    for (int u = 0; u < NF; ++u)
+      if (sg + SG * u < ns) v[u] = *reinterpret_cast<const float4*>(yp + (sg + SG * u) * yps);
+    __builtin_amdgcn_sched_barrier(0);
+    const float M = wave_max64(pm);
+    const float w = pm == -INFINITY ? 0.f : exp2f(pm - M);
+    const float l = wave_sum64(lane < ns ? w * pl : 0.f);
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < NF; ++u)
+      if (sg + SG * u < ns) {                          // (uniform over a wave: groups are whole waves)
+        const float wu = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), __builtin_amdgcn_readfirstlane(sg) + SG * u));
+        acc.x = fmaf(wu, v[u].x, acc.x); acc.y = fmaf(wu, v[u].y, acc.y);
+        acc.z = fmaf(wu, v[u].z, acc.z); acc.w = fmaf(wu, v[u].w, acc.w);
+      }
+    if constexpr (SG > 1) {
+      s_acc[sg][cq] = acc;
+      __syncthreads();
+      if (sg != 0) return;
+#pragma unroll
+      for (int g = 1; g < SG; ++g) {
+        acc.x += s_acc[g][cq].x; acc.y += s_acc[g][cq].y; acc.z += s_acc[g][cq].z; acc.w += s_acc[g][cq].w;
+      }
+    }
+    const float inv = l > 0.f ? 1.f / l : 0.f;       // l == 0: every counted token sits in the window
+    acc.x *= inv; acc.y *= inv; acc.z *= inv; acc.w *= inv;
+    *reinterpret_cast<float4*>(a.y + ((int64_t)b * a.H_q + h) * a.d_in + k) = acc;
+    if (blockIdx.x == 0 && tid == 0) {
+      a.y_ml[((int64_t)b * a.H_q + h) * 2] = M;
+      a.y_ml[((int64_t)b * a.H_q + h) * 2 + 1] = l;
+    }
+    return;
+  }
   float M = -INFINITY;
   for (int i = tid; i < ns; i += 256) M = fmaxf(M, mlp[i * mls]);
-  M = wave_max(M, 64);
+  M = wave_max64(M);
   if (lane == 0) s_red[wave] = M;
   __syncthreads();
   M = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
@@ -734,7 +778,7 @@ __global__ __launch_bounds__(256) void y_sum_kernel(Args a, SeqMeta meta) {
       acc.z = fmaf(wj, v.z, acc.z); acc.w = fmaf(wj, v.w, acc.w);
     }
   }
-  l = wave_sum(l, 64);
+  l = wave_sum64(l);
   s_acc[sg][cq] = acc;
   __syncthreads();              // s_red was read above by every thread
   if (lane == 0) s_red[wave] = l;
@@ -868,11 +912,11 @@ __global__ __launch_bounds__(256) void out_final_kernel(Args a, int nseq) {
   const int64_t n = (int64_t)nseq * a.H_q * a.d;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= n) return;
-  float v = 0.f;
-#pragma unroll 4
-  for (int ks = 0; ks < a.k_slices; ++ks) v += a.opart[(int64_t)ks * n + idx];
   const int64_t bh = idx / a.d;
   const float M2 = a.y_ml[bh * 2], lY = a.y_ml[bh * 2 + 1];
+  float v = 0.f;
+#pragma unroll 8
+  for (int ks = 0; ks < a.k_slices; ++ks) v += a.opart[(int64_t)ks * n + idx];
   float M = lY > 0.f ? M2 * 0.6931471805599453f : -INFINITY;     // natural-exponent units
   float denom = lY;
   if (a.win_po) {

@@ -27,6 +27,9 @@
 //   H_q/H_kv = 32/8, m = 512:  1 x 1000 tokens 84 -> 22 (with rotary tables and window 110 -> 26), 1 x 6000 86 -> 54
 //   H_q/H_kv = 32/32, m = 2048: 1 x 500 tokens 225 -> 59, 1 x 1000 225 -> 76
 //   fp32, 8 heads of 64, m = 256: 1 x 512 tokens 464 -> 17, 1 x 8000 509 -> 71
+// With scores and value sums of three and more query heads per KV head on the matrix pipe, wave reductions on the vector unit and the
+// merge without barriers, H_q/H_kv = 32/8, m = 512, rotary tables and window: 1 x 300 tokens 22.7 -> 20.8, 1 x 1000 23.0 -> 21.1, 1 x 3000 32.7 -> 30.1;
+// without: 1 x 1000 22.3 -> 20.9; m = 384, packed W, 4 x 500-1500 58.4 -> 55.5
 #pragma once
 #include "common.h"
 #include "fused_decode.h"
@@ -379,6 +382,30 @@ __device__ __forceinline__ void rope_score_shares(Acc<bf16_t, HD, TB>& acc, Smem
         hi[j + e] = fmaf(y, cs[e], x * sn[e]);
       }
     }
+    if (G > fused::kVectorHeads) {       // four query heads at a time on the matrix pipe (see fma_heads)
+#pragma nounroll
+      for (int g0 = 0; g0 < G; g0 += 4) {
+        const float* qs = &sm.q[(hw * G + min(g0 + (lane & 3), G - 1)) * HD + h0];
+        floatx4_t s4[2] = {floatx4_t{0.f, 0.f, 0.f, 0.f}, floatx4_t{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int j = 0; j < 32; j += 4) {
+          const float4 a4 = *reinterpret_cast<const float4*>(qs + j), b4 = *reinterpret_cast<const float4*>(qs + HD / 2 + j);
+          const float qa[4] = {a4.x, a4.y, a4.z, a4.w}, qb[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            s4[0] = fma_heads(qa[e], lo[j + e], s4[0]);
+            s4[1] = fma_heads(qb[e], hi[j + e], s4[1]);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float s = s4[0][i] + s4[1][i];
+          if constexpr (HD == 128) s = add_row_pair(s);
+          if (g0 + i < G && (HD == 64 || (o & 1) == 0)) sm.s[kq][hw * G + g0 + i][row] = s;
+        }
+      }
+      continue;
+    }
 #pragma nounroll
     for (int g = 0; g < G; ++g) {
       const float* qs = &sm.q[(hw * G + g) * HD + h0];
@@ -403,6 +430,35 @@ __device__ __forceinline__ void value_shares(Acc<T, HD, TB>& acc, Smem<TB>& sm, 
   using C = Cfg<T, HD>;
   const int c = lane & 15, o = lane >> 4;
   const int hw = C::HPT == 2 ? c >> 3 : 0;
+  if constexpr (sizeof(T) == 2) {
+    if (G > fused::kVectorHeads) {       // four query heads at a time on the matrix pipe (see fma_heads)
+#pragma nounroll
+      for (int g0 = 0; g0 < G; g0 += 4) {
+        const float* ps = sm.p[hw * G + min(g0 + (lane & 3), G - 1)] + 4 * o;
+        floatx4_t v[C::VW];
+#pragma unroll
+        for (int i = 0; i < C::VW; ++i) v[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) {
+          const float4 p4 = *reinterpret_cast<const float4*>(ps + tb * 16);
+          const float p[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int i = 0; i < C::VW; ++i) v[i] = fma_heads(p[r], acc.v[i][tb][r], v[i]);
+        }
+        float x[C::VW];
+#pragma unroll
+        for (int i = 0; i < C::VW; ++i) x[i] = sum_rows(v[i][0], v[i][1], v[i][2], v[i][3]);      // row o: query head g0 + o
+        if (g0 + o < G) {
+          float* dst = &sm.o[kq][(hw * G + g0 + o) * HD + C::VW * c % HD];
+          *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
+          *reinterpret_cast<float4*>(dst + 4) = make_float4(x[4], x[5], x[6], x[7]);
+        }
+      }
+      return;
+    }
+  }
 #pragma nounroll
   for (int g = 0; g < G; ++g) {
     const int pair = hw * G + g;
@@ -492,9 +548,9 @@ __device__ __forceinline__ void fused_tile(const Args<T>& a, const StreamMeta& m
       const int tok = j0 + lane;
       if (tok < x.lo || tok >= x.hi) s = -INFINITY;
     }
-    const float mx = wave_max(s, 64);
+    const float mx = wave_max64(s);
     const float p = s == -INFINITY ? 0.f : __expf(s - mx);
-    const float sum = wave_sum(p, 64);
+    const float sum = wave_sum64(p);
     if (lane < TOK) sm.p[pr][lane] = p;
     if (lane == 0) { sm.ml[pr][0] = mx; sm.ml[pr][1] = sum; }
   }

@@ -305,7 +305,7 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs<TO> a, SeqMeta meta
     if (dim == 0 && a.lse) a.lse[oh] = M + __logf(ll);
   };
   auto block_reduce = [&](float v, bool is_max) -> float {    // fixed order: same bits every run
-    v = is_max ? wave_max(v, 64) : wave_sum(v, 64);
+    v = is_max ? wave_max64(v) : wave_sum64(v);
     __syncthreads();                // s_red may still be read from the previous reduction
     if (lane == 0) s_red[wave] = v;
     __syncthreads();
@@ -320,26 +320,26 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs<TO> a, SeqMeta meta
   constexpr int NF = 8;
   if (DS == 1 && n <= NG * NF) {
     const int grp = tid >> 5, q4 = (tid & 31) * 4;
-    const float* ml = a.part_ml + ph_of(min(tid, n - 1)) * 2;
+    const float* ml = a.part_ml + ph_of(min(lane, n - 1)) * 2;
     const float pm = ml[0], pl = ml[1];
     float4 o[NF];
 #pragma unroll
     for (int u = 0; u < NF; ++u)
       if (grp + NG * u < n && q4 < a.d) o[u] = *reinterpret_cast<const float4*>(a.part_o + ph_of(grp + NG * u) * a.d + q4);
     __builtin_amdgcn_sched_barrier(0);
-    // (as below: a partial that covers no token has -inf and weight 0, and one at least covers a token)
-    const float M = block_reduce(tid < n ? pm : -INFINITY, true);
-    const float w = tid < n ? __expf(pm - M) : 0.f;
-    s_w[tid] = w;
-    const float ll = block_reduce(w * pl, false);      // (its barriers publish the weights, too)
+    // Every wave for itself: the barriers of two reductions over the workgroup took 0.5 us (fp32, 512 tokens, 14.7 -> 14.2; as below: a partial that covers no token has -inf and weight 0, and one at least covers a token)
+    const float M = wave_max64(lane < n ? pm : -INFINITY);
+    const float w = lane < n ? __expf(pm - M) : 0.f;
+    const float ll = wave_sum64(w * pl);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int u = 0; u < NF; ++u)
+    for (int u = 0; u < NF; ++u) {
+      const float wu = __shfl(w, grp + NG * u, 64);
       if (grp + NG * u < n && q4 < a.d) {
-        const float wu = s_w[grp + NG * u];
         acc[0] = fmaf(wu, o[u].x, acc[0]); acc[1] = fmaf(wu, o[u].y, acc[1]);
         acc[2] = fmaf(wu, o[u].z, acc[2]); acc[3] = fmaf(wu, o[u].w, acc[3]);
       }
+    }
     if (q4 < a.d) *reinterpret_cast<float4*>(&s_acc[grp][q4]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
     __syncthreads();
     if (tid < a.d) {
