@@ -1276,7 +1276,17 @@ int echokv_cache_append(const echokv_shape* shape, echokv_layer_cache* dst, cons
   if (total > 0 && (!k_new || !v_new)) return ECHOKV_ERR_NULL;
   if (total > INT32_MAX) return ECHOKV_ERR_SHAPE;
   hipStream_t st = (hipStream_t)hip_stream;
-  if (dst->width > 0) {
+  if (dst->width > 0 && total > 0 && total <= kListedRows) {
+    RowList c;
+    c.src[0] = (const char*)k_new; c.src[1] = (const char*)v_new;
+    c.dst[0] = (char*)dst->k; c.dst[1] = (char*)dst->v;
+    c.src_row_bytes = (int64_t)dm.D * dm.es; c.dst_row_bytes = (int64_t)dst->width * dm.es;
+    int r = 0;
+    for (int b = 0; b < dst->batch; ++b)
+      for (int i = 0; i < n_new[b]; ++i) c.to[r++] = dst->seq_start[b] + dst->seq_len[b] + i;
+    hipLaunchKernelGGL(copy_listed_rows_kernel, dim3(r, 2), dim3(256), 0, st, c);
+    LAUNCH_CHECK();
+  } else if (dst->width > 0) {
     int64_t done = 0;
     for (int b0 = 0; b0 < dst->batch; b0 += kMaxSeqPerLaunch) {
       SeqMeta mt;
@@ -1537,6 +1547,22 @@ int echokv_window_append(const echokv_shape* shape, void* win_k, void* win_v, in
   if (total == 0) return ECHOKV_OK;
   if (!k_new || !v_new) return ECHOKV_ERR_NULL;
   hipStream_t st = (hipStream_t)hip_stream;
+  if (total <= kListedRows) {
+    const Window w = {n_sink, n_recent};
+    RowList c;
+    c.src[0] = (const char*)k_new; c.src[1] = (const char*)v_new;
+    c.dst[0] = (char*)win_k; c.dst[1] = (char*)win_v;
+    c.src_row_bytes = c.dst_row_bytes = (int64_t)dm.D * dm.es;
+    int r = 0;
+    for (int b = 0; b < batch; ++b)
+      for (int i = 0; i < n_new[b]; ++i) {        // (written only if still inside the window once all rows are in: see window_append_kernel)
+        const int p = seq_len_before[b] + i, after = seq_len_before[b] + n_new[b];
+        c.to[r++] = p >= n_sink && p < after - n_recent ? -1 : (int64_t)b * w.rows() + w.row_of(p);
+      }
+    hipLaunchKernelGGL(copy_listed_rows_kernel, dim3(r, 2), dim3(256), 0, st, c);
+    LAUNCH_CHECK();
+    return ECHOKV_OK;
+  }
   int64_t src_row = 0;
   for (int b0 = 0; b0 < batch; b0 += kMaxSeqPerLaunch) {
     SeqMeta mt;

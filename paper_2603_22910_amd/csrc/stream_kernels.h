@@ -60,6 +60,28 @@ __global__ __launch_bounds__(256) void window_append_kernel(WinAppendArgs a, Seq
   }
 }
 
+// The same for few rows (a decode step's): row r goes to row to[r] of the destination (negative: nowhere), worked out by the host.  The
+// sequence metadata is 2.6 KB of arguments, which cost the host some 0.4 us a launch, and its search five reads of them one behind the
+// other.  Three calls of 1 - 32 rows: 14.2 - 14.9 us so, 15.5 - 15.9 as above (two processes each, 0.2 - 0.6 apart).  A list for 128 rows
+// is 1.1 KB of arguments again: 33 and 64 rows took 15.4 - 16.0 us with it and 15.6 - 16.0 as above, so the line lies at 32.
+// blockIdx.x: row, blockIdx.y: K / V.
+constexpr int kListedRows = 32;
+struct RowList {
+  const char* src[2];
+  char* dst[2];
+  int64_t src_row_bytes, dst_row_bytes;    // dst_row_bytes are copied
+  int64_t to[kListedRows];
+};
+__global__ __launch_bounds__(256) void copy_listed_rows_kernel(RowList a) {
+  const int which = blockIdx.y, r = blockIdx.x;
+  const int64_t to = a.to[r];
+  if (to < 0) return;
+  const int pieces = (int)(a.dst_row_bytes >> 4);
+  const uint4* s = reinterpret_cast<const uint4*>(a.src[which] + (int64_t)r * a.src_row_bytes);
+  uint4* d = reinterpret_cast<uint4*>(a.dst[which] + to * a.dst_row_bytes);
+  for (int i = threadIdx.x; i < pieces; i += 256) d[i] = s[i];
+}
+
 // Plain streaming read of a buffer, 8 independent 16-byte loads in flight per thread: the
 // yardstick the HBM-bound kernels are compared with (measurement aid, not part of the method).
 __global__ __launch_bounds__(256) void stream_read_kernel(const uint4* p, int64_t n16_per_block,
