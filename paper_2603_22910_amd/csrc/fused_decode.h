@@ -30,7 +30,10 @@ namespace echokv {
 namespace fused {
 
 constexpr int MAXPAIR = 8;   // query heads per 128 columns: (128 / head dim) * G at most
-constexpr int kVectorHeads = 2;   // up to so many query heads per KV head the epilogues use the vector unit, beyond it fma_heads
+// Up to so many query heads per KV head the epilogues use the vector unit, beyond it fma_heads, whose instruction costs the same for one
+// head and for four.  On the vector unit / the matrix pipe: one head, 8 x 4096 tokens 1222 / 1228 us, 20 x 1000 - 5000 1949 / 1966; two
+// heads, 8 x 3000 79.7 / 80.6; four heads (3140 - 24000 tokens, rope, window) 319 / 308.
+constexpr int kVectorHeads = 2;
 
 struct Args {
   const bf16_t* xa[2];   // anchor cache K, V      [pool, D]
