@@ -364,8 +364,12 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqM
   }
   write_chunk_partial<GT, NWAVES, LPR * VEC>(a, meta, b, chunk, qh0, s_m, s_l, s_o);
 }
+// Waves of a SIMD that the kernels of streaming workgroups alone are compiled for: their loads wait for each other's memory only.  Left to
+// itself the compiler takes 204 registers for attn_split_body4 (copies of its accumulators; 144 so), which leaves two.  Two / three, 8 KV heads, whole
+// calls, us: all 8 retained, 8 x 8000 tokens 67.8 / 62.0, with rope and window 113 / 97.3; 64 query heads, 16 x 3000 with rope 116 / 94.4.
+constexpr int kStreamOccupancy = 3;
 template <typename T, int LPR, int GT>
-__global__ __launch_bounds__(256) void attn_split_kernel(AttnArgs<T> a, SeqMeta meta) {
+__global__ __launch_bounds__(256, kStreamOccupancy) void attn_split_kernel(AttnArgs<T> a, SeqMeta meta) {
   __shared__ __attribute__((aligned(16))) char smem[attn_split_smem_bytes<T, LPR, GT, 4>()];
   const int b = find_seq(meta.tbase, meta.n, blockIdx.x);
   attn_split_body<T, LPR, GT, 4>(a, meta, b, blockIdx.x - meta.tbase[b], blockIdx.y, smem);
@@ -382,8 +386,8 @@ template <typename T> struct Streams {
   AttnArgs<T> ret, win;
   int32_t n_ret_chunks = 1, n_ret = 0, n_win = 0;     // chunks of all sequences; workgroups
 };
-template <typename T, int HD, int NWAVES>
-constexpr int stream_smem_bytes() { return attn_split_smem_bytes<T, HD * (int)sizeof(T) / 16, 4, NWAVES>(); }
+template <typename T, int HD, int NWAVES, int GT = 4>
+constexpr int stream_smem_bytes() { return attn_split_smem_bytes<T, HD * (int)sizeof(T) / 16, GT, NWAVES>(); }
 // Chunk x and head group y of workgroup wg, n chunks x ny groups: the groups of a chunk follow each other 8
 // workgroups apart, on one XCD and at one time, so that its L2 has the chunk's rows (whose heads lie side by side) and rotary
 // tables already.  One head after the other, 131072 tokens with four retained heads read their tables, half
@@ -398,7 +402,10 @@ __device__ __forceinline__ void stream_item(int wg, int n, int ny, int& x, int& 
     x = full + wg % (n - full); y = wg / (n - full);
   }
 }
-template <typename T, int HD, int NWAVES, int UN>
+// Query heads of a KV head that share a workgroup's pass over its rows.
+__host__ __device__ inline int stream_heads(int G) { return G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1; }
+// GT: query heads that share a pass over the rows, 0: by the number of them per KV head.
+template <typename T, int HD, int NWAVES, int UN, int GT = 0>
 __device__ __forceinline__ void stream_workgroup(const Streams<T>& st, const StreamMeta& meta, int wg, char* smem) {
   const bool ret = wg < st.n_ret;
   if (!ret) wg -= st.n_ret;
@@ -409,23 +416,29 @@ __device__ __forceinline__ void stream_workgroup(const Streams<T>& st, const Str
   const int b = ret ? find_seq(meta.cbase, meta.s.n, x) : x;
   const int chunk = ret ? x - meta.cbase[b] : 0;
   constexpr int LPR = HD * (int)sizeof(T) / 16;
-  if (a.G % 4 == 0) attn_split_body<T, LPR, 4, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
-  else if (a.G % 2 == 0) attn_split_body<T, LPR, 2, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
+  const int gt = GT ? GT : stream_heads(a.G);
+  if (gt == 4) attn_split_body<T, LPR, 4, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
+  else if (gt == 2) attn_split_body<T, LPR, 2, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
   else attn_split_body<T, LPR, 1, NWAVES, UN>(a, meta.s, b, chunk, y, smem);
 }
 
-// The same workgroups in a launch of their own: four waves each, so that a unit holds several.
+// The same workgroups in a launch of their own: four waves each, so that a unit holds several.  A kernel for each GT, as one for all has the
+// registers of the largest: one query head takes 114, two 138, four 145.  A kernel for all with 205 / so, us: 32 heads, 31 of them retained, 8 x
+// 8000 tokens, rope and window 655 / 578; 24 heads over 8, 7 retained, 8 x 8000 219 / 169, with rope and window 282 / 213; 56 over 8, 6 retained, 8 x 2000-12000
+// the same 287 / 223.
 constexpr int kStreamWaves = 4;
-template <typename T, int HD>
-__global__ __launch_bounds__(64 * kStreamWaves) void stream_kernel(Streams<T> st, StreamMeta meta) {
-  __shared__ __attribute__((aligned(16))) char smem[stream_smem_bytes<T, HD, kStreamWaves>()];
-  stream_workgroup<T, HD, kStreamWaves, 4>(st, meta, blockIdx.x, smem);
+template <typename T, int HD, int GT>
+__global__ __launch_bounds__(64 * kStreamWaves, kStreamOccupancy) void stream_kernel(Streams<T> st, StreamMeta meta) {
+  __shared__ __attribute__((aligned(16))) char smem[stream_smem_bytes<T, HD, kStreamWaves, GT>()];
+  stream_workgroup<T, HD, kStreamWaves, 4, GT>(st, meta, blockIdx.x, smem);
 }
 template <typename T>
 inline int launch_streams(const Streams<T>& s, const StreamMeta& meta, hipStream_t st) {
   const dim3 grid(s.n_ret + s.n_win), blk(64 * kStreamWaves);
-  if (s.ret.d == 128) hipLaunchKernelGGL((stream_kernel<T, 128>), grid, blk, 0, st, s, meta);
-  else hipLaunchKernelGGL((stream_kernel<T, 64>), grid, blk, 0, st, s, meta);
+  const int gt = stream_heads(s.ret.G);
+  auto launch = [&](auto* kernel) { hipLaunchKernelGGL(kernel, grid, blk, 0, st, s, meta); };
+  if (s.ret.d == 128) launch(gt == 4 ? stream_kernel<T, 128, 4> : gt == 2 ? stream_kernel<T, 128, 2> : stream_kernel<T, 128, 1>);
+  else launch(gt == 4 ? stream_kernel<T, 64, 4> : gt == 2 ? stream_kernel<T, 64, 2> : stream_kernel<T, 64, 1>);
   return hipGetLastError() != hipSuccess ? 7 : 0;
 }
 

@@ -221,7 +221,7 @@ int effective_weights(const Dims& dm, const void* w_k, const void* w_v, char* ws
 template <typename T>
 int launch_attn_split(const Dims& dm, AttnArgs<T> a, SeqMeta& mt, int n_kv_heads, hipStream_t st) {
   const int tiles = fill_tiles(mt, a.split_tokens);
-  const int GT = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1;
+  const int GT = stream_heads(dm.G);
   dim3 grid(tiles, n_kv_heads * (dm.G / GT));
   constexpr int LPR64 = 64 * (int)sizeof(T) / 16, LPR128 = 128 * (int)sizeof(T) / 16;
 #define ATTN_CASE(LPR_, GT_) \
@@ -250,7 +250,7 @@ int launch_window_attn(const Dims& dm, const echokv_decode_extras* ex, const KvE
   a.seq0 = b0; a.win_slot0 = win_slot0;
   SeqMeta wm = mt;                         // one chunk per sequence
   for (int b = 0; b <= wm.n; ++b) wm.tbase[b] = b;
-  const int GT = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1;
+  const int GT = stream_heads(dm.G);
   dim3 grid(wm.n, dm.H_kv * (dm.G / GT));
   constexpr int LPR64 = 64 * (int)sizeof(T) / 16, LPR128 = 128 * (int)sizeof(T) / 16;
 #define WIN_CASE(LPR_, GT_) hipLaunchKernelGGL((attn_split_kernel<T, LPR_, GT_>), grid, dim3(256), 0, st, a, wm)
@@ -323,7 +323,7 @@ inline int small_col_tile(const Dims& dm) { return dm.bf16 ? 128 : dm.d; }
 // predicted of 8, 8 x 1984 (all rows seven times) 96 / 80.  Over 132 such problems the choice costs 0.2 % in the mean, 8 % at most.
 template <typename T>
 bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgroups, bool rope, const Window& win) {
-  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1, win_heads = win.on() ? dm.H_kv : 0;
+  const int gt = stream_heads(dm.G), win_heads = win.on() ? dm.H_kv : 0;
   int64_t tokens = 0, t256 = 0;
   for (int b = 0; b < mt.n; ++b) { tokens += mt.len[b]; t256 += (mt.len[b] + 255) / 256; }
   const double rows = (double)(dm.G / gt) * (tokens * dm.g0 + (double)mt.n * win_heads * win.rows());
@@ -372,7 +372,7 @@ Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* q
                         const KvExtras& kx, float* po, float* pml, int b0, int slot_tokens, int min_chunk, int max_wgs, int max_chunk,
                         StreamMeta& mt, int* stream_step, int* win_slot0) {
   Streams<T> s;
-  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1, ny = dm.g0 * (dm.G / gt);
+  const int gt = stream_heads(dm.G), ny = dm.g0 * (dm.G / gt);
   AttnArgs<T>& r = s.ret;
   r.k = (const T*)tg->k; r.v = (const T*)tg->v; r.ld = dm.m; r.col0 = 0; r.head0 = 0; r.row_mode = 0;
   r.q = qq; r.H_q = dm.H_q; r.G = dm.G; r.d = dm.d; r.scale = dm.scale; r.part_o = po; r.part_ml = pml;
@@ -400,20 +400,23 @@ Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* q
 }
 
 // Streams of a bf16 call in a launch of their own ahead of the large kernel's, with several of their workgroups per unit.  As
-// workgroups of that kernel's launch, one per unit, they take about 1.14 times as long, but the units that the product's
+// workgroups of that kernel's launch, one per unit, they take longer (a factor of 1.14 is reckoned with), but the units that the product's
 // last round leaves idle work for nothing.  All times in us of one unit: a row and pass (query heads of a KV head that do not share
 // a workgroup pass over its rows again: 3, 5 or 7 of them) and 2 per workgroup; the launch costs 5, and what is less than 3 % of
-// the product is left alone.  In the launch / by themselves, us, 8 KV heads: G = 5, 6 retained, 128 x 300 tokens with window 374 / 261, 7 retained, 40 x
-// 4000 684 / 603, with rope 912 / 790; G = 8, 4 retained, 128 x 300 with window 365 / 302; G = 4, 4 retained, 8 x 6000 (many
-// units idle) 165 / 190; G = 7, 3 of 4 retained, 2 x 40000 170 / 180, 40 x 4000 397 / 353.
-// With 5 or 7 passes over sequences of up to 8192 tokens the launches of attn_split_kernel, head after head, are faster than
-// that (the product's launch takes 1.25 times as long, not 1.14) while the rows stay in the last cache or there are rotary tables to
-// wait for.  Launch of their own in the order of chunks / head after head: G = 5, 6 of 8 retained, 48 x 800 with rope and window 238 /
-// 207, 7 of 8, 8 x 6000 190 / 171, 40 x 4000 with rope 790 / 720; but G = 7, 40 x 4000 without rope 353 / 411, 2 x 40000 with it 253 / 358.
-// G = 3, 3 of 4, 8 x 6000 with rope and window: in the product's launch 87, head after head 98.
+// the product is left alone.  In the launch / by themselves, us, 8 KV heads: G = 5, 6 retained, 128 x 300 tokens with window 309 / 192, 7 retained, 40 x
+// 4000 669 / 518, with rope 835 / 657; G = 8, 4 retained, 128 x 300 with window 257 / 221; G = 4, 4 retained, 8 x 6000 (many
+// units idle) 156 / 174, 7 retained, 8 x 8000, rope and window 166 / 164; G = 3, 6 retained, 8 x 6000, the same 184 / 169, 4 retained 205 / 225; G = 7,
+// 3 of 4 retained, 2 x 40000 189 / 172, 40 x 4000 377 / 293.
+// With 5 or 7 passes over sequences of up to 8192 tokens while the rows stay in the last cache or there are rotary tables to wait for, the
+// launches of attn_split_kernel, head after head, are taken (1.25 in place of 1.14).  Launch of their own in the order of chunks /
+// head after head: G = 5, 6 of 8 retained, 48 x 800 with rope and window 225 / 204, 7 of 8, 8 x 6000 173 / 171, 40 x 4000 with rope 657 /
+// 658; but G = 7, 3 of 4, 40 x 4000 without rope 293 / 388, 7 of 8, 2 x 40000 with it 441 / 686.
+// G = 3, 6 of 8, 8 x 6000 with rope and window: in the product's launch 184, head after head 186.
+// (The factors are those of the launch of its own with the registers of four query heads per pass for one and two as well.  With one head per
+// pass and little idle the product's launch now takes 1.15 to 1.6 times as long, with two and four 1.0 to 1.16.)
 enum class StreamsIn { kProduct, kChunkOrder, kHeadOrder };
 StreamsIn place_of_streams(const Dims& dm, const SeqMeta& mt, bool rope, const Window& win) {
-  const int gt = (dm.G % 4 == 0) ? 4 : (dm.G % 2 == 0) ? 2 : 1, passes = dm.G / gt;
+  const int gt = stream_heads(dm.G), passes = dm.G / gt;
   int64_t tokens = 0, chunks = 0, tiles = 0;
   int max_len = 0;
   for (int b = 0; b < mt.n; ++b) {

@@ -1,4 +1,8 @@
 """The build's own checks on what the compiler made of kernels that wait for their loads by hand, on made-up listings."""
+import os
+import re
+import subprocess
+
 import pytest
 
 from paper_2603_22910_amd import build
@@ -48,3 +52,20 @@ def test_spills_are_found_in_the_kernels_that_count_their_loads():
     assert build.check_spills(clean + remark.format("_ZN6echokv12merge_kernelEv", 16, 2)) == []
     bad = remark.format("_ZN6echokv5fused17recon_mfma_kernelILi0EEEv", 8, 1)
     assert [n for _, n in build.check_spills(clean + bad)] == [8, 1]
+
+
+def test_streaming_kernels_keep_three_waves(tmp_path):
+    """The kernels that only stream rows hide the memory's latency by other waves: three of a SIMD at least (168 registers), for every
+    number of query heads that share a pass."""
+    src = tmp_path / "streams.hip"
+    kernels = "".join(f"template __global__ void echokv::attn_split_kernel<{t}, {lpr}, {gt}>(echokv::AttnArgs<{t}>, echokv::SeqMeta);\n"
+                      for t, lprs in (("echokv::bf16_t", (8, 16)), ("float", (16, 32))) for lpr in lprs for gt in (1, 2, 4))
+    src.write_text('#include "attn_split.h"\n' + kernels +
+                   "template int echokv::launch_streams<echokv::bf16_t>(const echokv::Streams<echokv::bf16_t>&, const echokv::StreamMeta&, hipStream_t);\n")
+    cmd = [build.hipcc_path(), *build.HIPCC_FLAGS, "--cuda-device-only", "-S", "-I", build.CSRC, "-I", os.path.join(build.HERE, "..", "include"),
+           "-o", str(tmp_path / "streams.s"), str(src)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+    found = re.findall(r"Function Name: (\S+)(?:.|\n)*?Occupancy \[waves/SIMD\]: (\d+)", res.stderr)
+    assert sum("attn_split_kernel" in k for k, _ in found) == 12 and any("13stream_kernel" in k for k, _ in found)
+    assert [(k, n) for k, n in found if int(n) < 3] == []
