@@ -32,7 +32,10 @@ namespace fused {
 constexpr int MAXPAIR = 8;   // query heads per 128 columns: (128 / head dim) * G at most
 // Up to so many query heads per KV head the epilogues use the vector unit, beyond it fma_heads, whose instruction costs the same for one
 // head and for four.  On the vector unit / the matrix pipe: one head, 8 x 4096 tokens 1222 / 1228 us, 20 x 1000 - 5000 1949 / 1966; two
-// heads, 8 x 3000 79.7 / 80.6; four heads (3140 - 24000 tokens, rope, window) 319 / 308.
+// heads, 8 x 3000 79.7 / 80.6; three, 8 x 6000 175.0 / 174.4, heads of 64 69.2 / 68.3, 4 x 1000-9000 with rope 54.2 / 53.3; four heads (3140 - 24000
+// tokens, rope, window) 319 / 308.  With rotary tables: the score kernel, one head, 40000 tokens 887 / 891, heads of 64, 8 x 4096
+// 240.5 / 242.7, two heads of 64 98.1 / 99.2; in the fused kernel, where the two waves of 64 tokens share the dims, one head, 8 x 4096 1249 / 1253 (runs
+// 9 apart), two, 8 x 6000 168.3 / 167.8: the matrix pipe alone there.
 constexpr int kVectorHeads = 2;
 
 struct Args {
@@ -155,7 +158,7 @@ __device__ __forceinline__ void k_scores(const Acc& acc, const float* q, float (
       // c + HD/2.  With a = k_c, b = k_{c+HD/2}:
       //   q_c (a cos - b sin) + q_{c+HD/2} (b cos + a sin)
       // The rotated values are temporaries (written back they would cost hundreds of spilled registers), used by all query heads of
-      // the group.  Masked tokens borrow the last valid table row.
+      // the group, in the fused kernel (SPLIT) by fma_heads for any number of them (see kVectorHeads).  Masked tokens borrow the last valid table row.
       constexpr int NG = MG / 4;             // groups of four query heads at most
       floatx4_t s[NG][4];
 #pragma unroll
@@ -178,18 +181,32 @@ __device__ __forceinline__ void k_scores(const Acc& acc, const float* q, float (
             rb[tb][i] = fmaf(kb[i], cc[i], ka[i] * ss[i]);
           }
         }
+        if (!SPLIT && G <= kVectorHeads) {
 #pragma unroll
-        for (int n = 0; n < NG; ++n) {
-          if (4 * n < G) {
-            const float* qs = qw + (hw * G + min(4 * n + (lane & 3), G - 1)) * HD + hb * 16;
+          for (int g = 0; g < kVectorHeads; ++g) {
+            if (g >= G) continue;
+            const float* qs = qw + (hw * G + g) * HD + hb * 16;
             const float4 qa = *reinterpret_cast<const float4*>(qs), qb = *reinterpret_cast<const float4*>(qs + HD / 2);
             const float q0[4] = {qa.x, qa.y, qa.z, qa.w}, q1[4] = {qb.x, qb.y, qb.z, qb.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int tb = 0; tb < 4; ++tb)
 #pragma unroll
-              for (int tb = 0; tb < 4; ++tb) s[n][tb] = fma_heads(q0[i], ra[tb][i], s[n][tb]);
+              for (int i = 0; i < 4; ++i) s[0][tb][g] = fmaf(ra[tb][i], q0[i], fmaf(rb[tb][i], q1[i], s[0][tb][g]));
+          }
+        } else {
 #pragma unroll
-              for (int tb = 0; tb < 4; ++tb) s[n][tb] = fma_heads(q1[i], rb[tb][i], s[n][tb]);
+          for (int n = 0; n < NG; ++n) {
+            if (4 * n < G) {
+              const float* qs = qw + (hw * G + min(4 * n + (lane & 3), G - 1)) * HD + hb * 16;
+              const float4 qa = *reinterpret_cast<const float4*>(qs), qb = *reinterpret_cast<const float4*>(qs + HD / 2);
+              const float q0[4] = {qa.x, qa.y, qa.z, qa.w}, q1[4] = {qb.x, qb.y, qb.z, qb.w};
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                for (int tb = 0; tb < 4; ++tb) s[n][tb] = fma_heads(q0[i], ra[tb][i], s[n][tb]);
+#pragma unroll
+                for (int tb = 0; tb < 4; ++tb) s[n][tb] = fma_heads(q1[i], rb[tb][i], s[n][tb]);
+              }
             }
           }
         }
