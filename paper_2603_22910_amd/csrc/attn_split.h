@@ -364,7 +364,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqM
   }
   write_chunk_partial<GT, NWAVES, LPR * VEC>(a, meta, b, chunk, qh0, s_m, s_l, s_o);
 }
-// Waves of a SIMD that the kernels of streaming workgroups alone are compiled for: their loads wait for each other's memory only.  Left to
+// Waves of a SIMD that the kernels of streaming workgroups alone are compiled for: nothing but other waves hides the wait for their rows.  Left to
 // itself the compiler takes 204 registers for attn_split_body4 (copies of its accumulators; 144 so), which leaves two.  Two / three, 8 KV heads, whole
 // calls, us: all 8 retained, 8 x 8000 tokens 67.8 / 62.0, with rope and window 113 / 97.3; 64 query heads, 16 x 3000 with rope 116 / 94.4.
 constexpr int kStreamOccupancy = 3;
@@ -606,7 +606,5 @@ __device__ __forceinline__ void rope_workgroup(const RopeRows& a, int wg) {
     *reinterpret_cast<uint4*>(dp[u] + half) = rope8<true>(lo[u], hi[u], cs[u], sn[u]);
   }
 }
-
-__global__ __launch_bounds__(256) inline void rope_rows_kernel(RopeRows a) { rope_workgroup<256>(a, blockIdx.x); }
 
 }  // namespace echokv

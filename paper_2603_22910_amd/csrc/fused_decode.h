@@ -756,14 +756,11 @@ inline int launch_fused_kscores(int H_q, int H_kv, int d, int m, int d_out, int 
 
 // K_hat and V_hat of the sequences in `mt` -> out_k / out_v [rows, ldo] at
 // column col0, output row = sbase[b]*kSlotTokens + j.  d_out = width of W (0: only the rows of `rope`).  With
-// rope.cos K_hat is rotated by token position, heads of rope.d dims, and rope's own rows (the retained keys) are as well, these
-// by workgroups of the product's launch.  K_hat on its way out of the product if that has kRopeTiles workgroups and more, by a
-// launch behind it otherwise: the tables' loads are then a latency at the end of a tile that nothing covers.  Whole prefill calls of
-// 32 heads over 8 of 128, behind the product / on its way out, us, and the product's workgroups: m = 512, 16 queries behind 500 tokens (12)
-// 53.7 / 56.6, 100 behind 3000 (52) 66.5 / 69.4, 2000 alone (32) 98.5 / 101.5; m = 64, 100 behind 3000 (104) 61.0 / 62.7.  From 120 to 240
-// the two were within 3 % of each other, and with 252 and more the product's way out ahead by 2 - 5 %, when the rotation was done on rounded
-// rows from LDS, whose table loads four by four took 13 us of a 50 us product (500 behind 7000, m = 64: now 37).
-constexpr int kRopeTiles = 120;
+// rope.cos K_hat is rotated by token position on its way out, heads of rope.d dims, and rope's own rows (the retained keys) are as well, by
+// workgroups of the product's launch.  (A launch behind the product for K_hat won for fewer than 120 of its workgroups while the rotation was done on
+// rounded rows from LDS.  Behind the product / on its way out of the accumulators, whole prefill calls of 32 heads over 8 of 128, us, and the product's
+// workgroups: m = 512, 16 queries behind 500 tokens (12) 52.8 / 52.4, 100 behind 3000 (52) 65.5 / 64.9, 2000 alone (32) 103.8 / 102.8; m = 64,
+// 100 behind 3000 (104) 60.3 / 58.7; 32 over 32, m = 2048, 300 behind 600 (64) 139.5 / 138.1.)
 template <typename T>
 inline int launch_recon_mfma(int D, int m, int d_out, const T* ka, const T* va, const T* kr, const T* vr,
                              const T* wk, const T* wv, T* out_k, T* out_v, int64_t ldo, int col0,
@@ -780,18 +777,11 @@ inline int launch_recon_mfma(int D, int m, int d_out, const T* ka, const T* va, 
     a.D = D; a.m = m; a.d_out = d_out; a.H_q = rope.d; a.G = 1; a.n_ret_heads = 0; a.scale = 0.f;
     a.n_col_tiles = (a.d_out + fused::BN - 1) / fused::BN;
     a.n_tiles = fused_fill_tiles(mt) * a.n_col_tiles;
-    const bool behind = rope.cos && a.n_tiles > 0 && 2 * a.n_tiles < kRopeTiles;
-    if (behind) a.rope_cos = a.rope_sin = nullptr;
     const dim3 g((unsigned)((a.n_tiles + 7) / 8 * 8 + rope_workgroups(rope, fused::NTHREADS)), 2), blk(fused::NTHREADS);
     if (out_f32) hipLaunchKernelGGL((fused::recon_mfma_kernel<0, true>), g, blk, 0, st, a, mt, rope);
     else if (act == 1) hipLaunchKernelGGL(fused::recon_mfma_kernel<1>, g, blk, 0, st, a, mt, rope);
     else if (act == 2) hipLaunchKernelGGL(fused::recon_mfma_kernel<2>, g, blk, 0, st, a, mt, rope);
     else hipLaunchKernelGGL(fused::recon_mfma_kernel<0>, g, blk, 0, st, a, mt, rope);
-    if (behind) {                            // (one sequence, rows from 0)
-      RopeRows r = rope;
-      r.src = r.dst = out_k + col0; r.ld_src = r.ld_dst = ldo; r.n_heads = d_out / rope.d;
-      hipLaunchKernelGGL(rope_rows_kernel, dim3((unsigned)rope_workgroups(r, 256)), dim3(256), 0, st, r);
-    }
     if (hipGetLastError() != hipSuccess) return 7;
     return 0;
   }

@@ -1,6 +1,6 @@
 """GPU parity of the prefill path's rotary embedding: predicted keys rotated on their way out of the predictor
-product (from 120 of its workgroups on) and by a launch behind it (below), retained keys by workgroups of the product's
-launch, also where no head is predicted; every output element against the fp64 oracle."""
+product, whatever the number of its workgroups, retained keys by workgroups of the product's launch, also where no head is
+predicted; every output element against the fp64 oracle."""
 import pytest
 import torch
 
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [                                # H_q, H_kv, d, m, tokens, queries
     (4, 2, 128, 128, 15104, 9),          # 59 token tiles x 1 column tile, twice: 118 workgroups
-    (4, 2, 128, 128, 15105, 9),          # 120: rotated on the way out; one row in the last tile
+    (4, 2, 128, 128, 15105, 9),          # 120: one row in the last tile
     (8, 4, 64, 64, 15300, 5),            # heads of 64, 192 predicted dims
     (12, 6, 64, 0, 7700, 33),            # no retained head; the second column tile is half empty
     (4, 2, 64, 128, 700, 70),            # no predicted head: the launch rotates retained keys only
