@@ -218,6 +218,18 @@ int effective_weights(const Dims& dm, const void* w_k, const void* w_v, char* ws
   return ECHOKV_OK;
 }
 
+int launch_listed_rows(const RowList<kListedRows>& c, int rows, hipStream_t st) {
+  if (rows > kShortList) {
+    hipLaunchKernelGGL(copy_listed_rows_kernel<kListedRows>, dim3(rows, 2), dim3(256), 0, st, c);
+  } else {
+    RowList<kShortList> s;
+    memcpy(&s, &c, sizeof(s));                 // (the same members in front, then the first entries)
+    hipLaunchKernelGGL(copy_listed_rows_kernel<kShortList>, dim3(rows, 2), dim3(256), 0, st, s);
+  }
+  LAUNCH_CHECK();
+  return ECHOKV_OK;
+}
+
 template <typename T>
 int launch_attn_split(const Dims& dm, AttnArgs<T> a, SeqMeta& mt, int n_kv_heads, hipStream_t st) {
   const int tiles = fill_tiles(mt, a.split_tokens);
@@ -1280,15 +1292,15 @@ int echokv_cache_append(const echokv_shape* shape, echokv_layer_cache* dst, cons
   if (total > INT32_MAX) return ECHOKV_ERR_SHAPE;
   hipStream_t st = (hipStream_t)hip_stream;
   if (dst->width > 0 && total > 0 && total <= kListedRows) {
-    RowList c;
+    RowList<kListedRows> c;
     c.src[0] = (const char*)k_new; c.src[1] = (const char*)v_new;
     c.dst[0] = (char*)dst->k; c.dst[1] = (char*)dst->v;
     c.src_row_bytes = (int64_t)dm.D * dm.es; c.dst_row_bytes = (int64_t)dst->width * dm.es;
     int r = 0;
     for (int b = 0; b < dst->batch; ++b)
       for (int i = 0; i < n_new[b]; ++i) c.to[r++] = dst->seq_start[b] + dst->seq_len[b] + i;
-    hipLaunchKernelGGL(copy_listed_rows_kernel, dim3(r, 2), dim3(256), 0, st, c);
-    LAUNCH_CHECK();
+    rc = launch_listed_rows(c, r, st);
+    if (rc) return rc;
   } else if (dst->width > 0) {
     int64_t done = 0;
     for (int b0 = 0; b0 < dst->batch; b0 += kMaxSeqPerLaunch) {
@@ -1552,7 +1564,7 @@ int echokv_window_append(const echokv_shape* shape, void* win_k, void* win_v, in
   hipStream_t st = (hipStream_t)hip_stream;
   if (total <= kListedRows) {
     const Window w = {n_sink, n_recent};
-    RowList c;
+    RowList<kListedRows> c;
     c.src[0] = (const char*)k_new; c.src[1] = (const char*)v_new;
     c.dst[0] = (char*)win_k; c.dst[1] = (char*)win_v;
     c.src_row_bytes = c.dst_row_bytes = (int64_t)dm.D * dm.es;
@@ -1562,8 +1574,8 @@ int echokv_window_append(const echokv_shape* shape, void* win_k, void* win_v, in
         const int p = seq_len_before[b] + i, after = seq_len_before[b] + n_new[b];
         c.to[r++] = p >= n_sink && p < after - n_recent ? -1 : (int64_t)b * w.rows() + w.row_of(p);
       }
-    hipLaunchKernelGGL(copy_listed_rows_kernel, dim3(r, 2), dim3(256), 0, st, c);
-    LAUNCH_CHECK();
+    rc = launch_listed_rows(c, r, st);
+    if (rc) return rc;
     return ECHOKV_OK;
   }
   int64_t src_row = 0;

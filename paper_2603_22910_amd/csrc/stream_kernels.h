@@ -62,17 +62,21 @@ __global__ __launch_bounds__(256) void window_append_kernel(WinAppendArgs a, Seq
 
 // The same for few rows (a decode step's): row r goes to row to[r] of the destination (negative: nowhere), worked out by the host.  The
 // sequence metadata is 2.6 KB of arguments, which cost the host some 0.4 us a launch, and its search five reads of them one behind the
-// other.  Three calls of 1 - 32 rows: 14.2 - 14.9 us so, 15.5 - 15.9 as above (two processes each, 0.2 - 0.6 apart).  A list for 128 rows
-// is 1.1 KB of arguments again: 33 and 64 rows took 15.4 - 16.0 us with it and 15.6 - 16.0 as above, so the line lies at 32.
+// other.  Three calls of up to 32 rows 14.2 - 14.9 us so, 15.5 - 15.9 by the metadata (two processes each, 0.2 - 0.6 apart); of 33 - 64 rows
+// 15.2 / 15.9 in the mean (eight calls, six processes each, at most 0.4 from their means).  By lists of 32 / 64 / 96 / 128 rows (0.3, 0.6, 0.8, 1.1 KB of
+// arguments), two processes each: up to 32 rows 12.9 / 13.1 / 13.0 / 13.3, 33 - 64 rows - / 13.1 / 13.2 / 13.3, by the metadata 13.7.  So the lists
+// end at 64 rows, and up to 32 take the shorter one.
 // blockIdx.x: row, blockIdx.y: K / V.
-constexpr int kListedRows = 32;
+constexpr int kListedRows = 64, kShortList = 32;
+template <int N>
 struct RowList {
   const char* src[2];
   char* dst[2];
   int64_t src_row_bytes, dst_row_bytes;    // dst_row_bytes are copied
-  int64_t to[kListedRows];
+  int64_t to[N];
 };
-__global__ __launch_bounds__(256) void copy_listed_rows_kernel(RowList a) {
+template <int N>
+__global__ __launch_bounds__(256) void copy_listed_rows_kernel(RowList<N> a) {
   const int which = blockIdx.y, r = blockIdx.x;
   const int64_t to = a.to[r];
   if (to < 0) return;

@@ -1,6 +1,6 @@
-"""Appends of few rows, whose destinations the host lists, on both sides of the limit (32; more go by the sequence metadata), with sequences
-that get none, and the window's ring with rows that leave it in the same call: every byte of the pools against an enumeration
-of the rows."""
+"""Appends of few rows, whose destinations the host lists, on both sides of the limits (lists of 32 and of 64 rows; more go by the
+sequence metadata), with sequences that get none, and the window's ring with rows that leave it in the same call: every byte of the
+pools against an enumeration of the rows."""
 import numpy as np
 import pytest
 import torch
@@ -23,7 +23,7 @@ def rows_of(batch, total):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("batch,total", [(1, 1), (5, 31), (32, 32), (40, 33), (3, 128), (150, 31), (1, 32)])
+@pytest.mark.parametrize("batch,total", [(1, 1), (5, 31), (32, 32), (40, 33), (64, 64), (1, 65), (3, 128), (150, 31), (150, 63), (1, 32)])
 def test_listed_rows(batch, total, dtype):
     n_sink, n_recent = 2, 5
     n_new = rows_of(batch, total)
