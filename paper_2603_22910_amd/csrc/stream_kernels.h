@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void window_append_kernel(WinAppendArgs a, Seq
 // The same for few rows (a decode step's): row r goes to row to[r] of the destination (negative: nowhere), worked out by the host.  The
 // sequence metadata is 2.6 KB of arguments, which cost the host some 0.4 us a launch, and its search five reads of them one behind the
 // other.  Three calls of up to 32 rows 14.2 - 14.9 us so, 15.5 - 15.9 by the metadata (two processes each, 0.2 - 0.6 apart); of 33 - 64 rows
-// 15.2 / 15.9 in the mean (eight calls, six processes each, at most 0.4 from their means).  By lists of 32 / 64 / 96 / 128 rows (0.3, 0.6, 0.8, 1.1 KB of
+// 15.2 / 15.9 in the mean (eight calls, six processes each, at most 0.5 from their means).  By lists of 32 / 64 / 96 / 128 rows (0.3, 0.6, 0.8, 1.1 KB of
 // arguments), two processes each: up to 32 rows 12.9 / 13.1 / 13.0 / 13.3, 33 - 64 rows - / 13.1 / 13.2 / 13.3, by the metadata 13.7.  So the lists
 // end at 64 rows, and up to 32 take the shorter one.
 // blockIdx.x: row, blockIdx.y: K / V.
@@ -344,6 +344,7 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs<TO> a, SeqMeta meta
   // is left of two (kernel 4.2 -> 3.2 us; whole calls: fp32, 512 tokens 15.9 -> 14.9, 8 KV heads with 4 retained, 1000 tokens, rope
   // and window 25.2 -> 24.2, 300 tokens 23.2 -> 21.9).
   constexpr int NF = 8;
+  static_assert(DS != 1 || NG * NF <= 64, "a wave keeps the weight of one partial per lane");
   if (DS == 1 && n <= NG * NF) {
     const int grp = tid >> 5, q4 = (tid & 31) * 4;
     const float* ml = a.part_ml + ph_of(min(lane, n - 1)) * 2;
@@ -353,7 +354,8 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs<TO> a, SeqMeta meta
     for (int u = 0; u < NF; ++u)
       if (grp + NG * u < n && q4 < a.d) o[u] = *reinterpret_cast<const float4*>(a.part_o + ph_of(grp + NG * u) * a.d + q4);
     __builtin_amdgcn_sched_barrier(0);
-    // Every wave for itself: the barriers of two reductions over the workgroup took 0.5 us (fp32, 512 tokens, 14.7 -> 14.2; as below: a partial that covers no token has -inf and weight 0, and one at least covers a token)
+    // Every wave for itself: the barriers of two reductions over the workgroup took 0.5 us (fp32, 512 tokens, 14.7 -> 14.2).  (As below: a
+    // partial that covers no token has -inf and weight 0, and one at least covers a token.)
     const float M = wave_max64(lane < n ? pm : -INFINITY);
     const float w = lane < n ? __expf(pm - M) : 0.f;
     const float ll = wave_sum64(w * pl);

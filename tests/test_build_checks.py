@@ -54,18 +54,37 @@ def test_spills_are_found_in_the_kernels_that_count_their_loads():
     assert [n for _, n in build.check_spills(clean + bad)] == [8, 1]
 
 
+def compile_header(tmp_path, text):
+    """The compiler's run over a source of explicit instances: its result, with the remarks on what each kernel takes."""
+    src = tmp_path / "instances.hip"
+    src.write_text(text)
+    cmd = [build.hipcc_path(), *build.HIPCC_FLAGS, "--cuda-device-only", "-S", "-I", build.CSRC, "-I", os.path.join(build.HERE, "..", "include"),
+           "-o", str(tmp_path / "instances.s"), str(src)]
+    return subprocess.run(cmd, capture_output=True, text=True)
+
+
+def remarks(res, what):
+    """{kernel: value} of one line of the remarks."""
+    assert res.returncode == 0, res.stderr
+    return {k: int(n) for k, n in re.findall(r"Function Name: (\S+)(?:(?!Function Name)(?:.|\n))*?" + re.escape(what) + r": (\d+)", res.stderr)}
+
+
 def test_streaming_kernels_keep_three_waves(tmp_path):
     """The kernels that only stream rows hide the memory's latency by other waves: three of a SIMD at least (168 registers), for every
     number of query heads that share a pass."""
-    src = tmp_path / "streams.hip"
     kernels = "".join(f"template __global__ void echokv::attn_split_kernel<{t}, {lpr}, {gt}>(echokv::AttnArgs<{t}>, echokv::SeqMeta);\n"
                       for t, lprs in (("echokv::bf16_t", (8, 16)), ("float", (16, 32))) for lpr in lprs for gt in (1, 2, 4))
-    src.write_text('#include "attn_split.h"\n' + kernels +
-                   "template int echokv::launch_streams<echokv::bf16_t>(const echokv::Streams<echokv::bf16_t>&, const echokv::StreamMeta&, hipStream_t);\n")
-    cmd = [build.hipcc_path(), *build.HIPCC_FLAGS, "--cuda-device-only", "-S", "-I", build.CSRC, "-I", os.path.join(build.HERE, "..", "include"),
-           "-o", str(tmp_path / "streams.s"), str(src)]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    assert res.returncode == 0, res.stderr
-    found = re.findall(r"Function Name: (\S+)(?:.|\n)*?Occupancy \[waves/SIMD\]: (\d+)", res.stderr)
-    assert sum("attn_split_kernel" in k for k, _ in found) == 12 and any("13stream_kernel" in k for k, _ in found)
-    assert [(k, n) for k, n in found if int(n) < 3] == []
+    found = remarks(compile_header(tmp_path, '#include "attn_split.h"\n' + kernels +
+                                   "template int echokv::launch_streams<echokv::bf16_t>(const echokv::Streams<echokv::bf16_t>&, "
+                                   "const echokv::StreamMeta&, hipStream_t);\n"), "Occupancy [waves/SIMD]")
+    assert sum("attn_split_kernel" in k for k in found) == 12 and any("13stream_kernel" in k for k in found)
+    assert {k: n for k, n in found.items() if n < 3} == {}
+
+
+@pytest.mark.parametrize("ds,nt,compiles", [(1, 256, True), (4, 1024, True), (1, 1024, False), (1, 512, False)])
+def test_merges_with_more_partials_than_lanes_do_not_compile(tmp_path, ds, nt, compiles):
+    """The merge of few partials keeps a weight per lane: 64 of them, which 256 threads never pass and more of them would."""
+    res = compile_header(tmp_path, f'#include "stream_kernels.h"\ntemplate __global__ void echokv::merge_kernel<float, {ds}, {nt}>'
+                         "(echokv::MergeArgs<float>, echokv::SeqMeta);\n")
+    assert (res.returncode == 0) == compiles, res.stderr
+    assert compiles or "one partial per lane" in res.stderr
