@@ -704,14 +704,15 @@ __global__ __launch_bounds__(kPvWaves * 64, QUARTERS ? 1 : 2) void pv_kernel(Arg
 //   M = max_s M_s,  l = sum_s l_s 2^(M_s - M),  y[b, h, k] = sum_s 2^(M_s - M) ypart_s[h, k] / l
 // and (M, l) for the last kernel.  grid = (ceil(d_in / (1024 / SG)), H_q, nseq).
 // ---------------------------------------------------------------------------
-template <int SG>       // thread groups that share a column quad and split the splits: 1 (few splits) or 4
+constexpr int kYFewSplits = 8;
+template <int SG>       // thread groups that share a column quad and split the splits: 1 (up to kYFewSplits) or 4
 __global__ __launch_bounds__(256) void y_sum_kernel(Args a, SeqMeta meta) {
   constexpr int CQ = 256 / SG;                   // column quads per workgroup
   const int h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int cq = tid % CQ, sg = tid / CQ;
   const int k = min((blockIdx.x * CQ + cq) * 4, a.d_in - 4);     // tail threads repeat the last quad
   const int s0 = meta.tbase[b], ns = meta.tbase[b + 1] - s0;
-  __shared__ float s_red[4];
+  __shared__ float s_red[4];             // (one group needs none of the three)
   __shared__ float s_w[256];
   __shared__ float4 s_acc[SG][CQ];
   const float* mlp = a.ml + ((int64_t)s0 * a.H_pad + h) * 2;
@@ -719,7 +720,8 @@ __global__ __launch_bounds__(256) void y_sum_kernel(Args a, SeqMeta meta) {
   // Few splits: every wave works out all weights itself, and the rows are requested ahead of them: one round trip to memory
   // and one barrier instead of three and four.  Whole calls, with the wave reductions on the vector unit, us: d_in 1536, 2 x 1500 tokens 33.9 -> 33.5,
   // 8 x 300-4000 56.2 -> 54.9, 40000 86.6 -> 85.3, value-absorbed 4 x 1000-9000 with rope and window 101.4 -> 100.0; d_in 5120, 300 tokens 47.8 -> 46.6.
-  constexpr int NF = SG == 1 ? 8 : 16;
+  constexpr int NF = SG == 1 ? kYFewSplits : 16;
+  static_assert(SG * NF <= 64, "a wave keeps the weight of one split per lane");
   if (ns <= SG * NF) {
     const float* ml = mlp + min(lane, ns - 1) * mls;
     const float pm = lane < ns ? ml[0] : -INFINITY, pl = ml[1];
@@ -759,52 +761,54 @@ __global__ __launch_bounds__(256) void y_sum_kernel(Args a, SeqMeta meta) {
     }
     return;
   }
-  float M = -INFINITY;
-  for (int i = tid; i < ns; i += 256) M = fmaxf(M, mlp[i * mls]);
-  M = wave_max64(M);
-  if (lane == 0) s_red[wave] = M;
-  __syncthreads();
-  M = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  float l = 0.f;
-  const float* yp = a.ypart + ((int64_t)s0 * a.H_pad + h) * a.d_in + k;
-  const int64_t yps = (int64_t)a.H_pad * a.d_in;
-  for (int c0 = 0; c0 < ns; c0 += 256) {
-    float wgt = 0.f;
-    if (c0 + tid < ns) {
-      const float ms = mlp[(c0 + tid) * mls];
-      wgt = ms == -INFINITY ? 0.f : exp2f(ms - M);
-      l += wgt * mlp[(c0 + tid) * mls + 1];
-    }
-    __syncthreads();            // the previous chunk's weights are no longer read
-    s_w[tid] = wgt;
+  if constexpr (SG > 1) {
+    float M = -INFINITY;
+    for (int i = tid; i < ns; i += 256) M = fmaxf(M, mlp[i * mls]);
+    M = wave_max64(M);
+    if (lane == 0) s_red[wave] = M;
     __syncthreads();
-    const int cn = min(256, ns - c0);
+    M = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    float l = 0.f;
+    const float* yp = a.ypart + ((int64_t)s0 * a.H_pad + h) * a.d_in + k;
+    const int64_t yps = (int64_t)a.H_pad * a.d_in;
+    for (int c0 = 0; c0 < ns; c0 += 256) {
+      float wgt = 0.f;
+      if (c0 + tid < ns) {
+        const float ms = mlp[(c0 + tid) * mls];
+        wgt = ms == -INFINITY ? 0.f : exp2f(ms - M);
+        l += wgt * mlp[(c0 + tid) * mls + 1];
+      }
+      __syncthreads();            // the previous chunk's weights are no longer read
+      s_w[tid] = wgt;
+      __syncthreads();
+      const int cn = min(256, ns - c0);
 #pragma unroll 8
-    for (int j = sg; j < cn; j += SG) {
-      const float4 v = *reinterpret_cast<const float4*>(yp + (c0 + j) * yps);
-      const float wj = s_w[j];
-      acc.x = fmaf(wj, v.x, acc.x); acc.y = fmaf(wj, v.y, acc.y);
-      acc.z = fmaf(wj, v.z, acc.z); acc.w = fmaf(wj, v.w, acc.w);
+      for (int j = sg; j < cn; j += SG) {
+        const float4 v = *reinterpret_cast<const float4*>(yp + (c0 + j) * yps);
+        const float wj = s_w[j];
+        acc.x = fmaf(wj, v.x, acc.x); acc.y = fmaf(wj, v.y, acc.y);
+        acc.z = fmaf(wj, v.z, acc.z); acc.w = fmaf(wj, v.w, acc.w);
+      }
     }
-  }
-  l = wave_sum64(l);
-  s_acc[sg][cq] = acc;
-  __syncthreads();              // s_red was read above by every thread
-  if (lane == 0) s_red[wave] = l;
-  __syncthreads();
-  if (sg != 0) return;
-  l = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
-  const float inv = l > 0.f ? 1.f / l : 0.f;       // l == 0: every counted token sits in the window
+    l = wave_sum64(l);
+    s_acc[sg][cq] = acc;
+    __syncthreads();              // s_red was read above by every thread
+    if (lane == 0) s_red[wave] = l;
+    __syncthreads();
+    if (sg != 0) return;
+    l = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
+    const float inv = l > 0.f ? 1.f / l : 0.f;       // l == 0: every counted token sits in the window
 #pragma unroll
-  for (int g = 1; g < SG; ++g) {
-    acc.x += s_acc[g][cq].x; acc.y += s_acc[g][cq].y; acc.z += s_acc[g][cq].z; acc.w += s_acc[g][cq].w;
-  }
-  acc.x *= inv; acc.y *= inv; acc.z *= inv; acc.w *= inv;
-  *reinterpret_cast<float4*>(a.y + ((int64_t)b * a.H_q + h) * a.d_in + k) = acc;
-  if (blockIdx.x == 0 && tid == 0) {
-    a.y_ml[((int64_t)b * a.H_q + h) * 2] = M;
-    a.y_ml[((int64_t)b * a.H_q + h) * 2 + 1] = l;
+    for (int g = 1; g < SG; ++g) {
+      acc.x += s_acc[g][cq].x; acc.y += s_acc[g][cq].y; acc.z += s_acc[g][cq].z; acc.w += s_acc[g][cq].w;
+    }
+    acc.x *= inv; acc.y *= inv; acc.z *= inv; acc.w *= inv;
+    *reinterpret_cast<float4*>(a.y + ((int64_t)b * a.H_q + h) * a.d_in + k) = acc;
+    if (blockIdx.x == 0 && tid == 0) {
+      a.y_ml[((int64_t)b * a.H_q + h) * 2] = M;
+      a.y_ml[((int64_t)b * a.H_q + h) * 2 + 1] = l;
+    }
   }
 }
 

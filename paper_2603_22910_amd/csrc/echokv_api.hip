@@ -1104,7 +1104,7 @@ int absorbed_impl(const Dims& dm, bool value_only, const echokv_layer_cache* an,
     LAUNCH_CHECK();
     if (max_splits == 1) {
       // (the value pass has written y and its (max, sum) itself)
-    } else if (max_splits > 8) hipLaunchKernelGGL(absorbed::y_sum_kernel<4>, dim3((dm.d_in + 255) / 256, dm.H_q, n), dim3(256), 0, st, a, mt);
+    } else if (max_splits > absorbed::kYFewSplits) hipLaunchKernelGGL(absorbed::y_sum_kernel<4>, dim3((dm.d_in + 255) / 256, dm.H_q, n), dim3(256), 0, st, a, mt);
     else hipLaunchKernelGGL(absorbed::y_sum_kernel<1>, dim3((dm.d_in + 1023) / 1024, dm.H_q, n), dim3(256), 0, st, a, mt);
     LAUNCH_CHECK();
     const dim3 og(dm.H_kv, pl.k_slices, (n * dm.G + 31) / 32);

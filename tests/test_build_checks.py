@@ -88,3 +88,10 @@ def test_merges_with_more_partials_than_lanes_do_not_compile(tmp_path, ds, nt, c
                          "(echokv::MergeArgs<float>, echokv::SeqMeta);\n")
     assert (res.returncode == 0) == compiles, res.stderr
     assert compiles or "one partial per lane" in res.stderr
+
+
+def test_merge_of_few_splits_has_no_long_form(tmp_path):
+    """The absorbed value pass' merge for up to kYFewSplits splits is one round of registers: no LDS."""
+    found = remarks(compile_header(tmp_path, '#include "absorbed_decode.h"\n' + "".join(
+        f"template __global__ void echokv::absorbed::y_sum_kernel<{sg}>(echokv::absorbed::Args, echokv::SeqMeta);\n" for sg in (1, 4))), "LDS Size [bytes/block]")
+    assert {("ILi1E" in k): n > 0 for k, n in found.items() if "y_sum_kernel" in k} == {True: False, False: True}
