@@ -281,10 +281,14 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqM
     int pos[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      int jj = j + u * NRG; if (jj >= jend) jj = jend - 1;
+      const int jj = min(j + u * NRG, jend - 1);
       load16<T>(a.k + (row0 + jj) * a.ld + col, kv[u]);
-      load16<T>(a.v + (row0 + jj) * a.ld + col, vv[u]);
+      uint4 vr = *reinterpret_cast<const uint4*>(a.v + (row0 + jj) * a.ld + col);
       pos[u] = wmode ? a.win.pos_of(jj, L) : jj;
+      if (j + u * NRG >= jend) pos[u] = -1;
+      const uint32_t m = pos[u] >= 0 ? ~0u : 0u;      // (0 times what a dead row holds may not be 0)
+      vr.x &= m; vr.y &= m; vr.z &= m; vr.w &= m;
+      unpack16<T>(vr, vv[u]);
       if (rope) {        // feature i pairs with i + d/2, held by the lane LPR / 2 away
         const int pr = max(pos[u], 0);
         float cs[VEC], sn[VEC];
@@ -311,12 +315,11 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqM
       float mn = mx[g];
 #pragma unroll
       for (int u = 0; u < UN; ++u) {
-        const bool live = (j + u * NRG) < jend && pos[u] >= 0;
         float t = 0.f;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) t = fmaf(qv[g][i], kv[u][i], t);
         t = row_sum<LPR>(t);
-        sc[u] = live ? t : -INFINITY;
+        sc[u] = pos[u] >= 0 ? t : -INFINITY;
         mn = fmaxf(mn, sc[u]);
       }
       if (mn != -INFINITY) {                       // (uniform over the lanes of a row)
@@ -423,7 +426,7 @@ __device__ __forceinline__ void stream_workgroup(const Streams<T>& st, const Str
 }
 
 // The same workgroups in a launch of their own: four waves each, so that a unit holds several.  A kernel for each GT, as one for all has the
-// registers of the largest: one query head takes 114, two 138, four 145.  A kernel for all with 205 / so, us: 32 heads, 31 of them retained, 8 x
+// registers of the largest: one query head takes 111, two 124 (four waves, either), four 145.  A kernel for all with 205 / so, us: 32 heads, 31 of them retained, 8 x
 // 8000 tokens, rope and window 655 / 578; 24 heads over 8, 7 retained, 8 x 8000 219 / 169, with rope and window 282 / 213; 56 over 8, 6 retained, 8 x 2000-12000
 // the same 287 / 223.
 constexpr int kStreamWaves = 4;

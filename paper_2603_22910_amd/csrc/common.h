@@ -62,8 +62,7 @@ __device__ __forceinline__ void unpack_bf16x8(uint4 raw, float (&out)[8]) {
   }
 }
 template <typename T>
-__device__ __forceinline__ void load16(const T* p, float (&out)[Elem<T>::kVec]) {
-  uint4 raw = *reinterpret_cast<const uint4*>(p);
+__device__ __forceinline__ void unpack16(uint4 raw, float (&out)[Elem<T>::kVec]) {
   if constexpr (sizeof(T) == 2) {
     unpack_bf16x8(raw, out);
   } else {
@@ -71,6 +70,8 @@ __device__ __forceinline__ void load16(const T* p, float (&out)[Elem<T>::kVec]) 
     out[2] = __uint_as_float(raw.z); out[3] = __uint_as_float(raw.w);
   }
 }
+template <typename T>
+__device__ __forceinline__ void load16(const T* p, float (&out)[Elem<T>::kVec]) { unpack16<T>(*reinterpret_cast<const uint4*>(p), out); }
 
 __device__ __forceinline__ float wave_max(float v, int width) {
   for (int o = width >> 1; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
