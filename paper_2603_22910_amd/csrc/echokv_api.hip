@@ -339,11 +339,11 @@ bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgrou
   int64_t tokens = 0, t256 = 0;
   for (int b = 0; b < mt.n; ++b) { tokens += mt.len[b]; t256 += (mt.len[b] + 255) / 256; }
   const double rows = (double)(dm.G / gt) * (tokens * dm.g0 + (double)mt.n * win_heads * win.rows());
-  const double streams = rows * dm.d * 2 * sizeof(T) / (rope ? 3.25e6 : 6.5e6) + 2.0 / 256 * (dm.G / gt) * mt.n * (dm.g0 + win_heads);
+  const double streams = rows * dm.d * 2 * sizeof(T) / (rope ? 3.4e6 : 6.5e6);
   const double rounds = 0.5 * ((double)workgroups / 256 + (double)((workgroups + 255) / 256));
-  const double small = 8 + rounds * (6 + (tb == 2 ? 0.0072 : 0.0112) * dm.d_in) + (dm.G / gt >= 3 ? 1.3 : 1.0) * streams;
+  const double small = 8.1 + rounds * (6.3 + (tb == 2 ? 0.0063 : 0.0109) * dm.d_in) + streams;
   const int64_t tiles = t256 * ((dm.d_out_v + 255) / 256);
-  const double large = 17 + (double)((tiles + 255) / 256) * 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0) + 0.5 * streams;
+  const double large = 15.2 + (double)((tiles + 255) / 256) * 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.69 : 1.06) + 0.32 * streams;
   return small <= large;
 }
 // Token blocks of 16 per workgroup (0: the problem is not small).
