@@ -326,13 +326,13 @@ constexpr int kSmallFewWgs = 240, kSmallMaxWgs = 704, kSmallMaxWgsF32 = 6144;
 inline int small_col_tile(const Dims& dm) { return dm.bf16 ? 128 : dm.d; }
 // Times of a bf16 call in us, with tb token blocks of 16 per workgroup and with the 256 x 256 kernel: launch and merge, rounds of
 // workgroups of the product, and the rows of the retained heads and the window, which the units stream at about 6.5 TB/s (with rotary tables
-// half of that; 1.3 times as long in the small kernel with three and more passes over the rows) and 2 us of a unit per sequence, head and
-// pass; in the large kernel's launch half of that hides behind the product.  A round of the small kernel is between a whole and a partial one (its workgroups end at different
-// times); the large kernel needs one round for up to 256 tiles, of 1.0 us per k-tile and pass, or 0.72 where all columns of a tile fit
-// one half of it.  Against the clock (64-token / 256 x 256 kernel, us): 8 KV heads,
-// one predicted, 8 x 2000 tokens 43.7 / 57.4, 8 x 3200 73.7 / 59.6, 8 x 5568 137 / 93; two, 8 x 1600 54.6 / 74.2, 8 x 2048 65.6 / 75.1,
-// 8 x 2752 90.9 / 75.4; four with 32 heads (d_in 7680) 222 / 277 at 8 x 1024, 297 / 280 at 8 x 1344; 7 query heads per KV head, one
-// predicted of 8, 8 x 1984 (all rows seven times) 96 / 80.  Over 132 such problems the choice costs 0.2 % in the mean, 8 % at most.
+// half of that); in the large kernel's launch two thirds of that hide behind the product.  A round of the small kernel is between a whole and a
+// partial one (its workgroups end at different times); the large kernel needs one round for up to 256 tiles, of 1.06 us per k-tile and pass, or
+// 0.69 where all columns of a tile fit one half of it.  Against the clock (64-token / 256 x 256 kernel, us): 8 KV heads,
+// one predicted, 8 x 2000 tokens 42.4 / 56.2, 8 x 3200 71.6 / 57.6, 8 x 5568 132 / 89; two, 8 x 1600 52.4 / 71.8, 8 x 2048 63.2 / 73.6,
+// 8 x 2752 89.1 / 73.7; four with 32 heads (d_in 7680) 217 / 274 at 8 x 1024, 292 / 276 at 8 x 1344; 7 query heads per KV head, one
+// predicted of 8, 8 x 1984 (all rows seven times) 93.8 / 70.9, 8 x 537 with rope and window 46.8 / 62.4.  The constants were fitted to 220 random
+// problems near the line; over 110 others the choice costs 0.2 % in the mean, 10 % at most.
 template <typename T>
 bool small_is_faster(const Dims& dm, const SeqMeta& mt, int tb, int64_t workgroups, bool rope, const Window& win) {
   const int gt = stream_heads(dm.G), win_heads = win.on() ? dm.H_kv : 0;
@@ -423,7 +423,7 @@ Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* q
 // launches of attn_split_kernel, head after head, are taken (1.25).  Launch of their own in the order of chunks /
 // head after head: G = 5, 6 of 8 retained, 48 x 800 with rope and window 225 / 204, 7 of 8, 8 x 6000 173 / 171, 40 x 4000 with rope 657 /
 // 658; but G = 7, 3 of 4, 40 x 4000 without rope 293 / 388, 7 of 8, 2 x 40000 with it 441 / 686.  Over 210 random calls the choice costs 0.5 % in the mean
-against the best of the three, 16 % at most (with 1.14 for every number of heads 1.8 and 24 %).
+// against the best of the three, 16 % at most (with 1.14 for every number of heads 1.8 and 24 %).
 enum class StreamsIn { kProduct, kChunkOrder, kHeadOrder };
 StreamsIn place_of_streams(const Dims& dm, const SeqMeta& mt, bool rope, const Window& win) {
   const int gt = stream_heads(dm.G), passes = dm.G / gt;
@@ -438,7 +438,7 @@ StreamsIn place_of_streams(const Dims& dm, const SeqMeta& mt, bool rope, const W
   const double rows = (double)passes * (tokens * dm.g0 + (double)mt.n * dm.H_kv * win.rows());
   const double streams = 256 * rows * dm.d * 4 / (rope ? 3.25e6 : 6.5e6) + 2 * wgs;
   const int64_t rounds = (tiles + 255) / 256;
-  const double tile = 9 + 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0);           // see small_is_faster
+  const double tile = 9 + 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0);           // about as in small_is_faster
   const double idle = (double)(rounds * 256 - tiles) * tile;
   const bool head_order = passes >= 5 && max_len <= 8192 && (rope || tokens * dm.m * 4 <= (int64_t)200 << 20);
   const double faster = head_order ? 0.25 : gt == 1 ? 0.5 : gt == 2 ? 0.3 : 0.14;
