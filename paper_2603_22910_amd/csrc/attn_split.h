@@ -115,14 +115,14 @@ __device__ __forceinline__ float sum_quad4(float t0, float t1, float t2, float t
   return (high ? a1 : a0) + dpp_move<0x4E>(high ? a0 : a1);
 }
 
-// attn_split_body for four query heads of a KV head and bf16 rows of 128 dims.  What bounds it: with rotary tables, the vector unit: a row is 16
+// One workgroup (see attn_split_body) for four query heads of a KV head and bf16 rows of 128 dims.  What bounds it: with rotary tables, the vector unit: a row is 16
 // lanes of 8 dims, and scores, softmax and value sums of four heads in each of them were 200 instructions per row.  Here lane % 4
 // stands for the query head wherever a value is the same for all lanes of a row: the scores' sums end there (11 instructions instead of 16), the
 // softmax is worked out once per quad instead of four times, the values are multiplied four heads at a time by v_mfma_f32_4x4x1
 // (fma_heads), rotation partners, eight lanes away, come by row rotation instead of through LDS.
 // Whole calls, 32 heads over 8, before / so, us: 8 x 2048-36864 tokens, 3 heads retained, rope and window 292 / 285, 2 x 40000, 4 retained, the same
 // 283 / 274, without rope 260 / 248, 8 x 6000, 7 retained, rope 135 / 120; 64 heads over 8, 4 x 5000, 4 retained, rope 93.9 / 83.6.  Rows of
-// 64 dims, whose quads are two to a row, lose what they win (4 x 5000 tokens 23.8 / 24.6): attn_split_body.
+// 64 dims, whose quads are two to a row, lose what they win (4 x 5000 tokens 23.8 / 24.6): attn_split_body_any.
 template <int NWAVES, int UN>
 __device__ __forceinline__ void attn_split_body4(const AttnArgs<bf16_t>& a, const SeqMeta& meta, int b, int chunk, int y, char* smem) {
   constexpr int GT = 4, LPR = 16, RPW = 64 / LPR, NRG = NWAVES * RPW;
@@ -235,15 +235,10 @@ __device__ __forceinline__ void attn_split_body4(const AttnArgs<bf16_t>& a, cons
   write_chunk_partial<GT, NWAVES, LPR * 8>(a, meta, b, chunk, qh0, s_m, s_l, s_o);
 }
 
-// One workgroup of NWAVES waves: chunk `chunk` of sequence b, y = KV head * (G / GT) + group of query heads.
-// UN: rows of a row group in flight (4; 8 where few waves share a compute unit).
-template <typename T, int LPR, int GT, int NWAVES, int UN = 4>
-__device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqMeta& meta, int b, int chunk,
-                                                int y, char* smem) {
-  if constexpr (GT == 4 && LPR == 16 && sizeof(T) == 2) {
-    attn_split_body4<NWAVES, UN>(a, meta, b, chunk, y, smem);
-    return;
-  }
+// The same for any number of query heads, rows and type.
+template <typename T, int LPR, int GT, int NWAVES, int UN>
+__device__ __forceinline__ void attn_split_body_any(const AttnArgs<T>& a, const SeqMeta& meta, int b, int chunk,
+                                                    int y, char* smem) {
   constexpr int VEC = Elem<T>::kVec;
   constexpr int RPW = 64 / LPR;        // row groups per wave
   constexpr int NRG = NWAVES * RPW;    // row groups per block
@@ -366,6 +361,13 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqM
     if (lane == 0) { s_m[wave][g] = M; s_l[wave][g] = l; }
   }
   write_chunk_partial<GT, NWAVES, LPR * VEC>(a, meta, b, chunk, qh0, s_m, s_l, s_o);
+}
+// One workgroup of NWAVES waves: chunk `chunk` of sequence b, y = KV head * (G / GT) + group of query heads.
+// UN: rows of a row group in flight (4; 8 where few waves share a compute unit).
+template <typename T, int LPR, int GT, int NWAVES, int UN = 4>
+__device__ __forceinline__ void attn_split_body(const AttnArgs<T>& a, const SeqMeta& meta, int b, int chunk, int y, char* smem) {
+  if constexpr (GT == 4 && LPR == 16 && sizeof(T) == 2) attn_split_body4<NWAVES, UN>(a, meta, b, chunk, y, smem);
+  else attn_split_body_any<T, LPR, GT, NWAVES, UN>(a, meta, b, chunk, y, smem);
 }
 // Waves of a SIMD that the kernels of streaming workgroups alone are compiled for: nothing but other waves hides the wait for their rows.  Left to
 // itself the compiler takes 204 registers for attn_split_body4 (copies of its accumulators; 144 so), which leaves two.  Two / three, 8 KV heads, whole

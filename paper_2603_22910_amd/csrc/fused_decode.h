@@ -4,15 +4,15 @@
 // One workgroup owns a tile of 256 cached tokens x 256 predicted columns
 // (two heads of 128, or four of 64).  For that tile it
 //   1. runs the predictor product for K (Eq. 3) with W as the row operand so that each
-//      lane ends up holding whole columns of K_hat^T for ONE token: the score
-//      q . k_hat_j (Eq. 7) is then a sum over the lane's own accumulators plus one
-//      cross-half add;
-//   2. takes the softmax numerators over each wave's 64 tokens (max, sum of
+//      lane ends up holding dims of K_hat^T for ONE token in each of four blocks: the score
+//      q . k_hat_j (Eq. 7) is then a sum over the lane's own accumulators, over the four lanes
+//      of a token, and with rotary tables, where a wave has half of every head's dims, over two waves;
+//   2. takes the softmax numerators over each group of 64 tokens (max, sum of
 //      exponentials), leaving p_j in LDS;
 //   3. runs the predictor product for V with X as the row operand, so each
 //      lane holds rows (tokens) of V_hat for one column per block and sum_j p_j v_hat_j
-//      is again lane-local;
-//   4. joins the two waves of a 128-token slot and writes one split-K partial
+//      is a sum over the lane's own accumulators and four lanes as well;
+//   4. joins the two groups of 64 tokens of a 128-token slot through LDS and writes one split-K partial
 //      (max, sum, unnormalised o) per slot and head.
 // K_hat and V_hat live only in accumulator registers: they never reach LDS or HBM.
 // The retained heads' streaming attention and the window's run in further workgroups of the same launch.

@@ -18,11 +18,11 @@
 // takes element i of every lane, so it owns the columns VW * (lane % 16) + i.  bf16 needs 8 input dims
 // per lane: eight such loads, transposed 8 x 8 in registers.
 //
-// What bounds it: bf16, operand traffic L2 -> registers: every workgroup reads its whole W slice
-// (2 * d_in * 128 elements) for 16 * TB tokens, 64 bytes per clock and compute unit at best (measured: 0.8 us
-// per step of eight waves and 32 tokens, 10 KB each = 100 GB/s per unit; with 64 tokens 1.25 us for 12 KB each);
-// fp32, the matrix pipes of the units that have a workgroup.  About 3 us of every launch are the first
-// round trip, 3-4 us the epilogues.
+// What bounds it: bf16, a chain: about 3 us of every launch are the first round trip, 3-4 us the epilogues, and in between every workgroup reads
+// its whole W slice (2 * d_in * 128 elements) for 16 * TB tokens through one unit's port to L2: 0.8 us per step of eight waves and 32 tokens, 10 KB
+// each = 100 GB/s per unit, 43 bytes per clock at 2.4 GHz; with 64 tokens 1.25 us for 12 KB each.  With the W loads of all steps but the
+// first left out, 1 x 1000 tokens (12 steps, 786 KB of W per workgroup) take 15.3 instead of 20.6 us with rotary tables and window, 14.7 instead of
+// 18.6 without: a quarter of the call is W.  fp32, the matrix pipes of the units that have a workgroup.
 // Measured against the 256 x 256 kernel with its separate launches (whole call, us, before -> after):
 //   H_q/H_kv = 32/8, m = 512:  1 x 1000 tokens 84 -> 22 (with rotary tables and window 110 -> 26), 1 x 6000 86 -> 54
 //   H_q/H_kv = 32/32, m = 2048: 1 x 500 tokens 225 -> 59, 1 x 1000 225 -> 76
