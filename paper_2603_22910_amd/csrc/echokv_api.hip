@@ -413,17 +413,18 @@ Streams<T> plan_streams(const Dims& dm, const echokv_layer_cache* tg, const T* q
 
 // Streams of a bf16 call in a launch of their own ahead of the large kernel's, with several of their workgroups per unit.  As
 // workgroups of that kernel's launch, one per unit, they take longer (1.14 times as long with four query heads per pass over the rows, 1.3 with two
-// and 1.5 with one, whose own kernels have four waves per SIMD), but the units that the product's last round leaves idle work for nothing.  All times
+// and 1.4 with one, whose own kernels have four waves per SIMD), but the units that the product's last round leaves idle work for nothing.  All times
 // in us of one unit: a row and pass (query heads of a KV head that do not share a workgroup pass over its rows again: 3, 5 or 7 of
 // them) and 2 per workgroup; the launch costs 5, and what is less than 3 % of the product is left alone.  In the launch / by themselves, us, 8 KV
 // heads: G = 8, 4 retained, 128 x 300 with window 257 / 221; G = 4, 4 retained, 8 x 6000 (many units idle) 156 / 174, 7 retained, 8 x 8000, rope and
-// window 166 / 164; G = 3, 6 retained, 16 x 3242 173 / 141, 8 x 6000 with rope and window 184 / 169, 4 retained the same 205 / 225; 7 of 8 heads of 64, 100 x 901 159 /
+// window 166 / 164; G = 3, 6 retained, 16 x 3242 173 / 141, 8 x 6000 with rope and window 184 / 169, 4 retained the same (a quarter of the units idle) 204 / 217; 7 of 8 heads of 64, 100 x 901 159 /
 // 140; G = 2, 4 of 8, 8 x 15474 with rope and window 433 / 421; G = 1, 8 of 16, 16 x 2494 560 / 581; G = 7, 3 of 4, 2 x 40000 189 / 172, 40 x 4000 377 / 293.
 // With 5 or 7 passes over sequences of up to 8192 tokens while the rows stay in the last cache or there are rotary tables to wait for, the
 // launches of attn_split_kernel, head after head, are taken (1.25).  Launch of their own in the order of chunks /
 // head after head: G = 5, 6 of 8 retained, 48 x 800 with rope and window 225 / 204, 7 of 8, 8 x 6000 173 / 171, 40 x 4000 with rope 657 /
-// 658; but G = 7, 3 of 4, 40 x 4000 without rope 293 / 388, 7 of 8, 2 x 40000 with it 441 / 686.  Over 210 random calls the choice costs 0.5 % in the mean
-// against the best of the three, 16 % at most (with 1.14 for every number of heads 1.8 and 24 %).
+// 658; but G = 7, 3 of 4, 40 x 4000 without rope 293 / 388, 7 of 8, 2 x 40000 with it 441 / 686.  Over 210 random calls the choice costs 0.7 %
+// in the mean against the best of the three (with 1.14 for every number of heads 1.8 %), and none but two (2 %) is slower than with 1.14; with 1.5 for one
+// head it is 0.5 %, but calls with idle units lose up to 7.
 enum class StreamsIn { kProduct, kChunkOrder, kHeadOrder };
 StreamsIn place_of_streams(const Dims& dm, const SeqMeta& mt, bool rope, const Window& win) {
   const int gt = stream_heads(dm.G), passes = dm.G / gt;
@@ -441,7 +442,7 @@ StreamsIn place_of_streams(const Dims& dm, const SeqMeta& mt, bool rope, const W
   const double tile = 9 + 2 * (dm.d_in / 64) * (dm.d_out_v <= 128 ? 0.72 : 1.0);           // about as in small_is_faster
   const double idle = (double)(rounds * 256 - tiles) * tile;
   const bool head_order = passes >= 5 && max_len <= 8192 && (rope || tokens * dm.m * 4 <= (int64_t)200 << 20);
-  const double faster = head_order ? 0.25 : gt == 1 ? 0.5 : gt == 2 ? 0.3 : 0.14;
+  const double faster = head_order ? 0.25 : gt == 1 ? 0.4 : gt == 2 ? 0.3 : 0.14;
   if ((faster * streams - (1 + faster) * idle) / 256 <= 5 + 0.03 * (double)rounds * tile) return StreamsIn::kProduct;
   return head_order ? StreamsIn::kHeadOrder : StreamsIn::kChunkOrder;
 }
