@@ -35,7 +35,7 @@ constexpr int MAXPAIR = 8;   // query heads per 128 columns: (128 / head dim) * 
 // heads, 8 x 3000 79.7 / 80.6; three, 8 x 6000 175.0 / 174.4, heads of 64 69.2 / 68.3, 4 x 1000-9000 with rope 54.2 / 53.3; four heads (3140 - 24000
 // tokens, rope, window) 319 / 308.  With rotary tables: the score kernel, one head, 40000 tokens 887 / 891, heads of 64, 8 x 4096
 // 240.5 / 242.7, two heads of 64 98.1 / 99.2; in the fused kernel, where the two waves of 64 tokens share the dims, one head, 8 x 4096 1249 / 1253 (runs
-// 9 apart), two, 8 x 6000 168.3 / 167.8: the matrix pipe alone there.
+// 9 apart), two, 8 x 6000 168.3 / 167.8, 17 calls of one and two heads of 64 and 128 within 1 % of each other: the matrix pipe alone there.
 constexpr int kVectorHeads = 2;
 
 struct Args {
