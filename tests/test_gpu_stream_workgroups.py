@@ -29,6 +29,9 @@ CASES = [
     (56, 8, 128, 768, (300,) * 128),          # G = 7, 256 tiles: no unit idle, the streams ahead of the product, head after head
     (24, 8, 64, 384, (512,) * 127 + (500,)),  # G = 3: the same by chunks
     (32, 4, 128, 384, (500,) * 128),          # G = 8: only with the window and rotary tables
+    (8, 8, 128, 896, (500,) * 128),           # G = 1, G = 2: 256 tiles and many retained rows, by chunks
+    (16, 8, 128, 896, (500,) * 128),
+    (16, 8, 64, 448, (500,) * 128),
 ]
 
 
