@@ -56,3 +56,49 @@ def test_row_read_again_past_the_end(H_q, H_kv, d, dtype, use_rope):
     assert (np.isposinf(got) == np.isposinf(want)).all()
     fin = np.isfinite(want)
     assert np.abs(got[fin] - want[fin]).max() <= TOL[dtype][0]
+
+
+def poison(dw, inp):
+    """NaN in every pool row outside the sequences and all over the workspace."""
+    outside = torch.ones(inp.pool_tokens, dtype=torch.bool)
+    for s, n in zip(inp.seq_start, inp.seq_len):
+        outside[s:s + n] = False
+    for t in (dw.K_a, dw.V_a, dw.K_r, dw.V_r):
+        t[outside.to(t.device)] = float("nan")
+    dw.workspace.fill_(255)
+
+
+@pytest.mark.parametrize("use_rope", [pytest.param(False, id="plain"), pytest.param(True, id="rope+window")])
+@pytest.mark.parametrize("dtype,flags", MODES + [pytest.param("bf16", ek.FLAG_ABSORBED, id="absorbed")])
+@pytest.mark.parametrize("H_q,H_kv,d", [(4, 4, 128), (16, 4, 128), (8, 4, 64)])
+@pytest.mark.parametrize("lens", [(300, 65, 1, 200), (1500, 1030)])
+def test_pool_rows_outside_the_sequences(lens, H_q, H_kv, d, dtype, flags, use_rope):
+    if use_rope and flags == ek.FLAG_ABSORBED:
+        pytest.skip("absorbed decode: position-free keys only")
+    inp = synth.generate(synth.Workload("dead", dtype, H_q, H_kv, d, 2 * d, seed=19, seq_lens=lens))
+    dw = make_dw(inp, flags)
+    poison(dw, inp)
+    if use_rope:
+        rope, window = synth.rope_tables(d, max(lens)), (*synth.window_rows(inp, 4, 24), 4, 24)
+        out, lse = dw.decode_ex(rope, window)
+        o_ref, l_ref = ref.decode_paper_ref(inp, rope, window)
+    else:
+        out, lse = dw.decode()
+        o_ref, l_ref = ref.decode_ref(inp)
+    torch.cuda.synchronize()
+    check(host(out), o_ref, dtype, f"{H_q} {H_kv} {d} {lens}")
+    assert np.abs(host(lse) - l_ref).max() <= (1e-5 if dtype == "f32" else 2e-2)
+
+
+@pytest.mark.parametrize("use_rope", [pytest.param(False, id="plain"), pytest.param(True, id="rope")])
+@pytest.mark.parametrize("dtype,plen,pq", [("bf16", 300, 70), ("bf16", 1500, 33), ("bf16", 1300, 1030), ("f32", 200, 19)])
+@pytest.mark.parametrize("H_q,H_kv,d", [(4, 4, 128), (16, 4, 128), (8, 4, 64)])
+def test_prefill_beside_unused_rows(H_q, H_kv, d, dtype, plen, pq, use_rope):
+    inp = synth.generate(synth.Workload("dead", dtype, H_q, H_kv, d, 2 * d, seed=20, seq_lens=(8,), prefill_len=plen, prefill_q=pq))
+    dw = make_dw(inp, 0)
+    poison(dw, inp)
+    rope = synth.rope_tables(d, plen) if use_rope else None
+    out, _ = dw.prefill_ex(rope) if use_rope else dw.prefill()
+    torch.cuda.synchronize()
+    o_ref, _ = ref.prefill_paper_ref(inp, rope) if use_rope else ref.prefill_ref(inp)
+    check(host(out), o_ref, dtype, f"{H_q} {H_kv} {d} {plen} {pq}")
