@@ -290,8 +290,10 @@ int echokv_decode_attn_static(const echokv_shape *shape, const echokv_layer_cach
  *   win_k, win_v : device [batch, n_sink + n_recent, D], dtype of the caches,
  *                  pre-rotation; position p of sequence b is row p if p < n_sink,
  *                  else row n_sink + (p - n_sink) % n_recent (a ring).
- * echokv_window_append keeps the rows current; the compressed cache still
- * receives every token (echokv_cache_append), the window is an extra copy. */
+ * Rows that hold no position of a sequence (seq_len < n_sink + n_recent) are
+ * not used, whatever they contain.  echokv_window_append keeps the rows current;
+ * the compressed cache still receives every token (echokv_cache_append), the
+ * window is an extra copy. */
 typedef struct {
   const float *rope_cos;
   const float *rope_sin;
